@@ -190,6 +190,10 @@ def work(case):
     if case["op"] == "kmv":
         n, m = case["n"], case["m"]
         size = 8 if case["dtype"] == "f64" else 4
+        if d == 1:
+            # on a line the entries need not be made one by one: sources that lie close together
+            # act through a short series.  What is left is the points themselves
+            return {"bytes": size * (n + (0 if case["z_is_x"] else m) + m) + 8 * n, "flops": 5 * (n + m)}
         # per entry the distance, the exponential counted as one operation, and the sum
         return {"bytes": size * (d * (n + (0 if case["z_is_x"] else m)) + m) + 8 * n, "flops": (2 * d + 3) * n * m}
     m, n = case["m"], case["n"]
@@ -207,3 +211,67 @@ def tolerance(case):
         return {"rel": 2e-13, "max": 2e-12} if case["dtype"] == "f64" else {"rel": 8e-7, "max": 1e-5}
     # against double precision 3.4e-8 was seen for A and 1.1e-7 for b
     return {"rel": 5e-7, "max": 5e-6}
+
+
+# ---- the same in 64 bits --------------------------------------------------------------------
+
+def exact(case, seed):
+    """What `run` returns, in double precision from plain torch; None where that takes too long.
+    A search's indices have no such value: neighbours that are equally far may come in any order."""
+    state = prepare(case, seed)
+    if case["op"] == "knn":
+        return _exact_knn(case, state["Q"].double(), state["X"].double())
+    if case["op"] == "kmv":
+        return _exact_kmv(case, state["X"].double(), state["Z"].double(), state["v"].double())
+    U, X, y = (state[a].double() for a in ("U", "X", "y"))
+    A = torch.zeros(case["m"], case["m"], dtype=torch.float64, device="cuda")
+    b = torch.zeros(case["m"], dtype=torch.float64, device="cuda")
+    for s in range(0, case["n"], 1 << 17):
+        K = _gaussian(U, X[s:s + (1 << 17)], case["lengthscale"])
+        A += K @ K.T
+        b += K @ y[s:s + (1 << 17)]
+    return A, b
+
+
+def _exact_knn(case, Q, X):
+    m, n, d, k = case["m"], case["n"], case["d"], case["k"]
+    if m * n > 2e10 or m * n * d > (1e12 if case["metric"] == "l1" else 2e13):
+        return None
+    dist = torch.empty(m, k, dtype=torch.float64, device="cuda")
+    rows = max(1, min(m, (1 << (24 if case["metric"] == "l1" else 29)) // n))
+    if case["metric"] == "cosine":
+        Q, X = Q / Q.norm(dim=1, keepdim=True), X / X.norm(dim=1, keepdim=True)
+    xn, Xt = (X * X).sum(1), X.T.contiguous()
+    for s in range(0, m, rows):
+        q = Q[s:s + rows]
+        if case["metric"] == "l1":
+            D = torch.zeros(q.shape[0], n, dtype=torch.float64, device="cuda")
+            for t in range(d):
+                D += (q[:, t, None] - Xt[None, t]).abs_()
+        elif case["metric"] == "cosine":
+            D = 1 - q @ X.T
+        elif d <= 8:
+            D = sum((q[:, t, None] - X[None, :, t]).square_() for t in range(d))
+        else:
+            D = torch.addmm(xn[None, :] + (q * q).sum(1)[:, None], q, X.T, alpha=-2)
+        dist[s:s + rows] = D.topk(k, dim=1, largest=False).values
+    return None, dist
+
+
+def _gaussian(X, Z, lengthscale):
+    c = 0.5 / lengthscale ** 2
+    if X.shape[1] <= 2:
+        return sum((X[:, t, None] - Z[None, :, t]).square_() for t in range(X.shape[1])).mul_(-c).exp_()
+    xn, zn = (X * X).sum(1), (Z * Z).sum(1)
+    return torch.addmm(xn[:, None] + zn[None, :], X, Z.T, alpha=-2).mul_(-c).exp_()
+
+
+def _exact_kmv(case, X, Z, v):
+    n, m, d = case["n"], case["m"], case["d"]
+    if n * m * d > 5e11 and d > 8:
+        return None
+    y = torch.empty(n, dtype=torch.float64, device="cuda")
+    rows = max(1, min(n, (1 << 25) // m))
+    for s in range(0, n, rows):
+        y[s:s + rows] = _gaussian(X[s:s + rows], Z, case["lengthscale"]) @ v
+    return y
