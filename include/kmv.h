@@ -76,6 +76,7 @@ int kmv_plan(int64_t n, int64_t m, int32_t d, int64_t mem_limit_bytes, kmv_plan_
  *   variance   sigma^2 >= 0, lengthscale l > 0 (both finite)
  *   workspace  DEVICE  256-byte aligned, workspace_bytes >= plan.workspace_bytes
  *              (may be NULL when the plan needs 0 bytes); contents are scratch
+ *              (kmv_workspace_bytes(...) of it lets d = 1 run through the series below)
  *   y          DEVICE  fp64 [n], fully overwritten (all zeros when m == 0)
  *   stream     hipStream_t (NULL: the default stream).  The call only
  *              enqueues work; it allocates nothing and does not synchronise.
@@ -87,6 +88,20 @@ int kmv_plan(int64_t n, int64_t m, int32_t d, int64_t mem_limit_bytes, kmv_plan_
 int kmv_apply(const float* X, int64_t ldx, const float* Z, int64_t ldz, const float* v, int64_t n,
               int64_t m, int32_t d, double variance, double lengthscale, int64_t mem_limit_bytes,
               void* workspace, int64_t workspace_bytes, double* y, void* stream);
+
+/*
+ * HOST.  The workspace a call of this shape is best given: plan.workspace_bytes, plus, for d = 1
+ * with enough entries (3e8; 4e7 in fp64) and where the limit has room, about 1.6 MB in which the
+ * sources are gathered into boxes a fraction of a lengthscale wide.  A box acts on every row
+ * through one short series (in fp64, cut where what is left out is below the precision of the
+ * entry point), so the work goes with n + m.  Whether the points allow that - finite, not
+ * spread over more than 1023 (fp64: 511) lengthscales, and at least 16 sources per box - is found
+ * on the device; where they do not, the general kernel runs as it does with the plan's workspace.
+ * Never above mem_limit_bytes; 0 if there is no plan.
+ */
+int64_t kmv_workspace_bytes(int64_t n, int64_t m, int32_t d, double lengthscale, int64_t mem_limit_bytes);
+int64_t kmv_workspace_bytes_f64(int64_t n, int64_t m, int32_t d, double lengthscale,
+                                int64_t mem_limit_bytes);
 
 /*
  * The same product in the precision section 5.1 evaluates it in: X, Z, v are

@@ -38,6 +38,7 @@ EXPORTED_SYMBOLS = (
     "knn_parse_size", "knn_chunk_rows", "knn_last_hip_error", "knn_profile_enable",
     "knn_profile_read", "knn_plan_metric", "knn_search_metric",
     "kmv_plan", "kmv_apply", "kmv_plan_f64", "kmv_apply_f64",
+    "kmv_workspace_bytes", "kmv_workspace_bytes_f64",
     "knn_plan_host_x", "knn_search_host_x", "sgpr_plan", "sgpr_accumulate",
     "knn_search_static", "knn_measure_mfma_peak",
 )
@@ -241,6 +242,10 @@ def load():
     lib.kmv_plan_f64.restype = ctypes.c_int
     lib.kmv_apply_f64.argtypes = lib.kmv_apply.argtypes
     lib.kmv_apply_f64.restype = ctypes.c_int
+    lib.kmv_workspace_bytes.argtypes = [i64, i64, i32, ctypes.c_double, i64]
+    lib.kmv_workspace_bytes.restype = i64
+    lib.kmv_workspace_bytes_f64.argtypes = lib.kmv_workspace_bytes.argtypes
+    lib.kmv_workspace_bytes_f64.restype = i64
     _lib = lib
     return lib
 
@@ -438,8 +443,8 @@ def kmv_apply(X, Z, v, variance: float, lengthscale: float, mem_limit_bytes: int
     """kmv_apply(X[n,d], Z[m,d], v[m], variance, lengthscale, mem_limit_bytes) -> y fp64[n].
 
     y = K(X, Z) v with the squared-exponential kernel.  X, Z, v are device tensors, all fp32
-    or all fp64 (the all-fp64 entry point then runs); rows may be strided.  The workspace (uint8, plan.workspace_bytes) is allocated here unless
-    given.  Work is enqueued on torch's current stream; no synchronisation is done.
+    or all fp64 (the all-fp64 entry point then runs); rows may be strided.  The workspace (uint8,
+    kmv_workspace_bytes; plan.workspace_bytes is the least) is allocated here unless given.  Work is enqueued on torch's current stream; no synchronisation is done.
     """
     import torch
 
@@ -455,10 +460,11 @@ def kmv_apply(X, Z, v, variance: float, lengthscale: float, mem_limit_bytes: int
         raise KnnError(KNN_ERR_INVALID_ARG, "v must have m contiguous entries; unit column strides")
     n, d = X.shape
     m = Z.shape[0]
-    plan = kmv_plan(n, m, d, mem_limit_bytes, dtype)
+    kmv_plan(n, m, d, mem_limit_bytes, dtype)  # raises what is wrong with the sizes
     if workspace is None:
-        workspace = torch.empty(max(int(plan.workspace_bytes), 256), dtype=torch.uint8,
-                                device=X.device)
+        fn = {"f32": load().kmv_workspace_bytes, "f64": load().kmv_workspace_bytes_f64}[dtype]
+        workspace = torch.empty(max(int(fn(n, m, d, float(lengthscale), mem_limit_bytes)), 256),
+                                dtype=torch.uint8, device=X.device)
     y = out if out is not None else torch.empty((n,), dtype=torch.float64, device=X.device)
     stream = torch.cuda.current_stream(X.device).cuda_stream
     ldx = X.stride(0) if n > 1 else max(d, X.stride(0))

@@ -93,7 +93,37 @@ int plan_impl(int64_t n, int64_t m, int32_t d, int64_t mem_limit_bytes, bool f64
     return KNN_OK;
 }
 
+// Workspace the call is best given: the plan's, and behind it what the series for d = 1 works
+// in, where the limit has room for both.
+int64_t roomy_bytes(const kmv_plan_t& plan, int64_t mem_limit_bytes, double lengthscale, bool f64) {
+    if (!kmv::series_applies(plan.n, plan.m, plan.d, lengthscale, f64)) return plan.workspace_bytes;
+    const int64_t want = plan.workspace_bytes + align_up(kmv::series_bytes());
+    return want <= mem_limit_bytes ? want : plan.workspace_bytes;
+}
+
+// whether this call's workspace holds the series' part as well
+bool use_series(const kmv_plan_t& plan, int64_t mem_limit_bytes, double lengthscale, bool f64,
+                const void* workspace, int64_t workspace_bytes) {
+    const int64_t roomy = roomy_bytes(plan, mem_limit_bytes, lengthscale, f64);
+    return roomy > plan.workspace_bytes && workspace_bytes >= roomy && workspace &&
+           reinterpret_cast<uintptr_t>(workspace) % knn::kAlign == 0;
+}
+
 }  // namespace
+
+extern "C" int64_t kmv_workspace_bytes(int64_t n, int64_t m, int32_t d, double lengthscale,
+                                       int64_t mem_limit_bytes) {
+    kmv_plan_t plan;
+    if (plan_impl(n, m, d, mem_limit_bytes, false, &plan) != KNN_OK) return 0;
+    return roomy_bytes(plan, mem_limit_bytes, lengthscale, false);
+}
+
+extern "C" int64_t kmv_workspace_bytes_f64(int64_t n, int64_t m, int32_t d, double lengthscale,
+                                           int64_t mem_limit_bytes) {
+    kmv_plan_t plan;
+    if (plan_impl(n, m, d, mem_limit_bytes, true, &plan) != KNN_OK) return 0;
+    return roomy_bytes(plan, mem_limit_bytes, lengthscale, true);
+}
 
 extern "C" int kmv_plan(int64_t n, int64_t m, int32_t d, int64_t mem_limit_bytes, kmv_plan_t* out) {
     return plan_impl(n, m, d, mem_limit_bytes, false, out);
@@ -136,9 +166,17 @@ extern "C" int kmv_apply(const float* X, int64_t ldx, const float* Z, int64_t ld
     double* partials = reinterpret_cast<double*>(ws + plan.norms_bytes);
     const int S = plan.n_splits;
     double* target = S > 1 ? partials : y;
+    const int* done = nullptr;
     if (plan.path == KMV_PATH_LOWD) {
         hipEvent_t t1 = knn::profile_mark(stream);
-        e = kmv::launch_lowd(X, ldx, Z, ldz, v, n, m, d, c2, variance, S, target, stream);
+        e = hipSuccess;
+        if (use_series(plan, mem_limit_bytes, lengthscale, false, workspace, workspace_bytes)) {
+            done = reinterpret_cast<const int*>(ws + plan.workspace_bytes);
+            e = kmv::launch_series(X, ldx, Z, ldz, v, n, m, lengthscale, variance, ws + plan.workspace_bytes, y,
+                                   stream);
+        }
+        if (e == hipSuccess)
+            e = kmv::launch_lowd(X, ldx, Z, ldz, v, n, m, d, c2, variance, S, target, stream, done);
         if (e != hipSuccess) {
             knn::profile_drop(t1);
             return hip_fail(e, "kmv low-d kernel");
@@ -156,7 +194,7 @@ extern "C" int kmv_apply(const float* X, int64_t ldx, const float* Z, int64_t ld
         knn::profile_close(t1, stream, 1);
     }
     if (S > 1) {
-        e = kmv::launch_reduce(partials, S, n, y, stream);
+        e = kmv::launch_reduce(partials, S, n, y, stream, done);
         if (e != hipSuccess) return hip_fail(e, "kmv reduce kernel");
     }
     return KNN_OK;
@@ -190,15 +228,23 @@ extern "C" int kmv_apply_f64(const double* X, int64_t ldx, const double* Z, int6
     const double negc = -0.5 / (lengthscale * lengthscale);
     double* partials = static_cast<double*>(workspace);
     const int S = plan.n_splits;
+    const int* done = nullptr;
     hipEvent_t t1 = knn::profile_mark(stream);
-    e = kmv::launch_f64(X, ldx, Z, ldz, v, n, m, d, negc, variance, S, S > 1 ? partials : y, stream);
+    e = hipSuccess;
+    if (use_series(plan, mem_limit_bytes, lengthscale, true, workspace, workspace_bytes)) {
+        unsigned char* extra = static_cast<unsigned char*>(workspace) + plan.workspace_bytes;
+        done = reinterpret_cast<const int*>(extra);
+        e = kmv::launch_series(X, ldx, Z, ldz, v, n, m, lengthscale, variance, extra, y, stream);
+    }
+    if (e == hipSuccess)
+        e = kmv::launch_f64(X, ldx, Z, ldz, v, n, m, d, negc, variance, S, S > 1 ? partials : y, stream, done);
     if (e != hipSuccess) {
         knn::profile_drop(t1);
         return hip_fail(e, "kmv fp64 kernel");
     }
     knn::profile_close(t1, stream, 1);
     if (S > 1) {
-        e = kmv::launch_reduce(partials, S, n, y, stream);
+        e = kmv::launch_reduce(partials, S, n, y, stream, done);
         if (e != hipSuccess) return hip_fail(e, "kmv reduce kernel");
     }
     return KNN_OK;

@@ -22,7 +22,7 @@ hipError_t launch_scaled_norms(const float* Z, int64_t ldz, int64_t m, int d, fl
 // d <= kLowdMaxD.  out[s * n + i] = variance * sum over range s of K-without-variance * v.
 hipError_t launch_lowd(const float* X, int64_t ldx, const float* Z, int64_t ldz, const float* v,
                        int64_t n, int64_t m, int d, float c2, double variance, int S, double* out,
-                       hipStream_t stream);
+                       hipStream_t stream, const int* done = nullptr);
 
 // d > kLowdMaxD: squared distance through the expansion, X Z^T on bf16 MFMA over three-piece
 // splits of the fp32 values (products as accurate as fp32's).
@@ -34,10 +34,21 @@ hipError_t launch_mfma(const float* X, int64_t ldx, const float* Z, int64_t ldz,
 // the row in registers, larger d re-reads it in chunks.  negc = -1 / (2 lengthscale^2).
 hipError_t launch_f64(const double* X, int64_t ldx, const double* Z, int64_t ldz, const double* v,
                       int64_t n, int64_t m, int d, double negc, double variance, int S, double* out,
-                      hipStream_t stream);
+                      hipStream_t stream, const int* done = nullptr);
 
 // y[i] = sum_s partials[s * n + i], s ascending.
-hipError_t launch_reduce(const double* partials, int S, int64_t n, double* y, hipStream_t stream);
+hipError_t launch_reduce(const double* partials, int S, int64_t n, double* y, hipStream_t stream,
+                         const int* done = nullptr);
+
+// d = 1 (kmv_series.hip): y through one series per box of sources.  Whether the points allow that
+// is found on the device; the first word of ws (series_bytes() bytes) then is 1 and y complete, else
+// 0 and y untouched.  launch_lowd, launch_f64 and launch_reduce, given that word as `done`, do
+// nothing where it is not 0.
+int64_t series_bytes();
+bool series_applies(int64_t n, int64_t m, int d, double lengthscale, bool f64);
+template <typename T>
+hipError_t launch_series(const T* X, int64_t ldx, const T* Z, int64_t ldz, const T* v, int64_t n, int64_t m,
+                         double lengthscale, double variance, void* ws, double* y, hipStream_t stream);
 
 // y[i] = 0.
 hipError_t launch_zero(double* y, int64_t n, hipStream_t stream);

@@ -50,7 +50,9 @@ __global__ __launch_bounds__(256) void kmv_zero_kernel(double* __restrict__ y, i
 }
 
 __global__ __launch_bounds__(256) void kmv_reduce_kernel(const double* __restrict__ partials, int S,
-                                                         int64_t n, double* __restrict__ y) {
+                                                         int64_t n, double* __restrict__ y,
+                                                         const int* __restrict__ done) {
+    if (done && *done) return;
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= n) return;
     double acc = partials[i];
@@ -67,7 +69,8 @@ template <int D, bool CONTIG>
 __global__ __launch_bounds__(kLowdTileRows) void kmv_lowd_kernel(
     const float* __restrict__ X, int64_t ldx, const float* __restrict__ Z, int64_t ldz_arg,
     const float* __restrict__ v, int n, int m, int split_len, float negc2, double variance,
-    double* __restrict__ out) {
+    double* __restrict__ out, const int* __restrict__ done) {
+    if (done && *done) return;  // the series made y
     constexpr int U = 8;
     const int64_t ldz = CONTIG ? (int64_t)D : ldz_arg;
     const int s = blockIdx.y;
@@ -415,7 +418,8 @@ template <int D, bool CONTIG>
 __global__ __launch_bounds__(kLowdTileRows) void kmv_lowd_f64_kernel(
     const double* __restrict__ X, int64_t ldx, const double* __restrict__ Z, int64_t ldz_arg,
     const double* __restrict__ v, int n, int m, int split_len, double negc, double variance,
-    double* __restrict__ out) {
+    double* __restrict__ out, const int* __restrict__ done) {
+    if (done && *done) return;  // the series made y
     constexpr int U = 4;
     const int64_t ldz = CONTIG ? (int64_t)D : ldz_arg;
     const int s = blockIdx.y;
@@ -533,41 +537,42 @@ hipError_t launch_zero(double* y, int64_t n, hipStream_t stream) {
     return hipGetLastError();
 }
 
-hipError_t launch_reduce(const double* partials, int S, int64_t n, double* y, hipStream_t stream) {
+hipError_t launch_reduce(const double* partials, int S, int64_t n, double* y, hipStream_t stream,
+                         const int* done) {
     if (n == 0) return hipSuccess;
-    kmv_reduce_kernel<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream>>>(partials, S, n, y);
+    kmv_reduce_kernel<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream>>>(partials, S, n, y, done);
     return hipGetLastError();
 }
 
 template <int D>
 static hipError_t launch_lowd_d(const float* X, int64_t ldx, const float* Z, int64_t ldz,
                                 const float* v, int64_t n, int64_t m, float c2, double variance,
-                                int S, double* out, hipStream_t stream) {
+                                int S, double* out, hipStream_t stream, const int* done) {
     const dim3 grid((unsigned)((n + kLowdTileRows - 1) / kLowdTileRows), (unsigned)S);
     const int split_len = (int)split_length(m, S, kGroup);
     if (ldz == D) {
         kmv_lowd_kernel<D, true><<<grid, dim3(kLowdTileRows), 0, stream>>>(
-            X, ldx, Z, ldz, v, (int)n, (int)m, split_len, -c2, variance, out);
+            X, ldx, Z, ldz, v, (int)n, (int)m, split_len, -c2, variance, out, done);
     } else {
         kmv_lowd_kernel<D, false><<<grid, dim3(kLowdTileRows), 0, stream>>>(
-            X, ldx, Z, ldz, v, (int)n, (int)m, split_len, -c2, variance, out);
+            X, ldx, Z, ldz, v, (int)n, (int)m, split_len, -c2, variance, out, done);
     }
     return hipGetLastError();
 }
 
 hipError_t launch_lowd(const float* X, int64_t ldx, const float* Z, int64_t ldz, const float* v,
                        int64_t n, int64_t m, int d, float c2, double variance, int S, double* out,
-                       hipStream_t stream) {
+                       hipStream_t stream, const int* done) {
     if (n == 0) return hipSuccess;
     switch (d) {
-        case 1: return launch_lowd_d<1>(X, ldx, Z, ldz, v, n, m, c2, variance, S, out, stream);
-        case 2: return launch_lowd_d<2>(X, ldx, Z, ldz, v, n, m, c2, variance, S, out, stream);
-        case 3: return launch_lowd_d<3>(X, ldx, Z, ldz, v, n, m, c2, variance, S, out, stream);
-        case 4: return launch_lowd_d<4>(X, ldx, Z, ldz, v, n, m, c2, variance, S, out, stream);
-        case 5: return launch_lowd_d<5>(X, ldx, Z, ldz, v, n, m, c2, variance, S, out, stream);
-        case 6: return launch_lowd_d<6>(X, ldx, Z, ldz, v, n, m, c2, variance, S, out, stream);
-        case 7: return launch_lowd_d<7>(X, ldx, Z, ldz, v, n, m, c2, variance, S, out, stream);
-        case 8: return launch_lowd_d<8>(X, ldx, Z, ldz, v, n, m, c2, variance, S, out, stream);
+        case 1: return launch_lowd_d<1>(X, ldx, Z, ldz, v, n, m, c2, variance, S, out, stream, done);
+        case 2: return launch_lowd_d<2>(X, ldx, Z, ldz, v, n, m, c2, variance, S, out, stream, done);
+        case 3: return launch_lowd_d<3>(X, ldx, Z, ldz, v, n, m, c2, variance, S, out, stream, done);
+        case 4: return launch_lowd_d<4>(X, ldx, Z, ldz, v, n, m, c2, variance, S, out, stream, done);
+        case 5: return launch_lowd_d<5>(X, ldx, Z, ldz, v, n, m, c2, variance, S, out, stream, done);
+        case 6: return launch_lowd_d<6>(X, ldx, Z, ldz, v, n, m, c2, variance, S, out, stream, done);
+        case 7: return launch_lowd_d<7>(X, ldx, Z, ldz, v, n, m, c2, variance, S, out, stream, done);
+        case 8: return launch_lowd_d<8>(X, ldx, Z, ldz, v, n, m, c2, variance, S, out, stream, done);
         default: return hipErrorInvalidValue;
     }
 }
@@ -575,32 +580,32 @@ hipError_t launch_lowd(const float* X, int64_t ldx, const float* Z, int64_t ldz,
 template <int D>
 static hipError_t launch_f64_d(const double* X, int64_t ldx, const double* Z, int64_t ldz,
                                const double* v, int64_t n, int64_t m, double negc, double variance,
-                               int S, double* out, hipStream_t stream) {
+                               int S, double* out, hipStream_t stream, const int* done) {
     const dim3 grid((unsigned)((n + kLowdTileRows - 1) / kLowdTileRows), (unsigned)S);
     const int split_len = (int)split_length(m, S, kGroup);
     if (ldz == D) {
         kmv_lowd_f64_kernel<D, true><<<grid, dim3(kLowdTileRows), 0, stream>>>(
-            X, ldx, Z, ldz, v, (int)n, (int)m, split_len, negc, variance, out);
+            X, ldx, Z, ldz, v, (int)n, (int)m, split_len, negc, variance, out, done);
     } else {
         kmv_lowd_f64_kernel<D, false><<<grid, dim3(kLowdTileRows), 0, stream>>>(
-            X, ldx, Z, ldz, v, (int)n, (int)m, split_len, negc, variance, out);
+            X, ldx, Z, ldz, v, (int)n, (int)m, split_len, negc, variance, out, done);
     }
     return hipGetLastError();
 }
 
 hipError_t launch_f64(const double* X, int64_t ldx, const double* Z, int64_t ldz, const double* v,
                       int64_t n, int64_t m, int d, double negc, double variance, int S, double* out,
-                      hipStream_t stream) {
+                      hipStream_t stream, const int* done) {
     if (n == 0) return hipSuccess;
     switch (d) {
-        case 1: return launch_f64_d<1>(X, ldx, Z, ldz, v, n, m, negc, variance, S, out, stream);
-        case 2: return launch_f64_d<2>(X, ldx, Z, ldz, v, n, m, negc, variance, S, out, stream);
-        case 3: return launch_f64_d<3>(X, ldx, Z, ldz, v, n, m, negc, variance, S, out, stream);
-        case 4: return launch_f64_d<4>(X, ldx, Z, ldz, v, n, m, negc, variance, S, out, stream);
-        case 5: return launch_f64_d<5>(X, ldx, Z, ldz, v, n, m, negc, variance, S, out, stream);
-        case 6: return launch_f64_d<6>(X, ldx, Z, ldz, v, n, m, negc, variance, S, out, stream);
-        case 7: return launch_f64_d<7>(X, ldx, Z, ldz, v, n, m, negc, variance, S, out, stream);
-        case 8: return launch_f64_d<8>(X, ldx, Z, ldz, v, n, m, negc, variance, S, out, stream);
+        case 1: return launch_f64_d<1>(X, ldx, Z, ldz, v, n, m, negc, variance, S, out, stream, done);
+        case 2: return launch_f64_d<2>(X, ldx, Z, ldz, v, n, m, negc, variance, S, out, stream, done);
+        case 3: return launch_f64_d<3>(X, ldx, Z, ldz, v, n, m, negc, variance, S, out, stream, done);
+        case 4: return launch_f64_d<4>(X, ldx, Z, ldz, v, n, m, negc, variance, S, out, stream, done);
+        case 5: return launch_f64_d<5>(X, ldx, Z, ldz, v, n, m, negc, variance, S, out, stream, done);
+        case 6: return launch_f64_d<6>(X, ldx, Z, ldz, v, n, m, negc, variance, S, out, stream, done);
+        case 7: return launch_f64_d<7>(X, ldx, Z, ldz, v, n, m, negc, variance, S, out, stream, done);
+        case 8: return launch_f64_d<8>(X, ldx, Z, ldz, v, n, m, negc, variance, S, out, stream, done);
         default: break;
     }
     const dim3 grid((unsigned)((n + kLowdTileRows - 1) / kLowdTileRows), (unsigned)S);

@@ -1,0 +1,283 @@
+// gfx950 (CDNA4, MI355X) kernels for y = K v on a line (d = 1): the sources z_j are grouped into
+// boxes a fraction of a lengthscale wide and act through one short series per box, so the work
+// goes with n + m and not with n m.  The general kernels (kmv_kernels.hip) make every entry of K.
+//
+// With a = (x - c) / l and b = (z - c) / l for a box of centre c,
+//     exp(-(x - z)^2 / (2 l^2)) = exp(-a^2 / 2) * exp(a b) * exp(-b^2 / 2)
+//     sum_j v_j K(x, z_j)       = exp(-a^2 / 2) * sum_p a^p * [ sum_j v_j exp(-b_j^2 / 2) b_j^p / p! ],
+// and the bracket, the box's moment p, does not depend on x.  |b| <= h, half a box's width in
+// lengthscales.  Cutting the series of exp(a b) after P terms leaves at most (|a| h)^P / P! beside
+// exp(-|a| h), for every |a| at which exp(-a^2 / 2) is not zero in the entry point's own precision:
+//     fp32 entry: h = 1/2, P = 34: relative to the entry itself below 2e-8 for |a| <= 13.2, where the
+//                 entry is the smallest normal number, and below 1e-16 for |a| <= 8
+//     fp64 entry: h = 1/4, P = 56: below 1e-15 for |a| <= 38.6, where the entry is zero
+// Boxes of half the width with P = 22 and 36 were 25 % slower: a box costs a row its P multiply-adds
+// and an exponential, about as much again.
+// Everything is computed in fp64, for the fp32 entry point too, whose own entries and 64-term sums
+// carry 1e-7.  Every sum has a fixed order.
+//
+// What bounds it: fp64 issue.  n = m = 1e6 in fp32, l = 1, normal points (10 boxes): bounds 5.6 us,
+// moments 44.5, table 5.4, rows 49, against 160 ms for the entries one by one; 2e5 x 2e5 in fp64:
+// 4.8, 59, 6.2, 43 us against 35.4 ms.  Error against 64 bits 7e-16 (fp32 entry by entry: 2.6e-7;
+// fp64: 5e-15).
+#include <hip/hip_runtime.h>
+
+#include <cmath>
+#include <cstdint>
+
+#include "kmv_kernels.h"
+#include "knn_config.h"
+
+namespace kmv {
+
+namespace {
+
+template <typename T>
+struct Series;
+template <>
+struct Series<float> {
+    static constexpr int P = 34;
+    static constexpr double h = 0.5;
+    static constexpr double far = 104.0;  // a^2 / 2 above which an entry is zero (fp32, denormals included)
+};
+template <>
+struct Series<double> {
+    static constexpr int P = 56;
+    static constexpr double h = 0.25;
+    static constexpr double far = 746.0;
+};
+
+constexpr int kRow = 64;          // doubles per box in the table: P moments, the centre at kRow - 1
+constexpr int kBoundsGroups = 256;
+constexpr int kMaxBoxes = 1024;
+constexpr int kMomentGroups = 2048;  // workgroups of the moment kernel: box x slice of the sources
+constexpr int kMaxSlices = 64;
+
+// workspace: header | bounds of the workgroups [3][256] | the boxes' table | partial moments
+struct Header {
+    int ok;      // the series applies: the general kernel has nothing to do
+    int boxes;
+    int slices;
+};
+constexpr int64_t kBoundsAt = 256;
+constexpr int64_t kTableAt = kBoundsAt + 3 * kBoundsGroups * 8;
+constexpr int64_t kPartialAt = kTableAt + (int64_t)kMaxBoxes * kRow * 8;
+constexpr int64_t kBytes = kPartialAt + (int64_t)kMomentGroups * kRow * 8;
+static_assert(kBoundsAt % 256 == 0 && kTableAt % 256 == 0 && kPartialAt % 256 == 0, "aligned pieces");
+
+// lowest and highest source, and whether all sources and weights are finite
+template <typename T>
+__global__ __launch_bounds__(256) void kmv_bounds_kernel(const T* __restrict__ Z, int64_t ldz,
+                                                         const T* __restrict__ v, int64_t m,
+                                                         double* __restrict__ bounds) {
+    __shared__ double part[3][4];
+    double lo = HUGE_VAL, hi = -HUGE_VAL, bad = 0.0;
+    for (int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x; j < m; j += 256 * kBoundsGroups) {
+        const double z = (double)Z[j * ldz], w = (double)v[j];
+        lo = fmin(lo, z);
+        hi = fmax(hi, z);
+        if (!(fabs(z) < HUGE_VAL) || !(fabs(w) < HUGE_VAL)) bad = 1.0;
+    }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+        lo = fmin(lo, __shfl_xor(lo, o));
+        hi = fmax(hi, __shfl_xor(hi, o));
+        bad = fmax(bad, __shfl_xor(bad, o));
+    }
+    const int wave = threadIdx.x >> 6;
+    if ((threadIdx.x & 63) == 0) {
+        part[0][wave] = lo;
+        part[1][wave] = hi;
+        part[2][wave] = bad;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        bounds[blockIdx.x] = fmin(fmin(part[0][0], part[0][1]), fmin(part[0][2], part[0][3]));
+        bounds[kBoundsGroups + blockIdx.x] = fmax(fmax(part[1][0], part[1][1]), fmax(part[1][2], part[1][3]));
+        bounds[2 * kBoundsGroups + blockIdx.x] = part[2][0] + part[2][1] + part[2][2] + part[2][3];
+    }
+}
+
+// Workgroup (box, slice): the moments of the box's sources among one slice of them.  A thread
+// walks its sources in ascending order; threads are added in a fixed tree.
+template <typename T>
+__global__ __launch_bounds__(256) void kmv_moments_kernel(const T* __restrict__ Z, int64_t ldz,
+                                                          const T* __restrict__ v, int64_t m,
+                                                          double lengthscale,
+                                                          const double* __restrict__ bounds,
+                                                          Header* __restrict__ header,
+                                                          double* __restrict__ table,
+                                                          double* __restrict__ partial) {
+    constexpr int P = Series<T>::P;
+    __shared__ double sum[4][P];
+    __shared__ double part[3][4];
+    const int wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63;
+    // every workgroup puts the bounds together for itself
+    double lo = bounds[threadIdx.x], hi = bounds[kBoundsGroups + threadIdx.x],
+           bad = bounds[2 * kBoundsGroups + threadIdx.x];
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+        lo = fmin(lo, __shfl_xor(lo, o));
+        hi = fmax(hi, __shfl_xor(hi, o));
+        bad = fmax(bad, __shfl_xor(bad, o));
+    }
+    if (lane == 0) {
+        part[0][wave] = lo;
+        part[1][wave] = hi;
+        part[2][wave] = bad;
+    }
+    __syncthreads();
+    lo = fmin(fmin(part[0][0], part[0][1]), fmin(part[0][2], part[0][3]));
+    hi = fmax(fmax(part[1][0], part[1][1]), fmax(part[1][2], part[1][3]));
+    bad = part[2][0] + part[2][1] + part[2][2] + part[2][3];
+    const double rl = 1.0 / lengthscale;
+    const double width = 2.0 * Series<T>::h * lengthscale;
+    const double rw = 1.0 / width;
+    const double span = (hi - lo) * rw;
+    // The general kernel takes over where a source or weight is not finite (its sums then say
+    // so), where the boxes would be too many, or so many that a row costs as much in boxes (about
+    // 60 fp64 operations each) as in sources (8 to 30), or where the coordinates' own spacing is no
+    // longer small beside a box (a centre could then not lie in the middle).
+    const bool ok = bad == 0.0 && span < (double)kMaxBoxes - 1.0 && (span + 1.0) * 16.0 <= (double)m &&
+                    fmax(fabs(lo), fabs(hi)) * 0x1p-52 <= width * 0x1p-7;
+    const int boxes = ok ? (int)span + 1 : 0;
+    int slices = 1;
+    if (ok) {
+        slices = kMomentGroups / boxes;
+        if (slices > kMaxSlices) slices = kMaxSlices;
+        const int64_t useful = (m + 1023) / 1024;
+        if (slices > useful) slices = (int)useful;
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) *header = Header{ok ? 1 : 0, boxes, slices};
+    const int box = (int)blockIdx.x / slices;
+    const int slice = (int)blockIdx.x - box * slices;
+    if (box >= boxes) return;  // whole workgroup
+    const double c = fma((double)box + 0.5, width, lo);
+    double acc[P];
+#pragma unroll
+    for (int p = 0; p < P; ++p) acc[p] = 0.0;
+    const int64_t len = (m + slices - 1) / slices;
+    const int64_t j0 = slice * len;
+    const int64_t j1 = j0 + len < m ? j0 + len : m;
+    constexpr int U = 4;
+    for (int64_t j = j0 + threadIdx.x; j < j1; j += 256 * U) {
+        double z[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t jj = j + 256 * u;
+            z[u] = (double)Z[(jj < j1 ? jj : j1 - 1) * ldz];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t jj = j + 256 * u;
+            int g = (int)((z[u] - lo) * rw);
+            if (g > boxes - 1) g = boxes - 1;
+            if (g == box && jj < j1) {
+                const double b = (z[u] - c) * rl;
+                double w = (double)v[jj] * exp(-0.5 * b * b);
+#pragma unroll
+                for (int p = 0; p < P; ++p) {
+                    acc[p] += w;
+                    w *= b;
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        double s = acc[p];
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) s += __shfl_xor(s, o);
+        if (lane == 0) sum[wave][p] = s;
+    }
+    __syncthreads();
+    const int t = threadIdx.x;
+    if (t < P) partial[(int64_t)blockIdx.x * kRow + t] = (sum[0][t] + sum[1][t]) + (sum[2][t] + sum[3][t]);
+    if (slice == 0 && t == P) table[(int64_t)box * kRow + kRow - 1] = c;
+}
+
+// table[box][p] = (sum over the slices, ascending) / p!
+template <typename T>
+__global__ __launch_bounds__(64) void kmv_table_kernel(const Header* __restrict__ header,
+                                                       const double* __restrict__ partial,
+                                                       double* __restrict__ table) {
+    constexpr int P = Series<T>::P;
+    static_assert(P < kRow && P <= 64, "one lane per moment, the centre behind them");
+    const int box = blockIdx.x, p = threadIdx.x;
+    if (!header->ok || box >= header->boxes || p >= P) return;
+    const int slices = header->slices;
+    double s = 0.0, factorial = 1.0;
+#pragma unroll 8
+    for (int i = 0; i < slices; ++i) s += partial[((int64_t)box * slices + i) * kRow + p];
+    for (int i = 2; i <= p; ++i) factorial *= (double)i;
+    table[(int64_t)box * kRow + p] = s / factorial;
+}
+
+// One row per lane; the boxes are the same for the whole wave, so their moments come through
+// scalar loads.  Per box and row: P multiply-adds and one exponential.
+template <typename T>
+__global__ __launch_bounds__(256) void kmv_series_kernel(const T* __restrict__ X, int64_t ldx, int64_t n,
+                                                         double lengthscale, double variance,
+                                                         const Header* __restrict__ header,
+                                                         const double* __restrict__ table,
+                                                         double* __restrict__ y) {
+    constexpr int P = Series<T>::P;
+    if (!header->ok) return;
+    const int boxes = header->boxes;
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const double rl = 1.0 / lengthscale;
+    const double x = (double)X[(i < n ? i : n - 1) * ldx];
+    double total = 0.0;
+    for (int box = 0; box < boxes; ++box) {
+        const double* __restrict__ row = table + (int64_t)box * kRow;
+        const double a = (x - row[kRow - 1]) * rl;
+        const double e = 0.5 * a * a;
+        if (__builtin_amdgcn_ballot_w64(e <= Series<T>::far) == 0) continue;
+        double s = row[P - 1];
+#pragma unroll
+        for (int p = P - 2; p >= 0; --p) s = fma(s, a, row[p]);
+        if (e <= Series<T>::far) total = fma(exp(-e), s, total);
+    }
+    if (x != x) total = x;  // as the sum over such entries of K
+    if (i < n) y[i] = variance * total;
+}
+
+}  // namespace
+
+int64_t series_bytes() { return kBytes; }
+
+bool series_applies(int64_t n, int64_t m, int d, double lengthscale, bool f64) {
+    // Below these sizes the entries themselves are made in less time than the launches here take:
+    // about 30 us, 6e12 entries per second in fp32 and 1e12 in fp64.
+    const double entries = (double)n * (double)m;
+    if (d != 1 || entries < (f64 ? 4e7 : 3e8)) return false;
+    // (the general kernels form 1 / (2 l^2): where that or its inverse leaves the range of the type
+    // they decide what comes out)
+    return f64 ? (lengthscale >= 1e-100 && lengthscale <= 1e100)
+               : (lengthscale >= 1e-15 && lengthscale <= 1e15);
+}
+
+template <typename T>
+hipError_t launch_series(const T* X, int64_t ldx, const T* Z, int64_t ldz, const T* v, int64_t n, int64_t m,
+                         double lengthscale, double variance, void* ws, double* y, hipStream_t stream) {
+    unsigned char* base = static_cast<unsigned char*>(ws);
+    Header* header = reinterpret_cast<Header*>(base);
+    double* bounds = reinterpret_cast<double*>(base + kBoundsAt);
+    double* table = reinterpret_cast<double*>(base + kTableAt);
+    double* partial = reinterpret_cast<double*>(base + kPartialAt);
+    kmv_bounds_kernel<T><<<dim3(kBoundsGroups), dim3(256), 0, stream>>>(Z, ldz, v, m, bounds);
+    kmv_moments_kernel<T><<<dim3(kMomentGroups), dim3(256), 0, stream>>>(Z, ldz, v, m, lengthscale, bounds,
+                                                                         header, table, partial);
+    kmv_table_kernel<T><<<dim3(kMaxBoxes), dim3(64), 0, stream>>>(header, partial, table);
+    kmv_series_kernel<T><<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream>>>(
+        X, ldx, n, lengthscale, variance, header, table, y);
+    return hipGetLastError();
+}
+
+template hipError_t launch_series<float>(const float*, int64_t, const float*, int64_t, const float*, int64_t,
+                                         int64_t, double, double, void*, double*, hipStream_t);
+template hipError_t launch_series<double>(const double*, int64_t, const double*, int64_t, const double*,
+                                          int64_t, int64_t, double, double, void*, double*, hipStream_t);
+
+}  // namespace kmv

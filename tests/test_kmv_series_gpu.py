@@ -1,0 +1,126 @@
+"""y = K v on a line (d = 1) through boxes of sources, against the fp64 oracle and the general kernel.
+
+Tolerance: the general kernels' own bounds (test_kmv_gpu.py), which the series stays inside: per
+entry and at eps = 2^-24 (fp32 entry point) 4e-6 + 5 eps a, at eps = 2^-53 (fp64) 2 ((m + 8) eps +
+5 eps a), a = (x - z)^2 / (2 l^2), times the sum of magnitudes.
+"""
+import numpy as np
+import pytest
+
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def K():
+    import paper_2206_14148_amd as K
+    assert torch.cuda.is_available(), "these tests need the GPU"
+    K.load()
+    return K
+
+
+def bound(x, Z, v, ls, dtype):
+    a = 0.5 * ((x - Z[:, 0].astype(np.float64)) / ls) ** 2
+    mag = np.exp(-a) * np.abs(v.astype(np.float64))
+    if dtype == "f64":
+        return 2 * (mag * ((len(v) + 8) * 2.0 ** -53 + 5 * 2.0 ** -53 * a)).sum() + 1e-300
+    return (mag * (4e-6 + 5 * 2.0 ** -24 * a)).sum() + 1e-37 * np.abs(v).sum()
+
+
+def general(K, X, Z, v, ls, dtype):
+    """The same call with the plan's workspace only: every entry of K is made."""
+    n, m = X.shape[0], Z.shape[0]
+    ws = torch.empty(max(256, K.kmv_plan(n, m, 1, W.GB, dtype).workspace_bytes), dtype=torch.uint8, device="cuda")
+    return K.kmv_apply(X, Z, v, 1.5, ls, W.GB, workspace=ws)
+
+
+# (dtype, n, m, lengthscale, span of the sources): boxes are l (fp64: l / 2) wide, 16 sources
+# a box are asked for, more than 1023 boxes are not taken
+CASES = [
+    ("f32", 60_001, 5_003, 1.0, 0.0),        # all sources in one place
+    ("f32", 20_011, 16_385, 1.0, 1.4),       # two boxes, slices of unequal length
+    ("f32", 300_007, 1_001, 2.0, 10.0),      # one slice
+    ("f32", 20_001, 20_001, 1e-3, 1.0),      # 1001 boxes: one slice each
+    ("f32", 20_001, 20_001, 1e-3, 1.1),      # more than 1023: the general kernel
+    ("f64", 60_001, 5_003, 1.0, 0.0),
+    ("f64", 20_003, 40_009, 1.0, 12.0),
+    ("f64", 60_001, 1_001, 3.0, 10.0),
+    ("f64", 20_001, 20_001, 1e-3, 0.5),      # 1001 boxes
+    ("f64", 20_001, 20_001, 1e-3, 0.52),     # 1041: the general kernel
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "%s_n%d_m%d_l%g_span%g" % c)
+def test_matches_oracle(K, oracle, case):
+    dtype, n, m, ls, span = case
+    real = np.float64 if dtype == "f64" else np.float32
+    rng = np.random.Generator(np.random.PCG64(n + m))
+    Z = (3.0 + span * rng.random((m, 1))).astype(real)
+    # rows among the sources, on both sides of them, and far away: an entry of 1e-30, an empty sum
+    X = (3.0 - 6 * ls + (span + 12 * ls) * rng.random((n, 1))).astype(real)
+    X[0] = 3.0 - 11.7 * ls
+    X[1] = 3.0 + span + 1e4 * ls
+    X[2], X[3] = Z.min(), Z.max()
+    v = rng.standard_normal(m).astype(real)
+    Xd, Zd, vd = (torch.from_numpy(a).cuda() for a in (X, Z, v))
+    y = K.kmv_apply(Xd, Zd, vd, 1.5, ls, W.GB)
+    again = K.kmv_apply(Xd, Zd, vd, 1.5, ls, W.GB)
+    # strided rows: the same numbers
+    Xw, Zw = torch.full((n, 3), 9.0, dtype=Xd.dtype, device="cuda"), torch.full((m, 2), -9.0, dtype=Xd.dtype, device="cuda")
+    Xw[:, :1], Zw[:, :1] = Xd, Zd
+    strided = K.kmv_apply(Xw[:, :1], Zw[:, :1], vd, 1.5, ls, W.GB)
+    other = general(K, Xd, Zd, vd, ls, dtype)
+    torch.cuda.synchronize()
+    assert torch.equal(y, again) and torch.equal(y, strided)
+    taken = not torch.equal(y, other)
+    assert taken == (span / (ls * (0.5 if dtype == "f64" else 1.0)) < 1023)
+    rows = np.unique(np.concatenate([np.arange(8), rng.integers(0, n, 40), [n - 1]]))
+    ref = (oracle.kmv_f64 if dtype == "f64" else oracle.kmv)(X, Z, v, 1.5, ls, rows=rows)
+    tol = np.array([1.5 * bound(float(X[i, 0]), Z, v, ls, dtype) for i in rows])
+    err = np.abs(y.cpu().numpy()[rows] - ref)
+    print("worst err/tol", float((err / tol).max()), "taken", taken, flush=True)
+    assert (err <= tol).all()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+def test_values_that_are_not_finite(K, dtype):
+    # a row that is not a number stays one, a row at infinity is zero; a source or a weight that is
+    # not finite leaves the call to the general kernel
+    real = torch.float64 if dtype == "f64" else torch.float32
+    n, m = 30_001, 20_001
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(1)
+    X, Z = (torch.randn(r, 1, generator=gen, device="cuda", dtype=real) for r in (n, m))
+    v = torch.randn(m, generator=gen, device="cuda", dtype=real)
+    X[5], X[6], X[7] = float("nan"), float("inf"), -float("inf")
+    y, ref = K.kmv_apply(X, Z, v, 1.5, 1.0, W.GB), general(K, X, Z, v, 1.0, dtype)
+    torch.cuda.synchronize()
+    assert not torch.equal(y[8:], ref[8:])
+    assert torch.isnan(y[5]) and torch.isnan(ref[5]) and (y[6:8] == 0).all() and (ref[6:8] == 0).all()
+    for what, value in (("v", float("inf")), ("v", float("nan")), ("Z", float("nan")), ("Z", float("inf"))):
+        Zb, vb = Z.clone(), v.clone()
+        (Zb if what == "Z" else vb)[m - 1] = value
+        a, b = K.kmv_apply(X, Zb, vb, 1.5, 1.0, W.GB), general(K, X, Zb, vb, 1.0, dtype)
+        torch.cuda.synchronize()
+        assert torch.equal(a.nan_to_num(0.25), b.nan_to_num(0.25)), (what, value)
+
+
+def test_workspace_stays_inside_its_bytes_and_the_limit(K):
+    n, m = 40_001, 20_001
+    full = K.load().kmv_workspace_bytes(n, m, 1, 1.0, W.GB)
+    plan = K.kmv_plan(n, m, 1, W.GB)
+    assert plan.workspace_bytes < full <= plan.workspace_bytes + 2 ** 21
+    assert K.load().kmv_workspace_bytes(n, m, 1, 1.0, full - 1) < full
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(2)
+    X, Z = (torch.randn(r, 1, generator=gen, device="cuda") for r in (n, m))
+    v = torch.randn(m, generator=gen, device="cuda")
+    buf = torch.full((full + 4096,), 0xA5, dtype=torch.uint8, device="cuda")
+    y = K.kmv_apply(X, Z, v, 1.0, 1.0, W.GB, workspace=buf[:full])
+    tight = K.kmv_apply(X, Z, v, 1.0, 1.0, 256)
+    torch.cuda.synchronize()
+    assert (buf[full:] == 0xA5).all()
+    assert not torch.equal(y, tight) and torch.allclose(y, tight, rtol=1e-4, atol=1e-3)
