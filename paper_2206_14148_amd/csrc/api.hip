@@ -218,6 +218,8 @@ knn_status run_search(const knn_plan_t& plan, const float* Q, int64_t ldq, const
             ? reinterpret_cast<float*>(xp + align_up((uint64_t)plan.slab_points * (uint64_t)pk_padded_chunks(d) * 32))
             : xn;
 
+    const int64_t chunk_rows = plan.chunk_rows < m ? plan.chunk_rows : m;
+
     hipError_t e;
     if (plan.path == KNN_PATH_MFMA_SPLIT || packed_plan) {
         hipEvent_t t0 = mark(stream);
@@ -245,7 +247,8 @@ knn_status run_search(const knn_plan_t& plan, const float* Q, int64_t ldq, const
     } else if (plan.path == KNN_PATH_LOWD_MFMA || plan.path == KNN_PATH_LOWD_BF16) {
         hipEvent_t t0 = mark(stream);
         e = plan.path == KNN_PATH_LOWD_BF16
-                ? launch_lowd_bf16(Q, ldq, X, ldx, ws, 0, n, d, k, S, true, plan.seed_cells, nullptr, nullptr, stream)
+                ? launch_lowd_bf16(Q, ldq, X, ldx, ws, 0, n, d, k, S, true, plan.seed_cells, chunk_rows, nullptr, nullptr,
+                                   nullptr, stream)
                 : launch_lowd_mfma(Q, ldq, X, ldx, ws, 0, n, d, k, S, true, nullptr, nullptr, stream);
         if (e != hipSuccess) {
             drop_bracket(t0);
@@ -272,8 +275,8 @@ knn_status run_search(const knn_plan_t& plan, const float* Q, int64_t ldq, const
         else if (plan.path == KNN_PATH_LOWD_MFMA)
             e = launch_lowd_mfma(Qc, ldq, X, ldx, ws, rows, n, d, k, S, false, lk, li, stream);
         else if (plan.path == KNN_PATH_LOWD_BF16)
-            e = launch_lowd_bf16(Qc, ldq, X, ldx, ws, rows, n, d, k, S, false, plan.seed_cells, lk,
-                                 li, stream);
+            e = launch_lowd_bf16(Qc, ldq, X, ldx, ws, rows, n, d, k, S, false, plan.seed_cells,
+                                 chunk_rows, idx + row0 * k, lk, li, stream);
         else if (plan.path == KNN_PATH_MFMA_SPLIT || packed_plan) {
             if (wide_plan && packed) {
                 // the queries' B operands bf16(-2 q) in operand order; thresholds start from +inf

@@ -34,6 +34,13 @@ constexpr int kSeedMaxD = 3;
 constexpr int kSeedMaxCells = 32768;
 constexpr int kSeedCellsPerPointNum = 2;
 constexpr int kSeedCellsPerPointDen = 3;
+// octree search (knn_grid.hip), d <= kSeedMaxD: header word that says it answers the call (the two
+// words from kGridWord + 2 on: its measure of how unevenly the points are spread), longest list kept
+// in registers, fewest points
+constexpr int kGridWord = 32;
+constexpr int kGridMaxK = 32;
+constexpr int64_t kGridMinPoints = 4096;
+constexpr int kGridMaxCells = 1 << 21;
 
 // fp32 MFMA tiles of the SGPR sums (sgpr_kernels.hip): LDS staging of 128-row tiles
 constexpr int kMfmaKC = 16;          // K columns staged in LDS per pipeline step

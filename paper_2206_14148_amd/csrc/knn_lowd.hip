@@ -9,6 +9,7 @@
 #include <cstdint>
 #include <type_traits>
 
+#include "knn_cells.h"
 #include "knn_config.h"
 #include "knn_device.h"
 #include "knn_kernels.h"
@@ -640,15 +641,6 @@ __device__ __forceinline__ unsigned bf16_bits(float x) {
 }
 __device__ __forceinline__ float bf16_value(unsigned bits) { return __uint_as_float(bits << 16); }
 
-// floats <-> unsigned keys with the same order (for atomicMin / atomicMax)
-__device__ __forceinline__ unsigned ordered_bits(float f) {
-    const unsigned u = __float_as_uint(f);
-    return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-}
-__device__ __forceinline__ float ordered_value(unsigned k) {
-    return __uint_as_float((k & 0x80000000u) ? (k & 0x7fffffffu) : ~k);
-}
-
 // header words of the packed area: 0 max ||x - c||^2 (bits of a non-negative float),
 // 1 .. kPbMaxD per-dimension minimum, kPbMaxD + 1 .. 2 kPbMaxD per-dimension maximum (ordered keys)
 __global__ void knn_bbox_init_kernel(unsigned* __restrict__ hdr) {
@@ -656,6 +648,7 @@ __global__ void knn_bbox_init_kernel(unsigned* __restrict__ hdr) {
     if (t == 0) hdr[0] = 0u;
     if (t >= 1 && t <= kPbMaxD) hdr[t] = 0xffffffffu;
     if (t > kPbMaxD && t <= 2 * kPbMaxD) hdr[t] = 0u;
+    if (t >= kGridWord && t < kGridWord + 4) hdr[t] = 0u;
 }
 
 template <int D>
@@ -718,42 +711,8 @@ __device__ __forceinline__ void bbox_centre(const unsigned* __restrict__ hdr, fl
 // Pairs beyond the bound never reach the exact test, which takes most of the list warm-up away;
 // results do not change, because every pair at or below the true k-th distance still passes.
 // ---------------------------------------------------------------------------------------
-template <int D>
-struct SeedGrid {
-    float mn[D], inv_w[D], w[D], slack[D];
-    int G;
-};
-
-template <int D>
-__device__ __forceinline__ SeedGrid<D> seed_grid(const unsigned* __restrict__ hdr, int G) {
-    SeedGrid<D> g;
-    g.G = G;
-#pragma unroll
-    for (int t = 0; t < D; ++t) {
-        const float mn = ordered_value(hdr[1 + t]);
-        const float mx = ordered_value(hdr[1 + kPbMaxD + t]);
-        float rg = mx - mn;
-        if (!(rg > 1e-30f)) rg = 1.f;  // all points share this coordinate: one cell holds them
-        g.mn[t] = mn;
-        g.inv_w[t] = (float)G / rg;
-        g.w[t] = rg / (float)G;
-        // A point whose computed cell number is c lies in mn + [c w, (c + 1) w] up to the
-        // roundings of (x - mn) * inv_w, of w and of the two ends: under 16 ulps of the
-        // magnitudes involved; the slack is twice that.
-        g.slack[t] = 0x1p-19f * (fabsf(mn) + fabsf(mx) + rg);
-    }
-    return g;
-}
-
-// cell number along axis t, the same expression for points and queries (queries outside the
-// box land in the nearest cell)
-template <int D>
-__device__ __forceinline__ int seed_cell(const SeedGrid<D>& g, int t, float x) {
-    const float u = (x - g.mn[t]) * g.inv_w[t];
-    return (int)fminf(fmaxf(u, 0.f), (float)(g.G - 1));  // NaN -> 0
-}
-
-__global__ void knn_zero_ints_kernel(int* __restrict__ p, int count) {
+__global__ void knn_zero_ints_kernel(const unsigned* __restrict__ hdr, int* __restrict__ p, int count) {
+    if (hdr[kGridWord]) return;  // (the octree's cells lie there)
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i < count) p[i] = 0;
 }
@@ -770,6 +729,7 @@ template <int D>
 __global__ __launch_bounds__(256) void knn_cell_count_kernel(const float* __restrict__ X, int64_t ldx,
                                                              int n, const unsigned* __restrict__ hdr,
                                                              int G, int* __restrict__ counts) {
+    if (hdr[kGridWord]) return;  // the octree search (knn_grid.hip) answers the call
     const int j = blockIdx.x * 256 + threadIdx.x;
     if (j >= n) return;
     const SeedGrid<D> g = seed_grid<D>(hdr, G);
@@ -778,8 +738,10 @@ __global__ __launch_bounds__(256) void knn_cell_count_kernel(const float* __rest
 
 // starts[c] = number of points in the cells before c (starts[ncell] = n); the counts are set
 // back to zero, to serve as the cells' fill cursors.  One workgroup: ncell <= kSeedMaxCells.
-__global__ __launch_bounds__(256) void knn_cell_scan_kernel(int* __restrict__ counts, int ncell,
+__global__ __launch_bounds__(256) void knn_cell_scan_kernel(const unsigned* __restrict__ hdr,
+                                                            int* __restrict__ counts, int ncell,
                                                             int* __restrict__ starts) {
+    if (hdr[kGridWord]) return;
     __shared__ int part[256];
     const int t = threadIdx.x;
     const int per = (ncell + 255) / 256;
@@ -814,6 +776,7 @@ __global__ __launch_bounds__(256) void knn_cell_fill_kernel(const float* __restr
                                                             int G, const int* __restrict__ starts,
                                                             int* __restrict__ cursor,
                                                             f32x4* __restrict__ sorted) {
+    if (hdr[kGridWord]) return;
     const int j = blockIdx.x * 256 + threadIdx.x;
     if (j >= n) return;
     const SeedGrid<D> g = seed_grid<D>(hdr, G);
@@ -950,6 +913,7 @@ __global__ __launch_bounds__(256) void knn_pack_bf16_kernel(const float* __restr
                                                             int64_t ldx, int n,
                                                             uint4* __restrict__ Xp,
                                                             unsigned* __restrict__ hdr) {
+    if (hdr[kGridWord]) return;
     constexpr int NM = FilterSlots<D>::kMfmas;
     const int j = blockIdx.x * 256 + threadIdx.x;
     float c[D];
@@ -1017,6 +981,7 @@ __global__ __launch_bounds__(256, FilterSlots<D>::kMfmas == 1 ? 4 : 3) void knn_
     sc.list_key = reinterpret_cast<float*>(sc.cand_idx + kWave);
     sc.list_idx = reinterpret_cast<int*>(sc.list_key + k);
 
+    if (hdr[kGridWord]) return;
     const int s = blockIdx.y;
     const int wave_row0 = (blockIdx.x * 4 + wave) * (NS * 32);
     if (wave_row0 >= rows) return;  // whole wave idle; no workgroup barrier is used below
@@ -1380,7 +1345,7 @@ static hipError_t launch_lowd_mfma_d(const float* Q, int64_t ldq, const float* X
 template <int D>
 static hipError_t launch_lowd_bf16_d(const float* Q, int64_t ldq, const float* X, int64_t ldx,
                                      void* packed, int64_t rows, int64_t n, int k, int S,
-                                     bool pack, int seed_cells, float* lk, int* li,
+                                     bool pack, int seed_cells, int64_t chunk_rows, int* order, float* lk, int* li,
                                      hipStream_t stream) {
     constexpr int NM = FilterSlots<D>::kMfmas;
     unsigned* hdr = static_cast<unsigned*>(packed);
@@ -1401,14 +1366,20 @@ static hipError_t launch_lowd_bf16_d(const float* Q, int64_t ldq, const float* X
         knn_bbox_init_kernel<<<dim3(1), dim3(64), 0, stream>>>(hdr);
         const unsigned bgrid = pgrid.x < 1024u ? pgrid.x : 1024u;
         knn_bbox_kernel<D><<<dim3(bgrid), dim3(256), 0, stream>>>(X, ldx, (int)n, hdr);
+        if constexpr (D <= kSeedMaxD) {
+            if (seed_cells > 0 && grid_applies(chunk_rows, n, k)) {
+                hipError_t eg = launch_grid_build(X, ldx, n, D, hdr, Xp, sorted, stream);
+                if (eg != hipSuccess) return eg;
+            }
+        }
         knn_pack_bf16_kernel<D><<<pgrid, dim3(256), 0, stream>>>(X, ldx, (int)n, Xp, hdr);
         if constexpr (D <= kSeedMaxD) {
             if (seed_cells > 0) {
                 knn_zero_ints_kernel<<<dim3((unsigned)((ncell + 255) / 256)), dim3(256), 0, stream>>>(
-                    cursor, ncell);
+                    hdr, cursor, ncell);
                 knn_cell_count_kernel<D><<<pgrid, dim3(256), 0, stream>>>(X, ldx, (int)n, hdr,
                                                                           seed_cells, cursor);
-                knn_cell_scan_kernel<<<dim3(1), dim3(256), 0, stream>>>(cursor, ncell, starts);
+                knn_cell_scan_kernel<<<dim3(1), dim3(256), 0, stream>>>(hdr, cursor, ncell, starts);
                 knn_cell_fill_kernel<D><<<pgrid, dim3(256), 0, stream>>>(
                     X, ldx, (int)n, hdr, seed_cells, starts, cursor, sorted);
             }
@@ -1417,6 +1388,12 @@ static hipError_t launch_lowd_bf16_d(const float* Q, int64_t ldq, const float* X
         if (e0 != hipSuccess) return e0;
     }
     if (rows == 0) return hipSuccess;
+    if constexpr (D <= kSeedMaxD) {
+        if (seed_cells > 0 && grid_applies(chunk_rows, n, k)) {
+            hipError_t eg = launch_grid_search(Q, ldq, X, ldx, rows, n, D, k, S, hdr, Xp, sorted, order, lk, li, stream);
+            if (eg != hipSuccess) return eg;
+        }
+    }
     const size_t per_wave = (size_t)(2 * kPbSets * 32 * kPbCand + 2 * kWave + 2 * k) * 4;
     const size_t lds = per_wave * 4;
     hipError_t e = raise_lds_limit(knn_lowd_bf16_kernel<D>, lds);
@@ -1432,16 +1409,16 @@ static hipError_t launch_lowd_bf16_d(const float* Q, int64_t ldq, const float* X
 
 hipError_t launch_lowd_bf16(const float* Q, int64_t ldq, const float* X, int64_t ldx, void* packed,
                             int64_t rows, int64_t n, int d, int k, int S, bool pack, int seed_cells,
-                            float* lk, int* li, hipStream_t stream) {
+                            int64_t chunk_rows, int* order, float* lk, int* li, hipStream_t stream) {
     switch (d) {
-        case 1: return launch_lowd_bf16_d<1>(Q, ldq, X, ldx, packed, rows, n, k, S, pack, seed_cells, lk, li, stream);
-        case 2: return launch_lowd_bf16_d<2>(Q, ldq, X, ldx, packed, rows, n, k, S, pack, seed_cells, lk, li, stream);
-        case 3: return launch_lowd_bf16_d<3>(Q, ldq, X, ldx, packed, rows, n, k, S, pack, seed_cells, lk, li, stream);
-        case 4: return launch_lowd_bf16_d<4>(Q, ldq, X, ldx, packed, rows, n, k, S, pack, seed_cells, lk, li, stream);
-        case 5: return launch_lowd_bf16_d<5>(Q, ldq, X, ldx, packed, rows, n, k, S, pack, seed_cells, lk, li, stream);
-        case 6: return launch_lowd_bf16_d<6>(Q, ldq, X, ldx, packed, rows, n, k, S, pack, seed_cells, lk, li, stream);
-        case 7: return launch_lowd_bf16_d<7>(Q, ldq, X, ldx, packed, rows, n, k, S, pack, seed_cells, lk, li, stream);
-        case 8: return launch_lowd_bf16_d<8>(Q, ldq, X, ldx, packed, rows, n, k, S, pack, seed_cells, lk, li, stream);
+        case 1: return launch_lowd_bf16_d<1>(Q, ldq, X, ldx, packed, rows, n, k, S, pack, seed_cells, chunk_rows, order, lk, li, stream);
+        case 2: return launch_lowd_bf16_d<2>(Q, ldq, X, ldx, packed, rows, n, k, S, pack, seed_cells, chunk_rows, order, lk, li, stream);
+        case 3: return launch_lowd_bf16_d<3>(Q, ldq, X, ldx, packed, rows, n, k, S, pack, seed_cells, chunk_rows, order, lk, li, stream);
+        case 4: return launch_lowd_bf16_d<4>(Q, ldq, X, ldx, packed, rows, n, k, S, pack, seed_cells, chunk_rows, order, lk, li, stream);
+        case 5: return launch_lowd_bf16_d<5>(Q, ldq, X, ldx, packed, rows, n, k, S, pack, seed_cells, chunk_rows, order, lk, li, stream);
+        case 6: return launch_lowd_bf16_d<6>(Q, ldq, X, ldx, packed, rows, n, k, S, pack, seed_cells, chunk_rows, order, lk, li, stream);
+        case 7: return launch_lowd_bf16_d<7>(Q, ldq, X, ldx, packed, rows, n, k, S, pack, seed_cells, chunk_rows, order, lk, li, stream);
+        case 8: return launch_lowd_bf16_d<8>(Q, ldq, X, ldx, packed, rows, n, k, S, pack, seed_cells, chunk_rows, order, lk, li, stream);
         default: return hipErrorInvalidValue;
     }
 }
