@@ -221,6 +221,32 @@ knn_status run_search(const knn_plan_t& plan, const float* Q, int64_t ldq, const
     const int64_t chunk_rows = plan.chunk_rows < m ? plan.chunk_rows : m;
 
     hipError_t e;
+    // Small searches of the squared-Euclidean metric skip the filter and all that prepares it: the
+    // whole workspace holds lists.  (One chunk only; a search over blocks of host points keeps its
+    // plan's path, whose thresholds carry over from block to block.)
+    if ((plan.path == KNN_PATH_MFMA_SPLIT || packed_plan) && metric == KNN_METRIC_L2SQ && plan.q_chunks == 1 &&
+        !block_d64 && few_applies(m, n, d, k)) {
+        const int S1 = few_splits(m, n, k, plan.workspace_bytes);
+        if (S1 > 0) {
+            float* lk = reinterpret_cast<float*>(ws);
+            int* li = reinterpret_cast<int*>(ws + align_up((uint64_t)m * S1 * k * 4));
+            hipEvent_t t1 = mark(stream);
+            e = launch_few(Q, ldq, X, ldx, m, n, d, k, S1, lk, li, stream);
+            if (e != hipSuccess) {
+                drop_bracket(t1);
+                return hip_fail(e, "search launch");
+            }
+            close_bracket(t1, stream, 1);
+            hipEvent_t t2 = mark(stream);
+            e = launch_merge_refine(Q, ldq, X, ldx, m, n, d, k, S1, (int)metric, lk, li, idx, dist, stream, nullptr);
+            if (e != hipSuccess) {
+                drop_bracket(t2);
+                return hip_fail(e, "merge/refine launch");
+            }
+            close_bracket(t2, stream, 2);
+            return KNN_OK;
+        }
+    }
     if (plan.path == KNN_PATH_MFMA_SPLIT || packed_plan) {
         hipEvent_t t0 = mark(stream);
         // (the header's second word: the points' largest bf16 rounding residual, which the

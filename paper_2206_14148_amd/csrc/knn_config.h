@@ -150,6 +150,11 @@ constexpr inline int64_t wd_lds_bytes(int k) {
 }
 static_assert(wd_lds_bytes(kWdMaxK) <= kPkLdsBytes, "the largest k must fit the LDS");
 
+// small searches, d > 8 (knn_few.hip): queries per wave, longest lists, most ranges
+constexpr int kFewQueries = 4;
+constexpr int kFewMaxK = 128;
+constexpr int kFewMaxSplits = 1024;
+
 // Workgroups the chip holds at once (LDS-limited): the planner sizes launches in rounds of these.
 constexpr int kLowdResidentWorkgroups = 4 * kNumCU;
 constexpr int kSpResidentWorkgroups = kNumCU;   // 8 waves of up to 256 registers: one per CU

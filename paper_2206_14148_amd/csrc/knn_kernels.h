@@ -77,6 +77,15 @@ hipError_t launch_split(const float* Q, int64_t ldq, const float* X, int64_t ldx
                         int64_t rows, int64_t n, int d, int k, int S, float* lk, int* li,
                         hipStream_t stream);
 
+// d > 8, small searches (knn_few.hip): every pair's exact key, no filter.
+//   few_applies  whether the sizes are small enough
+//   few_splits   point ranges for a chunk of rows: their lists are at most what fits into half of
+//                workspace_bytes for each of keys and indices (0: not even one range's do)
+bool few_applies(int64_t m, int64_t n, int d, int k);
+int few_splits(int64_t rows, int64_t n, int k, uint64_t workspace_bytes);
+hipError_t launch_few(const float* Q, int64_t ldq, const float* X, int64_t ldx, int64_t rows, int64_t n, int d,
+                      int k, int S, float* lk, int* li, hipStream_t stream);
+
 // 8 < d <= 256 with the points rounded to bf16 in the workspace (knn_packed.hip).
 //   launch_pack_operands  xp = `points` points from j_first on (j_first and points multiples of
 //                         64; rows past n are zero), pk_padded_chunks(d) x 32 bytes per point;

@@ -53,56 +53,14 @@ __device__ __forceinline__ double exact_l1dist(const float* __restrict__ q,
     return acc;
 }
 
-// metric: 0 squared Euclidean, 1 cosine, 2 L1 (the values of knn_metric)
-__global__ __launch_bounds__(256) void knn_merge_refine_kernel(
-    const float* __restrict__ Q, int64_t ldq, const float* __restrict__ X, int64_t ldx, int rows,
-    int n, int d, int k, int S, int metric, int aligned, const float* __restrict__ lk,
-    const int* __restrict__ li, int32_t* __restrict__ idx_out, float* __restrict__ dist_out,
-    double* __restrict__ d64_out) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
-    const int r = blockIdx.x * 4 + wave;
-    if (r >= rows) return;  // no workgroup barrier below
-    double* wd = reinterpret_cast<double*>(smem) + (size_t)wave * k;
-    int* wi = reinterpret_cast<int*>(reinterpret_cast<double*>(smem) + (size_t)4 * k) + (size_t)wave * k;
-    float* wk = reinterpret_cast<float*>(reinterpret_cast<int*>(reinterpret_cast<double*>(smem) + (size_t)4 * k) +
-                                         (size_t)4 * k) + (size_t)wave * k;  // the winners' list keys
-
-    const size_t rb = (size_t)r * S * k;
-    if (S == 1) {
-        for (int p = lane; p < k; p += kWave) {
-            wi[p] = li[rb + p];
-            wk[p] = lk[rb + p];
-        }
-    } else {
-        // rank of an entry = its position in its own list + entries of the other lists
-        // that come before it; indices are distinct, so ranks are too
-        const int total = S * k;
-        for (int e = lane; e < total; e += kWave) {
-            const int se = e / k;
-            const int p = e - se * k;
-            const float key = lk[rb + e];
-            const int id = li[rb + e];
-            int rank = p;
-            for (int s2 = 0; s2 < S && rank < k; ++s2) {
-                if (s2 == se) continue;
-                const float* k2 = lk + rb + (size_t)s2 * k;
-                const int* i2 = li + rb + (size_t)s2 * k;
-                int lo = 0, hi = k;
-                while (lo < hi) {
-                    const int mid = (lo + hi) >> 1;
-                    if (before(k2[mid], i2[mid], key, id)) lo = mid + 1;
-                    else hi = mid;
-                }
-                rank += lo;
-            }
-            if (rank < k) {
-                wi[rank] = id;
-                wk[rank] = key;
-            }
-        }
-    }
+// What follows the selection of a row's winners (wi: points, wk: list keys, wd: room; all in LDS): their
+// exact distances, and the row's output.  One wave.  metric: 0 squared Euclidean, 1 cosine, 2 L1
+// (the values of knn_metric)
+__device__ __forceinline__ void refine_row(const float* __restrict__ Q, int64_t ldq, const float* __restrict__ X,
+                                           int64_t ldx, int r, int n, int d, int k, int metric, int aligned,
+                                           double* wd, int* wi, float* wk, int lane,
+                                           int32_t* __restrict__ idx_out, float* __restrict__ dist_out,
+                                           double* __restrict__ d64_out) {
     wave_sync();
     if (metric == 0 && aligned) {
         // Squared-Euclidean distances of rows that are 16-byte aligned: eight lanes per winner, so
@@ -196,6 +154,119 @@ __global__ __launch_bounds__(256) void knn_merge_refine_kernel(
         idx_out[(size_t)r * k + rank] = jw;
         dist_out[(size_t)r * k + rank] = (float)dw;
     }
+}
+
+__global__ __launch_bounds__(256) void knn_merge_refine_kernel(
+    const float* __restrict__ Q, int64_t ldq, const float* __restrict__ X, int64_t ldx, int rows,
+    int n, int d, int k, int S, int metric, int aligned, const float* __restrict__ lk,
+    const int* __restrict__ li, int32_t* __restrict__ idx_out, float* __restrict__ dist_out,
+    double* __restrict__ d64_out) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int lane = threadIdx.x & 63;
+    const int wave = threadIdx.x >> 6;
+    const int r = blockIdx.x * 4 + wave;
+    if (r >= rows) return;  // no workgroup barrier below
+    double* wd = reinterpret_cast<double*>(smem) + (size_t)wave * k;
+    int* wi = reinterpret_cast<int*>(reinterpret_cast<double*>(smem) + (size_t)4 * k) + (size_t)wave * k;
+    float* wk = reinterpret_cast<float*>(reinterpret_cast<int*>(reinterpret_cast<double*>(smem) + (size_t)4 * k) +
+                                         (size_t)4 * k) + (size_t)wave * k;  // the winners' list keys
+
+    const size_t rb = (size_t)r * S * k;
+    if (S == 1) {
+        for (int p = lane; p < k; p += kWave) {
+            wi[p] = li[rb + p];
+            wk[p] = lk[rb + p];
+        }
+    } else {
+        // rank of an entry = its position in its own list + entries of the other lists
+        // that come before it; indices are distinct, so ranks are too
+        const int total = S * k;
+        for (int e = lane; e < total; e += kWave) {
+            const int se = e / k;
+            const int p = e - se * k;
+            const float key = lk[rb + e];
+            const int id = li[rb + e];
+            int rank = p;
+            for (int s2 = 0; s2 < S && rank < k; ++s2) {
+                if (s2 == se) continue;
+                const float* k2 = lk + rb + (size_t)s2 * k;
+                const int* i2 = li + rb + (size_t)s2 * k;
+                int lo = 0, hi = k;
+                while (lo < hi) {
+                    const int mid = (lo + hi) >> 1;
+                    if (before(k2[mid], i2[mid], key, id)) lo = mid + 1;
+                    else hi = mid;
+                }
+                rank += lo;
+            }
+            if (rank < k) {
+                wi[rank] = id;
+                wk[rank] = key;
+            }
+        }
+    }
+    refine_row(Q, ldq, X, ldx, r, n, d, k, metric, aligned, wd, wi, wk, lane, idx_out, dist_out, d64_out);
+}
+
+// The same for few rows with many lists each: a workgroup of eight waves per row.  A wave goes
+// through every eighth list, 64 entries at a time, and merges those under its own k-th entry into a
+// list of its own (LDS); the first wave then merges the eight and goes on as above.  (A wave per row
+// that ranks every entry by binary searches in all the other lists walks S log k dependent loads per
+// entry: 295 us for 16 rows of 64 lists of 10.)
+constexpr int kFewMergeWaves = 8;
+__global__ __launch_bounds__(64 * kFewMergeWaves) void knn_merge_refine_few_kernel(
+    const float* __restrict__ Q, int64_t ldq, const float* __restrict__ X, int64_t ldx, int n, int d, int k,
+    int S, int metric, int aligned, const float* __restrict__ lk, const int* __restrict__ li,
+    int32_t* __restrict__ idx_out, float* __restrict__ dist_out, double* __restrict__ d64_out) {
+    constexpr int NW = kFewMergeWaves;
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int lane = threadIdx.x & 63;
+    const int wave = threadIdx.x >> 6;
+    const int r = blockIdx.x;
+    double* wd = reinterpret_cast<double*>(smem);                    // [k]
+    float* own_k = reinterpret_cast<float*>(wd + k);                 // [NW][k]
+    int* own_i = reinterpret_cast<int*>(own_k + (size_t)NW * k);     // [NW][k]
+    float* scratch = reinterpret_cast<float*>(own_i + (size_t)NW * k) + (size_t)wave * (2 * kWave + 2 * k);
+    MergeScratch sc;
+    sc.cand_key = scratch;
+    sc.cand_idx = reinterpret_cast<int*>(scratch + kWave);
+    sc.list_key = scratch + 2 * kWave;
+    sc.list_idx = reinterpret_cast<int*>(scratch + 2 * kWave + k);
+    float* mk = own_k + (size_t)wave * k;
+    int* mi = own_i + (size_t)wave * k;
+    for (int p = lane; p < k; p += kWave) {
+        mk[p] = kInf;
+        mi[p] = kNoIdx;
+    }
+    wave_sync();
+    float tau = kInf;
+    int taui = kNoIdx;
+    // 64 entries of this wave's share, one per lane: those that come before its k-th entry are merged
+    auto take = [&](float key, int id) {
+        const uint64_t ok = __builtin_amdgcn_ballot_w64(before(key, id, tau, taui));
+        if (ok == 0) return;
+        if (!((ok >> lane) & 1)) {
+            key = kInf;
+            id = kNoIdx;
+        }
+        const uint64_t mr = wave_merge_pair(mk, mi, k, key, id, sc, lane, kWave);
+        tau = merged_key(mr);
+        taui = merged_idx(mr);
+    };
+    const float* rk = lk + (size_t)r * S * k;
+    const int* ri = li + (size_t)r * S * k;
+    const int total = S * k;
+    for (int e0 = wave * kWave; e0 < total; e0 += NW * kWave) {
+        const int e = e0 + lane;
+        take(e < total ? rk[e] : kInf, e < total ? ri[e] : kNoIdx);
+    }
+    __syncthreads();
+    if (wave != 0) return;
+    for (int e0 = k; e0 < NW * k; e0 += kWave) {  // the other waves' lists lie behind the first one's
+        const int e = e0 + lane;
+        take(e < NW * k ? own_k[e] : kInf, e < NW * k ? own_i[e] : kNoIdx);
+    }
+    refine_row(Q, ldq, X, ldx, r, n, d, k, metric, aligned, wd, mi, mk, lane, idx_out, dist_out, d64_out);
 }
 
 // Running result of a search over blocks of points, kept in the order of the list keys - the
@@ -324,12 +395,23 @@ hipError_t launch_merge_refine(const float* Q, int64_t ldq, const float* X, int6
                                int64_t rows, int64_t n, int d, int k, int S, int metric,
                                const float* lk, const int* li, int32_t* idx, float* dist,
                                hipStream_t stream, double* d64) {
+    const int aligned = (reinterpret_cast<uintptr_t>(Q) % 16 == 0) && (reinterpret_cast<uintptr_t>(X) % 16 == 0) &&
+                        (ldq % 4 == 0) && (ldx % 4 == 0) && (d % 4 == 0);
+    // a workgroup per row while the rows alone would leave the chip idle and their entries take a
+    // wave several rounds (LDS for its lists: k <= 256)
+    if (rows <= 4 * kNumCU && (int64_t)S * k > 4 * kWave && S > 1 && k <= 256) {
+        const size_t lds = (size_t)k * sizeof(double) + (size_t)kFewMergeWaves * k * 8 +
+                           (size_t)kFewMergeWaves * (2 * kWave + 2 * k) * 4;
+        hipError_t e = raise_lds_limit(knn_merge_refine_few_kernel, lds);
+        if (e != hipSuccess) return e;
+        knn_merge_refine_few_kernel<<<dim3((unsigned)rows), dim3(64 * kFewMergeWaves), lds, stream>>>(
+            Q, ldq, X, ldx, (int)n, d, k, S, metric, aligned, lk, li, idx, dist, d64);
+        return hipGetLastError();
+    }
     const size_t lds = (size_t)4 * k * (sizeof(double) + sizeof(int) + sizeof(float));
     hipError_t e = raise_lds_limit(knn_merge_refine_kernel, lds);
     if (e != hipSuccess) return e;
     dim3 grid((unsigned)((rows + 3) / 4));
-    const int aligned = (reinterpret_cast<uintptr_t>(Q) % 16 == 0) && (reinterpret_cast<uintptr_t>(X) % 16 == 0) &&
-                        (ldq % 4 == 0) && (ldx % 4 == 0) && (d % 4 == 0);
     knn_merge_refine_kernel<<<grid, dim3(256), lds, stream>>>(
         Q, ldq, X, ldx, (int)rows, (int)n, d, k, S, metric, aligned, lk, li, idx, dist, d64);
     return hipGetLastError();

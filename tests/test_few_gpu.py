@@ -1,0 +1,56 @@
+"""Small searches evaluate every pair: bit for bit the results of the filter paths, which the same
+call takes as a part of a larger one."""
+import pytest
+
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def K():
+    import paper_2206_14148_amd as K
+    assert torch.cuda.is_available(), "these tests need the GPU"
+    K.load()
+    return K
+
+
+# rows that are 16-byte aligned and not; a row's length at the ends of the staged pieces of 32 and of the
+# groups of 8 and 4; one point, one wave's worth and one more; queries that leave a group of four;
+# lists of one, of a wave and of the longest kept here
+@pytest.mark.parametrize("m,n,d,k", [
+    (1, 1, 9, 1), (3, 64, 9, 10), (4, 65, 12, 64), (5, 1000, 31, 65), (17, 5000, 32, 10), (9, 20_011, 33, 7),
+    (16, 20_000, 50, 10), (63, 3001, 63, 5), (64, 3001, 64, 128), (65, 2999, 65, 33), (2, 70_001, 100, 100),
+    (1, 70_000, 257, 10), (7, 1500, 300, 16), (300, 4000, 16, 10)])
+def test_same_as_the_filter_paths(K, oracle, m, n, d, k):
+    from parity import check
+    print("case", m, n, d, k, flush=True)
+    Q, X = W.random_case(8800 + m + d, m, n, d)
+    Qd, Xd = torch.from_numpy(Q).cuda(), torch.from_numpy(X).cuda()
+    idx, dist = K.knn_search(Qd, Xd, k, W.GB)
+    Xw = torch.full((n, d + 3), 7.0, device="cuda")
+    Xw[:, :d] = Xd
+    s_idx, s_dist = K.knn_search(Qd, Xw[:, :d], k, W.GB)
+    # the smallest limit: short lists, as many ranges as fit
+    t_idx, t_dist = K.knn_search(Qd, Xd, k, K.knn_plan(m, n, d, k, W.GB).min_limit_bytes)
+    # the same queries among so many that the filters answer
+    more = int(5.1e9 / (n * (d + 16))) + 1
+    if more < 200_000:
+        big = torch.cat([Qd, Xd[:1].expand(more, d)]).contiguous()
+        b_idx, b_dist = K.knn_search(big, Xd, k, 8 * W.GB)
+    torch.cuda.synchronize()
+    o_idx, o_dist, o_next = oracle.knn(Q, X, k)
+    check(idx.cpu().numpy(), dist.cpu().numpy(), o_idx, o_dist, o_next, n)
+    assert torch.equal(idx, s_idx) and torch.equal(dist, s_dist)
+    assert torch.equal(idx, t_idx) and torch.equal(dist, t_dist)
+    if more < 200_000:
+        assert torch.equal(idx, b_idx[:m]) and torch.equal(dist, b_dist[:m])
+
+
+def test_equal_points_keep_the_lowest_indices(K):
+    X = torch.full((30_000, 20), 0.75, device="cuda")
+    idx, dist = K.knn_search(X[:6] + 0.5, X, 9, W.GB)
+    torch.cuda.synchronize()
+    assert (idx == torch.arange(9, device="cuda", dtype=torch.int32)).all() and (dist == 5.0).all()
