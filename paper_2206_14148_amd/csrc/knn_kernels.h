@@ -27,6 +27,16 @@ hipError_t launch_l1(const float* Q, int64_t ldq, const float* X, int64_t ldx, v
                      int64_t rows, int64_t n, int d, int k, int S, float* lk, int* li,
                      hipStream_t stream);
 
+// The same keys and lists for the pairs that a filter of byte sums lets through, where that applies
+// (launch_l1 asks); `room` = the transposed queries' area.  Where the filter would let too much
+// through, which is seen on the device, every list's first index is kL1Redo instead and the general
+// kernel, launched behind, makes the lists.
+constexpr int kL1Redo = -7;
+bool l1_sad_applies(int64_t rows, int64_t n, int d, int k);
+hipError_t launch_l1_sad(const float* Q, int64_t ldq, const float* X, int64_t ldx, void* room,
+                         int64_t rows, int64_t n, int d, int k, int S, float* lk, int* li,
+                         hipStream_t stream);
+
 // d <= kPmMaxD with room for the packed points: the same keys as launch_lowd, found through an
 // MFMA filter.  `packed` = kAlign bytes (max ||x||^2 word) + 16 n bytes ([x0 x1 x2 ||x||^2] per
 // point); pack = true (re)builds it from X first; rows == 0 only packs.

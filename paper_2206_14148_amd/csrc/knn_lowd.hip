@@ -143,7 +143,8 @@ __global__ __launch_bounds__(kLowdTileQ) void knn_lowd_kernel(
 }
 
 // ---------------------------------------------------------------------------------------
-// L1 metric (the L1 rows of the paper's table): sum |q - x| hides no matrix product, so this
+// L1 metric (the L1 rows of the paper's table) where knn_l1sad.hip does not filter the pairs first
+// (few points per neighbour, d < 5, d > 192, k > 64): sum |q - x| hides no matrix product, so this
 // is a vector-ALU kernel for every d.  One query per lane; a group of 8 points is wave-uniform
 // and read with scalar loads; the dimension is walked in chunks of 16 with the query's chunk
 // in registers and one running sum per point of the group, so a query value is loaded once
@@ -156,7 +157,9 @@ __global__ __launch_bounds__(kLowdTileQ) void knn_lowd_kernel(
 // ---------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void knn_l1_transpose_kernel(const float* __restrict__ Q,
                                                                int64_t ldq, int rows, int d,
-                                                               f32x4* __restrict__ Qt) {
+                                                               f32x4* __restrict__ Qt,
+                                                               const int* __restrict__ redo) {
+    if (redo && *redo != kL1Redo) return;
     const int d4 = (d + 3) / 4;
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;  // (block of 64 rows, t / 4, lane)
     const int64_t total = (int64_t)((rows + kWave - 1) / kWave) * d4 * kWave;
@@ -175,7 +178,7 @@ __global__ __launch_bounds__(256) void knn_l1_transpose_kernel(const float* __re
 
 __global__ __launch_bounds__(kLowdTileQ) void knn_l1_kernel(
     const f32x4* __restrict__ Qt, const float* __restrict__ X, int64_t ldx, int rows, int n, int d,
-    int k, int S, int split_len, float* __restrict__ lk, int* __restrict__ li) {
+    int k, int S, int split_len, float* __restrict__ lk, int* __restrict__ li, int only_redo) {
     constexpr int P = 8;    // points per group
     constexpr int TC = 16;  // dimensions per register chunk
     constexpr int H = 4;    // points pushed between two overflow checks
@@ -197,6 +200,8 @@ __global__ __launch_bounds__(kLowdTileQ) void knn_l1_kernel(
     const int s = blockIdx.y;
     const int wave_row0 = (blockIdx.x * kLowdWaves + wave) * kWave;
     if (wave_row0 >= rows) return;  // whole wave idle; no workgroup barrier is used below
+    // (a wave looks at a list of its own: another's may be in the making already)
+    if (only_redo && li[((size_t)wave_row0 * S + s) * k] != kL1Redo) return;
     const int r = wave_row0 + lane;
     const bool active = r < rows;
     {
@@ -1281,10 +1286,16 @@ static hipError_t launch_lowd_d(const float* Q, int64_t ldq, const float* X, int
 hipError_t launch_l1(const float* Q, int64_t ldq, const float* X, int64_t ldx, void* qt,
                      int64_t rows, int64_t n, int d, int k, int S, float* lk, int* li,
                      hipStream_t stream) {
+    const int* redo = nullptr;  // null: run; else only where the first index of a list says so
+    if (l1_sad_applies(rows, n, d, k)) {
+        hipError_t e0 = launch_l1_sad(Q, ldq, X, ldx, qt, rows, n, d, k, S, lk, li, stream);
+        if (e0 != hipSuccess) return e0;
+        redo = li;
+    }
     {
         const int64_t total = (rows + kWave - 1) / kWave * ((d + 3) / 4) * kWave;
         knn_l1_transpose_kernel<<<dim3((unsigned)((total + 255) / 256)), dim3(256), 0, stream>>>(
-            Q, ldq, (int)rows, d, static_cast<f32x4*>(qt));
+            Q, ldq, (int)rows, d, static_cast<f32x4*>(qt), redo);
         hipError_t e0 = hipGetLastError();
         if (e0 != hipSuccess) return e0;
     }
@@ -1297,7 +1308,7 @@ hipError_t launch_l1(const float* Q, int64_t ldq, const float* X, int64_t ldx, v
     dim3 grid((unsigned)((rows + kLowdTileQ - 1) / kLowdTileQ), (unsigned)S);
     knn_l1_kernel<<<grid, dim3(kLowdTileQ), lds, stream>>>(static_cast<const f32x4*>(qt), X, ldx,
                                                            (int)rows, (int)n, d, k, S,
-                                                           (int)split_len, lk, li);
+                                                           (int)split_len, lk, li, redo != nullptr);
     return hipGetLastError();
 }
 
