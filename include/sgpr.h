@@ -64,7 +64,7 @@ knn_status sgpr_plan(int64_t m, int64_t n, int32_t d, uint64_t mem_limit_bytes,
  *   hip_stream        hipStream_t (NULL: default stream); the call only enqueues work and
  *                     allocates nothing.
  * Arithmetic: K_uf entries in fp32 (difference-form distance, hardware exp2); products and
- * their sums over one chunk in fp32 on the matrix cores; sums over chunks in fp64.  Every
+ * their sums over one chunk in fp32 on the matrix cores (entries as three exact bf16 pieces); sums over chunks in fp64.  Every
  * entry is summed in a fixed order; the result depends on the limit only through the chunk
  * length (last bits).
  */

@@ -42,9 +42,8 @@ constexpr int kGridMaxK = 32;
 constexpr int64_t kGridMinPoints = 4096;
 constexpr int kGridMaxCells = 1 << 21;
 
-// fp32 MFMA tiles of the SGPR sums (sgpr_kernels.hip): LDS staging of 128-row tiles
+// tiles of the SGPR sums (sgpr_kernels.hip)
 constexpr int kMfmaKC = 16;          // K columns staged in LDS per pipeline step
-constexpr int kMfmaRowStride = 20;   // floats per staged row (16 + 4 pad, keeps 16 B alignment)
 
 // d > kPbMaxD, and the cosine metric: bf16 matrix-core filter on rounded values + exact fp32 test,
 // 8 waves, each wave owns 32 queries x 128 points.

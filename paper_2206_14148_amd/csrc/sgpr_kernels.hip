@@ -111,46 +111,109 @@ __global__ __launch_bounds__(256) void sgpr_symmetrize_kernel(double* __restrict
 // ---------------------------------------------------------------------------------------
 // Chunk product on the matrix cores.  A workgroup of 4 waves owns one 128 x 128 tile of the
 // lower triangle (tile row tj >= tile column ti) and walks the chunk's columns in steps of 16:
-// rows of tile tj are the M side and rows of tile ti the N side of v_mfma_f32_32x32x2_f32,
-// both staged through LDS, double buffered, with the global loads of step s+2 in flight
-// during step s.  At the end every lane holds, per 32 x 32 block, 16 values of one column
-// i = lane % 32, so for a fixed register the 32 lanes of a half wave write 32 consecutive
-// fp64 entries of one row of A.
+// rows of tile tj are the M side and rows of tile ti the N side of v_mfma_f32_32x32x16_bf16.
+// Every fp32 entry is cut into three bf16 pieces, hi + mid + lo = the entry exactly (3 x 8
+// significant bits), while it is staged into LDS (double buffered, the global loads of step
+// s+2 in flight during step s); of the nine piece products the six of weight >= 2^-16 are
+// kept, each exact in the fp32 accumulator.  Six of these take 192 cycles per 16 columns
+// against 512 for eight v_mfma_f32_32x32x2_f32.  Whole call, 4000 inducing points, 2e6 rows of 11
+// features: 347 ms on fp32 MFMA, 312 now (error of A 3.4e-8 -> 2.3e-8 at 3e5 rows; all six products in
+// one accumulator 303 ms, but 5.1e-8); 300 points, 2e6 rows of 4 40.8 -> 32.9 ms.  What is left is not
+// the matrix cores, which would need about 85 ms, but the staging: the cut of every entry for every
+// tile, the trips through LDS and the chunk's re-reads.  At the end every lane holds, per 32 x 32
+// block, 16 values of one column i = lane % 32, so for a fixed register the 32 lanes of a
+// half wave write 32 consecutive fp64 entries of one row of A.
 // ---------------------------------------------------------------------------------------
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ void split3_pair(float a, float b, unsigned& hi, unsigned& mid, unsigned& lo) {
+    const f32x2 p = {a, b};
+    const bf16x2 hb = __builtin_convertvector(p, bf16x2);
+    const f32x2 r1 = p - __builtin_convertvector(hb, f32x2);
+    const bf16x2 mb = __builtin_convertvector(r1, bf16x2);
+    const f32x2 r2 = r1 - __builtin_convertvector(mb, f32x2);
+    const bf16x2 lb = __builtin_convertvector(r2, bf16x2);
+    hi = __builtin_bit_cast(unsigned, hb);
+    mid = __builtin_bit_cast(unsigned, mb);
+    lo = __builtin_bit_cast(unsigned, lb);
+}
+
+// A staged piece of a tile: per block of 32 rows the 16-byte words of the rows' first halves
+// (columns 0..7 of the step), 8 words of padding, then the second halves: no bank conflicts, neither
+// for the operand reads nor for the stores.
+constexpr int kStagedHalf = 32 + 8;
+constexpr int kStagedBlock = kStagedHalf + 32;
+constexpr int kStagedPiece = 4 * kStagedBlock;
+
+// Workgroup -> (column group, tile row tj, tile column ti <= tj).  Consecutive workgroup ids go
+// round-robin to the 8 XCDs, each with its own L2: every XCD takes a run of consecutive (group,
+// tile) pairs, the tiles of a group in blocks of 8 x 8, so that the 64 workgroups resident there
+// read 16 rows of tiles between them and not a pair each.  Returns false for a padding workgroup.
+__device__ __forceinline__ bool tile_of_workgroup(int T, int groups, int& grp, int& tj, int& ti) {
+    const int tiles = T * (T + 1) / 2;
+    const int per_xcd = gridDim.x >> 3;  // (gridDim.x is a multiple of 8)
+    const int seq = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
+    if (seq >= tiles * groups) return false;
+    grp = seq / tiles;
+    int left = seq - grp * tiles;
+    int r0 = 0, rows = min(8, T);
+    for (;;) {  // rows of blocks: r0 / 8 whole blocks of `rows` x 8 and a triangle
+        const int count = rows * r0 + rows * (rows + 1) / 2;
+        if (left < count) break;
+        left -= count;
+        r0 += 8;
+        rows = min(8, T - r0);
+    }
+    if (left < rows * r0) {
+        const int block = left / (rows * 8), in = left - block * rows * 8;
+        tj = r0 + in / 8;
+        ti = block * 8 + in % 8;
+    } else {
+        left -= rows * r0;
+        int j = 0;
+        while (left > j) {
+            left -= j + 1;
+            ++j;
+        }
+        tj = r0 + j;
+        ti = r0 + left;
+    }
+    return true;
+}
+
 __global__ __launch_bounds__(256, 2) void sgpr_syrk_kernel(const float* __restrict__ Kc_all,
                                                            int64_t ldk, int m, int cols_all,
-                                                           int group_cols,
+                                                           int group_cols, int groups,
                                                            double* __restrict__ A0, int64_t lda0,
                                                            double* __restrict__ copies,
                                                            int64_t copy_stride) {
-    // column group blockIdx.y: its run of columns and the matrix its sums go to
-    const int grp = blockIdx.y;
+    // column group grp, its run of columns and the matrix its sums go to; tile pair (tj, ti)
+    int grp, tj, ti;
+    if (!tile_of_workgroup((m + 127) / 128, groups, grp, tj, ti)) return;
     const float* __restrict__ Kc = Kc_all + (int64_t)grp * group_cols;
     const int cols = min(group_cols, cols_all - grp * group_cols);
     if (cols <= 0) return;  // whole workgroup, before any barrier
     double* __restrict__ A = grp == 0 ? A0 : copies + (int64_t)(grp - 1) * copy_stride;
     const int64_t lda = grp == 0 ? lda0 : (int64_t)m;
-    constexpr int T = 128, KC = knn::kMfmaKC, RS = knn::kMfmaRowStride;
+    constexpr int T = 128, KC = knn::kMfmaKC;
     extern __shared__ __align__(16) unsigned char smem[];
-    float* js = reinterpret_cast<float*>(smem);  // [2][T][RS] rows of tile tj
-    float* is = js + 2 * T * RS;                 // [2][T][RS] rows of tile ti
+    uint4* js = reinterpret_cast<uint4*>(smem);  // [2][3 pieces] rows of tile tj
+    uint4* is = js + 2 * 3 * kStagedPiece;       // [2][3 pieces] rows of tile ti
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = tid >> 6;
     const int i32 = lane & 31;
     const int h = lane >> 5;
 
-    // blockIdx.x = tj (tj + 1) / 2 + ti with ti <= tj
-    int tj = (int)((sqrtf(8.f * (float)blockIdx.x + 1.f) - 1.f) * 0.5f);
-    while ((tj + 1) * (tj + 2) / 2 <= (int)blockIdx.x) ++tj;
-    while (tj * (tj + 1) / 2 > (int)blockIdx.x) --tj;
-    const int ti = (int)blockIdx.x - tj * (tj + 1) / 2;
     const int row_j0 = tj * T, row_i0 = ti * T;
     const int my_i = wave * 32 + i32;
 
     const int total = (cols + KC - 1) / KC;
-    const int srow = tid >> 2;
-    const int scol = (tid & 3) * 4;
+    const int srow = tid >> 1;  // staging: this thread cuts 8 columns of one row of each tile
+    const int scol = (tid & 1) * 8;
+    const int slot = (srow >> 5) * kStagedBlock + (tid & 1) * kStagedHalf + (srow & 31);
 
     struct Staged {
         f32x4 j0, j1, i0, i1;
@@ -160,30 +223,37 @@ __global__ __launch_bounds__(256, 2) void sgpr_syrk_kernel(const float* __restri
     auto fetch = [&](int step, Staged& g) {
         const int col = step * KC + scol;
         g.j0 = load_row4<true>(Kc, ldk, (int64_t)row_j0 + srow, m, col, cols);
-        g.j1 = load_row4<true>(Kc, ldk, (int64_t)row_j0 + srow + 64, m, col, cols);
+        g.j1 = load_row4<true>(Kc, ldk, (int64_t)row_j0 + srow, m, col + 4, cols);
         g.i0 = load_row4<true>(Kc, ldk, (int64_t)row_i0 + srow, m, col, cols);
-        g.i1 = load_row4<true>(Kc, ldk, (int64_t)row_i0 + srow + 64, m, col, cols);
+        g.i1 = load_row4<true>(Kc, ldk, (int64_t)row_i0 + srow, m, col + 4, cols);
+    };
+    auto put = [&](uint4* at, const f32x4& x0, const f32x4& x1) {
+        uint4 hi, mid, lo;
+        split3_pair(x0[0], x0[1], hi.x, mid.x, lo.x);
+        split3_pair(x0[2], x0[3], hi.y, mid.y, lo.y);
+        split3_pair(x1[0], x1[1], hi.z, mid.z, lo.z);
+        split3_pair(x1[2], x1[3], hi.w, mid.w, lo.w);
+        at[0] = hi;
+        at[kStagedPiece] = mid;
+        at[2 * kStagedPiece] = lo;
     };
     auto stash = [&](int step, const Staged& g) {
         const int buf = step & 1;
         const int col = step * KC + scol;
-        float* jb = js + buf * T * RS;
-        float* ib = is + buf * T * RS;
-        *reinterpret_cast<f32x4*>(jb + srow * RS + scol) =
-            mask_row4(g.j0, row_j0 + srow < m, col, cols, 1.f);
-        *reinterpret_cast<f32x4*>(jb + (srow + 64) * RS + scol) =
-            mask_row4(g.j1, row_j0 + srow + 64 < m, col, cols, 1.f);
-        *reinterpret_cast<f32x4*>(ib + srow * RS + scol) =
-            mask_row4(g.i0, row_i0 + srow < m, col, cols, 1.f);
-        *reinterpret_cast<f32x4*>(ib + (srow + 64) * RS + scol) =
-            mask_row4(g.i1, row_i0 + srow + 64 < m, col, cols, 1.f);
+        const bool okj = row_j0 + srow < m, oki = row_i0 + srow < m;
+        put(js + buf * 3 * kStagedPiece + slot, mask_row4(g.j0, okj, col, cols, 1.f),
+            mask_row4(g.j1, okj, col + 4, cols, 1.f));
+        put(is + buf * 3 * kStagedPiece + slot, mask_row4(g.i0, oki, col, cols, 1.f),
+            mask_row4(g.i1, oki, col + 4, cols, 1.f));
     };
 
-    f32x16 acc[4];
+    // the products of the high pieces, and apart from them the five small ones: the first are then
+    // rounded once per 16 columns, the others against a sum that is 2^8 smaller
+    f32x16 acc[4], low[4];
 #pragma unroll
     for (int pb = 0; pb < 4; ++pb)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) acc[pb][e] = 0.f;
+        for (int e = 0; e < 16; ++e) acc[pb][e] = low[pb][e] = 0.f;
 
     Staged set_even, set_odd;
     if (total > 0) {
@@ -196,26 +266,26 @@ __global__ __launch_bounds__(256, 2) void sgpr_syrk_kernel(const float* __restri
     auto run_step = [&](int step, Staged& mine, const Staged& next) {
         const int buf = step & 1;
         fetch(step + 2 < total ? step + 2 : total - 1, mine);  // past the end: a harmless re-load
-        const float* jb = js + buf * T * RS;
-        const float* ib = is + buf * T * RS;
-        f32x4 b[KC / 8], a[KC / 8][4];
+        const uint4* jb = js + buf * 3 * kStagedPiece + h * kStagedHalf + i32;
+        const uint4* ib = is + buf * 3 * kStagedPiece + wave * kStagedBlock + h * kStagedHalf + i32;
+        bf16x8 b[3], a[4][3];
 #pragma unroll
-        for (int g = 0; g < KC / 8; ++g) {
-            const int col = g * 8 + h * 4;
-            b[g] = *reinterpret_cast<const f32x4*>(ib + my_i * RS + col);
+        for (int p = 0; p < 3; ++p) b[p] = __builtin_bit_cast(bf16x8, ib[p * kStagedPiece]);
 #pragma unroll
-            for (int pb = 0; pb < 4; ++pb)
-                a[g][pb] = *reinterpret_cast<const f32x4*>(jb + (pb * 32 + i32) * RS + col);
-        }
+        for (int pb = 0; pb < 4; ++pb)
 #pragma unroll
-        for (int g = 0; g < KC / 8; ++g) {
+            for (int p = 0; p < 3; ++p)
+                a[pb][p] = __builtin_bit_cast(bf16x8, jb[p * kStagedPiece + pb * kStagedBlock]);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-#pragma unroll
-                for (int pb = 0; pb < 4; ++pb)
-                    acc[pb] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[g][pb][e], b[g][e], acc[pb], 0, 0, 0);
-            }
-            if (g == 0 && step + 1 < total) stash(step + 1, next);
+        for (int pb = 0; pb < 4; ++pb) {
+            // smallest products first: lo.hi, hi.lo, mid.mid, then mid.hi, hi.mid, hi.hi
+            low[pb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[pb][2], b[0], low[pb], 0, 0, 0);
+            low[pb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[pb][0], b[2], low[pb], 0, 0, 0);
+            low[pb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[pb][1], b[1], low[pb], 0, 0, 0);
+            low[pb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[pb][1], b[0], low[pb], 0, 0, 0);
+            low[pb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[pb][0], b[1], low[pb], 0, 0, 0);
+            acc[pb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[pb][0], b[0], acc[pb], 0, 0, 0);
+            if (pb == 1 && step + 1 < total) stash(step + 1, next);
         }
         __syncthreads();
     };
@@ -232,7 +302,7 @@ __global__ __launch_bounds__(256, 2) void sgpr_syrk_kernel(const float* __restri
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 const int j = row_j0 + pb * 32 + 8 * (v >> 2) + 4 * h + (v & 3);
-                if (j < m) A[(int64_t)j * lda + i] += (double)acc[pb][v];
+                if (j < m) A[(int64_t)j * lda + i] += (double)acc[pb][v] + (double)low[pb][v];
             }
         }
     }
@@ -260,12 +330,15 @@ hipError_t launch_kuf(const float* U, int64_t ldu, const float* X, int64_t ldx, 
 hipError_t launch_syrk(const float* Kc, int64_t ldk, int64_t m, int64_t cols, int groups, double* A,
                        int64_t lda, double* copies, int64_t copy_stride, hipStream_t stream) {
     const int64_t T = (m + 127) / 128;
-    const size_t lds = (size_t)4 * 128 * knn::kMfmaRowStride * 4;
+    const size_t lds = (size_t)2 * 2 * 3 * kStagedPiece * 16;
     // equal runs of whole 16-column steps; the last run takes what is left
     int64_t group_cols = ((cols + groups - 1) / groups + 15) / 16 * 16;
     if (group_cols < 16) group_cols = 16;
-    sgpr_syrk_kernel<<<dim3((unsigned)(T * (T + 1) / 2), (unsigned)groups), dim3(256), lds, stream>>>(
-        Kc, ldk, (int)m, (int)cols, (int)group_cols, A, lda, copies, copy_stride);
+    hipError_t e = knn::raise_lds_limit(sgpr_syrk_kernel, lds);
+    if (e != hipSuccess) return e;
+    const int64_t wgs = T * (T + 1) / 2 * groups;
+    sgpr_syrk_kernel<<<dim3((unsigned)((wgs + 7) / 8 * 8)), dim3(256), lds, stream>>>(
+        Kc, ldk, (int)m, (int)cols, (int)group_cols, groups, A, lda, copies, copy_stride);
     return hipGetLastError();
 }
 
