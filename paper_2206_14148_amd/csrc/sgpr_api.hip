@@ -85,6 +85,12 @@ extern "C" knn_status sgpr_accumulate(const float* U, int64_t ldu, const float* 
     float* Kc = static_cast<float*>(workspace);
     const float c2 = (float)(0.5 / (lengthscale * lengthscale) * 1.4426950408889634);
 
+    // The entries are made with the variance's significand and the power of two goes into the fp64
+    // sums: exact, and the small products of an entry's pieces stay above the fp32 underflow.
+    int exponent = 0;
+    const float significand = (float)std::frexp(variance, &exponent);
+    const double scale = std::ldexp(1.0, exponent);
+
     const int G = plan.col_groups;
     const uint64_t chunk_bytes = knn::align_up((uint64_t)m * (uint64_t)plan.chunk_ld * 4);
     const uint64_t copy_bytes = knn::align_up((uint64_t)m * (uint64_t)m * 8);
@@ -97,7 +103,7 @@ extern "C" knn_status sgpr_accumulate(const float* U, int64_t ldu, const float* 
         const int64_t c0 = c * plan.chunk_cols;
         const int64_t cols = n - c0 < plan.chunk_cols ? n - c0 : plan.chunk_cols;
         hipEvent_t t0 = knn::profile_mark(stream);
-        e = sgpr::launch_kuf(U, ldu, X, ldx, m, c0, cols, d, c2, (float)variance, Kc, plan.chunk_ld,
+        e = sgpr::launch_kuf(U, ldu, X, ldx, m, c0, cols, d, c2, significand, Kc, plan.chunk_ld,
                              stream);
         if (e != hipSuccess) {
             knn::profile_drop(t0);
@@ -105,7 +111,7 @@ extern "C" knn_status sgpr_accumulate(const float* U, int64_t ldu, const float* 
         }
         knn::profile_close(t0, stream, 0);
         hipEvent_t t1 = knn::profile_mark(stream);
-        e = sgpr::launch_syrk(Kc, plan.chunk_ld, m, cols, G, A, lda, copies, (int64_t)(copy_bytes / 8),
+        e = sgpr::launch_syrk(Kc, plan.chunk_ld, m, cols, G, scale * scale, A, lda, copies, (int64_t)(copy_bytes / 8),
                               stream);
         if (e != hipSuccess) {
             knn::profile_drop(t1);
@@ -113,7 +119,7 @@ extern "C" knn_status sgpr_accumulate(const float* U, int64_t ldu, const float* 
         }
         knn::profile_close(t1, stream, 1);
         hipEvent_t t2 = knn::profile_mark(stream);
-        e = sgpr::launch_kufy(Kc, plan.chunk_ld, m, cols, y + c0, b, stream);
+        e = sgpr::launch_kufy(Kc, plan.chunk_ld, m, cols, y + c0, scale, b, stream);
         if (e != hipSuccess) {
             knn::profile_drop(t2);
             return hip_fail(e, "sgpr chunk times y");

@@ -17,7 +17,7 @@ hipError_t launch_kuf(const float* U, int64_t ldu, const float* X, int64_t ldx, 
 // Lower triangle (whole diagonal tiles): A[j][i] += sum_c Kc[j][c] * Kc[i][c].  The columns are
 // cut into `groups` runs (multiples of 16); run 0 adds into A, run g > 0 into the m x m copy
 // copies + (g - 1) * copy_stride (leading dimension m).
-hipError_t launch_syrk(const float* Kc, int64_t ldk, int64_t m, int64_t cols, int groups, double* A,
+hipError_t launch_syrk(const float* Kc, int64_t ldk, int64_t m, int64_t cols, int groups, double scale, double* A,
                        int64_t lda, double* copies, int64_t copy_stride, hipStream_t stream);
 
 // Lower triangle: A[j][i] += copy_0[j][i] + copy_1[j][i] + ... in that order.
@@ -25,8 +25,7 @@ hipError_t launch_add_copies(double* A, int64_t lda, const double* copies, int64
                              int ncopies, int64_t m, hipStream_t stream);
 
 // b[i] += sum_c Kc[i][c] * y[c0 + c].
-hipError_t launch_kufy(const float* Kc, int64_t ldk, int64_t m, int64_t cols, const float* y,
-                       double* b, hipStream_t stream);
+hipError_t launch_kufy(const float* Kc, int64_t ldk, int64_t m, int64_t cols, const float* y, double scale, double* b, hipStream_t stream);
 
 // A[i][j] = A[j][i] for j > i.
 hipError_t launch_symmetrize(double* A, int64_t lda, int64_t m, hipStream_t stream);

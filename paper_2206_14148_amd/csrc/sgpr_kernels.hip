@@ -66,7 +66,7 @@ __global__ __launch_bounds__(256) void sgpr_kuf_kernel(const float* __restrict__
 // (ascending), lanes added in a fixed butterfly.
 __global__ __launch_bounds__(256) void sgpr_kufy_kernel(const float* __restrict__ Kc, int64_t ldk,
                                                         int m, int cols,
-                                                        const float* __restrict__ y,
+                                                        const float* __restrict__ y, double scale,
                                                         double* __restrict__ b) {
     const int lane = threadIdx.x & 63;
     const int i = blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -76,7 +76,7 @@ __global__ __launch_bounds__(256) void sgpr_kufy_kernel(const float* __restrict_
     for (int c = lane; c < cols; c += 64) acc += (double)(row[c] * y[c]);
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) acc += __shfl_xor(acc, o);
-    if (lane == 0) b[i] += acc;
+    if (lane == 0) b[i] += scale * acc;
 }
 
 __global__ __launch_bounds__(256) void sgpr_add_copies_kernel(double* __restrict__ A, int64_t lda,
@@ -185,7 +185,7 @@ __device__ __forceinline__ bool tile_of_workgroup(int T, int groups, int& grp, i
 
 __global__ __launch_bounds__(256, 2) void sgpr_syrk_kernel(const float* __restrict__ Kc_all,
                                                            int64_t ldk, int m, int cols_all,
-                                                           int group_cols, int groups,
+                                                           int group_cols, int groups, double scale,
                                                            double* __restrict__ A0, int64_t lda0,
                                                            double* __restrict__ copies,
                                                            int64_t copy_stride) {
@@ -302,7 +302,7 @@ __global__ __launch_bounds__(256, 2) void sgpr_syrk_kernel(const float* __restri
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 const int j = row_j0 + pb * 32 + 8 * (v >> 2) + 4 * h + (v & 3);
-                if (j < m) A[(int64_t)j * lda + i] += (double)acc[pb][v] + (double)low[pb][v];
+                if (j < m) A[(int64_t)j * lda + i] += scale * ((double)acc[pb][v] + (double)low[pb][v]);
             }
         }
     }
@@ -327,7 +327,7 @@ hipError_t launch_kuf(const float* U, int64_t ldu, const float* X, int64_t ldx, 
     return hipGetLastError();
 }
 
-hipError_t launch_syrk(const float* Kc, int64_t ldk, int64_t m, int64_t cols, int groups, double* A,
+hipError_t launch_syrk(const float* Kc, int64_t ldk, int64_t m, int64_t cols, int groups, double scale, double* A,
                        int64_t lda, double* copies, int64_t copy_stride, hipStream_t stream) {
     const int64_t T = (m + 127) / 128;
     const size_t lds = (size_t)2 * 2 * 3 * kStagedPiece * 16;
@@ -338,7 +338,7 @@ hipError_t launch_syrk(const float* Kc, int64_t ldk, int64_t m, int64_t cols, in
     if (e != hipSuccess) return e;
     const int64_t wgs = T * (T + 1) / 2 * groups;
     sgpr_syrk_kernel<<<dim3((unsigned)((wgs + 7) / 8 * 8)), dim3(256), lds, stream>>>(
-        Kc, ldk, (int)m, (int)cols, (int)group_cols, groups, A, lda, copies, copy_stride);
+        Kc, ldk, (int)m, (int)cols, (int)group_cols, groups, scale, A, lda, copies, copy_stride);
     return hipGetLastError();
 }
 
@@ -351,9 +351,9 @@ hipError_t launch_add_copies(double* A, int64_t lda, const double* copies, int64
 }
 
 hipError_t launch_kufy(const float* Kc, int64_t ldk, int64_t m, int64_t cols, const float* y,
-                       double* b, hipStream_t stream) {
+                       double scale, double* b, hipStream_t stream) {
     sgpr_kufy_kernel<<<dim3((unsigned)((m + 3) / 4)), dim3(256), 0, stream>>>(Kc, ldk, (int)m,
-                                                                              (int)cols, y, b);
+                                                                              (int)cols, y, scale, b);
     return hipGetLastError();
 }
 

@@ -97,6 +97,18 @@ def test_inducing_points_among_the_data(K, oracle):
     parity(K, oracle, X[:150].copy(), X, y, 1.2, 0.9)
 
 
+@pytest.mark.parametrize("variance", [2.0 ** -62, 2.0 ** 70, 1.7e-17])
+def test_extreme_variances_scale_the_sums(K, variance):
+    # a power of two moves the exponent only; the pieces' small products must not underflow
+    U, X, y = W.random_sgpr_case(24, 150, 3000, 3)
+    A, b = run_gpu(K, U, X, y, variance, 1.0, 64 * W.MB)
+    A1, b1 = run_gpu(K, U, X, y, 1.0, 1.0, 64 * W.MB)
+    exact = np.log2(variance) == np.round(np.log2(variance))
+    rtol = 0.0 if exact else 3000 * EPS   # other roundings of the entries, sums of 3000 columns in fp32
+    assert np.allclose(A / variance ** 2, A1, rtol=rtol, atol=0 if exact else 1e-30)
+    assert (np.abs(b / variance - b1) <= rtol * 3000 * np.abs(y).max()).all()
+
+
 def test_limits_give_the_same_sums_up_to_rounding(K, oracle):
     U, X, y = W.random_sgpr_case(21, 260, 6000, 3)
     A1, b1 = parity(K, oracle, U, X, y, 1.0, 1.0, 64 * W.MB)
