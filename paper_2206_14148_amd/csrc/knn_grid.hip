@@ -14,6 +14,7 @@
 // looks through about a thousand points, an eighth of them for the lists.
 #include <hip/hip_runtime.h>
 
+#include <cfloat>
 #include <climits>
 #include <cmath>
 #include <cstdint>
@@ -199,8 +200,8 @@ __global__ __launch_bounds__(256) void knn_grid_queries_kernel(const float* __re
 }
 
 // (key, index) as the bits of a double: keys are not negative, so such doubles are in the order of
-// (key, index), and one v_min_f64 / v_max_f64 moves both.  +inf with its index is an ordinary large
-// number in that reading.
+// (key, index), and one v_min_f64 / v_max_f64 moves both.  +inf with no index, an empty place, is an
+// ordinary large number in that reading.
 __device__ __forceinline__ double pair_of(float key, int idx) {
     return __hiloint2double((int)__float_as_uint(key), idx);
 }
@@ -242,6 +243,10 @@ __global__ __launch_bounds__(256) void knn_grid_kernel(const float* __restrict__
     const SeedGrid<D> g = seed_grid<D>(hdr, 1 << L);
     float q[D];
     load_point<D>(Q, ldq, r, q);
+    // (a query that is not finite has no finite key: its list stays empty, as on every other path)
+    bool live = active;
+#pragma unroll
+    for (int t = 0; t < D; ++t) live &= fabsf(q[t]) < kInf;
 
     auto sqdist = [&](const f32x4& x) {
         float df = q[0] - x[0];
@@ -257,7 +262,7 @@ __global__ __launch_bounds__(256) void knn_grid_kernel(const float* __restrict__
     double best[K];
     auto reset = [&](double v) {
 #pragma unroll
-        for (int i = 0; i < K; ++i) best[i] = (i < K - k || !active) ? -1.0 : v;
+        for (int i = 0; i < K; ++i) best[i] = (i < K - k || !live) ? -1.0 : v;
     };
     auto insert = [&](double v) {
 #pragma unroll
@@ -267,8 +272,10 @@ __global__ __launch_bounds__(256) void knn_grid_kernel(const float* __restrict__
             best[i] = lo;
         }
     };
-    auto bound_key = [&]() {  // (an idle lane's -1.0 reads as a negative key)
-        return __uint_as_float((unsigned)__double2hiint(best[K - 1]));
+    // the largest key that can still enter the list; infinite keys enter none.  (An idle lane's -1.0
+    // reads as a negative key.)
+    auto bound_key = [&]() {
+        return fminf(__uint_as_float((unsigned)__double2hiint(best[K - 1])), FLT_MAX);
     };
     reset(top);
     const int own = morton_of<D>(g, L, q);
@@ -299,7 +306,9 @@ __global__ __launch_bounds__(256) void knn_grid_kernel(const float* __restrict__
         cnt = 0;
         tau = bound_key();
     };
-    // squared distance from the lane's query to a node's box: cell numbers c at the node's level
+    // squared distance from the lane's query to a node's box: cell numbers c at the node's level.  (A
+    // quarter of it, which overflows only beyond every finite key; the least normal number keeps the
+    // quarter of a tiny threshold from being rounded down.)
     auto reach = [&](int level, const int (&c)[3]) {
         float b = 0.f;
 #pragma unroll
@@ -307,9 +316,9 @@ __global__ __launch_bounds__(256) void knn_grid_kernel(const float* __restrict__
             const float lo = (g.mn[t] + (float)(c[t] << (L - level)) * g.w[t]) - g.slack[t];
             const float hi = (g.mn[t] + (float)((c[t] + 1) << (L - level)) * g.w[t]) + g.slack[t];
             const float gap = fmaxf(fmaxf(lo - q[t], q[t] - hi), 0.f);
-            b = fmaf(gap, gap, b);
+            b = fmaf(0.25f * gap, gap, b);
         }
-        return !(b * (1.f - 0x1p-17f) > tau);
+        return !(b * (1.f - 0x1p-17f) > fmaf(0.25f, tau, FLT_MIN));
     };
     int4(*st)[2] = stack[wave];
     if (lane == 0) {
@@ -329,7 +338,7 @@ __global__ __launch_bounds__(256) void knn_grid_kernel(const float* __restrict__
         const int e = __builtin_amdgcn_readfirstlane(nd.w);
         const int c0[3] = {__builtin_amdgcn_readfirstlane(nc.x), __builtin_amdgcn_readfirstlane(nc.y),
                            __builtin_amdgcn_readfirstlane(nc.z)};
-        if (__builtin_amdgcn_ballot_w64(active && reach(level, c0)) == 0) continue;  // (thresholds have moved)
+        if (__builtin_amdgcn_ballot_w64(live && reach(level, c0)) == 0) continue;  // (thresholds have moved)
         if (e - s <= kLeaf || level == L) {
             for (int p = s; p < e; p += 4) {
                 f32x4 x[4];
@@ -363,7 +372,7 @@ __global__ __launch_bounds__(256) void knn_grid_kernel(const float* __restrict__
             const int cs = __builtin_amdgcn_readlane(edge, c), ce = __builtin_amdgcn_readlane(edge, c + 1);
             if (cs == ce) continue;
             const int cc[3] = {2 * c0[0] + (c & 1), 2 * c0[1] + ((c >> 1) & 1), 2 * c0[2] + ((c >> 2) & 1)};
-            if (__builtin_amdgcn_ballot_w64(active && reach(level + 1, cc)) == 0) continue;
+            if (__builtin_amdgcn_ballot_w64(live && reach(level + 1, cc)) == 0) continue;
             if (lane == 0) {
                 st[sp][0] = int4{level + 1, (code << D) | c, cs, ce};
                 st[sp][1] = int4{cc[0], cc[1], cc[2], 0};
@@ -378,8 +387,8 @@ __global__ __launch_bounds__(256) void knn_grid_kernel(const float* __restrict__
     for (int i = 0; i < K; ++i) {
         const int p = i - (K - k);
         if (p >= 0) {
-            lk[lb + p] = __uint_as_float((unsigned)__double2hiint(best[i]));
-            li[lb + p] = __double2loint(best[i]);
+            lk[lb + p] = live ? __uint_as_float((unsigned)__double2hiint(best[i])) : kInf;
+            li[lb + p] = live ? __double2loint(best[i]) : kNoIdx;
         }
     }
     // (the lists of further point ranges stay empty)

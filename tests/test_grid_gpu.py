@@ -98,3 +98,21 @@ def test_query_chunks_share_one_tree(K):
     both(K, Q, X, 16, limit)
     spot = points("one_spot", 60_000, 2, gen)  # several chunks on the filter path behind the tree's check
     both(K, Q, spot, 16, limit)
+
+
+@pytest.mark.parametrize("d", [1, 2, 3])
+@pytest.mark.parametrize("k", [1, 5, 32])
+def test_keys_beyond_the_largest_float_enter_no_list(K, d, k):
+    # as on the path that looks at every pair: a pair whose fp32 distance is infinite is no neighbour
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(100 * d + k)
+    X, Q = points("uniform", 20_000, d, gen), points("uniform", 6000, d, gen)
+    far = Q.clone()
+    for i, v in enumerate((1e19, -1e19, 1.8446742e19, 3e19, 1e20, -1e25, 1e30, 3e38, -3e38)):
+        far[7 * i + 3, i % d] = v
+        far[2000 + i] = v
+    idx = both(K, far, X, k)
+    assert (idx[2004] == 2 ** 31 - 1).all()
+    for scale in (1e-28, 1e-25, 1e-20, 1e-19, 1e18, 1e19, 1e20, 1e25, 1e37):
+        print("scale", scale, flush=True)
+        both(K, Q * scale, X * scale, k)
