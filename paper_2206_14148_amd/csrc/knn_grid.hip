@@ -51,6 +51,34 @@ __device__ __forceinline__ void load_point(const float* __restrict__ P, int64_t 
     for (int t = 0; t < D; ++t) x[t] = P[j * ld + t];
 }
 
+// One more in counts[code] for every lane with `on`.  Lanes that follow each other may share a cell: while
+// the first lane's cell has at least eight of them, they share one atomic; the rest go one by one.
+// (With one per lane, where all go to one word each takes 12 ns: 1e5 queries beyond a corner of 1e5
+// points, d = 3, k = 16, took 2.52 ms a call and take 0.29, 1e6 of 1e6 23.8 and 1.4.  Uniform ones lose
+// nothing: 4.5 ms.)  Returns what the lane's own increment would have found (FETCH), else nothing useful.
+template <bool FETCH>
+__device__ __forceinline__ int count_up(int* __restrict__ counts, int code, bool on) {
+    const int lane = (int)__lane_id();
+    uint64_t todo = __builtin_amdgcn_ballot_w64(on);
+    int place = 0;
+    while (todo) {
+        const int lead = __builtin_ctzll(todo);
+        const int cell = __builtin_amdgcn_readlane(code, lead);
+        const uint64_t same = __builtin_amdgcn_ballot_w64(code == cell) & todo;
+        const int many = __builtin_popcountll(same);
+        if (many < 8) break;
+        int before = 0;
+        if (lane == lead) before = atomicAdd(counts + cell, many);
+        if (FETCH) {
+            before = __builtin_amdgcn_readlane(before, lead);
+            if ((same >> lane) & 1) place = before + __builtin_popcountll(same & ((1ull << lane) - 1));
+        }
+        todo &= ~same;
+    }
+    if ((todo >> lane) & 1) place = atomicAdd(counts + code, 1);
+    return place;
+}
+
 // The kernels that count and scan serve the points first, then every chunk of queries; `only_if` is
 // null for the points and the word hdr[kGridWord] for the queries, whose counts would otherwise be
 // written over what the filter path has packed into the same area.
@@ -67,11 +95,10 @@ __global__ __launch_bounds__(256) void knn_grid_count_kernel(const float* __rest
                                                              int* __restrict__ counts) {
     if (only_if && !*only_if) return;
     const int j = blockIdx.x * 256 + threadIdx.x;
-    if (j >= n) return;
     const SeedGrid<D> g = seed_grid<D>(hdr, 1 << L);
     float x[D];
-    load_point<D>(P, ld, j, x);
-    atomicAdd(counts + morton_of<D>(g, L, x), 1);
+    load_point<D>(P, ld, j < n ? j : n - 1, x);
+    count_up<false>(counts, morton_of<D>(g, L, x), j < n);
 }
 
 // sums[b] = points in the b-th run of kScanCells cells; skew (if given) += sum of the counts' squares
@@ -175,15 +202,16 @@ __global__ __launch_bounds__(256) void knn_grid_points_kernel(const float* __res
                                                               const unsigned* __restrict__ hdr, int L,
                                                               int* __restrict__ cursor,
                                                               f32x4* __restrict__ sorted) {
+    if (!hdr[kGridWord]) return;
     const int j = blockIdx.x * 256 + threadIdx.x;
-    if (j >= n || !hdr[kGridWord]) return;
     const SeedGrid<D> g = seed_grid<D>(hdr, 1 << L);
     float x[D];
-    load_point<D>(X, ldx, j, x);
+    load_point<D>(X, ldx, j < n ? j : n - 1, x);
     f32x4 v = {0.f, 0.f, 0.f, __int_as_float(j)};
 #pragma unroll
     for (int t = 0; t < D; ++t) v[t] = x[t];
-    sorted[atomicAdd(cursor + morton_of<D>(g, L, x), 1)] = v;
+    const int at = count_up<true>(cursor, morton_of<D>(g, L, x), j < n);
+    if (j < n) sorted[at] = v;
 }
 
 // the queries' numbers in cell order
@@ -191,12 +219,13 @@ template <int D>
 __global__ __launch_bounds__(256) void knn_grid_queries_kernel(const float* __restrict__ Q, int64_t ldq, int rows,
                                                                const unsigned* __restrict__ hdr, int L,
                                                                int* __restrict__ cursor, int* __restrict__ order) {
+    if (!hdr[kGridWord]) return;
     const int r = blockIdx.x * 256 + threadIdx.x;
-    if (r >= rows || !hdr[kGridWord]) return;
     const SeedGrid<D> g = seed_grid<D>(hdr, 1 << L);
     float q[D];
-    load_point<D>(Q, ldq, r, q);
-    order[atomicAdd(cursor + morton_of<D>(g, L, q), 1)] = r;
+    load_point<D>(Q, ldq, r < rows ? r : rows - 1, q);
+    const int at = count_up<true>(cursor, morton_of<D>(g, L, q), r < rows);
+    if (r < rows) order[at] = r;
 }
 
 // (key, index) as the bits of a double: keys are not negative, so such doubles are in the order of

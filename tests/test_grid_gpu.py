@@ -116,3 +116,17 @@ def test_keys_beyond_the_largest_float_enter_no_list(K, d, k):
     for scale in (1e-28, 1e-25, 1e-20, 1e-19, 1e18, 1e19, 1e20, 1e25, 1e37):
         print("scale", scale, flush=True)
         both(K, Q * scale, X * scale, k)
+
+
+@pytest.mark.parametrize("m", [8000, 8007, 8191])
+def test_queries_that_share_few_cells(K, m):
+    # counted by one atomic for all lanes of a cell: whole waves, the ragged last one, a few cells and many
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(m)
+    X = points("uniform", 30_000, 3, gen)
+    Q = points("uniform", m, 3, gen)
+    both(K, Q + 10, X, 16)
+    mixed = Q.clone()
+    mixed[::2] += 10
+    mixed[1::8] -= 10
+    both(K, mixed, X, 16)
