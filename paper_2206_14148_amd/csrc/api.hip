@@ -219,6 +219,7 @@ knn_status run_search(const knn_plan_t& plan, const float* Q, int64_t ldq, const
             : xn;
 
     const int64_t chunk_rows = plan.chunk_rows < m ? plan.chunk_rows : m;
+    const bool own = Q == X && ldq == ldx && m == n && chunk_rows == n;
 
     hipError_t e;
     // Small searches of the squared-Euclidean metric skip the filter and all that prepares it: the
@@ -273,8 +274,8 @@ knn_status run_search(const knn_plan_t& plan, const float* Q, int64_t ldq, const
     } else if (plan.path == KNN_PATH_LOWD_MFMA || plan.path == KNN_PATH_LOWD_BF16) {
         hipEvent_t t0 = mark(stream);
         e = plan.path == KNN_PATH_LOWD_BF16
-                ? launch_lowd_bf16(Q, ldq, X, ldx, ws, 0, n, d, k, S, true, plan.seed_cells, chunk_rows, nullptr, nullptr,
-                                   nullptr, stream)
+                ? launch_lowd_bf16(Q, ldq, X, ldx, ws, 0, n, d, k, S, true, plan.seed_cells, chunk_rows, own, true,
+                                   nullptr, nullptr, nullptr, stream)
                 : launch_lowd_mfma(Q, ldq, X, ldx, ws, 0, n, d, k, S, true, nullptr, nullptr, stream);
         if (e != hipSuccess) {
             drop_bracket(t0);
@@ -302,7 +303,7 @@ knn_status run_search(const knn_plan_t& plan, const float* Q, int64_t ldq, const
             e = launch_lowd_mfma(Qc, ldq, X, ldx, ws, rows, n, d, k, S, false, lk, li, stream);
         else if (plan.path == KNN_PATH_LOWD_BF16)
             e = launch_lowd_bf16(Qc, ldq, X, ldx, ws, rows, n, d, k, S, false, plan.seed_cells,
-                                 chunk_rows, idx + row0 * k, lk, li, stream);
+                                 chunk_rows, own, c == 0, idx + row0 * k, lk, li, stream);
         else if (plan.path == KNN_PATH_MFMA_SPLIT || packed_plan) {
             if (wide_plan && packed) {
                 // the queries' B operands bf16(-2 q) in operand order; thresholds start from +inf

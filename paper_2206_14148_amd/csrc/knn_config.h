@@ -34,10 +34,15 @@ constexpr int kSeedMaxD = 3;
 constexpr int kSeedMaxCells = 32768;
 constexpr int kSeedCellsPerPointNum = 2;
 constexpr int kSeedCellsPerPointDen = 3;
-// octree search (knn_grid.hip), d <= kSeedMaxD: header word that says it answers the call (the two
-// words from kGridWord + 2 on: its measure of how unevenly the points are spread), longest list kept
-// in registers, fewest points
+// octree search (knn_grid.hip), d <= kSeedMaxD.  Header words: that the tree serves the call; waves of the
+// present chunk of queries that gave up; two words of how unevenly the points are spread; that the area
+// holds the filter's points already, of an earlier chunk
 constexpr int kGridWord = 32;
+constexpr int kGridLeft = kGridWord + 1;
+constexpr int kGridSkew = kGridWord + 2;
+constexpr int kGridPacked = kGridWord + 4;
+constexpr int kGridWords = 5;
+// longest list kept in registers, fewest points, most cells
 constexpr int kGridMaxK = 32;
 constexpr int64_t kGridMinPoints = 4096;
 constexpr int kGridMaxCells = 1 << 21;

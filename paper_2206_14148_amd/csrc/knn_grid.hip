@@ -31,6 +31,7 @@ namespace {
 constexpr int kScanCells = 4096;  // cells per workgroup of the scan
 constexpr int kGridCand = 8;      // accepted pairs a lane holds before they sink into its list
 // (n = m = 1e6, d = 3, k = 16, the search in ms: 24 points 5.36, 48 4.23, 64 4.21, 96 4.21)
+constexpr float kGridLeast = 0x1p-100f, kGridMost = 0x1p116f;  // squared lengths that are safe with the filter
 constexpr int kLeaf = 48;         // a node of this many points or fewer is looked through, not split
 
 // Morton code of the cell of x: bit b of axis t is bit D b + t
@@ -153,7 +154,7 @@ __global__ __launch_bounds__(512) void knn_grid_sums_kernel(const unsigned* __re
     }
     if (t < runs) sums[t] = t > 0 ? v[t - 1] : 0;
     if (n > 0 && t == 0) {
-        const unsigned long long skew = *reinterpret_cast<const unsigned long long*>(hdr + kGridWord + 2);
+        const unsigned long long skew = *reinterpret_cast<const unsigned long long*>(hdr + kGridSkew);
         hdr[kGridWord] = (double)skew * 128.0 <= (double)n * (double)n ? 1u : 0u;
     }
 }
@@ -251,7 +252,8 @@ __global__ __launch_bounds__(256) void knn_grid_kernel(const float* __restrict__
                                                        const f32x4* __restrict__ sorted,
                                                        const int* __restrict__ starts,
                                                        const unsigned* __restrict__ hdr, int L, int rows, int n,
-                                                       int k, int S, int groups, float* __restrict__ lk,
+                                                       int k, int S, int groups, int budget,
+                                                       unsigned many, unsigned* __restrict__ left, float* __restrict__ lk,
                                                        int* __restrict__ li) {
     constexpr int CH = 1 << D;
     // entries of the stack: CH - 1 left over per level and the node in hand; D L <= 21
@@ -287,6 +289,39 @@ __global__ __launch_bounds__(256) void knn_grid_kernel(const float* __restrict__
         }
         return acc;
     };
+    // over the budget: the filter looks at every pair of these rows at less cost
+    auto leave = [&]() {
+        if (lane == 0) atomicAdd(left, 1u);
+        if (active)
+            for (int p = 0; p < S; ++p) li[((size_t)r * S + p) * k] = kGridRedo;
+    };
+    // what of a node's bound is sure in spite of the sums' roundings; nothing where they may overflow
+    float sure = 1.f - 0x1p-17f;
+    {
+        // At more than 2^13 box diagonals from the points what the sums' roundings allow (2^-17 of a key)
+        // is a good part of what sets their keys apart: hardly a node would be left out.  (Keys near
+        // the largest float or the least normal one stay here: the filter's sums would overflow or lose
+        // their pieces.  If even a quarter of the squared distance overflows, so do all keys, and the
+        // list stays empty.)
+        float b = 0.f, diagonal = 0.f;
+#pragma unroll
+        for (int t = 0; t < D; ++t) {
+            const float range = g.w[t] * (float)g.G;
+            const float gap = fmaxf(fmaxf(g.mn[t] - q[t], q[t] - (g.mn[t] + range)), 0.f);
+            b = fmaf(0.25f * gap, gap, b);
+            diagonal = fmaf(range, range, diagonal);
+        }
+        live &= !(b == kInf);
+        if (!(diagonal > kGridLeast && diagonal < kGridMost) ||
+            __builtin_amdgcn_ballot_w64(live && b > kGridMost) != 0) {
+            budget = INT_MAX;
+            if (!(diagonal < kGridMost) || __builtin_amdgcn_ballot_w64(live && b > kGridMost) != 0) sure = 0.f;
+        } else if (__builtin_amdgcn_ballot_w64(live && b > 0x1p24f * diagonal) != 0 ||
+                 (many && __hip_atomic_load(left, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > many)) {
+            leave();
+            return;
+        }
+    }
     const double top = pair_of(kInf, kNoIdx);
     double best[K];
     auto reset = [&](double v) {
@@ -329,15 +364,16 @@ __global__ __launch_bounds__(256) void knn_grid_kernel(const float* __restrict__
     // every point of a leaf cost the wave a round for one or two of its lanes.)
     double* buf = &cand[wave][0][lane];
     int cnt = 0;
+    int steps = 0;  // what the wave has done: two per node, one per group of four points, one or two per round
     auto drain = [&]() {
-        for (int c = 0; __builtin_amdgcn_ballot_w64(c < cnt) != 0; ++c)
+        for (int c = 0; __builtin_amdgcn_ballot_w64(c < cnt) != 0; ++c) {
             insert(c < cnt ? buf[c * 64] : top);
+            steps += (K + 8) / 16;
+        }
         cnt = 0;
         tau = bound_key();
     };
-    // squared distance from the lane's query to a node's box: cell numbers c at the node's level.  (A
-    // quarter of it, which overflows only beyond every finite key; the least normal number keeps the
-    // quarter of a tiny threshold from being rounded down.)
+    // squared distance from the lane's query to a node's box: cell numbers c at the node's level
     auto reach = [&](int level, const int (&c)[3]) {
         float b = 0.f;
 #pragma unroll
@@ -345,9 +381,9 @@ __global__ __launch_bounds__(256) void knn_grid_kernel(const float* __restrict__
             const float lo = (g.mn[t] + (float)(c[t] << (L - level)) * g.w[t]) - g.slack[t];
             const float hi = (g.mn[t] + (float)((c[t] + 1) << (L - level)) * g.w[t]) + g.slack[t];
             const float gap = fmaxf(fmaxf(lo - q[t], q[t] - hi), 0.f);
-            b = fmaf(0.25f * gap, gap, b);
+            b = fmaf(gap, gap, b);
         }
-        return !(b * (1.f - 0x1p-17f) > fmaf(0.25f, tau, FLT_MIN));
+        return !(b * sure > tau);
     };
     int4(*st)[2] = stack[wave];
     if (lane == 0) {
@@ -357,8 +393,9 @@ __global__ __launch_bounds__(256) void knn_grid_kernel(const float* __restrict__
     int sp = 1;
     // the child that most of the wave's queries are near: the way to the cell of its middle lane
     const int mid = __builtin_amdgcn_readlane(own, rows - base > 32 ? 32 : 0);
-    while (sp > 0) {
+    while (sp > 0 && steps <= budget) {
         --sp;
+        steps += 2;
         wave_sync();
         const int4 nd = st[sp][0], nc = st[sp][1];
         const int level = __builtin_amdgcn_readfirstlane(nd.x);
@@ -369,6 +406,7 @@ __global__ __launch_bounds__(256) void knn_grid_kernel(const float* __restrict__
                            __builtin_amdgcn_readfirstlane(nc.z)};
         if (__builtin_amdgcn_ballot_w64(live && reach(level, c0)) == 0) continue;  // (thresholds have moved)
         if (e - s <= kLeaf || level == L) {
+            steps += (e - s + 3) >> 2;
             for (int p = s; p < e; p += 4) {
                 f32x4 x[4];
 #pragma unroll
@@ -408,6 +446,10 @@ __global__ __launch_bounds__(256) void knn_grid_kernel(const float* __restrict__
             }
             ++sp;
         }
+    }
+    if (sp > 0) {
+        leave();
+        return;
     }
     drain();
     if (!active) return;
@@ -465,7 +507,7 @@ hipError_t count_and_scan(const float* P, int64_t ld, int64_t count, const Cells
         P, ld, (int)count, hdr, c.L, only_if, c.cursor);
     knn_grid_sum_kernel<<<dim3((unsigned)c.runs), dim3(256), 0, stream>>>(
         only_if, c.cursor, c.ncell, c.sums,
-        points ? reinterpret_cast<unsigned long long*>(hdr + kGridWord + 2) : nullptr);
+        points ? reinterpret_cast<unsigned long long*>(hdr + kGridSkew) : nullptr);
     knn_grid_sums_kernel<<<dim3(1), dim3(512), 0, stream>>>(only_if, c.sums, c.runs, points ? count : 0, hdr);
     knn_grid_scan_kernel<<<dim3((unsigned)c.runs), dim3(256), 0, stream>>>(
         only_if, c.sums, c.ncell, (int)count, c.cursor, points ? c.starts : nullptr);
@@ -488,7 +530,7 @@ hipError_t search_d(const float* Q, int64_t ldq, const float* X, int64_t ldx, in
                     int S, unsigned* hdr, void* area, const void* sorted, int* order, float* lk, int* li,
                     hipStream_t stream) {
     const Cells c = cells_of(n, D, area);
-    const bool same = Q == X && ldq == ldx && rows == n;  // the points' own order serves the queries
+    const bool same = Q == X && ldq == ldx && rows == n;  // the points' order serves the queries
     if (!same) {
         hipError_t e = count_and_scan<D>(Q, ldq, rows, c, hdr, false, stream);
         if (e != hipSuccess) return e;
@@ -496,10 +538,17 @@ hipError_t search_d(const float* Q, int64_t ldq, const float* X, int64_t ldx, in
             Q, ldq, (int)rows, hdr, c.L, c.cursor, order);
     }
     const int groups = (int)((rows + 255) / 256);
+    // Where queries and points lie alike no wave took more steps than 15, 23 and 45 sqrt(n) (lists of 8, 16
+    // and 32 in registers; n from 4096 to 1e6, uniform, normal, clumps, a shell; the worst waves are those
+    // whose queries follow each other across a gap of the order).  A step takes 0.2 to 0.35 us.
+    const int budget = (int)((6.0 + 1.5 * (k <= 8 ? 8 : (k <= 16 ? 16 : 32))) * sqrt((double)n));
+    // in a launch of several rounds the later waves leave at once if many have done so
+    const int64_t waves = (rows + 63) / 64;
+    const unsigned many = waves > 4 * 4 * kNumCU ? (unsigned)(waves / 16) : 0u;
     const dim3 grid((unsigned)((groups + 7) / 8 * 8));
     auto go = [&](auto kernel) {
         kernel<<<grid, dim3(256), 0, stream>>>(Q, ldq, same ? nullptr : order, static_cast<const f32x4*>(sorted),
-                                               c.starts, hdr, c.L, (int)rows, (int)n, k, S, groups, lk, li);
+                                               c.starts, hdr, c.L, (int)rows, (int)n, k, S, groups, budget, many, hdr + kGridLeft, lk, li);
     };
     if (k <= 8) go(knn_grid_kernel<D, 8>);
     else if (k <= 16) go(knn_grid_kernel<D, 16>);
@@ -507,12 +556,20 @@ hipError_t search_d(const float* Q, int64_t ldq, const float* X, int64_t ldx, in
     return hipGetLastError();
 }
 
+__global__ void knn_grid_again_kernel(unsigned* __restrict__ hdr) {
+    if (!hdr[kGridWord] || hdr[kGridLeft]) {
+        hdr[kGridWord] = 0u;
+        hdr[kGridPacked] = 1u;
+    }
+    hdr[kGridLeft] = 0u;
+}
+
 }  // namespace
 
 // The queries of a wave descend together, so they have to lie close to each other: with fewer than a
 // query for eight points a wave enters nearly as many nodes as its 64 queries would one by one.
-bool grid_applies(int64_t chunk_rows, int64_t n, int k) {
-    return n >= kGridMinPoints && k <= kGridMaxK && chunk_rows >= n / 8;
+bool grid_applies(int64_t rows, int64_t n, int /*d*/, int k, bool /*own*/) {
+    return n >= kGridMinPoints && k <= kGridMaxK && rows >= n / 8;
 }
 
 hipError_t launch_grid_build(const float* X, int64_t ldx, int64_t n, int d, unsigned* hdr, void* cells,
@@ -523,6 +580,11 @@ hipError_t launch_grid_build(const float* X, int64_t ldx, int64_t n, int d, unsi
         case 3: return build_d<3>(X, ldx, n, hdr, cells, sorted, stream);
         default: return hipErrorInvalidValue;
     }
+}
+
+hipError_t launch_grid_again(unsigned* hdr, hipStream_t stream) {
+    knn_grid_again_kernel<<<dim3(1), dim3(1), 0, stream>>>(hdr);
+    return hipGetLastError();
 }
 
 hipError_t launch_grid_search(const float* Q, int64_t ldq, const float* X, int64_t ldx, int64_t rows,

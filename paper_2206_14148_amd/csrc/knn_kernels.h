@@ -50,23 +50,32 @@ hipError_t launch_lowd_mfma(const float* Q, int64_t ldq, const float* X, int64_t
 // rows == 0 as above.  seed_cells > 0 (d <= kSeedMaxD only): the area continues with
 // seed_cells^d ints, the points counted into a grid of that many cells per axis, from which
 // every query's list gets a finite starting threshold.  Where grid_applies, the same area first
-// serves the octree search below, and the kernels of the filter do nothing if that one answers.
-// chunk_rows: rows of a full chunk (the same in every call of a search); order: rows ints that nobody else uses until the search is done (not read when rows == 0).
+// serves the octree search below; the points are then packed behind it, if it is turned down or
+// leaves queries over, and the filter answers those.
+// chunk_rows: rows of a full chunk, own: the queries are the points in their order and make one chunk
+// (both the same in every call of a search); first: the search's first chunk; order: rows ints that nobody else uses until the search is done (not read when rows == 0).
 hipError_t launch_lowd_bf16(const float* Q, int64_t ldq, const float* X, int64_t ldx, void* packed,
                             int64_t rows, int64_t n, int d, int k, int S, bool pack, int seed_cells,
-                            int64_t chunk_rows, int* order, float* lk, int* li, hipStream_t stream);
+                            int64_t chunk_rows, bool own, bool first, int* order, float* lk, int* li,
+                            hipStream_t stream);
 
 // d <= kSeedMaxD (knn_grid.hip): the same keys, found by descending an octree over the points.
 //   launch_grid_build   after the bounding box is in hdr: the points in cell order in `sorted` (16
 //                       bytes each), the cells' starts in `cells` (32 n bytes); hdr[kGridWord] = 1
 //                       if the points are spread well enough for the search to pay, else 0
-//   launch_grid_search  fills the lists of the rows if hdr[kGridWord] is 1, else does nothing
-bool grid_applies(int64_t chunk_rows, int64_t n, int k);
+//   launch_grid_search  if hdr[kGridWord] is 1 fills the lists of the rows, else does nothing.  Waves that
+//                       would look through too much of the tree give up: hdr[kGridLeft] counts
+//                       them, and the first index of each of their rows' lists is kGridRedo
+//   launch_grid_again   before a further chunk: if the area holds the filter's points by now, the
+//                       tree is gone
+constexpr int kGridRedo = -9;
+bool grid_applies(int64_t chunk_rows, int64_t n, int d, int k, bool own);
 hipError_t launch_grid_build(const float* X, int64_t ldx, int64_t n, int d, unsigned* hdr, void* cells,
                              void* sorted, hipStream_t stream);
 hipError_t launch_grid_search(const float* Q, int64_t ldq, const float* X, int64_t ldx, int64_t rows,
                               int64_t n, int d, int k, int S, unsigned* hdr, void* cells, const void* sorted,
                               int* order, float* lk, int* li, hipStream_t stream);
+hipError_t launch_grid_again(unsigned* hdr, hipStream_t stream);
 
 // d > kPbMaxD, and the cosine metric at any d: bf16 matrix-core filter on split values, exact
 // fp32 test of what passes it (knn_split.hip).

@@ -653,7 +653,7 @@ __global__ void knn_bbox_init_kernel(unsigned* __restrict__ hdr) {
     if (t == 0) hdr[0] = 0u;
     if (t >= 1 && t <= kPbMaxD) hdr[t] = 0xffffffffu;
     if (t > kPbMaxD && t <= 2 * kPbMaxD) hdr[t] = 0u;
-    if (t >= kGridWord && t < kGridWord + 4) hdr[t] = 0u;
+    if (t >= kGridWord && t < kGridWord + kGridWords) hdr[t] = 0u;
 }
 
 template <int D>
@@ -716,8 +716,13 @@ __device__ __forceinline__ void bbox_centre(const unsigned* __restrict__ hdr, fl
 // Pairs beyond the bound never reach the exact test, which takes most of the list warm-up away;
 // results do not change, because every pair at or below the true k-th distance still passes.
 // ---------------------------------------------------------------------------------------
+// Whether the area is to take the filter's points now: not while the octree (knn_grid.hip) serves there.
+__device__ __forceinline__ bool filter_to_pack(const unsigned* __restrict__ hdr) {
+    return (!hdr[kGridWord] || hdr[kGridLeft]) && !hdr[kGridPacked];
+}
+
 __global__ void knn_zero_ints_kernel(const unsigned* __restrict__ hdr, int* __restrict__ p, int count) {
-    if (hdr[kGridWord]) return;  // (the octree's cells lie there)
+    if (!filter_to_pack(hdr)) return;
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i < count) p[i] = 0;
 }
@@ -734,7 +739,7 @@ template <int D>
 __global__ __launch_bounds__(256) void knn_cell_count_kernel(const float* __restrict__ X, int64_t ldx,
                                                              int n, const unsigned* __restrict__ hdr,
                                                              int G, int* __restrict__ counts) {
-    if (hdr[kGridWord]) return;  // the octree search (knn_grid.hip) answers the call
+    if (!filter_to_pack(hdr)) return;
     const int j = blockIdx.x * 256 + threadIdx.x;
     if (j >= n) return;
     const SeedGrid<D> g = seed_grid<D>(hdr, G);
@@ -746,7 +751,7 @@ __global__ __launch_bounds__(256) void knn_cell_count_kernel(const float* __rest
 __global__ __launch_bounds__(256) void knn_cell_scan_kernel(const unsigned* __restrict__ hdr,
                                                             int* __restrict__ counts, int ncell,
                                                             int* __restrict__ starts) {
-    if (hdr[kGridWord]) return;
+    if (!filter_to_pack(hdr)) return;
     __shared__ int part[256];
     const int t = threadIdx.x;
     const int per = (ncell + 255) / 256;
@@ -781,7 +786,7 @@ __global__ __launch_bounds__(256) void knn_cell_fill_kernel(const float* __restr
                                                             int G, const int* __restrict__ starts,
                                                             int* __restrict__ cursor,
                                                             f32x4* __restrict__ sorted) {
-    if (hdr[kGridWord]) return;
+    if (!filter_to_pack(hdr)) return;
     const int j = blockIdx.x * 256 + threadIdx.x;
     if (j >= n) return;
     const SeedGrid<D> g = seed_grid<D>(hdr, G);
@@ -918,7 +923,7 @@ __global__ __launch_bounds__(256) void knn_pack_bf16_kernel(const float* __restr
                                                             int64_t ldx, int n,
                                                             uint4* __restrict__ Xp,
                                                             unsigned* __restrict__ hdr) {
-    if (hdr[kGridWord]) return;
+    if (!filter_to_pack(hdr)) return;
     constexpr int NM = FilterSlots<D>::kMfmas;
     const int j = blockIdx.x * 256 + threadIdx.x;
     float c[D];
@@ -986,13 +991,23 @@ __global__ __launch_bounds__(256, FilterSlots<D>::kMfmas == 1 ? 4 : 3) void knn_
     sc.list_key = reinterpret_cast<float*>(sc.cand_idx + kWave);
     sc.list_idx = reinterpret_cast<int*>(sc.list_key + k);
 
-    if (hdr[kGridWord]) return;
+    const bool tree = hdr[kGridWord];
+    if (tree && !hdr[kGridLeft]) return;  // the octree search has answered
     const int s = blockIdx.y;
     const int wave_row0 = (blockIdx.x * 4 + wave) * (NS * 32);
     if (wave_row0 >= rows) return;  // whole wave idle; no workgroup barrier is used below
+    // rows of this wave to search: all, or those that the octree search left
+    uint64_t mine = ~0ull;
+    if (tree) {
+        static_assert(NS * 32 == kWave, "one row per lane");
+        const int r = wave_row0 + lane;
+        mine = __builtin_amdgcn_ballot_w64(r < rows && li[((size_t)r * S + s) * k] == kGridRedo);
+        if (mine == 0) return;
+    }
 
     for (int qq = 0; qq < NS * 32; ++qq) {
         if (wave_row0 + qq >= rows) break;
+        if (!((mine >> qq) & 1)) continue;
         const size_t lb = ((size_t)(wave_row0 + qq) * S + s) * k;
         for (int p = lane; p < k; p += kWave) {
             lk[lb + p] = kInf;
@@ -1027,7 +1042,7 @@ __global__ __launch_bounds__(256, FilterSlots<D>::kMfmas == 1 ? 4 : 3) void knn_
 #pragma unroll
     for (int st = 0; st < NS; ++st) {
         const int r = wave_row0 + st * 32 + i32;
-        const bool active = r < rows;
+        const bool active = r < rows && ((mine >> (st * 32 + i32)) & 1);
         float qc[D];
 #pragma unroll
         for (int t = 0; t < D; ++t) {
@@ -1090,7 +1105,7 @@ __global__ __launch_bounds__(256, FilterSlots<D>::kMfmas == 1 ? 4 : 3) void knn_
             tcap[1] = h ? mine : other;
 #pragma unroll
             for (int st = 0; st < NS; ++st)
-                if (wave_row0 + st * 32 + i32 < rows) tau[st] = tcap[st];
+                if (tau[st] > -kInf) tau[st] = tcap[st];
         }
     }
 #pragma unroll
@@ -1356,8 +1371,8 @@ static hipError_t launch_lowd_mfma_d(const float* Q, int64_t ldq, const float* X
 template <int D>
 static hipError_t launch_lowd_bf16_d(const float* Q, int64_t ldq, const float* X, int64_t ldx,
                                      void* packed, int64_t rows, int64_t n, int k, int S,
-                                     bool pack, int seed_cells, int64_t chunk_rows, int* order, float* lk, int* li,
-                                     hipStream_t stream) {
+                                     bool pack, int seed_cells, int64_t chunk_rows, bool own, bool first,
+                                     int* order, float* lk, int* li, hipStream_t stream) {
     constexpr int NM = FilterSlots<D>::kMfmas;
     unsigned* hdr = static_cast<unsigned*>(packed);
     uint4* Xp = reinterpret_cast<uint4*>(static_cast<unsigned char*>(packed) + kAlign);
@@ -1373,16 +1388,9 @@ static hipError_t launch_lowd_bf16_d(const float* Q, int64_t ldq, const float* X
     f32x4* sorted = reinterpret_cast<f32x4*>(reinterpret_cast<unsigned char*>(cursor) +
                                              align_up((uint64_t)ncell * 4));
     const dim3 pgrid((unsigned)((n + 255) / 256));
-    if (pack) {
-        knn_bbox_init_kernel<<<dim3(1), dim3(64), 0, stream>>>(hdr);
-        const unsigned bgrid = pgrid.x < 1024u ? pgrid.x : 1024u;
-        knn_bbox_kernel<D><<<dim3(bgrid), dim3(256), 0, stream>>>(X, ldx, (int)n, hdr);
-        if constexpr (D <= kSeedMaxD) {
-            if (seed_cells > 0 && grid_applies(chunk_rows, n, k)) {
-                hipError_t eg = launch_grid_build(X, ldx, n, D, hdr, Xp, sorted, stream);
-                if (eg != hipSuccess) return eg;
-            }
-        }
+    const bool tree = D <= kSeedMaxD && seed_cells > 0 &&
+                      grid_applies(chunk_rows, n, D, k, own);
+    auto pack_points = [&]() {
         knn_pack_bf16_kernel<D><<<pgrid, dim3(256), 0, stream>>>(X, ldx, (int)n, Xp, hdr);
         if constexpr (D <= kSeedMaxD) {
             if (seed_cells > 0) {
@@ -1395,15 +1403,22 @@ static hipError_t launch_lowd_bf16_d(const float* Q, int64_t ldq, const float* X
                     X, ldx, (int)n, hdr, seed_cells, starts, cursor, sorted);
             }
         }
-        hipError_t e0 = hipGetLastError();
+        return hipGetLastError();
+    };
+    if (pack) {
+        knn_bbox_init_kernel<<<dim3(1), dim3(64), 0, stream>>>(hdr);
+        const unsigned bgrid = pgrid.x < 1024u ? pgrid.x : 1024u;
+        knn_bbox_kernel<D><<<dim3(bgrid), dim3(256), 0, stream>>>(X, ldx, (int)n, hdr);
+        hipError_t e0 = tree ? launch_grid_build(X, ldx, n, D, hdr, Xp, sorted, stream) : pack_points();
         if (e0 != hipSuccess) return e0;
     }
     if (rows == 0) return hipSuccess;
-    if constexpr (D <= kSeedMaxD) {
-        if (seed_cells > 0 && grid_applies(chunk_rows, n, k)) {
-            hipError_t eg = launch_grid_search(Q, ldq, X, ldx, rows, n, D, k, S, hdr, Xp, sorted, order, lk, li, stream);
-            if (eg != hipSuccess) return eg;
-        }
+    if (tree) {
+        hipError_t eg = first ? hipSuccess : launch_grid_again(hdr, stream);
+        if (eg == hipSuccess)
+            eg = launch_grid_search(Q, ldq, X, ldx, rows, n, D, k, S, hdr, Xp, sorted, order, lk, li, stream);
+        if (eg == hipSuccess) eg = pack_points();
+        if (eg != hipSuccess) return eg;
     }
     const size_t per_wave = (size_t)(2 * kPbSets * 32 * kPbCand + 2 * kWave + 2 * k) * 4;
     const size_t lds = per_wave * 4;
@@ -1420,16 +1435,17 @@ static hipError_t launch_lowd_bf16_d(const float* Q, int64_t ldq, const float* X
 
 hipError_t launch_lowd_bf16(const float* Q, int64_t ldq, const float* X, int64_t ldx, void* packed,
                             int64_t rows, int64_t n, int d, int k, int S, bool pack, int seed_cells,
-                            int64_t chunk_rows, int* order, float* lk, int* li, hipStream_t stream) {
+                            int64_t chunk_rows, bool own, bool first, int* order, float* lk, int* li,
+                            hipStream_t stream) {
     switch (d) {
-        case 1: return launch_lowd_bf16_d<1>(Q, ldq, X, ldx, packed, rows, n, k, S, pack, seed_cells, chunk_rows, order, lk, li, stream);
-        case 2: return launch_lowd_bf16_d<2>(Q, ldq, X, ldx, packed, rows, n, k, S, pack, seed_cells, chunk_rows, order, lk, li, stream);
-        case 3: return launch_lowd_bf16_d<3>(Q, ldq, X, ldx, packed, rows, n, k, S, pack, seed_cells, chunk_rows, order, lk, li, stream);
-        case 4: return launch_lowd_bf16_d<4>(Q, ldq, X, ldx, packed, rows, n, k, S, pack, seed_cells, chunk_rows, order, lk, li, stream);
-        case 5: return launch_lowd_bf16_d<5>(Q, ldq, X, ldx, packed, rows, n, k, S, pack, seed_cells, chunk_rows, order, lk, li, stream);
-        case 6: return launch_lowd_bf16_d<6>(Q, ldq, X, ldx, packed, rows, n, k, S, pack, seed_cells, chunk_rows, order, lk, li, stream);
-        case 7: return launch_lowd_bf16_d<7>(Q, ldq, X, ldx, packed, rows, n, k, S, pack, seed_cells, chunk_rows, order, lk, li, stream);
-        case 8: return launch_lowd_bf16_d<8>(Q, ldq, X, ldx, packed, rows, n, k, S, pack, seed_cells, chunk_rows, order, lk, li, stream);
+        case 1: return launch_lowd_bf16_d<1>(Q, ldq, X, ldx, packed, rows, n, k, S, pack, seed_cells, chunk_rows, own, first, order, lk, li, stream);
+        case 2: return launch_lowd_bf16_d<2>(Q, ldq, X, ldx, packed, rows, n, k, S, pack, seed_cells, chunk_rows, own, first, order, lk, li, stream);
+        case 3: return launch_lowd_bf16_d<3>(Q, ldq, X, ldx, packed, rows, n, k, S, pack, seed_cells, chunk_rows, own, first, order, lk, li, stream);
+        case 4: return launch_lowd_bf16_d<4>(Q, ldq, X, ldx, packed, rows, n, k, S, pack, seed_cells, chunk_rows, own, first, order, lk, li, stream);
+        case 5: return launch_lowd_bf16_d<5>(Q, ldq, X, ldx, packed, rows, n, k, S, pack, seed_cells, chunk_rows, own, first, order, lk, li, stream);
+        case 6: return launch_lowd_bf16_d<6>(Q, ldq, X, ldx, packed, rows, n, k, S, pack, seed_cells, chunk_rows, own, first, order, lk, li, stream);
+        case 7: return launch_lowd_bf16_d<7>(Q, ldq, X, ldx, packed, rows, n, k, S, pack, seed_cells, chunk_rows, own, first, order, lk, li, stream);
+        case 8: return launch_lowd_bf16_d<8>(Q, ldq, X, ldx, packed, rows, n, k, S, pack, seed_cells, chunk_rows, own, first, order, lk, li, stream);
         default: return hipErrorInvalidValue;
     }
 }
