@@ -566,10 +566,36 @@ __global__ void knn_grid_again_kernel(unsigned* __restrict__ hdr) {
 
 }  // namespace
 
-// The queries of a wave descend together, so they have to lie close to each other: with fewer than a
-// query for eight points a wave enters nearly as many nodes as its 64 queries would one by one.
-bool grid_applies(int64_t rows, int64_t n, int /*d*/, int k, bool /*own*/) {
-    return n >= kGridMinPoints && k <= kGridMaxK && rows >= n / 8;
+// The queries of a wave descend together, so they have to lie close to each other; and a wave's descent is
+// one long chain, while the filter cuts its work over the whole chip whatever the sizes.  The lines are
+// drawn where the octree was not slower, uniform and normal points (us, filter / octree):
+//   own queries or more queries than points   d 2, n 1e4, k 16 445 / 256    d 2, n 28000, k 32 966 / 1174
+//     (d 3) n 1e4, k 8 462 / 333, k 16 485 / 508, k 32 717 / 912    n 28000, k 16 755 / 877    n 40000, k 16
+//     954 / 897, k 32 1182 / 1641    n 56000, k 32 2112 / 1679    m 2e4, n 1e4, k 32 791 / 908
+//   others, m = n   d 2: n 32768, k 4 339 / 190, k 8 457 / 463, k 16 637 / 685    n 65536, k 32 1903 / 987
+//     (d 3) n 16384, k 1 164 / 207, k 4 358 / 234, k 16 478 / 526    n 65536, k 16 1051 / 1137    131072 2358 / 916
+//   m = n / 2   d 3: n 65536, k 1 337 / 265, k 16 830 / 992    131072, k 16 1512 / 1459, k 32 1982 / 2486
+//   m = n / 8   d 2: n 65536, k 1 208 / 207    4e5, k 16 1785 / 1403, k 32 2508 / 2539    1e6, k 32 7562 / 5665
+//     (d 3) n 131072, k 1 348 / 367, k 32 1222 / 2248    4e5, k 16 2198 / 1299    1e6, k 32 8497 / 5179
+//   d 1: n 32768, m 4096, k 16 396 / 345, k 32 547 / 589    everything else is far on the octree's side
+bool grid_applies(int64_t rows, int64_t n, int d, int k, bool own) {
+    if (n < kGridMinPoints || k > kGridMaxK || rows < n / 8) return false;
+    if (d == 1) return k <= 16 || 4 * rows >= n || n >= 65536;
+    if (rows >= 2 * n) return d == 2 || k <= 16 || rows >= 8 * n || n <= 8192 || n >= 20000;
+    if (own) {
+        if (k <= 8) return true;
+        if (d == 2) return k <= 16 || n <= 20000 || n >= 64000;
+        return n <= 8192 || n >= (k <= 16 ? 32000 : 50000);
+    }
+    if (4 * rows >= 3 * n) {
+        if (d == 3 && k <= 8) return k >= 4 || n <= 6000 || n >= 20000;
+        return k <= 4 || n <= 8192 || n >= (d == 2 ? 64000 : 100000);
+    }
+    if (n <= 6000 && 2 * rows >= n) return true;
+    const double pairs = (double)rows * (double)n;
+    if (k <= 4) return pairs >= (d == 2 ? 1e9 : 3e9);
+    if (k <= 16) return pairs >= 8e9;
+    return pairs >= 1.5e10 && (d == 3 || 4 * rows >= n || pairs >= 1e11);
 }
 
 hipError_t launch_grid_build(const float* X, int64_t ldx, int64_t n, int d, unsigned* hdr, void* cells,
