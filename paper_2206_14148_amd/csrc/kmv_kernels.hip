@@ -52,7 +52,7 @@ __global__ __launch_bounds__(256) void kmv_zero_kernel(double* __restrict__ y, i
 __global__ __launch_bounds__(256) void kmv_reduce_kernel(const double* __restrict__ partials, int S,
                                                          int64_t n, double* __restrict__ y,
                                                          const int* __restrict__ done) {
-    if (done && *done) return;
+    if (done && done[blockIdx.x]) return;  // (tiles of 256 rows here too)
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= n) return;
     double acc = partials[i];
@@ -70,7 +70,7 @@ __global__ __launch_bounds__(kLowdTileRows) void kmv_lowd_kernel(
     const float* __restrict__ X, int64_t ldx, const float* __restrict__ Z, int64_t ldz_arg,
     const float* __restrict__ v, int n, int m, int split_len, float negc2, double variance,
     double* __restrict__ out, const int* __restrict__ done) {
-    if (done && *done) return;  // the series made y
+    if (done && done[blockIdx.x]) return;  // the series made these rows
     constexpr int U = 8;
     const int64_t ldz = CONTIG ? (int64_t)D : ldz_arg;
     const int s = blockIdx.y;
@@ -419,7 +419,7 @@ __global__ __launch_bounds__(kLowdTileRows) void kmv_lowd_f64_kernel(
     const double* __restrict__ X, int64_t ldx, const double* __restrict__ Z, int64_t ldz_arg,
     const double* __restrict__ v, int n, int m, int split_len, double negc, double variance,
     double* __restrict__ out, const int* __restrict__ done) {
-    if (done && *done) return;  // the series made y
+    if (done && done[blockIdx.x]) return;  // the series made these rows
     constexpr int U = 4;
     const int64_t ldz = CONTIG ? (int64_t)D : ldz_arg;
     const int s = blockIdx.y;

@@ -7,19 +7,32 @@
 //     sum_j v_j K(x, z_j)       = exp(-a^2 / 2) * sum_p a^p * [ sum_j v_j exp(-b_j^2 / 2) b_j^p / p! ],
 // and the bracket, the box's moment p, does not depend on x.  |b| <= h, half a box's width in
 // lengthscales.  Cutting the series of exp(a b) after P terms leaves at most (|a| h)^P / P! beside
-// exp(-|a| h), for every |a| at which exp(-a^2 / 2) is not zero in the entry point's own precision:
+// exp(-|a| h):
 //     fp32 entry: h = 1/2, P = 34: relative to the entry itself below 2e-8 for |a| <= 13.2, where the
-//                 entry is the smallest normal number, and below 1e-16 for |a| <= 8
-//     fp64 entry: h = 1/4, P = 56: below 1e-15 for |a| <= 38.6, where the entry is zero
+//                 entry is the smallest normal number, 3e-6 for |a| <= 14.9, and below 1e-16 for |a| <= 8
+//     fp64 entry: h = 1/4, P = 56: below 1e-15 for |a| <= 38.9
+// (beyond that |a| every entry of the box is zero in the entry point's own precision).
+//
+// Rounding: where a and b have opposite signs the series alternates, and what it loses beside the
+// entry grows as 2^-53 exp(2 |a| h).  That is 3e-10 at most for the fp32 entry point, far below its own
+// 1e-7.  For the fp64 one it is 55 roundings at |a| = 8 and 1e8 at 38, so a row is answered
+// here only if what boxes beyond 8 may lose is nothing beside the entries of its nearer ones: in
+// bounds that hold for every source of a box,
+//     sum over boxes with |a| > 8 of exp(-a^2/2 + |a| h) W  <=  2.5 sum over boxes of exp(-a^2/2 - |a| h) W,
+// W the box's sum of |v_j| exp(-b_j^2 / 2).  A tile of rows with one that is not (a row far outside
+// the sources; weights that are zero but for some far away) goes to the general kernel, row for
+// row as without the series.
+//
 // Boxes of half the width with P = 22 and 36 were 25 % slower: a box costs a row its P multiply-adds
 // and an exponential, about as much again.
 // Everything is computed in fp64, for the fp32 entry point too, whose own entries and 64-term sums
 // carry 1e-7.  Every sum has a fixed order.
 //
-// What bounds it: fp64 issue.  n = m = 1e6 in fp32, l = 1, normal points (10 boxes): bounds 5.6 us,
-// moments 44.5, table 5.4, rows 49, against 160 ms for the entries one by one; 2e5 x 2e5 in fp64:
-// 4.8, 59, 6.2, 43 us against 35.4 ms.  Error against 64 bits 7e-16 (fp32 entry by entry: 2.6e-7;
-// fp64: 5e-15).
+// What bounds it: a wave's chain of boxes (the table's row, then P multiply-adds that wait for each
+// other), and for many sources the look of every box's workgroups at all of them.  n = m = 1e6 in fp32,
+// l = 1, normal points (10 boxes): bounds 5.6 us, moments 44.5, table 5.4, rows 49, against 160 ms
+// for the entries one by one; 2e5 x 2e5 in fp64: 4.8, 59, 6.2, 43 us against 35.4 ms.  Error against
+// 64 bits 7e-16 (fp32 entry by entry: 2.6e-7; fp64: 5e-15).
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -38,31 +51,36 @@ template <>
 struct Series<float> {
     static constexpr int P = 34;
     static constexpr double h = 0.5;
-    static constexpr double far = 104.0;  // a^2 / 2 above which an entry is zero (fp32, denormals included)
+    // a^2 / 2 above which every entry of a box is zero: (sqrt(2 x 104) + h)^2 / 2, an entry being zero in fp32,
+    // denormals included, below exp(-104)
+    static constexpr double far = 111.5;
 };
 template <>
 struct Series<double> {
     static constexpr int P = 56;
     static constexpr double h = 0.25;
-    static constexpr double far = 746.0;
+    static constexpr double far = 756.0;  // (from exp(-745.2))
 };
 
-constexpr int kRow = 64;          // doubles per box in the table: P moments, the centre at kRow - 1
+constexpr int kRow = 64;          // doubles per box: P moments, W, and in the table the centre at kRow - 1
+constexpr int kWeight = kRow - 2;  // in the table: log2 W as a float
+constexpr double kNear = 8.0;      // |a| up to which the series loses next to nothing
 constexpr int kBoundsGroups = 256;
 constexpr int kMaxBoxes = 1024;
 constexpr int kMomentGroups = 2048;  // workgroups of the moment kernel: box x slice of the sources
 constexpr int kMaxSlices = 64;
 
-// workspace: header | bounds of the workgroups [3][256] | the boxes' table | partial moments
+// workspace: header | bounds of the workgroups [3][256] | the boxes' table | partial moments | per tile of
+// 256 rows whether it is done
 struct Header {
-    int ok;      // the series applies: the general kernel has nothing to do
+    int ok;      // the series applies
     int boxes;
     int slices;
 };
 constexpr int64_t kBoundsAt = 256;
 constexpr int64_t kTableAt = kBoundsAt + 3 * kBoundsGroups * 8;
 constexpr int64_t kPartialAt = kTableAt + (int64_t)kMaxBoxes * kRow * 8;
-constexpr int64_t kBytes = kPartialAt + (int64_t)kMomentGroups * kRow * 8;
+constexpr int64_t kDoneAt = kPartialAt + (int64_t)kMomentGroups * kRow * 8;
 static_assert(kBoundsAt % 256 == 0 && kTableAt % 256 == 0 && kPartialAt % 256 == 0, "aligned pieces");
 
 // lowest and highest source, and whether all sources and weights are finite
@@ -109,7 +127,7 @@ __global__ __launch_bounds__(256) void kmv_moments_kernel(const T* __restrict__ 
                                                           double* __restrict__ table,
                                                           double* __restrict__ partial) {
     constexpr int P = Series<T>::P;
-    __shared__ double sum[4][P];
+    __shared__ double sum[4][P + 1];
     __shared__ double part[3][4];
     const int wave = threadIdx.x >> 6;
     const int lane = threadIdx.x & 63;
@@ -154,9 +172,9 @@ __global__ __launch_bounds__(256) void kmv_moments_kernel(const T* __restrict__ 
     const int slice = (int)blockIdx.x - box * slices;
     if (box >= boxes) return;  // whole workgroup
     const double c = fma((double)box + 0.5, width, lo);
-    double acc[P];
+    double acc[P + 1];  // the moments and the sum of the terms' magnitudes
 #pragma unroll
-    for (int p = 0; p < P; ++p) acc[p] = 0.0;
+    for (int p = 0; p <= P; ++p) acc[p] = 0.0;
     const int64_t len = (m + slices - 1) / slices;
     const int64_t j0 = slice * len;
     const int64_t j1 = j0 + len < m ? j0 + len : m;
@@ -176,6 +194,7 @@ __global__ __launch_bounds__(256) void kmv_moments_kernel(const T* __restrict__ 
             if (g == box && jj < j1) {
                 const double b = (z[u] - c) * rl;
                 double w = (double)v[jj] * exp(-0.5 * b * b);
+                acc[P] += fabs(w);
 #pragma unroll
                 for (int p = 0; p < P; ++p) {
                     acc[p] += w;
@@ -185,7 +204,7 @@ __global__ __launch_bounds__(256) void kmv_moments_kernel(const T* __restrict__ 
         }
     }
 #pragma unroll
-    for (int p = 0; p < P; ++p) {
+    for (int p = 0; p <= P; ++p) {
         double s = acc[p];
 #pragma unroll
         for (int o = 32; o >= 1; o >>= 1) s += __shfl_xor(s, o);
@@ -193,59 +212,80 @@ __global__ __launch_bounds__(256) void kmv_moments_kernel(const T* __restrict__ 
     }
     __syncthreads();
     const int t = threadIdx.x;
-    if (t < P) partial[(int64_t)blockIdx.x * kRow + t] = (sum[0][t] + sum[1][t]) + (sum[2][t] + sum[3][t]);
-    if (slice == 0 && t == P) table[(int64_t)box * kRow + kRow - 1] = c;
+    if (t <= P) partial[(int64_t)blockIdx.x * kRow + t] = (sum[0][t] + sum[1][t]) + (sum[2][t] + sum[3][t]);
+    if (slice == 0 && t == kRow - 1) table[(int64_t)box * kRow + kRow - 1] = c;
 }
 
-// table[box][p] = (sum over the slices, ascending) / p!
+// table[box][p] = (sum over the slices, ascending) / p!; at kWeight log2 of the magnitudes' sum
 template <typename T>
 __global__ __launch_bounds__(64) void kmv_table_kernel(const Header* __restrict__ header,
                                                        const double* __restrict__ partial,
                                                        double* __restrict__ table) {
     constexpr int P = Series<T>::P;
-    static_assert(P < kRow && P <= 64, "one lane per moment, the centre behind them");
+    static_assert(P < kWeight, "a lane per moment and one for their magnitude, the centre behind them");
     const int box = blockIdx.x, p = threadIdx.x;
-    if (!header->ok || box >= header->boxes || p >= P) return;
+    if (!header->ok || box >= header->boxes || p > P) return;
     const int slices = header->slices;
     double s = 0.0, factorial = 1.0;
 #pragma unroll 8
     for (int i = 0; i < slices; ++i) s += partial[((int64_t)box * slices + i) * kRow + p];
+    if (p == P) {
+        *reinterpret_cast<float*>(table + (int64_t)box * kRow + kWeight) = (float)log2(s);
+        return;
+    }
     for (int i = 2; i <= p; ++i) factorial *= (double)i;
     table[(int64_t)box * kRow + p] = s / factorial;
 }
 
 // One row per lane; the boxes are the same for the whole wave, so their moments come through
-// scalar loads.  Per box and row: P multiply-adds and one exponential.
+// scalar loads.  Per box and row: P multiply-adds and one exponential.  done[tile] = 1 where y is
+// complete, 0 where the general kernel has to make the tile's rows.
 template <typename T>
 __global__ __launch_bounds__(256) void kmv_series_kernel(const T* __restrict__ X, int64_t ldx, int64_t n,
                                                          double lengthscale, double variance,
                                                          const Header* __restrict__ header,
                                                          const double* __restrict__ table,
-                                                         double* __restrict__ y) {
+                                                         int* __restrict__ done, double* __restrict__ y) {
     constexpr int P = Series<T>::P;
-    if (!header->ok) return;
+    if (!header->ok) {
+        if (threadIdx.x == 0) done[blockIdx.x] = 0;
+        return;
+    }
     const int boxes = header->boxes;
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const double rl = 1.0 / lengthscale;
     const double x = (double)X[(i < n ? i : n - 1) * ldx];
     double total = 0.0;
+    float surely = -HUGE_VALF, lost = -HUGE_VALF;  // log2: the largest terms of the two sums above
     for (int box = 0; box < boxes; ++box) {
         const double* __restrict__ row = table + (int64_t)box * kRow;
         const double a = (x - row[kRow - 1]) * rl;
         const double e = 0.5 * a * a;
         if (__builtin_amdgcn_ballot_w64(e <= Series<T>::far) == 0) continue;
+        if constexpr (sizeof(T) == 8) {
+            constexpr float kLog2e = 1.44269504f;
+            const float fa = fabsf((float)a);
+            const float w = *reinterpret_cast<const float*>(row + kWeight) - 0.5f * kLog2e * fa * fa;
+            const float spread = (float)Series<T>::h * kLog2e * fa;
+            surely = fmaxf(surely, w - spread);
+            if (fa > (float)kNear) lost = fmaxf(lost, w + spread);
+        }
         double s = row[P - 1];
 #pragma unroll
         for (int p = P - 2; p >= 0; --p) s = fma(s, a, row[p]);
         if (e <= Series<T>::far) total = fma(exp(-e), s, total);
     }
+    // (at most 160 boxes are within reach of a row: 160 / 2^6 = 2.5)
+    const int leave = i < n && lost > surely - 6.f;
     if (x != x) total = x;  // as the sum over such entries of K
     if (i < n) y[i] = variance * total;
+    const int any = __syncthreads_or(leave);
+    if (threadIdx.x == 0) done[blockIdx.x] = any ? 0 : 1;
 }
 
 }  // namespace
 
-int64_t series_bytes() { return kBytes; }
+int64_t series_bytes(int64_t n) { return kDoneAt + (n + 255) / 256 * 4; }
 
 bool series_applies(int64_t n, int64_t m, int d, double lengthscale, bool f64) {
     // Below these sizes the entries themselves are made in less time than the launches here take:
@@ -260,24 +300,27 @@ bool series_applies(int64_t n, int64_t m, int d, double lengthscale, bool f64) {
 
 template <typename T>
 hipError_t launch_series(const T* X, int64_t ldx, const T* Z, int64_t ldz, const T* v, int64_t n, int64_t m,
-                         double lengthscale, double variance, void* ws, double* y, hipStream_t stream) {
+                         double lengthscale, double variance, void* ws, double* y, hipStream_t stream,
+                         const int** done) {
     unsigned char* base = static_cast<unsigned char*>(ws);
     Header* header = reinterpret_cast<Header*>(base);
     double* bounds = reinterpret_cast<double*>(base + kBoundsAt);
     double* table = reinterpret_cast<double*>(base + kTableAt);
     double* partial = reinterpret_cast<double*>(base + kPartialAt);
+    static_assert(kLowdTileRows == 256, "a flag per workgroup of the general kernels");
+    *done = reinterpret_cast<int*>(base + kDoneAt);
     kmv_bounds_kernel<T><<<dim3(kBoundsGroups), dim3(256), 0, stream>>>(Z, ldz, v, m, bounds);
     kmv_moments_kernel<T><<<dim3(kMomentGroups), dim3(256), 0, stream>>>(Z, ldz, v, m, lengthscale, bounds,
                                                                          header, table, partial);
     kmv_table_kernel<T><<<dim3(kMaxBoxes), dim3(64), 0, stream>>>(header, partial, table);
     kmv_series_kernel<T><<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream>>>(
-        X, ldx, n, lengthscale, variance, header, table, y);
+        X, ldx, n, lengthscale, variance, header, table, const_cast<int*>(*done), y);
     return hipGetLastError();
 }
 
 template hipError_t launch_series<float>(const float*, int64_t, const float*, int64_t, const float*, int64_t,
-                                         int64_t, double, double, void*, double*, hipStream_t);
+                                         int64_t, double, double, void*, double*, hipStream_t, const int**);
 template hipError_t launch_series<double>(const double*, int64_t, const double*, int64_t, const double*,
-                                          int64_t, int64_t, double, double, void*, double*, hipStream_t);
+                                          int64_t, int64_t, double, double, void*, double*, hipStream_t, const int**);
 
 }  // namespace kmv

@@ -86,6 +86,40 @@ def test_matches_oracle(K, oracle, case):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("m,span,ls", [(5003, 0.0, 1.0), (5003, 0.02, 0.5), (20_011, 3.3, 1.0)])
+@pytest.mark.parametrize("weights", ["all", "one", "ends"])
+def test_rows_far_from_their_sources(K, oracle, dtype, m, span, ls, weights):
+    # where a row lies to one side of a box and its sources to the other the series alternates: 0 to 38
+    # lengthscales on both sides, sources all at one edge of their box, weights that leave out the near ones
+    real = np.float64 if dtype == "f64" else np.float32
+    rng = np.random.Generator(np.random.PCG64(m + len(weights)))
+    n = 80_001
+    Z = np.sort((3.0 + span * rng.random((m, 1))).astype(real), axis=0)
+    X = (3.0 - 2 * ls + (span + 4 * ls) * rng.random((n, 1))).astype(real)
+    t = np.linspace(0.0, 38.0, 153) * ls
+    X[1000:1153, 0], X[50_000:50_153, 0] = 3.0 + span + t, 3.0 - t
+    v = rng.standard_normal(m).astype(real)
+    if weights == "one":
+        v[1:] = 0
+    elif weights == "ends":
+        v[m // 50: m - m // 50] *= real(1e-30)
+    Xd, Zd, vd = (torch.from_numpy(a).cuda() for a in (X, Z, v))
+    y, other = K.kmv_apply(Xd, Zd, vd, 1.5, ls, W.GB), general(K, Xd, Zd, vd, ls, dtype)
+    torch.cuda.synchronize()
+    rows = np.concatenate([np.arange(1000, 1153), np.arange(50_000, 50_153), rng.integers(0, n, 40)])
+    ref = (oracle.kmv_f64 if dtype == "f64" else oracle.kmv)(X, Z, v, 1.5, ls, rows=rows)
+    tol = np.array([1.5 * bound(float(X[i, 0]), Z, v, ls, dtype) for i in rows])
+    y, other = y.cpu().numpy(), other.cpu().numpy()
+    err = np.abs(y[rows] - ref)
+    print("worst err/tol", float((err / tol).max()), "general", float((np.abs(other[rows] - ref) / tol).max()), flush=True)
+    assert (err <= tol).all()
+    # tiles of 256 rows without such a row are still the series'
+    assert not np.array_equal(y[10_240:49_920], other[10_240:49_920])
+    if dtype == "f64":
+        assert np.array_equal(y[1024:1152], other[1024:1152]) and np.array_equal(y[50_000:50_153], other[50_000:50_153])
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
 def test_values_that_are_not_finite(K, dtype):
     # a row that is not a number stays one, a row at infinity is zero; a source or a weight that is
     # not finite leaves the call to the general kernel
@@ -112,7 +146,7 @@ def test_workspace_stays_inside_its_bytes_and_the_limit(K):
     n, m = 40_001, 20_001
     full = K.load().kmv_workspace_bytes(n, m, 1, 1.0, W.GB)
     plan = K.kmv_plan(n, m, 1, W.GB)
-    assert plan.workspace_bytes < full <= plan.workspace_bytes + 2 ** 21
+    assert plan.workspace_bytes < full <= plan.workspace_bytes + 2 ** 21  # (4 bytes per 256 rows of it)
     assert K.load().kmv_workspace_bytes(n, m, 1, 1.0, full - 1) < full
     gen = torch.Generator(device="cuda")
     gen.manual_seed(2)
