@@ -83,7 +83,7 @@ constexpr int64_t kPartialAt = kTableAt + (int64_t)kMaxBoxes * kRow * 8;
 constexpr int64_t kDoneAt = kPartialAt + (int64_t)kMomentGroups * kRow * 8;
 static_assert(kBoundsAt % 256 == 0 && kTableAt % 256 == 0 && kPartialAt % 256 == 0, "aligned pieces");
 
-// lowest and highest source, and whether all sources and weights are finite
+// lowest and highest source, and whether all sources and weights are finite and not too large
 template <typename T>
 __global__ __launch_bounds__(256) void kmv_bounds_kernel(const T* __restrict__ Z, int64_t ldz,
                                                          const T* __restrict__ v, int64_t m,
@@ -94,7 +94,8 @@ __global__ __launch_bounds__(256) void kmv_bounds_kernel(const T* __restrict__ Z
         const double z = (double)Z[j * ldz], w = (double)v[j];
         lo = fmin(lo, z);
         hi = fmax(hi, z);
-        if (!(fabs(z) < HUGE_VAL) || !(fabs(w) < HUGE_VAL)) bad = 1.0;
+        // (weights whose sum without the entries of K could overflow are left to the general kernel)
+        if (!(fabs(z) < HUGE_VAL) || !(fabs(w) * (double)m < 1e300)) bad = 1.0;
     }
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) {

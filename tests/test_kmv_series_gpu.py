@@ -119,6 +119,18 @@ def test_rows_far_from_their_sources(K, oracle, dtype, m, span, ls, weights):
         assert np.array_equal(y[1024:1152], other[1024:1152]) and np.array_equal(y[50_000:50_153], other[50_000:50_153])
 
 
+def test_weights_whose_sum_overflows(K):
+    # finite through K's small entries: the series would sum the weights alone
+    n, m = 30_001, 20_001
+    X = torch.full((n, 1), 9.0, device="cuda", dtype=torch.float64)
+    X[:64, 0] = torch.linspace(8, 12, 64, dtype=torch.float64)
+    Z = torch.zeros((m, 1), device="cuda", dtype=torch.float64)
+    v = torch.full((m,), 1e306, device="cuda", dtype=torch.float64)
+    y, ref = K.kmv_apply(X, Z, v, 1.5, 1.0, W.GB), general(K, X, Z, v, 1.0, "f64")
+    torch.cuda.synchronize()
+    assert torch.isfinite(ref).all() and torch.equal(y, ref)
+
+
 @pytest.mark.parametrize("dtype", ["f32", "f64"])
 def test_values_that_are_not_finite(K, dtype):
     # a row that is not a number stays one, a row at infinity is zero; a source or a weight that is
