@@ -91,12 +91,15 @@ int kmv_apply(const float* X, int64_t ldx, const float* Z, int64_t ldz, const fl
 
 /*
  * HOST.  The workspace a call of this shape is best given: plan.workspace_bytes, plus, for d = 1
- * with enough entries (3e8; 4e7 in fp64) and where the limit has room, about 1.6 MB in which the
- * sources are gathered into boxes a fraction of a lengthscale wide.  A box acts on every row
- * through one short series (in fp64, cut where what is left out is below the precision of the
- * entry point), so the work goes with n + m.  Whether the points allow that - finite, not
- * spread over more than 1023 (fp64: 511) lengthscales, and at least 16 sources per box - is found
- * on the device; where they do not, the general kernel runs as it does with the plan's workspace.
+ * with enough entries (4e8; 8e7 in fp64; fewer where the rows alone would leave the GPU idle) and where
+ * the limit has room, about 1.6 MB and 4 bytes per 256 rows in which the sources are gathered into
+ * boxes a fraction of a lengthscale wide.  A box acts on every row through one short series (in fp64,
+ * cut where what is left out is below the precision of the entry point) instead of entry by entry.
+ * Whether that is done is found on the device: the points and weights have to be finite, spread over
+ * no more than 1023 (fp64: 511) lengthscales, with at least 16 sources per box, and the boxes'
+ * work, which goes with boxes (n + m), below that of the n m entries.  In fp64 rows that
+ * are far from all sources with a weight that counts are left out, 256 at a time.  What is not
+ * done there the general kernel does, as with the plan's workspace.
  * Never above mem_limit_bytes; 0 if there is no plan.
  */
 int64_t kmv_workspace_bytes(int64_t n, int64_t m, int32_t d, double lengthscale, int64_t mem_limit_bytes);

@@ -96,7 +96,7 @@ int plan_impl(int64_t n, int64_t m, int32_t d, int64_t mem_limit_bytes, bool f64
 // Workspace the call is best given: the plan's, and behind it what the series for d = 1 works
 // in, where the limit has room for both.
 int64_t roomy_bytes(const kmv_plan_t& plan, int64_t mem_limit_bytes, double lengthscale, bool f64) {
-    if (!kmv::series_applies(plan.n, plan.m, plan.d, lengthscale, f64)) return plan.workspace_bytes;
+    if (!kmv::series_applies(plan.n, plan.m, plan.n_splits, plan.d, lengthscale, f64)) return plan.workspace_bytes;
     const int64_t want = plan.workspace_bytes + align_up(kmv::series_bytes(plan.n));
     return want <= mem_limit_bytes ? want : plan.workspace_bytes;
 }
@@ -171,7 +171,7 @@ extern "C" int kmv_apply(const float* X, int64_t ldx, const float* Z, int64_t ld
         hipEvent_t t1 = knn::profile_mark(stream);
         e = hipSuccess;
         if (use_series(plan, mem_limit_bytes, lengthscale, false, workspace, workspace_bytes)) {
-            e = kmv::launch_series(X, ldx, Z, ldz, v, n, m, lengthscale, variance, ws + plan.workspace_bytes, y,
+            e = kmv::launch_series(X, ldx, Z, ldz, v, n, m, S, lengthscale, variance, ws + plan.workspace_bytes, y,
                                    stream, &done);
         }
         if (e == hipSuccess)
@@ -232,7 +232,7 @@ extern "C" int kmv_apply_f64(const double* X, int64_t ldx, const double* Z, int6
     e = hipSuccess;
     if (use_series(plan, mem_limit_bytes, lengthscale, true, workspace, workspace_bytes)) {
         unsigned char* extra = static_cast<unsigned char*>(workspace) + plan.workspace_bytes;
-        e = kmv::launch_series(X, ldx, Z, ldz, v, n, m, lengthscale, variance, extra, y, stream, &done);
+        e = kmv::launch_series(X, ldx, Z, ldz, v, n, m, S, lengthscale, variance, extra, y, stream, &done);
     }
     if (e == hipSuccess)
         e = kmv::launch_f64(X, ldx, Z, ldz, v, n, m, d, negc, variance, S, S > 1 ? partials : y, stream, done);

@@ -40,14 +40,14 @@ hipError_t launch_f64(const double* X, int64_t ldx, const double* Z, int64_t ldz
 hipError_t launch_reduce(const double* partials, int S, int64_t n, double* y, hipStream_t stream,
                          const int* done = nullptr);
 
-// d = 1 (kmv_series.hip): y through one series per box of sources, in series_bytes(n) bytes at ws.  Whether
-// the points allow that is found on the device: *done gets a flag per tile of kLowdTileRows rows, 1
+// d = 1 (kmv_series.hip): y through one series per box of sources, in series_bytes(n) bytes at ws.  S: the
+// general kernels' ranges.  Whether the points allow that, and whether it takes less time than they do, is found on the device: *done gets a flag per tile of kLowdTileRows rows, 1
 // where y is complete.  launch_lowd, launch_f64 and launch_reduce, given it, make the other tiles.
 int64_t series_bytes(int64_t n);
-bool series_applies(int64_t n, int64_t m, int d, double lengthscale, bool f64);
+bool series_applies(int64_t n, int64_t m, int S, int d, double lengthscale, bool f64);
 template <typename T>
 hipError_t launch_series(const T* X, int64_t ldx, const T* Z, int64_t ldz, const T* v, int64_t n, int64_t m,
-                         double lengthscale, double variance, void* ws, double* y, hipStream_t stream,
+                         int S, double lengthscale, double variance, void* ws, double* y, hipStream_t stream,
                          const int** done);
 
 // y[i] = 0.

@@ -54,12 +54,15 @@ struct Series<float> {
     // a^2 / 2 above which every entry of a box is zero: (sqrt(2 x 104) + h)^2 / 2, an entry being zero in fp32,
     // denormals included, below exp(-104)
     static constexpr double far = 111.5;
+    // what the four kernels take, us: all, per source, per box, per box and source, per box and row
+    static constexpr double base_us = 28.0, source_us = 3e-5, box_us = 1.4, box_source_us = 2.3e-6, box_row_us = 3.6e-6;
 };
 template <>
 struct Series<double> {
     static constexpr int P = 56;
     static constexpr double h = 0.25;
     static constexpr double far = 756.0;  // (from exp(-745.2))
+    static constexpr double base_us = 28.0, source_us = 4e-5, box_us = 2.6, box_source_us = 4e-6, box_row_us = 3e-6;
 };
 
 constexpr int kRow = 64;          // doubles per box: P moments, W, and in the table the centre at kRow - 1
@@ -121,8 +124,8 @@ __global__ __launch_bounds__(256) void kmv_bounds_kernel(const T* __restrict__ Z
 // walks its sources in ascending order; threads are added in a fixed tree.
 template <typename T>
 __global__ __launch_bounds__(256) void kmv_moments_kernel(const T* __restrict__ Z, int64_t ldz,
-                                                          const T* __restrict__ v, int64_t m,
-                                                          double lengthscale,
+                                                          const T* __restrict__ v, int64_t m, int64_t n,
+                                                          double lengthscale, double general_us,
                                                           const double* __restrict__ bounds,
                                                           Header* __restrict__ header,
                                                           double* __restrict__ table,
@@ -155,11 +158,17 @@ __global__ __launch_bounds__(256) void kmv_moments_kernel(const T* __restrict__ 
     const double rw = 1.0 / width;
     const double span = (hi - lo) * rw;
     // The general kernel takes over where a source or weight is not finite (its sums then say
-    // so), where the boxes would be too many, or so many that a row costs as much in boxes (about
-    // 60 fp64 operations each) as in sources (8 to 30), or where the coordinates' own spacing is no
-    // longer small beside a box (a centre could then not lie in the middle).
+    // so), where the boxes would be too many or hold fewer than 16 sources each, where the coordinates'
+    // own spacing is no longer small beside a box (a centre could then not lie in the middle), or
+    // where it takes less time.  Measured, us, m from 300 to 1e7, n from 40 to 1e6, 1 to 1000 boxes: a box costs
+    // a row's wave its chain whatever the sizes are, its own workgroups a look at all sources, and every
+    // row its terms.  (In fp32: n = m = 2e4, 10 boxes 41, 60 120, 300 443, the general kernel 90;
+    // n = 300, m = 1e6 82, 266, 875 against 258; n = 1e6, m = 1000 59, 241, - against 157.)
+    const double series_us = Series<T>::base_us + Series<T>::source_us * (double)m +
+                             (span + 1.0) * (Series<T>::box_us + Series<T>::box_source_us * (double)m +
+                                             Series<T>::box_row_us * (double)n);
     const bool ok = bad == 0.0 && span < (double)kMaxBoxes - 1.0 && (span + 1.0) * 16.0 <= (double)m &&
-                    fmax(fabs(lo), fabs(hi)) * 0x1p-52 <= width * 0x1p-7;
+                    fmax(fabs(lo), fabs(hi)) * 0x1p-52 <= width * 0x1p-7 && series_us <= general_us;
     const int boxes = ok ? (int)span + 1 : 0;
     int slices = 1;
     if (ok) {
@@ -288,11 +297,19 @@ __global__ __launch_bounds__(256) void kmv_series_kernel(const T* __restrict__ X
 
 int64_t series_bytes(int64_t n) { return kDoneAt + (n + 255) / 256 * 4; }
 
-bool series_applies(int64_t n, int64_t m, int d, double lengthscale, bool f64) {
-    // Below these sizes the entries themselves are made in less time than the launches here take:
-    // about 30 us, 6e12 entries per second in fp32 and 1e12 in fp64.
-    const double entries = (double)n * (double)m;
-    if (d != 1 || entries < (f64 ? 4e7 : 3e8)) return false;
+// What the general kernels take at least, us: all entries at 6.4e12 (fp64 1.3e12) per second, or one
+// wave's range of the sources at 16 ns (90) each, where rows and ranges leave the chip idle.
+static double general_time_us(int64_t n, int64_t m, int S, bool f64) {
+    const double entries = (double)n * (double)m / (f64 ? 1.3e6 : 6.4e6);
+    const double range = (double)m / S * (f64 ? 0.09 : 0.016);
+    return entries > range ? entries : range;
+}
+
+bool series_applies(int64_t n, int64_t m, int S, int d, double lengthscale, bool f64) {
+    // The launches here take about 30 us.  Where the device then finds that the points do not allow the
+    // series, four of them and a look at the sources have been in vain: 12 us, 90 -> 102 at n = m = 2e4 in
+    // fp32, and with 4e6 sources 120 us, 1655 -> 1777.  So calls that cannot gain much are left alone.
+    if (d != 1 || general_time_us(n, m, S, f64) < 60.0) return false;
     // (the general kernels form 1 / (2 l^2): where that or its inverse leaves the range of the type
     // they decide what comes out)
     return f64 ? (lengthscale >= 1e-100 && lengthscale <= 1e100)
@@ -301,7 +318,7 @@ bool series_applies(int64_t n, int64_t m, int d, double lengthscale, bool f64) {
 
 template <typename T>
 hipError_t launch_series(const T* X, int64_t ldx, const T* Z, int64_t ldz, const T* v, int64_t n, int64_t m,
-                         double lengthscale, double variance, void* ws, double* y, hipStream_t stream,
+                         int S, double lengthscale, double variance, void* ws, double* y, hipStream_t stream,
                          const int** done) {
     unsigned char* base = static_cast<unsigned char*>(ws);
     Header* header = reinterpret_cast<Header*>(base);
@@ -311,8 +328,8 @@ hipError_t launch_series(const T* X, int64_t ldx, const T* Z, int64_t ldz, const
     static_assert(kLowdTileRows == 256, "a flag per workgroup of the general kernels");
     *done = reinterpret_cast<int*>(base + kDoneAt);
     kmv_bounds_kernel<T><<<dim3(kBoundsGroups), dim3(256), 0, stream>>>(Z, ldz, v, m, bounds);
-    kmv_moments_kernel<T><<<dim3(kMomentGroups), dim3(256), 0, stream>>>(Z, ldz, v, m, lengthscale, bounds,
-                                                                         header, table, partial);
+    kmv_moments_kernel<T><<<dim3(kMomentGroups), dim3(256), 0, stream>>>(
+        Z, ldz, v, m, n, lengthscale, general_time_us(n, m, S, sizeof(T) == 8), bounds, header, table, partial);
     kmv_table_kernel<T><<<dim3(kMaxBoxes), dim3(64), 0, stream>>>(header, partial, table);
     kmv_series_kernel<T><<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream>>>(
         X, ldx, n, lengthscale, variance, header, table, const_cast<int*>(*done), y);
@@ -320,8 +337,9 @@ hipError_t launch_series(const T* X, int64_t ldx, const T* Z, int64_t ldz, const
 }
 
 template hipError_t launch_series<float>(const float*, int64_t, const float*, int64_t, const float*, int64_t,
-                                         int64_t, double, double, void*, double*, hipStream_t, const int**);
+                                         int64_t, int, double, double, void*, double*, hipStream_t, const int**);
 template hipError_t launch_series<double>(const double*, int64_t, const double*, int64_t, const double*,
-                                          int64_t, int64_t, double, double, void*, double*, hipStream_t, const int**);
+                                          int64_t, int64_t, int, double, double, void*, double*, hipStream_t,
+                                          const int**);
 
 }  // namespace kmv

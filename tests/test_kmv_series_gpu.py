@@ -37,25 +37,30 @@ def general(K, X, Z, v, ls, dtype):
     return K.kmv_apply(X, Z, v, 1.5, ls, W.GB, workspace=ws)
 
 
-# (dtype, n, m, lengthscale, span of the sources): boxes are l (fp64: l / 2) wide, 16 sources
-# a box are asked for, more than 1023 boxes are not taken
+# (dtype, n, m, lengthscale, span of the sources, whether the series answers): boxes are l (fp64: l / 2) wide,
+# 16 sources a box are asked for, more than 1023 boxes are not taken, nor so many that the general
+# kernel is faster
 CASES = [
-    ("f32", 60_001, 5_003, 1.0, 0.0),        # all sources in one place
-    ("f32", 20_011, 16_385, 1.0, 1.4),       # two boxes, slices of unequal length
-    ("f32", 300_007, 1_001, 2.0, 10.0),      # one slice
-    ("f32", 20_001, 20_001, 1e-3, 1.0),      # 1001 boxes: one slice each
-    ("f32", 20_001, 20_001, 1e-3, 1.1),      # more than 1023: the general kernel
-    ("f64", 60_001, 5_003, 1.0, 0.0),
-    ("f64", 20_003, 40_009, 1.0, 12.0),
-    ("f64", 60_001, 1_001, 3.0, 10.0),
-    ("f64", 20_001, 20_001, 1e-3, 0.5),      # 1001 boxes
-    ("f64", 20_001, 20_001, 1e-3, 0.52),     # 1041: the general kernel
+    ("f32", 80_001, 5_003, 1.0, 0.0, True),        # all sources in one place
+    ("f32", 24_011, 16_385, 1.0, 1.4, True),       # two boxes, slices of unequal length
+    ("f32", 400_007, 1_001, 2.0, 10.0, True),      # one slice
+    ("f32", 200_001, 200_001, 1e-3, 1.0, True),    # 1001 boxes: two slices each
+    ("f32", 200_001, 200_001, 1e-3, 1.1, False),   # more than 1023: the general kernel
+    ("f32", 1_000, 300_000, 1.0, 9.5, True),       # ten boxes
+    ("f32", 1_000, 300_000, 1.0, 299.5, False),    # 300, in few rows
+    ("f32", 20_001, 20_001, 1e-3, 0.3, False),     # 300, and few rows and sources
+    ("f64", 60_001, 5_003, 1.0, 0.0, True),
+    ("f64", 20_003, 40_009, 1.0, 12.0, True),
+    ("f64", 60_001, 2_003, 3.0, 10.0, True),
+    ("f64", 100_001, 100_001, 1e-3, 0.5, True),    # 1001 boxes
+    ("f64", 100_001, 100_001, 1e-3, 0.52, False),  # 1041: the general kernel
+    ("f64", 10_000, 30_000, 1e-3, 0.15, False),    # 300
 ]
 
 
-@pytest.mark.parametrize("case", CASES, ids=lambda c: "%s_n%d_m%d_l%g_span%g" % c)
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "%s_n%d_m%d_l%g_span%g_%s" % c)
 def test_matches_oracle(K, oracle, case):
-    dtype, n, m, ls, span = case
+    dtype, n, m, ls, span, expected = case
     real = np.float64 if dtype == "f64" else np.float32
     rng = np.random.Generator(np.random.PCG64(n + m))
     Z = (3.0 + span * rng.random((m, 1))).astype(real)
@@ -76,7 +81,7 @@ def test_matches_oracle(K, oracle, case):
     torch.cuda.synchronize()
     assert torch.equal(y, again) and torch.equal(y, strided)
     taken = not torch.equal(y, other)
-    assert taken == (span / (ls * (0.5 if dtype == "f64" else 1.0)) < 1023)
+    assert taken == expected
     rows = np.unique(np.concatenate([np.arange(8), rng.integers(0, n, 40), [n - 1]]))
     ref = (oracle.kmv_f64 if dtype == "f64" else oracle.kmv)(X, Z, v, 1.5, ls, rows=rows)
     tol = np.array([1.5 * bound(float(X[i, 0]), Z, v, ls, dtype) for i in rows])
