@@ -72,8 +72,8 @@ typedef enum { KNN_METRIC_L2SQ = 0, KNN_METRIC_COSINE = 1, KNN_METRIC_L1 = 2 } k
                                  was this path's fp32 matrix-core predecessor.)  Under a plan of
                                  this path, 6 or 7 a small squared-Euclidean search (one query chunk,
                                  k <= 128, up to about 5e9 coordinates of pairs, more for a handful
-                                 of queries) evaluates every pair exactly instead: same workspace,
-                                 same keys, same results. */
+                                 of queries, fewer for short lists) evaluates every pair exactly instead:
+                                 same workspace, same keys, same results. */
 
 #define KNN_PATH_MFMA_PACKED 6 /* 8 < d <= 256 squared-Euclidean, d <= 256 cosine (on the rows x / |x|, whole copy
                                   only), m >= 64 (2048 up to d = 16), n >= 65536 and room for the

@@ -178,16 +178,33 @@ __global__ __launch_bounds__(64 * kFewWaves) void knn_few_kernel(
 
 }  // namespace
 
-// A pair costs d + 16 or so (the rest is its share of the test against the threshold), the filters
-// a pass over the points and the restarts of their lists before they gain anything, the more so the
-// fewer queries there are.  Measured, us a call here / on the filter paths, by m, n, d, k:
+// A pair costs d + 16 or so (the rest is its share of the test against the threshold), 1e13 of these a
+// second where rows can be loaded 16 bytes at a time and 5.7e12 where not; the filters cost a pass over
+// the points and the restarts of their lists before they gain anything, the more so the fewer
+// queries there are and the longer the lists.  Measured, us a call here / on the filter paths, by m, n, d, k:
 //   16, 1e5, 50, 10: 97 / 590       1000, 1e4, 16, 10: 106 / 457     300, 1e5, 64, 10: 226 / 531
 //   1000, 1e5, 16, 10: 356 / 702    1e4, 1e4, 16, 10: 408 / 516      1000, 2e4, 100, 100: 449 / 4845
 //   1000, 1e5, 64, 10: 584 / 548    3000, 1e5, 16, 10: 831 / 539     3000, 3e4, 100, 10: 851 / 740
 //   64, 1e6, 128, 10: 722 / 1003    64, 1e6, 256, 32: 1851 / 1859    16, 1e6, 1000, 10: 2709 / 6423
-bool few_applies(int64_t m, int64_t n, int d, int k) {
+// and at the other end of k, where lists restart hardly at all:
+//   1000, 1e4, 16, 1: 68 / 161      1000, 1e4, 128, 1: 133 / 220     1000, 1e4, 300, 1: 287 / 382
+//   1000, 65536, 16, 1: 214 / 206   1000, 65536, 9, 1: 336 / 221     1000, 65536, 9, 10: 394 / 754
+//   1000, 2e5, 9, 1: 877 / 286      2e4, 1e4, 9, 10: 939 / 687       4000, 1e4, 50, 10: 513 / 649
+// From 65 queries on the line is a bound from below of what the filters take, up to 5e9 in all.
+bool few_applies(int64_t m, int64_t n, int d, int k, bool aligned) {
     const double work = (double)m * (double)n * (double)(d + 16);
-    return k <= kFewMaxK && work <= (m <= 16 ? 2e10 : (m <= 64 ? 1e10 : 5e9));
+    if (k > kFewMaxK) return false;
+    if (m <= 64) return work <= (m <= 16 ? 2e10 : 1e10);
+    const double here_us = 40.0 + work * (aligned ? 1.0e-7 : 1.75e-7);
+    const double copy_us = 3e-5 * (double)n * d;
+    const double filter_us = (aligned ? 150.0 + 0.75 * d : 165.0 + 1.5 * d) + (copy_us < 150.0 ? copy_us : 150.0) +
+                             (k - 1) * (n >= 50000 ? 55.0 : (aligned ? 22.0 : 30.0));
+    return work <= 5e9 && here_us <= filter_us;
+}
+
+// rows of X whose groups of four coordinates can be loaded at once
+bool few_aligned(const float* X, int64_t ldx, int d) {
+    return reinterpret_cast<uintptr_t>(X) % 16 == 0 && ldx % 4 == 0 && d % 4 == 0;
 }
 
 int few_splits(int64_t rows, int64_t n, int k, uint64_t workspace_bytes) {
@@ -209,7 +226,7 @@ hipError_t launch_few(const float* Q, int64_t ldq, const float* X, int64_t ldx, 
     const size_t lds = kFewWaves * few_lds_per_wave(NQ, k);
     int64_t split_len = (n + S - 1) / S;
     split_len = (split_len + 63) / 64 * 64;
-    const bool aligned = (reinterpret_cast<uintptr_t>(X) % 16 == 0) && (ldx % 4 == 0) && (d % 4 == 0);
+    const bool aligned = few_aligned(X, ldx, d);
     const dim3 grid((unsigned)(((rows + NQ - 1) / NQ * S + kFewWaves - 1) / kFewWaves));
     hipError_t e = aligned ? raise_lds_limit(knn_few_kernel<NQ, true>, lds)
                            : raise_lds_limit(knn_few_kernel<NQ, false>, lds);
