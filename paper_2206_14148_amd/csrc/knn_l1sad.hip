@@ -590,8 +590,18 @@ static hipError_t launch_sad_words(SadCall c) {
     double share = sqrt(40000.0 * c.k / ((double)c.n * c.d));
     if (share > 1.0 / 3) share = 1.0 / 3;
     int per_group = (int)(share * (double)c.n / kSadPoints / c.k);
-    if (per_group < 1) per_group = 1;
     const unsigned gx = (unsigned)((c.rows + 127) / 128);
+    // Where the groups are too few to fill the chip a group's tiles are a chain of 0.75 us each, and the
+    // pairs that a smaller sample lets through, n / (64 per_group) a query and more for longer lists, are
+    // shared by the S ranges' waves at 0.2 us each: the least total of the two.  (1 and 16 queries x 1e5 points, d = 5, k = 1:
+    // 758 us and 768 with 441 tiles in one chain, 212 and 226 so, 432 and 544 without the filter.)
+    if ((int64_t)gx * c.k < 512) {
+        const double lanes = c.rows < 128 ? (double)c.rows : 128.0;
+        double chain = sqrt(lanes * (double)c.n * 0.2 * (1.0 + 3.0 * log((double)c.k)) / (64.0 * c.S * 0.75));
+        if (chain < 32.0) chain = 32.0;
+        if (per_group > chain) per_group = (int)chain;
+    }
+    if (per_group < 1) per_group = 1;
     knn_l1_seed_kernel<W><<<dim3(gx, (unsigned)c.k), dim3(256), 0, c.stream>>>(
         c.X, c.ldx, c.qb, c.qr, c.tsh, c.head, (int)c.rows, (int)c.n, c.d, c.k, per_group, c.aligned, 0);
     const int probes = 16;
