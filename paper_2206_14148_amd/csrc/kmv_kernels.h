@@ -41,8 +41,10 @@ hipError_t launch_reduce(const double* partials, int S, int64_t n, double* y, hi
                          const int* done = nullptr);
 
 // d = 1 (kmv_series.hip): y through one series per box of sources, in series_bytes(n) bytes at ws.  S: the
-// general kernels' ranges.  Whether the points allow that, and whether it takes less time than they do, is found on the device: *done gets a flag per tile of kLowdTileRows rows, 1
-// where y is complete.  launch_lowd, launch_f64 and launch_reduce, given it, make the other tiles.
+// general kernels' ranges.  Whether the points allow that, and whether it takes less time than they
+// do, is found on the device: *done gets 0 where y is complete, -1 where nothing is done, else the
+// number of tiles of kLowdTileRows rows that are left, and behind it a flag per tile, 1 where its rows
+// are complete.  launch_lowd, launch_f64 and launch_reduce, given it, make what is missing.
 int64_t series_bytes(int64_t n);
 bool series_applies(int64_t n, int64_t m, int S, int d, double lengthscale, bool f64);
 template <typename T>

@@ -49,10 +49,17 @@ __global__ __launch_bounds__(256) void kmv_zero_kernel(double* __restrict__ y, i
     if (i < n) y[i] = 0.0;
 }
 
+// whether the series (launch_series) has made the rows of this workgroup's tile
+__device__ __forceinline__ bool series_made(const int* __restrict__ done) {
+    if (!done) return false;
+    const int left = done[0];
+    return left == 0 || (left > 0 && done[1 + blockIdx.x]);
+}
+
 __global__ __launch_bounds__(256) void kmv_reduce_kernel(const double* __restrict__ partials, int S,
                                                          int64_t n, double* __restrict__ y,
                                                          const int* __restrict__ done) {
-    if (done && done[blockIdx.x]) return;  // (tiles of 256 rows here too)
+    if (series_made(done)) return;  // (tiles of 256 rows here too)
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= n) return;
     double acc = partials[i];
@@ -70,7 +77,7 @@ __global__ __launch_bounds__(kLowdTileRows) void kmv_lowd_kernel(
     const float* __restrict__ X, int64_t ldx, const float* __restrict__ Z, int64_t ldz_arg,
     const float* __restrict__ v, int n, int m, int split_len, float negc2, double variance,
     double* __restrict__ out, const int* __restrict__ done) {
-    if (done && done[blockIdx.x]) return;  // the series made these rows
+    if (series_made(done)) return;
     constexpr int U = 8;
     const int64_t ldz = CONTIG ? (int64_t)D : ldz_arg;
     const int s = blockIdx.y;
@@ -419,7 +426,7 @@ __global__ __launch_bounds__(kLowdTileRows) void kmv_lowd_f64_kernel(
     const double* __restrict__ X, int64_t ldx, const double* __restrict__ Z, int64_t ldz_arg,
     const double* __restrict__ v, int n, int m, int split_len, double negc, double variance,
     double* __restrict__ out, const int* __restrict__ done) {
-    if (done && done[blockIdx.x]) return;  // the series made these rows
+    if (series_made(done)) return;
     constexpr int U = 4;
     const int64_t ldz = CONTIG ? (int64_t)D : ldz_arg;
     const int s = blockIdx.y;

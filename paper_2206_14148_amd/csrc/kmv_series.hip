@@ -73,8 +73,8 @@ constexpr int kMaxBoxes = 1024;
 constexpr int kMomentGroups = 2048;  // workgroups of the moment kernel: box x slice of the sources
 constexpr int kMaxSlices = 64;
 
-// workspace: header | bounds of the workgroups [3][256] | the boxes' table | partial moments | per tile of
-// 256 rows whether it is done
+// workspace: header | bounds of the workgroups [3][256] | the boxes' table | partial moments | how many tiles
+// of 256 rows are left to the general kernel (-1: all), and for each (fp64) whether it is done
 struct Header {
     int ok;      // the series applies
     int boxes;
@@ -93,12 +93,13 @@ __global__ __launch_bounds__(256) void kmv_bounds_kernel(const T* __restrict__ Z
                                                          double* __restrict__ bounds) {
     __shared__ double part[3][4];
     double lo = HUGE_VAL, hi = -HUGE_VAL, bad = 0.0;
+    const double most = 1e300 / (double)m;
     for (int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x; j < m; j += 256 * kBoundsGroups) {
         const double z = (double)Z[j * ldz], w = (double)v[j];
         lo = fmin(lo, z);
         hi = fmax(hi, z);
         // (weights whose sum without the entries of K could overflow are left to the general kernel)
-        if (!(fabs(z) < HUGE_VAL) || !(fabs(w) * (double)m < 1e300)) bad = 1.0;
+        if (!(fabs(z) < HUGE_VAL) || !(fabs(w) < most)) bad = 1.0;
     }
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) {
@@ -129,9 +130,10 @@ __global__ __launch_bounds__(256) void kmv_moments_kernel(const T* __restrict__ 
                                                           const double* __restrict__ bounds,
                                                           Header* __restrict__ header,
                                                           double* __restrict__ table,
-                                                          double* __restrict__ partial) {
+                                                          double* __restrict__ partial, int* __restrict__ done) {
     constexpr int P = Series<T>::P;
-    __shared__ double sum[4][P + 1];
+    constexpr int N = P + (sizeof(T) == 8 ? 1 : 0);  // sums: the moments, and in fp64 their terms' magnitude
+    __shared__ double sum[4][N];
     __shared__ double part[3][4];
     const int wave = threadIdx.x >> 6;
     const int lane = threadIdx.x & 63;
@@ -177,14 +179,17 @@ __global__ __launch_bounds__(256) void kmv_moments_kernel(const T* __restrict__ 
         const int64_t useful = (m + 1023) / 1024;
         if (slices > useful) slices = (int)useful;
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) *header = Header{ok ? 1 : 0, boxes, slices};
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        *header = Header{ok ? 1 : 0, boxes, slices};
+        done[0] = ok ? 0 : -1;
+    }
     const int box = (int)blockIdx.x / slices;
     const int slice = (int)blockIdx.x - box * slices;
     if (box >= boxes) return;  // whole workgroup
     const double c = fma((double)box + 0.5, width, lo);
-    double acc[P + 1];  // the moments and the sum of the terms' magnitudes
+    double acc[N];
 #pragma unroll
-    for (int p = 0; p <= P; ++p) acc[p] = 0.0;
+    for (int p = 0; p < N; ++p) acc[p] = 0.0;
     const int64_t len = (m + slices - 1) / slices;
     const int64_t j0 = slice * len;
     const int64_t j1 = j0 + len < m ? j0 + len : m;
@@ -204,7 +209,7 @@ __global__ __launch_bounds__(256) void kmv_moments_kernel(const T* __restrict__ 
             if (g == box && jj < j1) {
                 const double b = (z[u] - c) * rl;
                 double w = (double)v[jj] * exp(-0.5 * b * b);
-                acc[P] += fabs(w);
+                if constexpr (N > P) acc[P] += fabs(w);
 #pragma unroll
                 for (int p = 0; p < P; ++p) {
                     acc[p] += w;
@@ -214,7 +219,7 @@ __global__ __launch_bounds__(256) void kmv_moments_kernel(const T* __restrict__ 
         }
     }
 #pragma unroll
-    for (int p = 0; p <= P; ++p) {
+    for (int p = 0; p < N; ++p) {
         double s = acc[p];
 #pragma unroll
         for (int o = 32; o >= 1; o >>= 1) s += __shfl_xor(s, o);
@@ -222,7 +227,7 @@ __global__ __launch_bounds__(256) void kmv_moments_kernel(const T* __restrict__ 
     }
     __syncthreads();
     const int t = threadIdx.x;
-    if (t <= P) partial[(int64_t)blockIdx.x * kRow + t] = (sum[0][t] + sum[1][t]) + (sum[2][t] + sum[3][t]);
+    if (t < N) partial[(int64_t)blockIdx.x * kRow + t] = (sum[0][t] + sum[1][t]) + (sum[2][t] + sum[3][t]);
     if (slice == 0 && t == kRow - 1) table[(int64_t)box * kRow + kRow - 1] = c;
 }
 
@@ -234,7 +239,7 @@ __global__ __launch_bounds__(64) void kmv_table_kernel(const Header* __restrict_
     constexpr int P = Series<T>::P;
     static_assert(P < kWeight, "a lane per moment and one for their magnitude, the centre behind them");
     const int box = blockIdx.x, p = threadIdx.x;
-    if (!header->ok || box >= header->boxes || p > P) return;
+    if (!header->ok || box >= header->boxes || p > P || (p == P && sizeof(T) != 8)) return;
     const int slices = header->slices;
     double s = 0.0, factorial = 1.0;
 #pragma unroll 8
@@ -248,8 +253,8 @@ __global__ __launch_bounds__(64) void kmv_table_kernel(const Header* __restrict_
 }
 
 // One row per lane; the boxes are the same for the whole wave, so their moments come through
-// scalar loads.  Per box and row: P multiply-adds and one exponential.  done[tile] = 1 where y is
-// complete, 0 where the general kernel has to make the tile's rows.
+// scalar loads.  Per box and row: P multiply-adds and one exponential.  In fp64 done[1 + tile] = 1 where y
+// is complete, 0 where the general kernel has to make the tile's rows; done[0] counts those.
 template <typename T>
 __global__ __launch_bounds__(256) void kmv_series_kernel(const T* __restrict__ X, int64_t ldx, int64_t n,
                                                          double lengthscale, double variance,
@@ -257,10 +262,7 @@ __global__ __launch_bounds__(256) void kmv_series_kernel(const T* __restrict__ X
                                                          const double* __restrict__ table,
                                                          int* __restrict__ done, double* __restrict__ y) {
     constexpr int P = Series<T>::P;
-    if (!header->ok) {
-        if (threadIdx.x == 0) done[blockIdx.x] = 0;
-        return;
-    }
+    if (!header->ok) return;
     const int boxes = header->boxes;
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const double rl = 1.0 / lengthscale;
@@ -285,17 +287,21 @@ __global__ __launch_bounds__(256) void kmv_series_kernel(const T* __restrict__ X
         for (int p = P - 2; p >= 0; --p) s = fma(s, a, row[p]);
         if (e <= Series<T>::far) total = fma(exp(-e), s, total);
     }
-    // (at most 160 boxes are within reach of a row: 160 / 2^6 = 2.5)
-    const int leave = i < n && lost > surely - 6.f;
     if (x != x) total = x;  // as the sum over such entries of K
     if (i < n) y[i] = variance * total;
-    const int any = __syncthreads_or(leave);
-    if (threadIdx.x == 0) done[blockIdx.x] = any ? 0 : 1;
+    if constexpr (sizeof(T) == 8) {
+        // (at most 160 boxes are within reach of a row: 160 / 2^6 = 2.5)
+        const int leave = __syncthreads_or(i < n && lost > surely - 6.f);
+        if (threadIdx.x == 0) {
+            done[1 + blockIdx.x] = leave ? 0 : 1;
+            if (leave) atomicAdd(done, 1);
+        }
+    }
 }
 
 }  // namespace
 
-int64_t series_bytes(int64_t n) { return kDoneAt + (n + 255) / 256 * 4; }
+int64_t series_bytes(int64_t n) { return kDoneAt + 4 + (n + 255) / 256 * 4; }
 
 // What the general kernels take at least, us: all entries at 6.4e12 (fp64 1.3e12) per second, or one
 // wave's range of the sources at 16 ns (90) each, where rows and ranges leave the chip idle.
@@ -326,13 +332,14 @@ hipError_t launch_series(const T* X, int64_t ldx, const T* Z, int64_t ldz, const
     double* table = reinterpret_cast<double*>(base + kTableAt);
     double* partial = reinterpret_cast<double*>(base + kPartialAt);
     static_assert(kLowdTileRows == 256, "a flag per workgroup of the general kernels");
-    *done = reinterpret_cast<int*>(base + kDoneAt);
+    int* const flags = reinterpret_cast<int*>(base + kDoneAt);
+    *done = flags;
     kmv_bounds_kernel<T><<<dim3(kBoundsGroups), dim3(256), 0, stream>>>(Z, ldz, v, m, bounds);
     kmv_moments_kernel<T><<<dim3(kMomentGroups), dim3(256), 0, stream>>>(
-        Z, ldz, v, m, n, lengthscale, general_time_us(n, m, S, sizeof(T) == 8), bounds, header, table, partial);
+        Z, ldz, v, m, n, lengthscale, general_time_us(n, m, S, sizeof(T) == 8), bounds, header, table, partial, flags);
     kmv_table_kernel<T><<<dim3(kMaxBoxes), dim3(64), 0, stream>>>(header, partial, table);
     kmv_series_kernel<T><<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream>>>(
-        X, ldx, n, lengthscale, variance, header, table, const_cast<int*>(*done), y);
+        X, ldx, n, lengthscale, variance, header, table, flags, y);
     return hipGetLastError();
 }
 
