@@ -97,16 +97,30 @@ def test_inducing_points_among_the_data(K, oracle):
     parity(K, oracle, X[:150].copy(), X, y, 1.2, 0.9)
 
 
-@pytest.mark.parametrize("variance", [2.0 ** -62, 2.0 ** 70, 1.7e-17])
+@pytest.mark.parametrize("variance", [2.0 ** -62, 2.0 ** 70, 1.7e-17, 3e25])
 def test_extreme_variances_scale_the_sums(K, variance):
-    # a power of two moves the exponent only; the pieces' small products must not underflow
+    # the power of two moves the exponent only; the pieces' small products must not underflow
     U, X, y = W.random_sgpr_case(24, 150, 3000, 3)
+    significand, exponent = np.frexp(variance)
     A, b = run_gpu(K, U, X, y, variance, 1.0, 64 * W.MB)
-    A1, b1 = run_gpu(K, U, X, y, 1.0, 1.0, 64 * W.MB)
-    exact = np.log2(variance) == np.round(np.log2(variance))
-    rtol = 0.0 if exact else 3000 * EPS   # other roundings of the entries, sums of 3000 columns in fp32
-    assert np.allclose(A / variance ** 2, A1, rtol=rtol, atol=0 if exact else 1e-30)
-    assert (np.abs(b / variance - b1) <= rtol * 3000 * np.abs(y).max()).all()
+    A1, b1 = run_gpu(K, U, X, y, float(significand), 1.0, 64 * W.MB)
+    assert np.array_equal(A, np.ldexp(A1, 2 * int(exponent))) and np.array_equal(b, np.ldexp(b1, int(exponent)))
+
+
+def test_inducing_points_many_lengthscales_apart(K, oracle):
+    # entries of A far below the others, down to where a product of two entries of K_uf is below the least
+    # fp32 number: every term is positive, so the bound holds relative to the entry itself
+    rng = np.random.Generator(np.random.PCG64(26))
+    U = np.linspace(0.0, 19.0, 140).astype(np.float32).reshape(-1, 1)
+    X = np.concatenate([19.0 * rng.random((2500, 1)), U[::2].astype(np.float64)]).astype(np.float32)
+    y = rng.standard_normal(len(X)).astype(np.float32)
+    A, _ = run_gpu(K, U, X, y, 1.0, 1.0, 64 * W.MB)
+    ref, _ = oracle.sgpr_accumulate(U, X, y, 1.0, 1.0)
+    # (entries of K_uf below the least normal number, exponents beyond 87, belong to points 13.2 or more from one
+    # of the two and 3.7 from their middle: 2e-7 of the sum)
+    tol = ref * (1e-5 + 2 * 5 * EPS * 87 + len(X) * EPS)
+    say("worst", float((np.abs(A - ref) / tol).max()), "least entry", float(ref.min()))
+    assert ref.min() < 2e-37 and (np.abs(A - ref) <= tol).all()
 
 
 def test_limits_give_the_same_sums_up_to_rounding(K, oracle):
