@@ -604,13 +604,15 @@ static hipError_t launch_sad_words(SadCall c) {
     if (per_group < 1) per_group = 1;
     knn_l1_seed_kernel<W><<<dim3(gx, (unsigned)c.k), dim3(256), 0, c.stream>>>(
         c.X, c.ldx, c.qb, c.qr, c.tsh, c.head, (int)c.rows, (int)c.n, c.d, c.k, per_group, c.aligned, 0);
+    // (the probe takes the first 2^19 queries at most: the pairs that it counts stay below 2^32)
     const int probes = 16;
-    knn_l1_seed_kernel<W><<<dim3(gx, probes), dim3(256), 0, c.stream>>>(
+    const unsigned px = gx < 4096u ? gx : 4096u;
+    knn_l1_seed_kernel<W><<<dim3(px, probes), dim3(256), 0, c.stream>>>(
         c.X, c.ldx, c.qb, c.qr, c.tsh, c.head, (int)c.rows, (int)c.n, c.d, c.k, per_group, c.aligned, 1);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const int64_t most = c.rows * probes * kSadPoints / kSadPassDivisor;
-    c.most_passed = most < 0xffffffffll ? (unsigned)most : 0xffffffffu;
+    const int64_t probed = c.rows < 128 * (int64_t)px ? c.rows : 128 * (int64_t)px;
+    c.most_passed = (unsigned)(probed * probes * kSadPoints / kSadPassDivisor);
     // Two queries per lane halve the LDS reads; one where two would leave compute units without work.
     if ((c.rows + 511) / 512 * c.S >= kSadTwoWorkgroups) return launch_sad<W, 2>(c);
     return launch_sad<W, 1>(c);
