@@ -25,9 +25,19 @@ def K():
     return K
 
 
-def search(K, Q, X, k, plain=False):
-    idx, dist = K.knn_search(Q, X, 65 if plain else k, 256 * W.MB, metric="l1")
+def search(K, Q, X, k, plain=False, filtered=None):
+    """filtered: whether the lists have to be the filter's.  (The kernel without it works on transposed
+    queries, which then lie where the filter keeps its scale.)"""
+    kk = 65 if plain else k
+    plan = K.knn_plan(Q.shape[0], X.shape[0], Q.shape[1], kk, 256 * W.MB, "l1")
+    assert plan.q_chunks == 1
+    ws = torch.full((plan.workspace_bytes,), 0xA5, dtype=torch.uint8, device="cuda")
+    idx, dist = K.knn_search(Q, X, kk, 256 * W.MB, metric="l1", workspace=ws)
     torch.cuda.synchronize()
+    transposed = torch.equal(ws[:16].view(torch.float32).view(torch.int32), Q[0, :4].clone().view(torch.int32))
+    print("filtered", not transposed, flush=True)
+    if filtered is not None:
+        assert transposed != filtered
     return idx[:, :k].cpu().numpy(), dist[:, :k].cpu().numpy()
 
 
@@ -39,6 +49,17 @@ def data(seed, m, n, d, kind):
         c = 100.0 * g.standard_normal((50, d)).astype(np.float32)
         X = c[g.integers(0, 50, n)] + np.float32(0.01) * X
         Q = c[g.integers(0, 50, m)] + np.float32(0.01) * Q
+    elif kind == "many_clusters":  # the same, but a query's own cluster is less than the filter may let through
+        c = 100.0 * g.standard_normal((500, d)).astype(np.float32)
+        X = c[g.integers(0, 500, n)] + np.float32(0.01) * X
+        Q = c[g.integers(0, 500, m)] + np.float32(0.01) * Q
+    elif kind == "gmm":     # clusters as wide as they are apart
+        c = 2.0 * g.standard_normal((100, d)).astype(np.float32)
+        X += c[g.integers(0, 100, n)]
+        Q += c[g.integers(0, 100, m)]
+    elif kind == "outliers":  # a few points with values far outside the scale, and beyond 1e30
+        X[g.integers(0, n, 50), g.integers(0, d, 50)] *= 100
+        X[g.integers(0, n, 20), g.integers(0, d, 20)] = 1e32
     elif kind == "tails":   # some values far outside the sample's range, others beyond 1e30
         X *= np.exp(3.0 * g.standard_normal((n, d))).astype(np.float32)
         X[g.integers(0, n, 20), g.integers(0, d, 20)] = 1e32
@@ -52,23 +73,28 @@ def data(seed, m, n, d, kind):
     return Q, X
 
 
-CASES = [(129, 4096, 16, 1, "normal"), (257, 30_001, 17, 10, "normal"), (1025, 30_003, 100, 10, "normal"),
-         (700, 31_001, 100, 10, "clusters"), (300, 30_000, 33, 7, "tails"), (513, 50_100, 185, 16, "normal"),
-         (100, 196_000, 192, 64, "offset"), (2000, 51_191, 20, 17, "ties"), (150, 30_159, 64, 10, "equal"),
-         (11_000, 9200, 128, 3, "normal"), (140, 70_000, 57, 5, "normal"), (300, 30_011, 16, 2, "normal"),
-         (1, 10_000, 24, 1, "normal"), (64, 50_000, 5, 8, "normal"), (65, 15_007, 9, 5, "tails"),
-         (1500, 12_000, 8, 4, "normal")]
+# and whether the filter answers (where it would let too much through it says so, and the kernel without it
+# makes the lists)
+CASES = [(129, 4096, 16, 1, "normal", True), (257, 30_001, 17, 10, "normal", True), (1025, 30_003, 100, 10, "normal", True),
+         (700, 31_001, 100, 10, "clusters", False), (700, 31_001, 100, 10, "many_clusters", True),
+         (300, 30_000, 33, 7, "tails", False), (300, 30_000, 33, 7, "outliers", True),
+         (513, 50_100, 185, 16, "normal", False), (513, 50_100, 185, 16, "gmm", True),
+         (100, 196_000, 192, 64, "offset", False), (100, 196_000, 192, 64, "gmm", True), (300, 30_000, 16, 7, "offset", True),
+         (2000, 51_191, 20, 17, "ties", True), (150, 30_159, 64, 10, "equal", False),
+         (11_000, 9200, 128, 3, "normal", True), (140, 70_000, 57, 5, "normal", True), (300, 30_011, 16, 2, "normal", True),
+         (1, 10_000, 24, 1, "normal", True), (64, 50_000, 5, 8, "normal", True), (65, 15_007, 9, 5, "tails", False),
+         (65, 15_007, 9, 5, "outliers", True), (1500, 12_000, 8, 4, "normal", True)]
 
 
-@pytest.mark.parametrize("m,n,d,k,kind", CASES)
-def test_matches_oracle_and_the_search_without_the_filter(K, oracle, m, n, d, k, kind):
+@pytest.mark.parametrize("m,n,d,k,kind,filtered", CASES)
+def test_matches_oracle_and_the_search_without_the_filter(K, oracle, m, n, d, k, kind, filtered):
     print("case", m, n, d, k, kind, flush=True)
     Q, X = data(m + d, m, n, d, kind)
     Qd, Xd = torch.from_numpy(Q).cuda(), torch.from_numpy(X).cuda()
-    idx, dist = search(K, Qd, Xd, k)
-    idx0, dist0 = search(K, Qd, Xd, k, plain=True)
+    idx, dist = search(K, Qd, Xd, k, filtered=filtered)
+    idx0, dist0 = search(K, Qd, Xd, k, plain=True, filtered=False)
     assert np.array_equal(idx, idx0) and np.array_equal(dist, dist0)
-    if kind != "tails":  # (1e32 sums leave the oracle's error bound for fp32 keys meaningless)
+    if kind not in ("tails", "outliers"):  # (1e32 sums leave the oracle's error bound for fp32 keys meaningless)
         rows = np.unique(np.linspace(0, m - 1, 60).astype(np.int64))
         o_idx, o_dist, o_next = oracle.knn(Q, X, k, rows=rows, metric="l1")
         check(idx[rows], dist[rows], o_idx, o_dist, o_next, n)
@@ -85,7 +111,7 @@ def test_infinities_nan_and_strided_rows(K):
     Xw, Qw = torch.zeros(n, 39).cuda(), torch.zeros(300, 37).cuda()
     Xw[:, :36] = torch.from_numpy(X).cuda()
     Qw[:, :36] = torch.from_numpy(Q).cuda()
-    idx, dist = search(K, Qw[:, :36], Xw[:, :36], 5)
+    idx, dist = search(K, Qw[:, :36], Xw[:, :36], 5, filtered=True)
     idx0, dist0 = search(K, Qw[:, :36], Xw[:, :36], 5, plain=True)
     assert np.array_equal(idx, idx0) and np.array_equal(dist, dist0, equal_nan=True)
     finite = np.ones(300, bool)
