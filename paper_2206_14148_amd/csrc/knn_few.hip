@@ -9,9 +9,10 @@
 // wave and come through scalar loads, and every point value read feeds NQ queries.  Pairs under a
 // query's current k-th key wait in a buffer of 64 and are merged into its list when that is full.
 //
-// What bounds it: two VALU operations per pair and coordinate; at 16 queries x 1e5 points, d = 50,
-// k = 10 (63 us here and 33 us for the merge of 376 lists a query) the round trips of a wave's five
-// groups of points.
+// What bounds it: the round trips of a wave's groups of points more than its arithmetic, two VALU
+// operations per pair and coordinate (1000 x 1e4, d = 16: vector units busy a third of the wave cycles,
+// waits another third); at 16 queries x 1e5 points, d = 50, k = 10 63 us here and 33 us for the merge of
+// 376 lists a query.
 #include <hip/hip_runtime.h>
 
 #include <climits>
@@ -208,10 +209,12 @@ bool few_aligned(const float* X, int64_t ldx, int d) {
 }
 
 int few_splits(int64_t rows, int64_t n, int k, uint64_t workspace_bytes) {
-    // as many waves as the chip holds at once (three a SIMD, by their LDS) where the points last
-    // (ranges of at least 256), lists that fit
+    // as many waves as the chip holds at once (two a SIMD, by the 173 registers of the variant for rows
+    // that are not aligned; three of the other) where the points last (ranges of at least 256), lists that
+    // fit.  (Three for both: 1000 x 1e4, d = 9, k = 10 139 us against 102, d = 50 202 against 158, d = 16
+    // 98.5 against 90.4; 16 x 1e6, d = 50 322 against 246: a second round of workgroups that is nearly empty.)
     const int64_t groups = (rows + kFewQueries - 1) / kFewQueries;
-    int64_t S = 3 * 4 * kNumCU / groups;
+    int64_t S = 2 * 4 * kNumCU / groups;
     if (S > (n + 255) / 256) S = (n + 255) / 256;
     if (S > kFewMaxSplits) S = kFewMaxSplits;
     const uint64_t room = workspace_bytes / 2 / kAlign * kAlign;  // keys and indices, each aligned
