@@ -36,17 +36,18 @@ PEAK_HBM_GBS = 8000.0
 # a workload on the kernel named; a run with other sizes, another limit or another kernel reports
 # null.  {workload: (kernel, bytes, profile)}
 PROFILED_TRAFFIC = {
-    "c1_random_d16": ("knn_split_kernel", 11.8e6, "profiles/knn_split_kernel_c1.md"),
-    "c2_pointcloud_d3": ("knn_lowd_bf16_kernel", 211.4e9, "profiles/knn_lowd_bf16_kernel_c2.md"),
+    "c1_random_d16": ("knn_few_kernel", 8.3e6, "profiles/knn_few_kernel_c1.md"),
+    "c2_pointcloud_d3": ("knn_grid_kernel", 0.315e9, "profiles/knn_grid_kernel_c2.md"),
     "c3_imagelike_d784": ("knn_wide_kernel", 50.6e9, "profiles/knn_wide_kernel_c3.md"),
     "c4_clustered_d128": ("knn_packed_kernel", 435.6e9, "profiles/knn_packed_kernel_c4.md"),
     "c5_memsweep_d256": ("knn_packed_kernel", 15.2e9, "profiles/knn_packed_kernel_c5_1GB.md"),  # per launch, two a step
     "c6_cosine_d100": ("knn_packed_kernel", 8.37e9, "profiles/knn_packed_kernel_c6.md"),
-    "c7_l1_d100": ("knn_l1_kernel", 25.8e9, "profiles/knn_l1_kernel_c7.md"),
-    "kmv1_d1": ("kmv_lowd_kernel", 1.84e9, "profiles/kmv_lowd_kernel_kmv1.md"),
+    "c7_l1_d100": ("knn_l1_sad_kernel", 12.1e9, "profiles/knn_l1_sad_kernel_c7.md"),
+    "kmv1_d1": ("kmv_series_kernel", 12.1e6, "profiles/kmv_series_kernel_kmv1.md"),
     "kmv2_d32": ("kmv_mfma_kernel", 1.47e9, "profiles/kmv_mfma_kernel_kmv2.md"),
-    "kmv3_d1_f64": ("kmv_lowd_f64_kernel", 4.02e9, "profiles/kmv_lowd_f64_kernel_kmv3.md"),
-    "sgpr1_road_d3_m10000": ("sgpr_syrk_kernel", 8.99e9, "profiles/sgpr_syrk_kernel_sgpr1.md"),
+    "kmv3_d1_f64": ("kmv_series_kernel", 16.3e6, "profiles/kmv_series_kernel_kmv3.md"),
+    "sgpr1_road_d3_m10000": ("sgpr_syrk_kernel", 3.71e9, "profiles/sgpr_syrk_kernel_sgpr1.md"),
+    "sgpr2_electric_d11_m4000": ("sgpr_syrk_kernel", 0.949e9, "profiles/sgpr_syrk_kernel_sgpr2.md"),
 }
 
 
@@ -86,12 +87,16 @@ def bench_kmv(args) -> int:
     vd = torch.from_numpy(v).to(dev)
     plan = K.kmv_plan(w.n, w.m, w.d, limit, w.dtype)
     assert plan.workspace_bytes <= limit
-    ws = torch.empty(max(plan.workspace_bytes, 256), dtype=torch.uint8, device=dev)
+    # (what a call without a workspace allocates: for d = 1 the series' part as well)
+    roomy = K.load().kmv_workspace_bytes_f64 if w.dtype == "f64" else K.load().kmv_workspace_bytes
+    workspace_bytes = int(roomy(w.n, w.m, w.d, w.lengthscale, limit))
+    assert workspace_bytes <= limit
+    ws = torch.empty(max(workspace_bytes, 256), dtype=torch.uint8, device=dev)
     y = torch.empty((w.n,), dtype=torch.float64, device=dev)
     path_name = {0: "lowd", 1: "mfma", 2: "valu"}[plan.path]
     okmv = (lambda *a, **k: __import__("oracle").kmv_f64(*a, **k)) if w.dtype == "f64" \
         else (lambda *a, **k: __import__("oracle").kmv(*a, **k))
-    log(f"[bench] plan: path={path_name} ranges={plan.n_splits} workspace={plan.workspace_bytes} B "
+    log(f"[bench] plan: path={path_name} ranges={plan.n_splits} workspace={workspace_bytes} B "
         f"(limit {limit} B)")
 
     def step():
@@ -122,7 +127,20 @@ def bench_kmv(args) -> int:
     value = pairs * args.steps / elapsed
     log(f"[bench] {ms_per_step:.2f} ms/step, {value:.3e} pairs/s; kernels per call {call_ms:.3f} ms")
     rate = pairs / (call_ms * 1e-3)
-    if w.dtype == "f64":
+    # whether the series answered (its part of the workspace begins with that word and the number of boxes)
+    boxes = 0
+    if workspace_bytes > plan.workspace_bytes:
+        ok, boxes = ws[plan.workspace_bytes:plan.workspace_bytes + 8].view(torch.int32).tolist()
+        boxes = boxes if ok == 1 else 0
+    if boxes:
+        # P multiply-adds per row and box, and per source, all in fp64; the entries of K are not made
+        terms = 56 if w.dtype == "f64" else 34
+        flops = 2.0 * terms * (float(w.n) * boxes + float(w.m))
+        roofline = {"bound": "alu", "kernel": "kmv_series_kernel", "achieved": flops / (call_ms * 1e-3) / 1e12,
+                    "peak": 78.6, "unit": "TFLOP/s", "frac": flops / (call_ms * 1e-3) / 1e12 / 78.6, "traffic": None,
+                    "boxes": boxes, "terms": terms,
+                    "unit_note": "fp64 multiply-adds of the series; value counts the entries they stand for"}
+    elif w.dtype == "f64":
         # per pair: d subtractions, d multiply-adds, the scaling, exp (a polynomial of about 25
         # fp64 operations in the math library, counted as one flop here) and the multiply-add
         fpp = 3 * w.d + 3
@@ -190,7 +208,8 @@ def bench_kmv(args) -> int:
     if not args.mem_limit:
         for lim in (0 if plan.path != K.KMV_PATH_MFMA else plan.norms_bytes, 10 ** 6, 10 ** 8, 10 ** 9, 32 * 10 ** 9):
             p2 = K.kmv_plan(w.n, w.m, w.d, lim, w.dtype)
-            ws2 = torch.empty(max(p2.workspace_bytes, 256), dtype=torch.uint8, device=dev)
+            bytes2 = int(roomy(w.n, w.m, w.d, w.lengthscale, lim))
+            ws2 = torch.empty(max(bytes2, 256), dtype=torch.uint8, device=dev)
             y2 = torch.empty_like(y)
             K.kmv_apply(Xd, Zd, vd, w.variance, w.lengthscale, lim, workspace=ws2, out=y2)
             torch.cuda.synchronize()
@@ -199,10 +218,10 @@ def bench_kmv(args) -> int:
                 K.kmv_apply(Xd, Zd, vd, w.variance, w.lengthscale, lim, workspace=ws2, out=y2)
             torch.cuda.synchronize()
             dt = (time.perf_counter() - t0) / args.steps
-            sweep.append({"mem_limit_bytes": lim, "workspace_bytes": p2.workspace_bytes,
+            sweep.append({"mem_limit_bytes": lim, "workspace_bytes": bytes2,
                           "point_ranges": p2.n_splits, "ms_per_step": dt * 1e3,
                           "max_abs_diff": float((y2 - y).abs().max())})
-            log(f"[bench] sweep limit={lim}: {dt*1e3:.1f} ms, workspace {p2.workspace_bytes} B, "
+            log(f"[bench] sweep limit={lim}: {dt*1e3:.3f} ms, workspace {bytes2} B, "
                 f"ranges {p2.n_splits}")
             del ws2, y2
 
@@ -213,8 +232,8 @@ def bench_kmv(args) -> int:
         "vs_baseline": None, "dtype": w.dtype, "data": "synthetic",
         "config": {"workload": w.name, "n": w.n, "m": w.m, "d": w.d, "variance": w.variance,
                    "lengthscale": w.lengthscale, "mem_limit_bytes": limit,
-                   "workspace_bytes": plan.workspace_bytes, "point_ranges": plan.n_splits,
-                   "path": path_name},
+                   "workspace_bytes": workspace_bytes, "point_ranges": plan.n_splits,
+                   "path": "series" if boxes else path_name},
         "roofline": roofline, "cpu_baseline": cpu_baseline, "parity": parity,
     }
     if sweep:
@@ -286,9 +305,12 @@ def bench_sgpr(args) -> int:
     avg_launch_s = syrk_ms / max(launches, 1) * 1e-3
     flops_per_launch = float(w.flops) * args.steps / max(launches, 1)
     achieved = flops_per_launch / avg_launch_s / 1e12
+    # The products run as six bf16 MFMAs over exact three-piece splits of the fp32 entries: the
+    # method's own flops against the bf16 peak, and what is issued for them beside it.
     roofline = {"bound": "mfma", "kernel": "sgpr_syrk_kernel", "achieved": achieved,
-                "peak": PEAK_FP32_MATRIX_TFLOPS, "unit": "TFLOP/s",
-                "frac": achieved / PEAK_FP32_MATRIX_TFLOPS,
+                "peak": PEAK_BF16_MATRIX_TFLOPS, "unit": "TFLOP/s",
+                "frac": achieved / PEAK_BF16_MATRIX_TFLOPS, "issued_tflops": 6 * achieved,
+                "issued_frac": 6 * achieved / PEAK_BF16_MATRIX_TFLOPS,
                 "traffic": None, "flops_per_pair": w.m + 1, "avg_launch_ms": avg_launch_s * 1e3}
     roofline["traffic"], roofline["traffic_source"] = profiled_traffic(
         w.name, "sgpr_syrk_kernel", not (args.n or args.m or args.mem_limit))
@@ -407,7 +429,33 @@ def knn_record(w, limit, steps, warmup, cpu_seconds, peaks, default_shape, host_
     launches_per_step = max(launches, 1) / steps
     pairs_per_launch = float(w.m) * float(w.n) / launches_per_step
     hbm_equiv = (pairs_per_launch / avg_launch_s) * 8.0 / (PEAK_HBM_GBS * 1e9)
-    if plan.path in (K.KNN_PATH_MFMA_SPLIT, K.KNN_PATH_MFMA_PACKED, K.KNN_PATH_MFMA_WIDE):
+    # What ran under the plan's path: a small search has no preparation, the octree says so in the
+    # header's word 32 (33: waves it left to the filter), and the byte filter of the L1 metric keeps its
+    # scale where the kernel without it keeps the transposed queries.
+    few = prep_ms == 0.0 and plan.path in (K.KNN_PATH_MFMA_SPLIT, K.KNN_PATH_MFMA_PACKED, K.KNN_PATH_MFMA_WIDE)
+    octree = plan.path == K.KNN_PATH_LOWD_BF16 and w.d <= 3 and int(ws[128:132].view(torch.int32)) == 1
+    sad = plan.path == K.KNN_PATH_L1 and plan.q_chunks == 1 and w.d >= 5 and not torch.equal(
+        ws[:16].view(torch.int32), Qd[0, :4].clone().view(torch.int32))
+    if few:
+        # d subtractions and d multiply-adds per pair
+        achieved = 3.0 * w.d * pairs_per_launch / avg_launch_s / 1e12
+        roofline = {"bound": "alu", "kernel": "knn_few_kernel", "achieved": achieved, "peak": PEAK_FP32_VECTOR_TFLOPS,
+                    "unit": "TFLOP/s", "frac": achieved / PEAK_FP32_VECTOR_TFLOPS, "flops_per_pair": 3 * w.d}
+    elif octree:
+        # not every pair is looked at: what the call cannot do without is its inputs and outputs
+        achieved = (4.0 * (w.n + (0 if w.q_is_x else w.m)) * w.d + 8.0 * w.m * w.k) / (avg_launch_s * launches_per_step) / 1e9
+        roofline = {"bound": "hbm", "kernel": "knn_grid_kernel", "achieved": achieved, "peak": PEAK_HBM_GBS,
+                    "unit": "GB/s", "frac": achieved / PEAK_HBM_GBS,
+                    "unit_note": "inputs and outputs once; the kernel itself is a chain of dependent steps per wave",
+                    "waves_left_to_the_filter": int(ws[132:136].view(torch.int32))}
+    elif sad:
+        # one v_sad_u8 per four coordinates, words in pairs, at half the rate of an fp32 operation
+        lane_ops = 2.0 * ((w.d + 7) // 8 * 2)
+        peak = 256 * 4 * 16 * 2.4e9 / 1e12
+        achieved = lane_ops * pairs_per_launch / avg_launch_s / 1e12
+        roofline = {"bound": "alu", "kernel": "knn_l1_sad_kernel", "achieved": achieved, "peak": peak,
+                    "unit": "Tlane-op/s", "frac": achieved / peak, "lane_ops_per_pair": lane_ops}
+    elif plan.path in (K.KNN_PATH_MFMA_SPLIT, K.KNN_PATH_MFMA_PACKED, K.KNN_PATH_MFMA_WIDE):
         # The -2 Q X^T contraction of the filter runs on bf16 roundings of the values: 2 d bf16
         # flops per pair on the matrix cores, with d rounded up to the 16 coordinates of an MFMA,
         # against the dense bf16 peak.

@@ -81,8 +81,10 @@ int kmv_plan(int64_t n, int64_t m, int32_t d, int64_t mem_limit_bytes, kmv_plan_
  *   stream     hipStream_t (NULL: the default stream).  The call only
  *              enqueues work; it allocates nothing and does not synchronise.
  * Each y_i is a sum in a fixed order (64-point groups in fp32, groups and
- * ranges in fp64), so results do not depend on timing; they may differ in the
- * last bits between two limits that give different n_splits.
+ * ranges in fp64; through the series for d = 1 below, moments of the sources in
+ * fp64, boxes ascending), so results do not depend on timing; they may differ in
+ * the last bits between two limits that give different n_splits, and between the
+ * series and the entries (d = 1) by the fp32 roundings that the entries have.
  * Errors as kmv_plan, plus KNN_ERR_WORKSPACE_TOO_SMALL and KNN_ERR_HIP.
  */
 int kmv_apply(const float* X, int64_t ldx, const float* Z, int64_t ldz, const float* v, int64_t n,
@@ -111,7 +113,9 @@ int64_t kmv_workspace_bytes_f64(int64_t n, int64_t m, int32_t d, double lengthsc
  * fp64 (DEVICE, row-major, leading dimensions in elements) and every
  * operation is fp64 - difference-form squared distance with the columns in
  * ascending order, the math library's exp, one fused multiply-add per point
- * into a single accumulator with the points in ascending order (per range).
+ * into a single accumulator with the points in ascending order (per range) -
+ * or, for d = 1 where kmv_workspace_bytes_f64 describes it, the series over
+ * boxes of sources, to the same relative accuracy of the sum of magnitudes.
  * Vector-ALU kernels for every d (path 0 or 2); the workspace holds only the
  * partial sums of the ranges (norms_bytes == 0).  Otherwise as kmv_plan /
  * kmv_apply.

@@ -59,12 +59,19 @@ typedef enum { KNN_METRIC_L2SQ = 0, KNN_METRIC_COSINE = 1, KNN_METRIC_L1 = 2 } k
 
 /* kernel families (knn_plan_t.path) */
 #define KNN_PATH_LOWD 0 /* d <= 8: difference-form distances on the vector ALU  */
-#define KNN_PATH_L1 3   /* L1 metric: absolute differences on the vector ALU, any d   */
+#define KNN_PATH_L1 3   /* L1 metric: absolute differences on the vector ALU, any d.  For
+                           5 <= d <= 192, k <= 64 and n >= max(4096, 3000 k) a filter of byte sums
+                           goes first; where it would let too much through, found on the device,
+                           every pair is evaluated after all: same workspace, same results */
 #define KNN_PATH_LOWD_MFMA 2 /* d <= 3 and room for 16 n bytes of packed points:
                                 matrix-core filter + the same exact test as path 0 */
 #define KNN_PATH_LOWD_BF16 4 /* d <= 8 and room for 32 n bytes (d <= 4) or 64 n bytes: the filter
                                 in bf16 pieces on points moved by their bounding box's midpoint,
-                                same exact test */
+                                same exact test.  For d <= 3, k <= 32 and sizes where it was
+                                measured to be faster an octree over the points goes first, in the
+                                same workspace; points too unevenly spread for it, and queries that
+                                would look through too much of it, are found on the device and
+                                left to the filter: same keys, same results */
 #define KNN_PATH_MFMA_SPLIT 5 /* d > 8, and the cosine metric at any d: -2 Q X^T (plus norms)
                                  from the values rounded to bf16, one matrix-core product per
                                  coordinate, as a filter whose threshold allows for the

@@ -5,7 +5,7 @@
 //
 // A wave owns 64 points at a time, one per lane, and NQ queries.  Pieces of 32 coordinates of the
 // points go through LDS (read there with rows side by side, 128 bytes each; used with a lane per
-// row, rows 33 words apart: no bank conflicts), the queries' coordinates are the same for the whole
+// row, rows 33 words apart: conflicts in 1.5 % of the cycles), the queries' coordinates are the same for the whole
 // wave and come through scalar loads, and every point value read feeds NQ queries.  Pairs under a
 // query's current k-th key wait in a buffer of 64 and are merged into its list when that is full.
 //

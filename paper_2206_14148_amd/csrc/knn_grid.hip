@@ -9,9 +9,14 @@
 // the same order, descend together: a node is entered if any lane's own query could still find a
 // point in it that belongs in its list.
 //
-// n = m = 1e6, d = 3, k = 16: 4.2 ms for the search and 0.2 ms for the order, where the matrix-core
-// filter spends 42.5 ms on all pairs.  What bounds it is issue: a wave of 64 neighbouring queries
-// looks through about a thousand points, an eighth of them for the lists.
+// A wave's descent has a budget of steps; the rows of one that exceeds it are left to the filter.
+//
+// n = m = 1e6, own queries, d = 3, k = 16: 3.25 ms for the search and 0.2 ms for the order, where the
+// matrix-core filter spends 42.5 ms on all pairs.  What bounds it is the chain of a wave's steps at three
+// waves a SIMD (146 registers): of the wave cycles the vector units are busy in 34 %, 48 % wait for an
+// instruction or a load.  A wave of 64 neighbouring queries looks through about a thousand points, an
+// eighth of them for the lists.  (Lists of 32 take 256 registers: one wave a SIMD, 13.9 ms at k = 32,
+// where the filter takes 52.7.)
 #include <hip/hip_runtime.h>
 
 #include <cfloat>

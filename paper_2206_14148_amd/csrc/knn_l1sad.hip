@@ -350,7 +350,7 @@ __global__ __launch_bounds__(256) void knn_l1_seed_kernel(const float* __restric
 // rounds a tile of 64 points to bytes in LDS and every wave reads a point's bytes as a broadcast.
 // Two queries per lane and two workgroups per compute unit: the second hides the first one's
 // flushes and barriers (four queries per lane, one workgroup: 27.6 ms against 21.6).  Whole search
-// at that size, k = 10: 65.6 -> 22.4 ms; 1000 queries 13.8 -> 4.8, 16 queries 12.5 -> 3.2.
+// at that size, k = 10: 65.6 -> 22.4 ms; 1000 queries 13.8 -> 4.8, 16 queries 12.5 -> 3.0.
 template <int W, int QL>
 __global__ __launch_bounds__(256, W <= 32 ? 2 : 1) void knn_l1_sad_kernel(
     const float* __restrict__ Q, int64_t ldq, const float* __restrict__ X, int64_t ldx,
