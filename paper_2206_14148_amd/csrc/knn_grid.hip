@@ -19,7 +19,6 @@
 // where the filter takes 52.7.)
 #include <hip/hip_runtime.h>
 
-#include <cfloat>
 #include <climits>
 #include <cmath>
 #include <cstdint>
@@ -235,8 +234,8 @@ __global__ __launch_bounds__(256) void knn_grid_queries_kernel(const float* __re
 }
 
 // (key, index) as the bits of a double: keys are not negative, so such doubles are in the order of
-// (key, index), and one v_min_f64 / v_max_f64 moves both.  +inf with no index, an empty place, is an
-// ordinary large number in that reading.
+// (key, index), and one v_min_f64 / v_max_f64 moves both.  An empty place is +inf with index 0, an
+// ordinary large number in that reading that no pair with an infinite key comes before.
 __device__ __forceinline__ double pair_of(float key, int idx) {
     return __hiloint2double((int)__float_as_uint(key), idx);
 }
@@ -321,13 +320,14 @@ __global__ __launch_bounds__(256) void knn_grid_kernel(const float* __restrict__
             __builtin_amdgcn_ballot_w64(live && b > kGridMost) != 0) {
             budget = INT_MAX;
             if (!(diagonal < kGridMost) || __builtin_amdgcn_ballot_w64(live && b > kGridMost) != 0) sure = 0.f;
-        } else if (__builtin_amdgcn_ballot_w64(live && b > 0x1p24f * diagonal) != 0 ||
-                 (many && __hip_atomic_load(left, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > many)) {
+        } else if (__builtin_amdgcn_ballot_w64(live && b > 0x1p24f * diagonal) != 0) {
             leave();
             return;
         }
     }
-    const double top = pair_of(kInf, kNoIdx);
+    // (asked for here, used behind the first pass over the neighbours)
+    const unsigned gone = many ? __hip_atomic_load(left, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+    const double top = pair_of(kInf, 0);
     double best[K];
     auto reset = [&](double v) {
 #pragma unroll
@@ -341,10 +341,8 @@ __global__ __launch_bounds__(256) void knn_grid_kernel(const float* __restrict__
             best[i] = lo;
         }
     };
-    // the largest key that can still enter the list; infinite keys enter none.  (An idle lane's -1.0
-    // reads as a negative key.)
-    auto bound_key = [&]() {
-        return fminf(__uint_as_float((unsigned)__double2hiint(best[K - 1])), FLT_MAX);
+    auto bound_key = [&]() {  // (an idle lane's -1.0 reads as a negative key)
+        return __uint_as_float((unsigned)__double2hiint(best[K - 1]));
     };
     reset(top);
     const int own = morton_of<D>(g, L, q);
@@ -361,6 +359,10 @@ __global__ __launch_bounds__(256) void knn_grid_kernel(const float* __restrict__
         // the next double up: the least that is not accepted
         const double above = b < top ? __longlong_as_double(__double_as_longlong(b) + 1) : top;
         reset(above);
+    }
+    if (gone > many && budget != INT_MAX) {
+        leave();
+        return;
     }
     float tau = bound_key();
 
@@ -463,8 +465,9 @@ __global__ __launch_bounds__(256) void knn_grid_kernel(const float* __restrict__
     for (int i = 0; i < K; ++i) {
         const int p = i - (K - k);
         if (p >= 0) {
-            lk[lb + p] = live ? __uint_as_float((unsigned)__double2hiint(best[i])) : kInf;
-            li[lb + p] = live ? __double2loint(best[i]) : kNoIdx;
+            const float key = live ? __uint_as_float((unsigned)__double2hiint(best[i])) : kInf;
+            lk[lb + p] = key;
+            li[lb + p] = key < kInf ? __double2loint(best[i]) : kNoIdx;
         }
     }
     // (the lists of further point ranges stay empty)

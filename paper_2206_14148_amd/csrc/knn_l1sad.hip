@@ -649,6 +649,8 @@ hipError_t launch_l1_sad(const float* Q, int64_t ldq, const float* X, int64_t ld
                                                                          c.tsh);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
+    // (a kernel per pair of words: 1e4 queries, 1e6 points, k = 10, d = 100 22.9 ms with 26 words, d = 112 24.1
+    // with 28)
     switch (words) {
         case 2: return launch_sad_words<2>(c);
         case 4: return launch_sad_words<4>(c);

@@ -69,3 +69,19 @@ def test_empty_and_invalid_shapes():
     with pytest.raises(K.KnnError) as ei:
         K.kmv_plan(2 ** 31, 5, 3, 10 ** 9)
     assert ei.value.status == K.KNN_ERR_UNSUPPORTED
+
+
+@pytest.mark.parametrize("f64", [False, True])
+@pytest.mark.parametrize("n,m", [(0, 5), (1, 1), (300, 10 ** 6), (20_001, 20_001), (10 ** 6, 300), (10 ** 6, 10 ** 6)])
+def test_workspace_with_room_for_the_series(f64, n, m):
+    # never less than the plan's, never above the limit, more only for d = 1 with enough entries
+    fn = K.load().kmv_workspace_bytes_f64 if f64 else K.load().kmv_workspace_bytes
+    for d in (1, 2):
+        for limit in (0, 10 ** 6, 2 * 10 ** 6, 10 ** 8, W.GB):
+            plan = K.kmv_plan(n, m, d, limit, "f64" if f64 else "f32").workspace_bytes
+            full = fn(n, m, d, 1.0, limit)
+            assert plan <= full <= max(plan, limit)
+            if d > 1 or n * m < 10 ** 7:
+                assert full == plan
+    assert (fn(10 ** 6, 10 ** 6, 1, 1.0, W.GB) > 0) and fn(10 ** 6, 10 ** 6, 1, 1e-200, W.GB) == 0
+    assert fn(10, 10, 1, 1.0, -1) == 0
