@@ -278,7 +278,7 @@ __global__ __launch_bounds__(256) void knn_grid_kernel(const float* __restrict__
     const SeedGrid<D> g = seed_grid<D>(hdr, 1 << L);
     float q[D];
     load_point<D>(Q, ldq, r, q);
-    // (a query that is not finite has no finite key: its list stays empty, as on every other path)
+    // (a query that is not finite has no finite key: its list stays empty, as on the other paths)
     bool live = active;
 #pragma unroll
     for (int t = 0; t < D; ++t) live &= fabsf(q[t]) < kInf;
