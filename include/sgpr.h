@@ -53,6 +53,13 @@ knn_status sgpr_plan(int64_t m, int64_t n, int32_t d, uint64_t mem_limit_bytes,
                      sgpr_plan_t *out /* HOST */);
 
 /*
+ * HOST.  The workspace a call is best given: with it the entries of K_uf are made as pieces for the
+ * 16-bit matrix cores, and the plan's chunks do not apply.  At least plan.workspace_bytes and at most the
+ * limit; 0 where sgpr_plan fails.
+ */
+uint64_t sgpr_workspace_bytes(int64_t m, int64_t n, int32_t d, uint64_t mem_limit_bytes);
+
+/*
  * sgpr_accumulate - A = K_uf K_fu and b = K_uf y (section 5.3).
  *   U [m, d], ldu     DEVICE in, fp32 inducing points
  *   X [n, d], ldx     DEVICE in, fp32 data points
@@ -63,10 +70,11 @@ knn_status sgpr_plan(int64_t m, int64_t n, int32_t d, uint64_t mem_limit_bytes,
  *   b [m]             DEVICE out, fp64; fully overwritten
  *   hip_stream        hipStream_t (NULL: default stream); the call only enqueues work and
  *                     allocates nothing.
- * Arithmetic: K_uf entries in fp32 (difference-form distance, hardware exp2); products and
- * their sums over one chunk in fp32 on the matrix cores (entries as three exact bf16 pieces); sums over chunks in fp64.  Every
- * entry is summed in a fixed order; the result depends on the limit only through the chunk
- * length (last bits).
+ * Arithmetic: K_uf entries in fp32 (difference-form distance, hardware exp2); products in fp32 on the
+ * matrix cores, of entries as three exact bf16 pieces or, where no entry can be below 2^-16 of the
+ * variance, as two fp16 pieces (23 bits); their sums over one chunk in fp32 (in the workspace of
+ * sgpr_workspace_bytes over 384 columns, and with the rounding errors kept beyond), over chunks in fp64.
+ * Every entry is summed in a fixed order; the result depends on the limit only in its last bits.
  */
 knn_status sgpr_accumulate(const float *U, int64_t ldu, const float *X, int64_t ldx,
                            const float *y, int64_t m, int64_t n, int32_t d, double variance,

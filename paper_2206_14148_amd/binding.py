@@ -39,7 +39,7 @@ EXPORTED_SYMBOLS = (
     "knn_profile_read", "knn_plan_metric", "knn_search_metric",
     "kmv_plan", "kmv_apply", "kmv_plan_f64", "kmv_apply_f64",
     "kmv_workspace_bytes", "kmv_workspace_bytes_f64",
-    "knn_plan_host_x", "knn_search_host_x", "sgpr_plan", "sgpr_accumulate",
+    "knn_plan_host_x", "knn_search_host_x", "sgpr_plan", "sgpr_workspace_bytes", "sgpr_accumulate",
     "knn_search_static", "knn_measure_mfma_peak",
 )
 KMV_PATH_LOWD = 0
@@ -230,6 +230,8 @@ def load():
     lib.knn_search_host_x.restype = ctypes.c_int
     lib.sgpr_plan.argtypes = [i64, i64, i32, u64, ctypes.POINTER(SgprPlanStruct)]
     lib.sgpr_plan.restype = ctypes.c_int
+    lib.sgpr_workspace_bytes.argtypes = [i64, i64, i32, u64]
+    lib.sgpr_workspace_bytes.restype = u64
     lib.sgpr_accumulate.argtypes = [vp, i64, vp, i64, vp, i64, i64, i32, ctypes.c_double,
                                     ctypes.c_double, u64, vp, u64, vp, i64, vp, vp]
     lib.sgpr_accumulate.restype = ctypes.c_int
@@ -547,13 +549,18 @@ def sgpr_plan(m: int, n: int, d: int, mem_limit_bytes: int) -> SgprPlan:
                     ps.workspace_bytes, ps.min_limit_bytes)
 
 
+def sgpr_workspace_bytes(m: int, n: int, d: int, mem_limit_bytes: int) -> int:
+    """The workspace a call is best given; 0 where sgpr_plan fails."""
+    return int(load().sgpr_workspace_bytes(m, n, d, mem_limit_bytes))
+
+
 def sgpr_accumulate(U, X, y, variance: float, lengthscale: float, mem_limit_bytes: int,
                     workspace=None, out=None):
     """sgpr_accumulate(U[m,d], X[n,d], y[n], ...) -> (A fp64[m,m], b fp64[m]).
 
     A = K_uf K_fu and b = K_uf y for the squared-exponential kernel between the inducing points
     U and the data X.  fp32 device tensors in, fp64 device tensors out; the workspace (uint8,
-    plan.workspace_bytes) is allocated here unless given.  Work is enqueued on torch's current
+    sgpr_workspace_bytes; plan.workspace_bytes is the least) is allocated here unless given.  Work is enqueued on torch's current
     stream; no synchronisation is done.
     """
     import torch
@@ -566,10 +573,10 @@ def sgpr_accumulate(U, X, y, variance: float, lengthscale: float, mem_limit_byte
         raise KnnError(KNN_ERR_INVALID_ARG, "shapes or strides do not fit")
     m, d = U.shape
     n = X.shape[0]
-    plan = sgpr_plan(m, n, d, mem_limit_bytes)
+    sgpr_plan(m, n, d, mem_limit_bytes)  # raises where the limit is too small
     if workspace is None:
-        workspace = torch.empty(max(int(plan.workspace_bytes), 256), dtype=torch.uint8,
-                                device=U.device)
+        workspace = torch.empty(max(sgpr_workspace_bytes(m, n, d, mem_limit_bytes), 256),
+                                dtype=torch.uint8, device=U.device)
     if out is None:
         A = torch.empty((m, m), dtype=torch.float64, device=U.device)
         b = torch.empty((m,), dtype=torch.float64, device=U.device)

@@ -10,7 +10,7 @@ CSRC = os.path.join(PKG_DIR, "csrc")
 OBJ_DIR = os.path.join(PKG_DIR, "_build")
 LIB_PATH = os.path.join(PKG_DIR, "libknn_mi355x.so")
 SOURCES = ["planner.cpp", "api.hip", "knn_lowd.hip", "knn_grid.hip", "knn_few.hip", "knn_l1sad.hip", "knn_norms.hip", "knn_split.hip", "knn_packed.hip", "knn_wide.hip", "knn_refine.hip", "knn_peak.hip",
-           "kmv_api.hip", "kmv_kernels.hip", "kmv_series.hip", "sgpr_api.hip", "sgpr_kernels.hip"]
+           "kmv_api.hip", "kmv_kernels.hip", "kmv_series.hip", "sgpr_api.hip", "sgpr_kernels.hip", "sgpr_pieces.hip"]
 HEADERS = ["knn_config.h", "knn_device.h", "knn_cells.h", "knn_exact.h", "knn_kernels.h", "kmv_kernels.h", "sgpr_kernels.h",
            os.path.join("..", "..", "include", "sgpr.h"),
            os.path.join("..", "..", "include", "knn.h"),
@@ -19,11 +19,13 @@ HEADERS = ["knn_config.h", "knn_device.h", "knn_cells.h", "knn_exact.h", "knn_ke
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC",
          # packed fp32 VALU forms are kept out of the generated code on purpose
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-         # MFMA results go to ordinary VGPRs so the filter reads them without copies
-         "-mllvm", "-amdgpu-mfma-vgpr-form=1",
          # the chunk loop of the register-resident-query kernel must unroll completely
          "-mllvm", "-pragma-unroll-threshold=100000",
          "-Wno-unused-command-line-argument"]
+# MFMA results go to ordinary VGPRs so that what follows reads them without copies; not where the accumulators
+# alone need more than those
+VGPR_FORM = ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]
+ACCUMULATOR_FORM_SOURCES = ["sgpr_pieces.hip"]
 
 
 def is_stale() -> bool:
@@ -40,7 +42,8 @@ def build(verbose: bool = False) -> str:
 
     def compile_one(name: str) -> str:
         obj = os.path.join(OBJ_DIR, os.path.splitext(name)[0] + ".o")
-        cmd = [hipcc] + FLAGS + ["-c", os.path.join(CSRC, name), "-o", obj]
+        form = [] if name in ACCUMULATOR_FORM_SOURCES else VGPR_FORM
+        cmd = [hipcc] + FLAGS + form + ["-c", os.path.join(CSRC, name), "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)
         subprocess.run(cmd, check=True)

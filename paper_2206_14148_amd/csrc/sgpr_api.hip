@@ -64,6 +64,55 @@ extern "C" knn_status sgpr_plan(int64_t m, int64_t n, int32_t d, uint64_t mem_li
     return KNN_OK;
 }
 
+namespace {
+
+// The layout for K_uf as pieces in `bytes` of workspace (cols = 0: no room for it).
+sgpr::PiecesPlan pieces_in(int64_t m, int64_t n, int32_t d, uint64_t bytes) {
+    return sgpr::plan_pieces(m, n, d, bytes / knn::kAlign * knn::kAlign);
+}
+
+knn_status accumulate_pieces(const sgpr::PiecesPlan& p, const float* U, int64_t ldu, const float* X, int64_t ldx,
+                             const float* y, int64_t m, int64_t n, int32_t d, float c2, float significand, double scale,
+                             unsigned char* ws, double* A, int64_t lda, double* b, hipStream_t stream) {
+    hipError_t e = sgpr::launch_radii(p, ws, U, ldu, X, ldx, m, n, d, stream);
+    if (e != hipSuccess) return hip_fail(e, "sgpr radii kernels");
+    for (int64_t c0 = 0; c0 < n; c0 += p.cols) {
+        const int64_t cols = n - c0 < p.cols ? n - c0 : p.cols;
+        const int first = c0 == 0;
+        hipEvent_t t0 = knn::profile_mark(stream);
+        e = sgpr::launch_entries(p, ws, U, ldu, X, ldx, y, m, c0, cols, d, c2, significand, first, stream);
+        if (e != hipSuccess) {
+            knn::profile_drop(t0);
+            return hip_fail(e, "sgpr entries kernel");
+        }
+        knn::profile_close(t0, stream, 0);
+        hipEvent_t t1 = knn::profile_mark(stream);
+        e = sgpr::launch_products(p, ws, m, cols, c2, scale * scale, A, lda, first, stream);
+        if (e != hipSuccess) {
+            knn::profile_drop(t1);
+            return hip_fail(e, "sgpr product kernels");
+        }
+        knn::profile_close(t1, stream, 1);
+    }
+    hipEvent_t t2 = knn::profile_mark(stream);
+    e = sgpr::launch_finish(p, ws, m, scale, A, lda, b, stream);
+    if (e != hipSuccess) {
+        knn::profile_drop(t2);
+        return hip_fail(e, "sgpr last kernels");
+    }
+    knn::profile_close(t2, stream, 2);
+    return KNN_OK;
+}
+
+}  // namespace
+
+extern "C" uint64_t sgpr_workspace_bytes(int64_t m, int64_t n, int32_t d, uint64_t mem_limit_bytes) {
+    sgpr_plan_t plan;
+    if (sgpr_plan(m, n, d, mem_limit_bytes, &plan) != KNN_OK) return 0;
+    const sgpr::PiecesPlan p = pieces_in(m, n, d, mem_limit_bytes);
+    return p.cols > 0 && (uint64_t)p.bytes > plan.workspace_bytes ? (uint64_t)p.bytes : plan.workspace_bytes;
+}
+
 extern "C" knn_status sgpr_accumulate(const float* U, int64_t ldu, const float* X, int64_t ldx,
                                       const float* y, int64_t m, int64_t n, int32_t d,
                                       double variance, double lengthscale,
@@ -90,6 +139,13 @@ extern "C" knn_status sgpr_accumulate(const float* U, int64_t ldu, const float* 
     int exponent = 0;
     const float significand = (float)std::frexp(variance, &exponent);
     const double scale = std::ldexp(1.0, exponent);
+
+    // the layout that sgpr_workspace_bytes stands for, or what of it the given workspace holds; never above the limit
+    const sgpr::PiecesPlan pieces =
+        pieces_in(m, n, d, workspace_bytes < mem_limit_bytes ? workspace_bytes : mem_limit_bytes);
+    if (pieces.cols > 0)
+        return accumulate_pieces(pieces, U, ldu, X, ldx, y, m, n, d, c2, significand, scale,
+                                 static_cast<unsigned char*>(workspace), A, lda, b, stream);
 
     const int G = plan.col_groups;
     const uint64_t chunk_bytes = knn::align_up((uint64_t)m * (uint64_t)plan.chunk_ld * 4);
