@@ -38,7 +38,7 @@ constexpr int64_t kLeastCols = 2048;            // of a chunk that is not the wh
 // Where things lie in the workspace, from its start; cols = 0: not enough room.
 struct PiecesPlan {
     int64_t cols;  // per chunk
-    int64_t head_at, centre_at, sums_at, buffers_at, fragments_at, bytes;
+    int64_t head_at, centre_at, turned_at, sums_at, buffers_at, fragments_at, bytes;
     int row_blocks, tiles, shares, part_limit, slots, units;  // who makes what: see Shares
 };
 PiecesPlan plan_pieces(int64_t m, int64_t n, int d, uint64_t bytes);

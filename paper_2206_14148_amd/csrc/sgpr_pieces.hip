@@ -38,6 +38,7 @@ constexpr int kTile = 128;           // rows and columns of a workgroup's tile o
 constexpr int kXcds = 8, kPerXcd = 2 * knn::kNumCU / kXcds, kGroups = kXcds * kPerXcd;  // two workgroups per compute unit
 constexpr int kStageCols = 16;       // columns of K_uf per pipeline stage
 constexpr int kKufCols = 256;        // columns of K_uf per workgroup of the kernel that makes them
+constexpr int kMostResident = 16;     // coordinates that a lane keeps in registers
 constexpr float kHalfScale = 32768.f;
 
 // ---------------------------------------------------------------------------------------
@@ -99,10 +100,19 @@ __device__ __forceinline__ bool two_pieces(const unsigned* __restrict__ head, fl
 // ---------------------------------------------------------------------------------------
 // Entries of K_uf and the sums with y.  A wave makes 64 rows x 8 columns at a time: the row's coordinates
 // stay in the lane's registers, the columns' coordinates are the same for the whole wave and come through
-// scalar loads.  Difference form, coordinates in ascending order.  D = 0: any number of coordinates.
+// scalar loads.  Difference form, coordinates in ascending order.  D = 0: any number of coordinates, 16 at a
+// time from a transposed copy of U, whose loads are coalesced (64 coordinates, 1000 points, 1e5
+// rows: 12.4 ms with U read as it lies, 1.1 this way).
 // fragments: [16 columns][piece][32 rows] of 1024 bytes, a lane's 16 bytes being 8 columns of a row.
 // sums[column block][row]: fp64 sums of the fp32 products with y.
 // ---------------------------------------------------------------------------------------
+__global__ __launch_bounds__(256) void sgpr_transpose_kernel(const float* __restrict__ U, int64_t ldu, int m, int d,
+                                                             int rows, float* __restrict__ turned) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i >= rows) return;
+    for (int t = blockIdx.y; t < d; t += gridDim.y) turned[(int64_t)t * rows + i] = U[(int64_t)min(i, m - 1) * ldu + t];
+}
+
 template <int D>
 __global__ __launch_bounds__(256) void sgpr_entries_kernel(const float* __restrict__ U, int64_t ldu,
                                                            const float* __restrict__ X, int64_t ldx,
@@ -110,6 +120,7 @@ __global__ __launch_bounds__(256) void sgpr_entries_kernel(const float* __restri
                                                            int d_any, float c2, float variance,
                                                            const unsigned* __restrict__ head,
                                                            unsigned char* __restrict__ fragments, int row_blocks,
+                                                           const float* __restrict__ turned,
                                                            double* __restrict__ sums, int first) {
     __shared__ double part[4][64];
     const int d = D ? D : d_any;
@@ -129,25 +140,41 @@ __global__ __launch_bounds__(256) void sgpr_entries_kernel(const float* __restri
     for (int g = 0; g < kKufCols / 4 / 8; ++g) {
         const int c = blockIdx.x * kKufCols + wave * (kKufCols / 4) + g * 8;
         if (c >= last) break;
-        float k[8];
+        float k[8], sq[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) sq[j] = 0.f;
+        const auto add = [&](const float* __restrict__ at, auto count, int t0) {
+            constexpr int N = decltype(count)::value;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const float* __restrict__ xp = X + (c0 + min(c + j, cols - 1)) * ldx + t0;
+#pragma unroll
+                for (int t = 0; t < N; ++t) {
+                    const float df = xp[t] - at[t];
+                    sq[j] = fmaf(df, df, sq[j]);
+                }
+            }
+        };
+        if constexpr (D > 0) {
+            add(u, std::integral_constant<int, D>{}, 0);
+        } else {
+            const int rows = row_blocks * 32;
+            int t0 = 0;
+            for (; t0 + 16 <= d; t0 += 16) {
+                float part_u[16];
+#pragma unroll
+                for (int t = 0; t < 16; ++t) part_u[t] = turned[(int64_t)(t0 + t) * rows + row];
+                add(part_u, std::integral_constant<int, 16>{}, t0);
+            }
+            for (; t0 < d; ++t0) {
+                const float one = turned[(int64_t)t0 * rows + row];
+                add(&one, std::integral_constant<int, 1>{}, t0);
+            }
+        }
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             const int cj = min(c + j, cols - 1);
-            const float* __restrict__ xp = X + (c0 + cj) * ldx;
-            float sq = 0.f;
-            if constexpr (D > 0) {
-#pragma unroll
-                for (int t = 0; t < D; ++t) {
-                    const float df = xp[t] - u[t];
-                    sq = fmaf(df, df, sq);
-                }
-            } else {
-                for (int t = 0; t < d; ++t) {
-                    const float df = xp[t] - up[t];
-                    sq = fmaf(df, df, sq);
-                }
-            }
-            k[j] = (c + j < cols ? factor : 0.f) * __builtin_amdgcn_exp2f(sq * -c2);
+            k[j] = (c + j < cols ? factor : 0.f) * __builtin_amdgcn_exp2f(sq[j] * -c2);
             if (row >= m || c + j >= cols) k[j] = 0.f;  // (a NaN of the row or point that was read instead)
             sum += c + j < cols ? (double)(k[j] * y[c0 + cj]) : 0.0;
         }
@@ -565,6 +592,7 @@ PiecesPlan plan_pieces(int64_t m, int64_t n, int d, uint64_t bytes) {
         };
         p.head_at = take(64);
         p.centre_at = take(4 * (int64_t)d);
+        p.turned_at = take(d > kMostResident ? 4 * rows * d : 0);
         p.sums_at = take(up(cols, kKufCols) / kKufCols * m * 8);
         p.buffers_at = take((int64_t)kXcds * p.units * p.slots * kTile * kTile * 8);
         p.fragments_at = take(cols * rows * 6);
@@ -597,12 +625,12 @@ namespace {
 template <int D>
 void entries(dim3 grid, hipStream_t stream, const float* U, int64_t ldu, const float* X, int64_t ldx, const float* y,
              int m, int64_t c0, int cols, int d, float c2, float variance, const unsigned* head,
-             unsigned char* fragments, int row_blocks, double* sums, int first) {
+             unsigned char* fragments, int row_blocks, const float* turned, double* sums, int first) {
     if constexpr (D > 0) {
-        if (d != D) return entries<D - 1>(grid, stream, U, ldu, X, ldx, y, m, c0, cols, d, c2, variance, head, fragments, row_blocks, sums, first);
+        if (d != D) return entries<D - 1>(grid, stream, U, ldu, X, ldx, y, m, c0, cols, d, c2, variance, head, fragments, row_blocks, turned, sums, first);
     }
     sgpr_entries_kernel<D><<<grid, dim3(256), 0, stream>>>(U, ldu, X, ldx, y, m, c0, cols, d, c2, variance, head,
-                                                           fragments, row_blocks, sums, first);
+                                                           fragments, row_blocks, turned, sums, first);
 }
 
 }  // namespace
@@ -615,6 +643,11 @@ hipError_t launch_radii(const PiecesPlan& p, unsigned char* ws, const float* U, 
     const int64_t blocks = (n + m + 255) / 256;
     sgpr_radius_kernel<<<dim3((unsigned)(blocks < 2048 ? blocks : 2048)), dim3(256), 0, stream>>>(U, ldu, (int)m, X, ldx, n,
                                                                                                d, centre, head);
+    if (d > kMostResident) {
+        const int rows = p.row_blocks * 32;
+        sgpr_transpose_kernel<<<dim3((unsigned)((rows + 255) / 256), (unsigned)(d < 1024 ? d : 1024)), dim3(256), 0, stream>>>(
+            U, ldu, (int)m, d, rows, reinterpret_cast<float*>(ws + p.turned_at));
+    }
     return hipGetLastError();
 }
 
@@ -624,12 +657,12 @@ hipError_t launch_entries(const PiecesPlan& p, unsigned char* ws, const float* U
     const dim3 grid((unsigned)((cols + kKufCols - 1) / kKufCols), (unsigned)(p.row_blocks / 2));
     unsigned* head = reinterpret_cast<unsigned*>(ws + p.head_at);
     double* sums = reinterpret_cast<double*>(ws + p.sums_at);
-    if (d <= 16) {
-        entries<16>(grid, stream, U, ldu, X, ldx, y, (int)m, c0, (int)cols, d, c2, variance, head, ws + p.fragments_at,
-                    p.row_blocks, sums, first);
+    if (d <= kMostResident) {
+        entries<kMostResident>(grid, stream, U, ldu, X, ldx, y, (int)m, c0, (int)cols, d, c2, variance, head, ws + p.fragments_at,
+                    p.row_blocks, reinterpret_cast<const float*>(ws + p.turned_at), sums, first);
     } else {
         entries<0>(grid, stream, U, ldu, X, ldx, y, (int)m, c0, (int)cols, d, c2, variance, head, ws + p.fragments_at,
-                   p.row_blocks, sums, first);
+                   p.row_blocks, reinterpret_cast<const float*>(ws + p.turned_at), sums, first);
     }
     return hipGetLastError();
 }
