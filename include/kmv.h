@@ -76,7 +76,8 @@ int kmv_plan(int64_t n, int64_t m, int32_t d, int64_t mem_limit_bytes, kmv_plan_
  *   variance   sigma^2 >= 0, lengthscale l > 0 (both finite)
  *   workspace  DEVICE  256-byte aligned, workspace_bytes >= plan.workspace_bytes
  *              (may be NULL when the plan needs 0 bytes); contents are scratch
- *              (kmv_workspace_bytes(...) of it lets d = 1 run through the series below)
+ *              (kmv_workspace_bytes(...) of it lets d = 1 run through the series below, and 9 <= d <= 64
+ *              with two fp16 pieces of a coordinate in place of three bf16 ones)
  *   y          DEVICE  fp64 [n], fully overwritten (all zeros when m == 0)
  *   stream     hipStream_t (NULL: the default stream).  The call only
  *              enqueues work; it allocates nothing and does not synchronise.
@@ -102,6 +103,8 @@ int kmv_apply(const float* X, int64_t ldx, const float* Z, int64_t ldz, const fl
  * work, which goes with boxes (n + m), below that of the n m entries.  In fp64 rows that
  * are far from all sources with a weight that counts are left out, 256 at a time.  What is not
  * done there the general kernel does, as with the plan's workspace.
+ * For 9 <= d <= 64 (fp32): plan.workspace_bytes plus 64 bytes for every point and 16 coordinates begun, and
+ * 20 to 32 bytes per point, for the points as fp16 pieces with their norms and weights.
  * Never above mem_limit_bytes; 0 if there is no plan.
  */
 int64_t kmv_workspace_bytes(int64_t n, int64_t m, int32_t d, double lengthscale, int64_t mem_limit_bytes);

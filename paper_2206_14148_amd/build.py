@@ -10,7 +10,7 @@ CSRC = os.path.join(PKG_DIR, "csrc")
 OBJ_DIR = os.path.join(PKG_DIR, "_build")
 LIB_PATH = os.path.join(PKG_DIR, "libknn_mi355x.so")
 SOURCES = ["planner.cpp", "api.hip", "knn_lowd.hip", "knn_grid.hip", "knn_few.hip", "knn_l1sad.hip", "knn_norms.hip", "knn_split.hip", "knn_packed.hip", "knn_wide.hip", "knn_refine.hip", "knn_peak.hip",
-           "kmv_api.hip", "kmv_kernels.hip", "kmv_series.hip", "sgpr_api.hip", "sgpr_kernels.hip", "sgpr_pieces.hip"]
+           "kmv_api.hip", "kmv_kernels.hip", "kmv_series.hip", "kmv_pieces.hip", "sgpr_api.hip", "sgpr_kernels.hip", "sgpr_pieces.hip"]
 HEADERS = ["knn_config.h", "knn_device.h", "knn_cells.h", "knn_exact.h", "knn_kernels.h", "kmv_kernels.h", "sgpr_kernels.h",
            os.path.join("..", "..", "include", "sgpr.h"),
            os.path.join("..", "..", "include", "knn.h"),

@@ -94,16 +94,20 @@ int plan_impl(int64_t n, int64_t m, int32_t d, int64_t mem_limit_bytes, bool f64
 }
 
 // Workspace the call is best given: the plan's, and behind it what the series for d = 1 works
-// in, where the limit has room for both.
+// in, or the points as pieces for the matrix cores, where the limit has room for both.
 int64_t roomy_bytes(const kmv_plan_t& plan, int64_t mem_limit_bytes, double lengthscale, bool f64) {
-    if (!kmv::series_applies(plan.n, plan.m, plan.n_splits, plan.d, lengthscale, f64)) return plan.workspace_bytes;
-    const int64_t want = plan.workspace_bytes + align_up(kmv::series_bytes(plan.n));
+    int64_t more = 0;
+    if (kmv::series_applies(plan.n, plan.m, plan.n_splits, plan.d, lengthscale, f64))
+        more = kmv::series_bytes(plan.n);
+    else if (plan.path == KMV_PATH_MFMA)
+        more = kmv::pieces_bytes(plan.n, plan.m, plan.d);
+    const int64_t want = plan.workspace_bytes + align_up(more);
     return want <= mem_limit_bytes ? want : plan.workspace_bytes;
 }
 
-// whether this call's workspace holds the series' part as well
-bool use_series(const kmv_plan_t& plan, int64_t mem_limit_bytes, double lengthscale, bool f64,
-                const void* workspace, int64_t workspace_bytes) {
+// whether this call's workspace holds that part as well
+bool has_room(const kmv_plan_t& plan, int64_t mem_limit_bytes, double lengthscale, bool f64,
+              const void* workspace, int64_t workspace_bytes) {
     const int64_t roomy = roomy_bytes(plan, mem_limit_bytes, lengthscale, f64);
     return roomy > plan.workspace_bytes && workspace_bytes >= roomy && workspace &&
            reinterpret_cast<uintptr_t>(workspace) % knn::kAlign == 0;
@@ -170,7 +174,7 @@ extern "C" int kmv_apply(const float* X, int64_t ldx, const float* Z, int64_t ld
     if (plan.path == KMV_PATH_LOWD) {
         hipEvent_t t1 = knn::profile_mark(stream);
         e = hipSuccess;
-        if (use_series(plan, mem_limit_bytes, lengthscale, false, workspace, workspace_bytes)) {
+        if (has_room(plan, mem_limit_bytes, lengthscale, false, workspace, workspace_bytes)) {
             e = kmv::launch_series(X, ldx, Z, ldz, v, n, m, S, lengthscale, variance, ws + plan.workspace_bytes, y,
                                    stream, &done);
         }
@@ -179,6 +183,15 @@ extern "C" int kmv_apply(const float* X, int64_t ldx, const float* Z, int64_t ld
         if (e != hipSuccess) {
             knn::profile_drop(t1);
             return hip_fail(e, "kmv low-d kernel");
+        }
+        knn::profile_close(t1, stream, 1);
+    } else if (has_room(plan, mem_limit_bytes, lengthscale, false, workspace, workspace_bytes)) {
+        hipEvent_t t1 = knn::profile_mark(stream);
+        e = kmv::launch_pieces(X, ldx, Z, ldz, v, ws + plan.workspace_bytes, n, m, d, lengthscale, variance, S, target,
+                               stream);
+        if (e != hipSuccess) {
+            knn::profile_drop(t1);
+            return hip_fail(e, "kmv pieces kernels");
         }
         knn::profile_close(t1, stream, 1);
     } else {
@@ -230,7 +243,7 @@ extern "C" int kmv_apply_f64(const double* X, int64_t ldx, const double* Z, int6
     const int* done = nullptr;
     hipEvent_t t1 = knn::profile_mark(stream);
     e = hipSuccess;
-    if (use_series(plan, mem_limit_bytes, lengthscale, true, workspace, workspace_bytes)) {
+    if (has_room(plan, mem_limit_bytes, lengthscale, true, workspace, workspace_bytes)) {
         unsigned char* extra = static_cast<unsigned char*>(workspace) + plan.workspace_bytes;
         e = kmv::launch_series(X, ldx, Z, ldz, v, n, m, S, lengthscale, variance, extra, y, stream, &done);
     }

@@ -30,6 +30,12 @@ hipError_t launch_mfma(const float* X, int64_t ldx, const float* Z, int64_t ldz,
                        const float* zn, int64_t n, int64_t m, int d, float c2, double variance, int S,
                        double* out, hipStream_t stream);
 
+// The same for d <= kMfmaKC * kMfmaResidentChunks with the points as fp16 pieces in pieces_bytes(n, m, d)
+// bytes at ws (kmv_pieces.hip); 0 bytes: does not apply.
+int64_t pieces_bytes(int64_t n, int64_t m, int d);
+hipError_t launch_pieces(const float* X, int64_t ldx, const float* Z, int64_t ldz, const float* v, void* ws, int64_t n,
+                         int64_t m, int d, double lengthscale, double variance, int S, double* out, hipStream_t stream);
+
 // fp64 inputs and arithmetic (the precision of paper section 5.1), any d: d <= kLowdMaxD keeps
 // the row in registers, larger d re-reads it in chunks.  negc = -1 / (2 lengthscale^2).
 hipError_t launch_f64(const double* X, int64_t ldx, const double* Z, int64_t ldz, const double* v,

@@ -1,0 +1,81 @@
+"""GPU tests of y = K v over fp16 pieces (9 to 64 coordinates): edges of chunks, tiles and ranges, rows and points out
+of the pieces' range, against the fp64 oracle.
+
+Tolerance (eps = 2^-24, c = 1 / (2 l^2)): a coordinate in exponent units is moved by at most 2 eps of itself or 2 eps,
+so an exponent by 2 eps (|a| + |b|) (|a - b| + sqrt(d)); the sums of products and the norms round a few times at
+(|a| + |b|)^2 / 2: together within (d + 8) eps (sqrt(c) (|x| + |z|) + 1)^2.  Sums of at most 64 entries in fp32 and
+exp2's last bit add 4e-6 of the magnitudes."""
+import numpy as np
+import pytest
+
+import workloads as W
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+EPS = 2.0 ** -24
+
+
+def run(X, Z, v, lengthscale, limit=W.GB, workspace=None):
+    import paper_2206_14148_amd as K
+
+    y = K.kmv_apply(*(torch.from_numpy(a).cuda() for a in (X, Z, v)), 1.5, lengthscale, limit, workspace=workspace)
+    return y.cpu().numpy()
+
+
+def bound(X, Z, v, lengthscale):
+    X, Z, d = X.astype(np.float64), Z.astype(np.float64), X.shape[1]
+    c = 0.5 / lengthscale ** 2
+    tol = np.empty(len(X))
+    for i, x in enumerate(X):
+        mag = 1.5 * np.exp(-c * ((x - Z) ** 2).sum(1)) * np.abs(v)
+        e = (np.sqrt(c) * (np.sqrt((x * x).sum()) + np.sqrt((Z * Z).sum(1))) + 1) ** 2
+        tol[i] = (mag * (4e-6 + (d + 8) * EPS * e)).sum()
+    return tol + 1e-37 * np.abs(v).sum()
+
+
+# chunks of 16 coordinates; tiles of 128 points (64 above 32 coordinates); 128 rows of a workgroup; several ranges
+CASES = [(1, 1, 9), (127, 127, 16), (128, 128, 17), (129, 129, 32), (130, 63, 33), (31, 64, 48), (33, 65, 49),
+         (200, 193, 64), (40, 9_000, 20), (1_000, 2_500, 10)]
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "n%d_m%d_d%d" % c)
+@pytest.mark.parametrize("wide", [0.4, 1.5])
+def test_matches_oracle(oracle, case, wide):
+    import paper_2206_14148_amd as K
+
+    n, m, d = case
+    print("case", case, wide, flush=True)
+    lengthscale = wide * d ** 0.5
+    X, Z, v = W.random_kmv_case(n + d, n, m, d)
+    want = K.load().kmv_workspace_bytes(n, m, d, lengthscale, W.GB)
+    assert want > K.kmv_plan(n, m, d, W.GB).workspace_bytes
+    buf = torch.full((want + 4096,), 0xA5, dtype=torch.uint8, device="cuda")
+    y = run(X, Z, v, lengthscale, workspace=buf[:want])
+    assert (buf[want:] == 0xA5).all()
+    err, tol = np.abs(y - oracle.kmv(X, Z, v, 1.5, lengthscale)), bound(X, Z, v, lengthscale)
+    print("  worst", float((err / tol).max()), flush=True)
+    assert (err <= tol).all()
+    assert np.array_equal(y, run(X, Z, v, lengthscale))
+
+
+def test_a_point_with_itself_is_one():
+    # the norms are those of the pieces, so the exponent of a point with itself has no rounding of the inputs in it
+    X, _, _ = W.random_kmv_case(5, 100, 1, 30)
+    X *= 50.0  # nothing else is near: 50 lengthscales apart and more
+    y = run(X, X, np.ones(100, np.float32), 1.0)
+    assert np.allclose(y, 1.5, rtol=30 * EPS * (X.astype(np.float64) ** 2).sum(1).max())
+
+
+@pytest.mark.parametrize("d", [12, 40])
+def test_rows_and_points_out_of_range(oracle, d):
+    # coordinates beyond 32768 exponent units: their tile and their rows take the products of three pieces
+    X, Z, v = W.random_kmv_case(77, 300, 500, d)
+    X[40, 3], Z[200, d - 1], Z[201] = 1e6, -3e5, 4e4
+    y = run(X, Z, v, 3.0)
+    ref = oracle.kmv(X, Z, v, 1.5, 3.0)
+    keep = np.arange(300) != 40
+    near = np.ones(500, bool)
+    near[[200, 201]] = False  # entries of exactly 0 for every row, out of the bound's formula
+    assert y[40] == 0.0 and ref[40] == 0.0
+    assert (np.abs(y - ref)[keep] <= bound(X[keep], Z[near], v[near], 3.0)).all()
