@@ -185,17 +185,22 @@ knn_status run_search(const knn_plan_t& plan, const float* Q, int64_t ldq, const
     float* xn = reinterpret_cast<float*>(ws);
     // path 5: [squared norms][header: their maximum] | [split queries][query norms][shared
     // thresholds] | lists; L1 path: [transposed queries] | lists
-    const bool wide_plan = plan.path == KNN_PATH_MFMA_WIDE;
+    // A wide plan's room holds what path 5 needs.  Its kernel is the better one for lists of one or two and rows that are
+    // not long, where there are a few tiles of queries: too few workgroups for path 7's tiles of 512, and little to gain
+    // from its thresholds.  (m = 1000, us here / on path 7, by n, d, k: 150001, 259, 1 970 / 1371; 150001, 399, 1 1391 /
+    // 1657; 150001, 301, 2 1240 / 1536; 450000, 301, 1 1786 / 2038; but 150001, 515, 1 1720 / 1600, 450000, 301, 3 2256 /
+    // 2124; m = 1500 70001, 301, 1 1052 / 1184, 300000, 301, 1 2065 / 1792; m = 257 200000, 301, 3 1579 / 1278.)
+    const bool short_lists = d + 64 * (k - 1) <= 420 && m > 256 &&
+                             ((m <= 1024 && n <= 500000) || (m <= 1536 && n <= 160000)) && !block_d64;
+    const bool wide_plan = plan.path == KNN_PATH_MFMA_WIDE && !short_lists;
     const bool packed_plan = plan.path == KNN_PATH_MFMA_PACKED || wide_plan;
     const uint64_t n64 = ((uint64_t)n + kPkStep - 1) / kPkStep * kPkStep;
     unsigned char* hdr = ws + align_up((packed_plan ? n64 : (uint64_t)n) * 4);
     unsigned char* xp = hdr + kAlign;  // paths 6, 7: the points rounded to bf16
-    // paths 6, 7 need 16-byte aligned rows; other calls run their plans on path 5's kernel
-    const bool packed = packed_plan && packed_rows_aligned(Q, ldq, X, ldx, d);
     unsigned char* qs = ws + plan.norms_bytes;
     // (path 7: the B operands in operand order, rows rounded up to 64, chunks to an even count)
     const uint64_t qs_bytes =
-        wide_plan ? ((uint64_t)plan.chunk_rows + 63) / 64 * 64 * 32 * (uint64_t)pk_padded_chunks(d)
+        plan.path == KNN_PATH_MFMA_WIDE ? ((uint64_t)plan.chunk_rows + 63) / 64 * 64 * 32 * (uint64_t)pk_padded_chunks(d)
                   : (uint64_t)plan.chunk_rows * 32 * (((uint64_t)d + kSpKC - 1) / kSpKC);
     float* qn = reinterpret_cast<float*>(qs + align_up(qs_bytes));
     unsigned char* tsh = reinterpret_cast<unsigned char*>(qn) + align_up((uint64_t)plan.chunk_rows * 4);
@@ -225,8 +230,8 @@ knn_status run_search(const knn_plan_t& plan, const float* Q, int64_t ldq, const
     // Small searches of the squared-Euclidean metric skip the filter and all that prepares it: the
     // whole workspace holds lists.  (One chunk only; a search over blocks of host points keeps its
     // plan's path, whose thresholds carry over from block to block.)
-    if ((plan.path == KNN_PATH_MFMA_SPLIT || packed_plan) && metric == KNN_METRIC_L2SQ && plan.q_chunks == 1 &&
-        !block_d64 && few_applies(m, n, d, k, few_aligned(X, ldx, d))) {
+    if ((plan.path == KNN_PATH_MFMA_SPLIT || plan.path == KNN_PATH_MFMA_WIDE || packed_plan) && metric == KNN_METRIC_L2SQ && plan.q_chunks == 1 &&
+        !block_d64 && few_applies(m, n, d, k, whole_rows(d))) {
         const int S1 = few_splits(m, n, k, plan.workspace_bytes);
         if (S1 > 0) {
             float* lk = reinterpret_cast<float*>(ws);
@@ -248,24 +253,25 @@ knn_status run_search(const knn_plan_t& plan, const float* Q, int64_t ldq, const
             return KNN_OK;
         }
     }
-    if (plan.path == KNN_PATH_MFMA_SPLIT || packed_plan) {
+    const bool split_plan = plan.path == KNN_PATH_MFMA_SPLIT || (plan.path == KNN_PATH_MFMA_WIDE && !wide_plan);
+    if (split_plan || packed_plan) {
         hipEvent_t t0 = mark(stream);
         // (the header's second word: the points' largest bf16 rounding residual, which the
         // filters' allowance is built from; not used by the cosine metric)
         e = launch_header_init(hdr, stream);
         // (one slab: the copy is made here, once for all query chunks, and the pass that makes it
         // takes the norms and the largest rounding residual along)
-        const bool copy_now = packed && plan.slab_points >= (int64_t)n64;
+        const bool copy_now = packed_plan && plan.slab_points >= (int64_t)n64;
         if (e == hipSuccess && copy_now && !cosine)
             e = launch_pack_operands(X, ldx, n, d, 0, (int64_t)n64, xp, stream, 1.f, xn, hdr);
         if (e == hipSuccess && (!copy_now || cosine))
             e = launch_row_norms(X, ldx, n, d, cosine, xn, stream, cosine ? nullptr : hdr + 4);
         if (e == hipSuccess) e = launch_max_norm(xn, n, hdr, stream);
-        if (e == hipSuccess && packed && cosine) {  // (plans of the cosine metric hold the whole copy)
+        if (e == hipSuccess && packed_plan && cosine) {  // (plans of the cosine metric hold the whole copy)
             e = launch_pack_operands(X, ldx, n, d, 0, (int64_t)n64, xp, stream, 1.f, nullptr, hdr, xn);
             if (e == hipSuccess) e = launch_fill_words(sum0, (int64_t)n64, 0u, stream);
         }
-        if (e == hipSuccess && packed) e = launch_pad_norms(sum0, n, stream);
+        if (e == hipSuccess && packed_plan) e = launch_pad_norms(sum0, n, stream);
         if (e != hipSuccess) {
             drop_bracket(t0);
             return hip_fail(e, "row norms launch");
@@ -304,8 +310,8 @@ knn_status run_search(const knn_plan_t& plan, const float* Q, int64_t ldq, const
         else if (plan.path == KNN_PATH_LOWD_BF16)
             e = launch_lowd_bf16(Qc, ldq, X, ldx, ws, rows, n, d, k, S, false, plan.seed_cells,
                                  chunk_rows, own, c == 0, idx + row0 * k, lk, li, stream);
-        else if (plan.path == KNN_PATH_MFMA_SPLIT || packed_plan) {
-            if (wide_plan && packed) {
+        else if (split_plan || packed_plan) {
+            if (wide_plan) {
                 // the queries' B operands bf16(-2 q) in operand order; thresholds start from +inf
                 e = launch_pack_operands(Qc, ldq, rows, d, 0, (rows + kPkStep - 1) / kPkStep * kPkStep, qs,
                                          stream, -2.f);
@@ -314,13 +320,13 @@ knn_status run_search(const knn_plan_t& plan, const float* Q, int64_t ldq, const
                 e = launch_split_queries(Qc, ldq, rows, d, qs, tsh, !keep_thresholds, stream);
             }
             if (e == hipSuccess) e = launch_row_norms(Qc, ldq, rows, d, false, qn, stream);
-            if (e == hipSuccess && !packed)
+            if (e == hipSuccess && !packed_plan)
                 e = launch_split(Qc, ldq, X, ldx, qs, qn, tsh, xn, hdr, cosine, rows, n, d, k, S, lk,
                                  li, stream);
             // path 6: the thresholds start from the filter keys of a sample of the first slab
             // (preparation in the event brackets), then the packed kernel searches the points slab
             // after slab, S ranges each; the lists of slab b + 1 continue those of slab b
-            if (e == hipSuccess && packed) {
+            if (e == hipSuccess && packed_plan) {
                 const int64_t slab = plan.slab_points;
                 const bool one = slab >= (int64_t)n64;
                 for (int64_t j0 = 0; j0 < (int64_t)n64 && e == hipSuccess; j0 += slab) {

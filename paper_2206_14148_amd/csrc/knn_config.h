@@ -182,6 +182,9 @@ constexpr int kPbPrivateBytesPerLane = 64;
 constexpr uint64_t kPbPrivateBytes = (uint64_t)kPbPrivateBytesPerLane * kWave * 16 * kNumCU;
 
 constexpr uint64_t kAlign = 256;
+// rows that are whole groups of four coordinates, loaded 16 bytes at a time as they lie (any multiple of 4 bytes);
+// the last group of others needs shifting (load4_ragged)
+constexpr inline bool whole_rows(int d) { return d % 4 == 0; }
 constexpr inline uint64_t align_up(uint64_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
 }  // namespace knn

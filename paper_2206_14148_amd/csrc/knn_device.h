@@ -344,21 +344,42 @@ __device__ __forceinline__ void init_lists32(float* __restrict__ lk, int* __rest
     }
 }
 
+// Four floats from an address that is a multiple of 4 bytes: one global_load_dwordx4 all the same.
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ f32x4 load4(const float* __restrict__ p) { return *reinterpret_cast<const f32x4_any*>(p); }
+
+// Columns col .. col + 3 of a row of d, col < d: one load, which for the row's last group begins at
+// column d - 4 and is shifted into place (what then lies past d is another of the row's values).  Rows of
+// fewer than four (the cosine metric has them) are loaded one by one: nothing outside the row is read.
+__device__ __forceinline__ f32x4 load4_ragged(const float* __restrict__ row, int col, int d) {
+    f32x4 w;
+    if (d < 4) {  // (the same for the whole launch)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) w[e] = row[col + e < d ? col + e : 0];
+        return w;
+    }
+    const int at = min(col, d - 4), over = col - at;
+    const f32x4 v = load4(row + at);
+    w[0] = over == 0 ? v[0] : over == 1 ? v[1] : over == 2 ? v[2] : v[3];
+    w[1] = over == 0 ? v[1] : over == 1 ? v[2] : v[3];
+    w[2] = over == 0 ? v[2] : v[3];
+    w[3] = v[3];
+    return w;
+}
+
 // Four consecutive columns of one row, loaded from an address clamped into the matrix so that
 // the loads of a pipeline step issue back to back without control flow; mask_row4 zeroes
-// what was out of range once the data is used.  ALIGNED: rows are 16-byte aligned and d is
-// a multiple of 4, so one vector load covers the four columns.
+// what was out of range once the data is used.  ALIGNED: d is a multiple of 4, so that a row is whole groups of
+// four (rows of these may begin at any multiple of 4 bytes).
 template <bool ALIGNED>
 __device__ __forceinline__ f32x4 load_row4(const float* __restrict__ base, int64_t ld,
                                            int64_t row, int64_t nrows, int col, int d) {
     const float* p = base + (row < nrows ? row : nrows - 1) * ld;
     f32x4 v;
-    if (ALIGNED) {
-        v = *reinterpret_cast<const f32x4*>(p + (col < d ? col : 0));
-    } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = p[col + e < d ? col + e : 0];
-    }
+    if (ALIGNED)
+        v = load4(p + (col < d ? col : 0));
+    else
+        v = load4_ragged(p, col < d ? col : 0, d);
     return v;
 }
 

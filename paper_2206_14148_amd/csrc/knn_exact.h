@@ -44,7 +44,7 @@ constexpr unsigned kInfWord = 0xff800000u;  // key_word(+inf)
 // are issued before the first is used (U = 2), or of U groups: more in flight shorten the wait
 // for a long row and cost registers, which the caller may or may not have to spare.  U does not
 // change the order of the additions.
-// QMODE (aligned rows) 1: the query's groups are read where they are used instead of together with
+// ALIGNED: d % 4 == 0.  QMODE 1: the query's groups are read where they are used instead of together with
 // the candidate's - for a query row that the caller has staged in LDS (qp), so that all U groups
 // in flight are the candidate's.  2: the same with the staging done here: the wave copies the
 // row qp to qst (LDS, d floats) behind the requests for the candidate's first U groups, so that
@@ -52,9 +52,19 @@ constexpr unsigned kInfWord = 0xff800000u;  // key_word(+inf)
 template <bool ALIGNED, bool DOT, int U, int QMODE = 0>
 __device__ __forceinline__ float exact_partial(const float* __restrict__ qp, const float* __restrict__ xp,
                                                int d, int part, float* qst = nullptr, int lane = 0) {
-    static_assert(QMODE == 0 || ALIGNED, "late query reads: aligned rows only");
     float sum = 0.f;
-    const int ng = (d + 3) >> 2;  // groups of four coordinates (the last may be ragged)
+    const int ng = d >> 2;  // whole groups of four coordinates
+    // what is left of a row that is not whole groups: the last group of the lane whose turn it is
+    float xt[3], qt[3];
+    const int tail = ALIGNED ? 0 : d & 3;
+    if constexpr (!ALIGNED) {
+#pragma unroll
+        for (int e = 0; e < 3; ++e) {
+            const int t = e < tail ? 4 * ng + e : 0;
+            xt[e] = xp[t];
+            qt[e] = qp[t];
+        }
+    }
     const float* const qsrc = QMODE == 2 ? qst : qp;
     int trip = 0;
     for (int g0 = part; g0 < ng; g0 += 2 * U, ++trip) {
@@ -63,24 +73,15 @@ __device__ __forceinline__ float exact_partial(const float* __restrict__ qp, con
         for (int u = 0; u < U; ++u) {
             const int g = g0 + 2 * u;
             const int gc = g < ng ? g : part;  // a valid group; its value is not used
-            if (ALIGNED) {
-                xv[u] = *reinterpret_cast<const f32x4*>(xp + 4 * gc);
-                if (!QMODE) qv[u] = *reinterpret_cast<const f32x4*>(qp + 4 * gc);
-            } else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int t = 4 * gc + e < d ? 4 * gc + e : 0;
-                    xv[u][e] = xp[t];
-                    qv[u][e] = qp[t];
-                }
-            }
+            xv[u] = load4(xp + 4 * gc);
+            if (!QMODE) qv[u] = load4(qp + 4 * gc);
         }
         if (QMODE == 2 && trip == 0) {
             for (int g = lane; g < ng; g += kWave)
-                *reinterpret_cast<f32x4*>(qst + 4 * g) = *reinterpret_cast<const f32x4*>(qp + 4 * g);
+                *reinterpret_cast<f32x4*>(qst + 4 * g) = load4(qp + 4 * g);
             wave_sync();
         }
-        // A coordinate past the row's end (or a group past it) leaves the sum as it is: its x is
+        // A group past the row's end leaves the sum as it is: its x is
         // replaced by q (a zero difference), for the dot product by 0, and sum + 0 = sum exactly -
         // a select on the operand, so that the chain stays one straight run of fused multiply-adds
         // (a select on the sum was compiled into a branch per coordinate).
@@ -91,12 +92,19 @@ __device__ __forceinline__ float exact_partial(const float* __restrict__ qp, con
             const f32x4 qg = QMODE ? *reinterpret_cast<const f32x4*>(qsrc + 4 * (ok_g ? g : part)) : qv[QMODE ? 0 : u];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const bool ok = ALIGNED ? ok_g : (ok_g && 4 * g + e < d);  // (aligned rows: d % 4 == 0)
                 const float qe = qg[e];
-                const float xe = ok ? xv[u][e] : (DOT ? 0.f : qe);
+                const float xe = ok_g ? xv[u][e] : (DOT ? 0.f : qe);
                 const float df = qe - xe;
                 sum = DOT ? fmaf(qe, xe, sum) : fmaf(df, df, sum);
             }
+        }
+    }
+    if constexpr (!ALIGNED) {
+#pragma unroll
+        for (int e = 0; e < 3; ++e) {
+            const float df = qt[e] - xt[e];
+            const float more = DOT ? fmaf(qt[e], xt[e], sum) : fmaf(df, df, sum);
+            sum = e < tail && part == (ng & 1) ? more : sum;
         }
     }
     return sum;

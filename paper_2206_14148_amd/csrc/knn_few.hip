@@ -35,7 +35,7 @@ constexpr size_t few_lds_per_wave(int nq, int k) {
     return (size_t)(64 * kStride + nq * 2 * kWave + 2 * kWave + 2 * k) * 4;
 }
 
-// (a row of X starts at any multiple of 4 bytes; ALIGNED: of 16)
+// (ALIGNED: d % 4 == 0; rows begin at any multiple of 4 bytes)
 template <int NQ, bool ALIGNED>
 __global__ __launch_bounds__(64 * kFewWaves) void knn_few_kernel(
     const float* __restrict__ Q, int64_t ldq, const float* __restrict__ X, int64_t ldx, int rows, int n, int d,
@@ -92,12 +92,10 @@ __global__ __launch_bounds__(64 * kFewWaves) void knn_few_kernel(
         for (int u = 0; u < 8; ++u) {
             const float* row = X + (int64_t)min(j + 8 * u + srow, j1 - 1) * ldx;
             const int t = t0 + scol;
-            if (ALIGNED) {
-                g[u] = *reinterpret_cast<const f32x4*>(row + (t < d ? t : 0));
-            } else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) g[u][e] = row[t + e < d ? t + e : 0];
-            }
+            if (ALIGNED)
+                g[u] = load4(row + (t < d ? t : 0));
+            else
+                g[u] = load4(row + min(t, d - 4));  // (the last group begins earlier: see the stores)
         }
     };
     if (j0 < j1) fetch(j0, 0);
@@ -108,10 +106,20 @@ __global__ __launch_bounds__(64 * kFewWaves) void knn_few_kernel(
         for (int i = 0; i < NQ; ++i) s0[i] = s1[i] = 0.f;
         for (int t0 = 0; t0 < d; t0 += kPiece) {
             wave_sync();
+            // (where a lane's group begins earlier than its place, it stores what its neighbour does, the same values)
+            const int to = ALIGNED ? scol : min(t0 + scol, d - 4) - t0;
+            if (ALIGNED || t0 + 4 <= d) {
 #pragma unroll
-            for (int u = 0; u < 8; ++u)
+                for (int u = 0; u < 8; ++u)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) xt[(8 * u + srow) * kStride + scol + e] = g[u][e];
+                    for (int e = 0; e < 4; ++e) xt[(8 * u + srow) * kStride + to + e] = g[u][e];
+            } else {  // fewer than four coordinates in the row's last piece: some of the group belong to the piece before
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (to + e >= 0) xt[(8 * u + srow) * kStride + to + e] = g[u][e];
+            }
             wave_sync();
             if (t0 + kPiece < d) fetch(j, t0 + kPiece);
             else if (j + 64 < j1) fetch(j + 64, 0);
@@ -203,11 +211,6 @@ bool few_applies(int64_t m, int64_t n, int d, int k, bool aligned) {
     return work <= 5e9 && here_us <= filter_us;
 }
 
-// rows of X whose groups of four coordinates can be loaded at once
-bool few_aligned(const float* X, int64_t ldx, int d) {
-    return reinterpret_cast<uintptr_t>(X) % 16 == 0 && ldx % 4 == 0 && d % 4 == 0;
-}
-
 int few_splits(int64_t rows, int64_t n, int k, uint64_t workspace_bytes) {
     // as many waves as the chip holds at once (two a SIMD, by the 173 registers of the variant for rows
     // that are not aligned; three of the other) where the points last (ranges of at least 256), lists that
@@ -229,7 +232,7 @@ hipError_t launch_few(const float* Q, int64_t ldq, const float* X, int64_t ldx, 
     const size_t lds = kFewWaves * few_lds_per_wave(NQ, k);
     int64_t split_len = (n + S - 1) / S;
     split_len = (split_len + 63) / 64 * 64;
-    const bool aligned = few_aligned(X, ldx, d);
+    const bool aligned = whole_rows(d);
     const dim3 grid((unsigned)(((rows + NQ - 1) / NQ * S + kFewWaves - 1) / kFewWaves));
     hipError_t e = aligned ? raise_lds_limit(knn_few_kernel<NQ, true>, lds)
                            : raise_lds_limit(knn_few_kernel<NQ, false>, lds);

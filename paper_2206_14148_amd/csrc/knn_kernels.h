@@ -97,10 +97,9 @@ hipError_t launch_split(const float* Q, int64_t ldq, const float* X, int64_t ldx
                         hipStream_t stream);
 
 // d > 8, small searches (knn_few.hip): every pair's exact key, no filter.
-//   few_applies  whether the sizes are small enough (aligned: few_aligned of the points)
+//   few_applies  whether the sizes are small enough (aligned: whole_rows of the points)
 //   few_splits   point ranges for a chunk of rows: their lists are at most what fits into half of
 //                workspace_bytes for each of keys and indices (0: not even one range's do)
-bool few_aligned(const float* X, int64_t ldx, int d);
 bool few_applies(int64_t m, int64_t n, int d, int k, bool aligned);
 int few_splits(int64_t rows, int64_t n, int k, uint64_t workspace_bytes);
 hipError_t launch_few(const float* Q, int64_t ldq, const float* X, int64_t ldx, int64_t rows, int64_t n, int d,
@@ -110,10 +109,10 @@ hipError_t launch_few(const float* Q, int64_t ldq, const float* X, int64_t ldx, 
 //   launch_pack_operands  xp = `points` points from j_first on (j_first and points multiples of
 //                         64; rows past n are zero), pk_padded_chunks(d) x 32 bytes per point;
 //                         scale = -2 packs queries as B operands (n = their number); xn != null
-//                         (16-byte aligned rows only): the same pass also writes the rows'
+//                         : the same pass also writes the rows'
 //                         squared norms to xn[j_first ..] and raises hdr word 1 to the largest
 //                         squared norm of a rounding residual, as launch_row_norms would;
-//                         row_scale != null (aligned rows, hdr != null): row j is multiplied by
+//                         row_scale != null (hdr != null): row j is multiplied by
 //                         row_scale[j] before it is rounded (the cosine metric's x / |x|), and
 //                         the residuals (and norms, if xn != null) are those of the scaled rows
 //   launch_pad_norms      xn[n .. next multiple of 64) = +inf
@@ -125,7 +124,6 @@ hipError_t launch_few(const float* Q, int64_t ldq, const float* X, int64_t ldx, 
 //                         other points), the others start empty; tsr = [rows][S] words, set to
 //                         0xff800000 (+inf) beforehand: the key at position ceil(k / S) - 1 of
 //                         every range's list, through which the ranges bound each other.
-//                         Rows must be 16-byte aligned (packed_rows_aligned).
 //                         Cosine metric: rn = 1 / |x| of all points, xp packed with row_scale =
 //                         rn, xn = zeros (+inf from n to the next multiple of 64), and
 //                         launch_seed_thresholds with cosine = true.
@@ -140,7 +138,6 @@ hipError_t launch_pad_norms(float* xn, int64_t n, hipStream_t stream);
 hipError_t launch_seed_thresholds(const float* Q, int64_t ldq, const void* xp, const float* xn, const void* qs,
                                   const float* qn, void* tsh, const void* hdr, int64_t rows, int64_t n, int d,
                                   int k, int64_t seed_points, hipStream_t stream, bool cosine = false);
-bool packed_rows_aligned(const float* Q, int64_t ldq, const float* X, int64_t ldx, int d);
 hipError_t launch_packed(const float* Q, int64_t ldq, const float* X, int64_t ldx, const void* xp,
                          int64_t slab_first, const void* qs, const float* qn, void* tsh, void* tsr,
                          const float* xn, const void* hdr, int64_t rows, int64_t n, int d, int k, int S,
@@ -151,7 +148,7 @@ hipError_t launch_packed(const float* Q, int64_t ldq, const float* X, int64_t ld
 //                 xp (launch_pack_operands) that holds slab_points points from slab_first on, for
 //                 queries whose B operands qp were packed by launch_pack_operands with scale -2
 //                 (rows rounded up to 64), qn / tsh / tsr / xn / hdr / init_from as for
-//                 launch_packed.  S <= 64.  Rows must be 16-byte aligned (packed_rows_aligned).
+//                 launch_packed.  S <= 64.
 hipError_t launch_wide(const float* Q, int64_t ldq, const float* X, int64_t ldx, const void* xp,
                        int64_t slab_first, int64_t slab_points, const void* qp, const float* qn, void* tsh,
                        void* tsr, const float* xn, const void* hdr, int64_t rows, int64_t n, int d, int k,

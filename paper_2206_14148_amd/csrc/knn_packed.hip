@@ -5,7 +5,7 @@
 // filters; what passes is evaluated exactly (knn_exact.h) and merged into the query's list, so
 // the distance tile never leaves the registers (section 4.3) and the results do not depend on
 // the filter.  What differs from knn_split_kernel is where the operands live:
-//   - the points are rounded to bf16 ONCE, by knn_pack_operands_kernel, into a copy in the
+//   - the points are rounded to bf16 ONCE, by knn_pack_block_kernel, into a copy in the
 //     workspace that is laid out in the order of the MFMA's A operand, so that a wave fetches an
 //     operand with one coalesced 1 KB load straight into registers: no conversion, no LDS
 //     staging, no workgroup barrier in the search loop;
@@ -43,31 +43,8 @@ namespace {
 
 // The points of a slab rounded to bf16 in A-operand order: step (64 points) -> row block (32) ->
 // chunk of 16 coordinates -> lane: lane (i32, h) holds coordinates 16 c + 8 h .. + 7 of point
-// 32 pb + i32, zero past d and past n.  This kernel serves rows that are not 16-byte aligned (one
-// thread per (point, chunk, half), element-wise loads); aligned rows take knn_pack_block_kernel.  `scale` (a power of two:
-// it commutes with the rounding) is 1 for points and -2 for queries packed as B operands.
-__global__ __launch_bounds__(256) void knn_pack_operands_kernel(const float* __restrict__ X,
-                                                                int64_t ldx, int n, int d, int nch,
-                                                                int j_first, int64_t pieces,
-                                                                float scale, uint4* __restrict__ Xp) {
-    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= pieces) return;
-    const int per_row = nch * 2;
-    const int rel = (int)(idx / per_row);
-    const int piece = (int)(idx - (int64_t)rel * per_row);
-    const int c = piece >> 1, h = piece & 1;
-    const int j = j_first + rel;
-    const bool ok = j < n;
-    const int col = c * 16 + h * 8;
-    const f32x4 v0 = mask_row4(load_row4<false>(X, ldx, j, n, col, d), ok, col, d, scale);
-    const f32x4 v1 = mask_row4(load_row4<false>(X, ldx, j, n, col + 4, d), ok, col + 4, d, scale);
-    const uint4 w = {round_pair(v0[0], v0[1]), round_pair(v0[2], v0[3]), round_pair(v1[0], v1[1]),
-                     round_pair(v1[2], v1[3])};
-    const int st = rel >> 6, pb = (rel >> 5) & 1, i32 = rel & 31;
-    Xp[((size_t)(st * 2 + pb) * nch + c) * 64 + h * 32 + i32] = w;
-}
-
-// The same copy for rows that are 16-byte aligned, a row block of 32 points per workgroup, through
+// 32 pb + i32, zero past d and past n.  `scale` (a power of two: it commutes with the rounding) is 1 for
+// points and -2 for queries packed as B operands.  A row block of 32 points per workgroup, through
 // LDS: each of the four waves reads eight rows (32 bytes a lane, whole rows at a stretch) and
 // writes their rounded pieces into the block's operands in LDS; the block's operands - nch KB in a
 // row in the copy - then go out as whole 1 KB stores.  Rows longer than kPbSeg chunks take several
@@ -77,7 +54,7 @@ __global__ __launch_bounds__(256) void knn_pack_operands_kernel(const float* __r
 // (With row_scale both are those of the scaled rows; xn may be null.)
 constexpr int kPbSeg = 32;               // chunks per pass
 constexpr int kPbOperandStride = 64 + 2; // uint4 per operand in LDS (a half of 32 rows + one: no bank conflicts)
-template <bool NORMS>
+template <bool NORMS, bool WHOLE>
 __global__ __launch_bounds__(256) void knn_pack_block_kernel(const float* __restrict__ X, int64_t ldx, int n,
                                                              int d, int nch, int j_first, int nblocks,
                                                              float scale, const float* __restrict__ row_scale,
@@ -99,8 +76,8 @@ __global__ __launch_bounds__(256) void knn_pack_block_kernel(const float* __rest
 #pragma unroll
                 for (int rr = 0; rr < 8; ++rr) {
                     const int j = j_first + blk * 32 + wave * 8 + rr;
-                    v0[rr] = load_row4<true>(X, ldx, j, n, col, d);
-                    v1[rr] = load_row4<true>(X, ldx, j, n, col + 4, d);
+                    v0[rr] = load_row4<WHOLE>(X, ldx, j, n, col, d);
+                    v1[rr] = load_row4<WHOLE>(X, ldx, j, n, col + 4, d);
                 }
 #pragma unroll
                 for (int rr = 0; rr < 8; ++rr) {
@@ -494,8 +471,8 @@ __global__ __launch_bounds__(64 * WV, WV / 4) void knn_packed_kernel(const PkArg
         float rq2 = 0.f;
         {
             const float* qrow = a.Q + (int64_t)rc * a.ldq;
-            for (int t = 0; t < a.d; t += 4) {  // rows are 16-byte aligned, d % 4 == 0
-                const f32x4 v = *reinterpret_cast<const f32x4*>(qrow + t);
+            for (int t = 0; t < a.d; t += 4) {
+                const f32x4 v = mask_row4(load_row4<ALIGNED>(qrow, 0, 0, 1, t, a.d), true, t, a.d, 1.f);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const float r = bf16_residual(-2.f * v[e]);
@@ -698,7 +675,7 @@ __global__ __launch_bounds__(64 * WV, WV / 4) void knn_packed_kernel(const PkArg
                 }
                 ++item;
                 if (n_c > 0) {
-                    t_bits = flush_query_exact<ALIGNED, 8, true>(a.Q + (int64_t)r * a.ldq, a.X, a.ldx, a.d,
+                    t_bits = flush_query_exact<ALIGNED, ALIGNED ? 8 : 6, true>(a.Q + (int64_t)r * a.ldq, a.X, a.ldx, a.d,
                                                            a.j_valid, cbuf, jb, n_c, a.lk + lb, a.li + lb,
                                                            k, my_scratch, a.tsh + r, COS ? a.rn : nullptr, lane, pos_s,
                                                            &key_s);
@@ -771,25 +748,15 @@ hipError_t launch_pack_operands(const float* X, int64_t ldx, int64_t n, int d, i
                                 int64_t points, void* xp, hipStream_t stream, float scale, float* xn,
                                 void* hdr, const float* row_scale) {
     const int nch = pk_padded_chunks(d);
-    const bool aligned = (reinterpret_cast<uintptr_t>(X) % 16 == 0) && (ldx % 4 == 0) && (d % 4 == 0);
-    if ((xn || row_scale) && (!aligned || !hdr)) return hipErrorInvalidValue;
-    if (aligned) {
-        const int nblocks = (int)(points / 32);
-        const dim3 grid((unsigned)(nblocks < 16384 ? nblocks : 16384));
-        if (xn || row_scale)
-            knn_pack_block_kernel<true><<<grid, dim3(256), 0, stream>>>(X, ldx, (int)n, d, nch, (int)j_first, nblocks,
-                                                                         scale, row_scale, static_cast<uint4*>(xp),
-                                                                         xn, static_cast<unsigned*>(hdr));
-        else
-            knn_pack_block_kernel<false><<<grid, dim3(256), 0, stream>>>(X, ldx, (int)n, d, nch, (int)j_first,
-                                                                          nblocks, scale, nullptr,
-                                                                          static_cast<uint4*>(xp), nullptr, nullptr);
-        return hipGetLastError();
-    }
-    const int64_t pieces = points * nch * 2;
-    const dim3 grid((unsigned)((pieces + 255) / 256));
-    knn_pack_operands_kernel<<<grid, dim3(256), 0, stream>>>(X, ldx, (int)n, d, nch, (int)j_first,
-                                                                    pieces, scale, static_cast<uint4*>(xp));
+    if ((xn || row_scale) && !hdr) return hipErrorInvalidValue;
+    const int nblocks = (int)(points / 32);
+    const dim3 grid((unsigned)(nblocks < 16384 ? nblocks : 16384));
+    auto go = [&](auto kernel) {
+        kernel<<<grid, dim3(256), 0, stream>>>(X, ldx, (int)n, d, nch, (int)j_first, nblocks, scale, row_scale,
+                                               static_cast<uint4*>(xp), xn, static_cast<unsigned*>(hdr));
+    };
+    if (xn || row_scale) whole_rows(d) ? go(knn_pack_block_kernel<true, true>) : go(knn_pack_block_kernel<true, false>);
+    else whole_rows(d) ? go(knn_pack_block_kernel<false, true>) : go(knn_pack_block_kernel<false, false>);
     return hipGetLastError();
 }
 
@@ -833,11 +800,6 @@ hipError_t launch_pad_norms(float* xn, int64_t n, hipStream_t stream) {
     return hipGetLastError();
 }
 
-bool packed_rows_aligned(const float* Q, int64_t ldq, const float* X, int64_t ldx, int d) {
-    return (reinterpret_cast<uintptr_t>(Q) % 16 == 0) && (reinterpret_cast<uintptr_t>(X) % 16 == 0) &&
-           (ldq % 4 == 0) && (ldx % 4 == 0) && (d % 4 == 0);
-}
-
 hipError_t launch_packed(const float* Q, int64_t ldq, const float* X, int64_t ldx, const void* xp,
                          int64_t slab_first, const void* qs, const float* qn, void* tsh, void* tsr,
                          const float* xn, const void* hdr, int64_t rows, int64_t n, int d, int k, int S,
@@ -845,8 +807,7 @@ hipError_t launch_packed(const float* Q, int64_t ldq, const float* X, int64_t ld
                          hipStream_t stream, const float* rn) {
     const int nch_real = (d + kSpKC - 1) / kSpKC;
     const int nch = pk_padded_chunks(d);
-    if (d > kPkMaxD || sets < 1 || sets > pk_max_sets(nch, k) || !packed_rows_aligned(Q, ldq, X, ldx, d) ||
-        j_first % kPkStep != 0 || slab_first % kPkStep != 0 || j_first < slab_first || j_end <= j_first ||
+    if (d > kPkMaxD || sets < 1 || sets > pk_max_sets(nch, k) || j_first % kPkStep != 0 || slab_first % kPkStep != 0 || j_first < slab_first || j_end <= j_first ||
         j_end > n)
         return hipErrorInvalidValue;
     PkArgs a;
@@ -885,16 +846,19 @@ hipError_t launch_packed(const float* Q, int64_t ldq, const float* X, int64_t ld
     const size_t lds = (size_t)pk_lds_bytes(nch, k, sets);
     const dim3 grid((unsigned)(a.tiles * S));
     const int waves = pk_waves(nch, k);
+    hipError_t e2 = hipSuccess;
+    auto go = [&](auto kernel, int threads) {
+        e2 = raise_lds_limit(kernel, lds);
+        if (e2 == hipSuccess) kernel<<<grid, dim3(threads), lds, stream>>>(a);
+    };
 #define KNN_PACKED_LAUNCH_W(N, W)                                                              \
     do {                                                                                       \
-        if (rn) {                                                                              \
-            hipError_t e2 = raise_lds_limit(knn_packed_kernel<N, true, W, true>, lds);         \
-            if (e2 != hipSuccess) return e2;                                                   \
-            knn_packed_kernel<N, true, W, true><<<grid, dim3(64 * W), lds, stream>>>(a);       \
+        if (whole_rows(d)) {                                                                   \
+            if (rn) go(knn_packed_kernel<N, true, W, true>, 64 * W);                           \
+            else go(knn_packed_kernel<N, true, W, false>, 64 * W);                             \
         } else {                                                                               \
-            hipError_t e2 = raise_lds_limit(knn_packed_kernel<N, true, W, false>, lds);        \
-            if (e2 != hipSuccess) return e2;                                                   \
-            knn_packed_kernel<N, true, W, false><<<grid, dim3(64 * W), lds, stream>>>(a);      \
+            if (rn) go(knn_packed_kernel<N, false, W, true>, 64 * W);                          \
+            else go(knn_packed_kernel<N, false, W, false>, 64 * W);                            \
         }                                                                                      \
     } while (0)
 #define KNN_PACKED_LAUNCH(N)                                                                   \
@@ -919,7 +883,7 @@ hipError_t launch_packed(const float* Q, int64_t ldq, const float* X, int64_t ld
     }
 #undef KNN_PACKED_LAUNCH_W
 #undef KNN_PACKED_LAUNCH
-    return hipGetLastError();
+    return e2 == hipSuccess ? hipGetLastError() : e2;
 }
 
 }  // namespace knn

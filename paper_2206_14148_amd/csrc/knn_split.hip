@@ -169,7 +169,7 @@ __global__ __launch_bounds__(512, 2) void knn_split_kernel(
         float rq2 = 0.f;
         if (ALIGNED) {
             for (int g = h; 4 * g < d; g += 2) {
-                const f32x4 v = *reinterpret_cast<const f32x4*>(qrp + 4 * g);
+                const f32x4 v = load4(qrp + 4 * g);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const float r = bf16_residual(-2.f * v[e]);
@@ -592,7 +592,7 @@ hipError_t launch_split_queries(const float* Q, int64_t ldq, int64_t rows, int d
         knn_fill_words_kernel<<<dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, stream>>>(
             static_cast<unsigned*>(tsh), rows, kInfWord);  // +inf: nothing published yet
     const int64_t items = rows * nch;
-    const bool aligned = (reinterpret_cast<uintptr_t>(Q) % 16 == 0) && (ldq % 4 == 0) && (d % 4 == 0);
+    const bool aligned = whole_rows(d);
     const dim3 grid((unsigned)((items + 255) / 256));
     if (aligned)
         knn_split_queries_kernel<true><<<grid, dim3(256), 0, stream>>>(Q, ldq, (int)rows, d, nch,
@@ -621,9 +621,7 @@ hipError_t launch_split(const float* Q, int64_t ldq, const float* X, int64_t ldx
     const int BQ = 1, BS = 1;
     const int blocks = T * S;
     const dim3 grid((unsigned)((blocks + 7) / 8 * 8));
-    const bool aligned = (reinterpret_cast<uintptr_t>(Q) % 16 == 0) &&
-                         (reinterpret_cast<uintptr_t>(X) % 16 == 0) && (ldq % 4 == 0) &&
-                         (ldx % 4 == 0) && (d % 4 == 0);
+    const bool aligned = whole_rows(d);
 #define KNN_SPLIT_LAUNCH(W, N, A)                                                                 \
     do {                                                                                          \
         const size_t lds = lds_fixed + (size_t)2 * (W) * kSpTileX * 2 * 16;                       \
@@ -638,8 +636,7 @@ hipError_t launch_split(const float* Q, int64_t ldq, const float* X, int64_t ldx
     // in registers (up to d = 256; W * N is the chunk count rounded up to a shape that is
     // instantiated), N = 0: any d, queries streamed.  Wide steps keep more bytes of the point
     // stream in flight, which is what the kernel waits for; the shapes are the fastest measured
-    // among those that fit the register budget (the element-wise loads of unaligned rows need
-    // more registers, so those take narrower steps).
+    // among those that fit the register budget (rows that are not whole groups of four take narrower steps).
     // (No shape with one step per tile: its loop is unrolled over two tiles and then spills two
     // registers to private memory, which the runtime would have to provide beside the workspace.)
     if (aligned) {

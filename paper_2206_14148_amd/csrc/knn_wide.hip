@@ -62,6 +62,7 @@ struct WdArgs {
     int q_stage;          // 1: the LDS has room for one query row per wave (the stops' exact keys read it there)
 };
 
+template <bool WHOLE>  // whole_rows(d)
 __global__ __launch_bounds__(64 * kWdWaves, 1) void knn_wide_kernel(const WdArgs a) {
     constexpr int TQ = kWdTileQ, TX = kWdTileX, C = kWdCand, W = kWdW, NT = kWdSets;
     static_assert(4 * W == kWdWaves, "one A operand per wave and stage");
@@ -144,8 +145,8 @@ __global__ __launch_bounds__(64 * kWdWaves, 1) void knn_wide_kernel(const WdArgs
             // |bf16(-2 q) - (-2 q)|^2 of the lane's query: the two halves of the wave share the sum
             const float* qrp = a.Q + (int64_t)rc * a.ldq;
             float rq2 = 0.f;
-            for (int g = h; 4 * g < a.d; g += 2) {  // rows are 16-byte aligned, d % 4 == 0
-                const f32x4 v = *reinterpret_cast<const f32x4*>(qrp + 4 * g);
+            for (int g = h; 4 * g < a.d; g += 2) {
+                const f32x4 v = mask_row4(load_row4<WHOLE>(qrp, 0, 0, 1, 4 * g, a.d), true, 4 * g, a.d, 1.f);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const float res = bf16_residual(-2.f * v[e]);
@@ -281,18 +282,18 @@ __global__ __launch_bounds__(64 * kWdWaves, 1) void knn_wide_kernel(const WdArgs
             // requests, knn_exact.h) it leaves them all to the candidates - sixteen groups a trip
             // instead of eight, the same sums.
             const float* qrow = a.Q + (int64_t)r * a.ldq;
-            float* const qst = qstage0 + (size_t)wave * a.d;
+            float* const qst = qstage0 + (size_t)wave * (a.d & ~3);
             for (int item = 0; item < (o ? 5 : 1); ++item) {
                 const int* cbuf = item == 0 ? ci + q * C : nullptr;
                 const int jb = tile_base + 32 * (item - 1);
                 const int n_c = item == 0 ? cc : min(32, j1 - jb);
                 if (n_c > 0) {
                     if (a.q_stage)
-                        t_bits = flush_query_exact<true, 16, true, 2>(qrow, a.X, a.ldx, a.d, j0, cbuf, jb, n_c,
+                        t_bits = flush_query_exact<WHOLE, 16, true, 2>(qrow, a.X, a.ldx, a.d, j0, cbuf, jb, n_c,
                                                                       a.lk + lb, a.li + lb, k, my_scratch,
                                                                       a.tsh + r, nullptr, ln, pos_s, &key_s, qst);
                     else
-                        t_bits = flush_query_exact<true, 8, true>(qrow, a.X, a.ldx, a.d, j0, cbuf, jb, n_c,
+                        t_bits = flush_query_exact<WHOLE, 8, true>(qrow, a.X, a.ldx, a.d, j0, cbuf, jb, n_c,
                                                                   a.lk + lb, a.li + lb, k, my_scratch, a.tsh + r,
                                                                   nullptr, ln, pos_s, &key_s);
                     merged = true;
@@ -644,8 +645,7 @@ hipError_t launch_wide(const float* Q, int64_t ldq, const float* X, int64_t ldx,
                        int S, int64_t j_first, int64_t j_end, int init_from, float* lk, int* li,
                        hipStream_t stream) {
     const int nch = pk_padded_chunks(d);
-    if (nch % kWdW != 0 || S < 1 || S > kWave || !packed_rows_aligned(Q, ldq, X, ldx, d) ||
-        j_first % kPkStep != 0 || slab_first % kPkStep != 0 || slab_points % kPkStep != 0 ||
+    if (nch % kWdW != 0 || S < 1 || S > kWave || j_first % kPkStep != 0 || slab_first % kPkStep != 0 || slab_points % kPkStep != 0 ||
         j_first < slab_first || j_end <= j_first || j_end > n || j_end > slab_first + slab_points)
         return hipErrorInvalidValue;
     WdArgs a;
@@ -680,12 +680,16 @@ hipError_t launch_wide(const float* Q, int64_t ldq, const float* X, int64_t ldx,
     a.range_len = (int)per;
     a.init_from = init_from;
     // (room left in the LDS for one query row per wave: the stops stage the row they work on)
-    a.q_stage = wd_lds_bytes(k) + (int64_t)kWdWaves * d * 4 <= kPkLdsBytes ? 1 : 0;
-    const size_t lds = (size_t)wd_lds_bytes(k) + (a.q_stage ? (size_t)kWdWaves * d * 4 : 0);
-    hipError_t e = raise_lds_limit(knn_wide_kernel, lds);
-    if (e != hipSuccess) return e;
-    knn_wide_kernel<<<dim3((unsigned)(a.tiles * S)), dim3(64 * kWdWaves), lds, stream>>>(a);
-    return hipGetLastError();
+    const int64_t row = (int64_t)(d / 4) * 16;
+    a.q_stage = wd_lds_bytes(k) + kWdWaves * row <= kPkLdsBytes ? 1 : 0;
+    const size_t lds = (size_t)(wd_lds_bytes(k) + (a.q_stage ? kWdWaves * row : 0));
+    hipError_t e = hipSuccess;
+    auto go = [&](auto kernel) {
+        e = raise_lds_limit(kernel, lds);
+        if (e == hipSuccess) kernel<<<dim3((unsigned)(a.tiles * S)), dim3(64 * kWdWaves), lds, stream>>>(a);
+    };
+    whole_rows(d) ? go(knn_wide_kernel<true>) : go(knn_wide_kernel<false>);
+    return e == hipSuccess ? hipGetLastError() : e;
 }
 
 }  // namespace knn

@@ -227,8 +227,7 @@ extern "C" knn_status knn_plan_metric(int64_t m, int64_t n, int32_t d, int32_t k
     }
     // 8 < d <= 256 and many points: with room for the points rounded to bf16 in operand order
     // the search runs with the queries resident in LDS (knn_packed.hip).  Its workspace is that
-    // of path 5 plus the packed copy, so a call whose rows turn out not to be 16-byte aligned
-    // still runs under this plan, on path 5's kernel.
+    // of path 5 plus the packed copy.
     // The cosine metric runs there too, on a copy of the rows x / |x|, with one more array of n
     // words (what the sums start from; the first holds 1 / |x|) and the whole copy only, no slabs.
     const bool cosine6 = metric == KNN_METRIC_COSINE;
@@ -318,9 +317,7 @@ extern "C" knn_status knn_plan_metric(int64_t m, int64_t n, int32_t d, int32_t k
     }
     // d > 256 with many points and queries: tiles of 512 queries x 128 points on bf16 copies of
     // both operands (knn_wide.hip).  The workspace is path 5's plus the packed points (all of them,
-    // or one slab at a time as on path 6) with the queries' B operands in operand order, so a
-    // call whose rows turn out not to be 16-byte aligned still runs under this plan on path 5's
-    // kernel.
+    // or one slab at a time as on path 6) with the queries' B operands in operand order.
     if (split && metric == KNN_METRIC_L2SQ && d > kPkMaxD && k <= kWdMaxK && n >= kWdMinPoints &&
         m >= kWdMinQueries) {
         const int nch_p = pk_padded_chunks(d);
