@@ -262,15 +262,11 @@ knn_status run_search(const knn_plan_t& plan, const float* Q, int64_t ldq, const
         // (one slab: the copy is made here, once for all query chunks, and the pass that makes it
         // takes the norms and the largest rounding residual along)
         const bool copy_now = packed_plan && plan.slab_points >= (int64_t)n64;
-        if (e == hipSuccess && copy_now && !cosine)
-            e = launch_pack_operands(X, ldx, n, d, 0, (int64_t)n64, xp, stream, 1.f, xn, hdr);
-        if (e == hipSuccess && (!copy_now || cosine))
-            e = launch_row_norms(X, ldx, n, d, cosine, xn, stream, cosine ? nullptr : hdr + 4);
-        if (e == hipSuccess) e = launch_max_norm(xn, n, hdr, stream);
-        if (e == hipSuccess && packed_plan && cosine) {  // (plans of the cosine metric hold the whole copy)
-            e = launch_pack_operands(X, ldx, n, d, 0, (int64_t)n64, xp, stream, 1.f, nullptr, hdr, xn);
-            if (e == hipSuccess) e = launch_fill_words(sum0, (int64_t)n64, 0u, stream);
-        }
+        if (e == hipSuccess && copy_now)  // (as always on path 6 with the cosine metric)
+            e = launch_pack_operands(X, ldx, n, d, 0, (int64_t)n64, xp, stream, 1.f, xn, hdr, cosine);
+        else if (e == hipSuccess)
+            e = launch_row_norms(X, ldx, n, d, cosine, xn, stream, hdr);
+        if (e == hipSuccess && packed_plan && cosine) e = launch_fill_words(sum0, (int64_t)n64, 0u, stream);
         if (e == hipSuccess && packed_plan) e = launch_pad_norms(sum0, n, stream);
         if (e != hipSuccess) {
             drop_bracket(t0);

@@ -12,10 +12,10 @@ namespace knn {
 
 // xn[j] = sum_t X[j][t]^2 in fp32 (the sum x^2 term of paper section 4.1); inverse = true writes
 // 1 / sqrt(that) instead (0 for a zero row), the row scale of the cosine metric.
-// resid != null (a word zeroed beforehand, launch_header_init): it also gets the bits of
+// hdr != null (two words zeroed beforehand, launch_header_init): they get the bits of the largest xn[j] and of
 // max_j |x_j - bf16(x_j)|^2.
 hipError_t launch_row_norms(const float* X, int64_t ldx, int64_t n, int d, bool inverse, float* xn,
-                            hipStream_t stream, void* resid = nullptr);
+                            hipStream_t stream, void* hdr = nullptr);
 
 // d <= kLowdMaxD: key = fp32 difference-form squared distance.
 hipError_t launch_lowd(const float* Q, int64_t ldq, const float* X, int64_t ldx, int64_t rows,
@@ -80,7 +80,6 @@ hipError_t launch_grid_again(unsigned* hdr, hipStream_t stream);
 // d > kPbMaxD, and the cosine metric at any d: bf16 matrix-core filter on split values, exact
 // fp32 test of what passes it (knn_split.hip).
 //   launch_header_init   hdr words 0 and 1 = 0 (hdr: kAlign bytes)
-//   launch_max_norm      hdr word 0 = max of xn[0..n), after launch_header_init
 //   launch_split_queries qs = the B operands of `rows` queries: ceil(d / 16) * 64 bytes per row;
 //                        tsh = [rows] words, the thresholds the ranges share: set to +inf, or
 //                        (reset_thresholds false) kept from an earlier search of other points
@@ -88,7 +87,6 @@ hipError_t launch_grid_again(unsigned* hdr, hipStream_t stream);
 //   launch_split         the search; qn = squared norms of the chunk's queries (fp32, [rows]);
 //                        cosine: xn holds 1 / |x| and the keys are -2 q.x / |x|
 hipError_t launch_header_init(void* hdr, hipStream_t stream);
-hipError_t launch_max_norm(const float* xn, int64_t n, void* hdr, hipStream_t stream);
 hipError_t launch_split_queries(const float* Q, int64_t ldq, int64_t rows, int d, void* qs,
                                 void* tsh, bool reset_thresholds, hipStream_t stream);
 hipError_t launch_split(const float* Q, int64_t ldq, const float* X, int64_t ldx, const void* qs,
@@ -108,13 +106,12 @@ hipError_t launch_few(const float* Q, int64_t ldq, const float* X, int64_t ldx, 
 // 8 < d <= 256 with the points rounded to bf16 in the workspace (knn_packed.hip).
 //   launch_pack_operands  xp = `points` points from j_first on (j_first and points multiples of
 //                         64; rows past n are zero), pk_padded_chunks(d) x 32 bytes per point;
-//                         scale = -2 packs queries as B operands (n = their number); xn != null
-//                         : the same pass also writes the rows'
-//                         squared norms to xn[j_first ..] and raises hdr word 1 to the largest
-//                         squared norm of a rounding residual, as launch_row_norms would;
-//                         row_scale != null (hdr != null): row j is multiplied by
-//                         row_scale[j] before it is rounded (the cosine metric's x / |x|), and
-//                         the residuals (and norms, if xn != null) are those of the scaled rows
+//                         scale = -2 packs queries as B operands (n = their number); xn and hdr
+//                         != null: the same pass also writes the rows' squared norms to
+//                         xn[j_first ..] and raises hdr words 0 and 1 to the largest of them and
+//                         the largest squared norm of a rounding residual; cosine: the rows are
+//                         x / |x|, xn gets 1 / |x| (what launch_row_norms makes of them) and the
+//                         header its largest value and the residuals of the scaled rows
 //   launch_pad_norms      xn[n .. next multiple of 64) = +inf
 //   launch_packed         the search of points [j_first, j_end) (j_first a multiple of 64) out of
 //                         the copy xp whose first point is slab_first, for queries whose B
@@ -124,12 +121,12 @@ hipError_t launch_few(const float* Q, int64_t ldq, const float* X, int64_t ldx, 
 //                         other points), the others start empty; tsr = [rows][S] words, set to
 //                         0xff800000 (+inf) beforehand: the key at position ceil(k / S) - 1 of
 //                         every range's list, through which the ranges bound each other.
-//                         Cosine metric: rn = 1 / |x| of all points, xp packed with row_scale =
+//                         Cosine metric: rn = 1 / |x| of all points, xp packed with cosine =
 //                         rn, xn = zeros (+inf from n to the next multiple of 64), and
 //                         launch_seed_thresholds with cosine = true.
 hipError_t launch_pack_operands(const float* X, int64_t ldx, int64_t n, int d, int64_t j_first,
                                 int64_t points, void* xp, hipStream_t stream, float scale = 1.f,
-                                float* xn = nullptr, void* hdr = nullptr, const float* row_scale = nullptr);
+                                float* xn = nullptr, void* hdr = nullptr, bool cosine = false);
 hipError_t launch_pad_norms(float* xn, int64_t n, hipStream_t stream);
 //   launch_seed_thresholds  tsh[r] = min(tsh[r], an upper bound of query r's k-th smallest distance
 //                         found from the filter keys of seed_points points spread over the packed

@@ -31,6 +31,7 @@
 #include <climits>
 #include <cmath>
 #include <cstdint>
+#include <type_traits>
 
 #include "knn_config.h"
 #include "knn_device.h"
@@ -45,49 +46,85 @@ namespace {
 // chunk of 16 coordinates -> lane: lane (i32, h) holds coordinates 16 c + 8 h .. + 7 of point
 // 32 pb + i32, zero past d and past n.  `scale` (a power of two: it commutes with the rounding) is 1 for
 // points and -2 for queries packed as B operands.  A row block of 32 points per workgroup, through
-// LDS: each of the four waves reads eight rows (32 bytes a lane, whole rows at a stretch) and
+// LDS: each of the four waves reads eight rows (32 bytes a lane, P lanes to a row and so 64 / P rows at once) and
 // writes their rounded pieces into the block's operands in LDS; the block's operands - nch KB in a
 // row in the copy - then go out as whole 1 KB stores.  Rows longer than kPbSeg chunks take several
-// passes.  NORMS: the squared norms of the rows (one fma chain per lane over its pieces, lanes added
-// up by a butterfly: a fixed order) go to xn, and the largest squared norm of a rounding residual
-// x - bf16(x) to hdr[1] - the pass over X that knn_row_norms_kernel would otherwise repeat.
-// (With row_scale both are those of the scaled rows; xn may be null.)
+// passes.
+// What the pass takes along, to what the header holds of all points:
+//   kPackNorms   the squared norms of the rows (one fma chain per lane over its pieces, lanes added
+//                up by a butterfly: a fixed order) to xn, the largest to hdr[0], and the largest squared norm of a
+//                rounding residual x - bf16(x) to hdr[1]
+//   kPackCosine  rows are scaled by 1 / |x|, which goes to xn (the largest to hdr[0]) and is made here, with the
+//                bits of knn_row_norms_kernel, from the rows that the second look then finds in the cache; hdr[1]
+//                as above, of the scaled rows
+// Bound by the memory: 1.2e6 rows of 100, cosine 300 us (670 with the norms and their maximum from passes of their
+// own, 64 lanes to a row and every workgroup raising the header's words); 1e7 rows of 128 1.49 ms (2.70).
+enum PackKind { kPackPlain, kPackNorms, kPackCosine };
 constexpr int kPbSeg = 32;               // chunks per pass
 constexpr int kPbOperandStride = 64 + 2; // uint4 per operand in LDS (a half of 32 rows + one: no bank conflicts)
-template <bool NORMS, bool WHOLE>
+template <PackKind KIND, bool WHOLE, int P>
 __global__ __launch_bounds__(256) void knn_pack_block_kernel(const float* __restrict__ X, int64_t ldx, int n,
                                                              int d, int nch, int j_first, int nblocks,
-                                                             float scale, const float* __restrict__ row_scale,
-                                                             uint4* __restrict__ Xp,
+                                                             float scale, uint4* __restrict__ Xp,
                                                              float* __restrict__ xn, unsigned* __restrict__ hdr) {
+    constexpr int G = kWave / P, RR = 8 / G;  // rows at once, and how many of these a wave's eight rows take
     __shared__ uint4 ops[kPbSeg * kPbOperandStride];
-    __shared__ float wmax[4];
+    __shared__ float wmax[2][4];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    float worst = 0.f;
+    const int sub = lane / P, m0 = lane % P;
+    float worst = 0.f, most = 0.f;
     for (int blk = blockIdx.x; blk < nblocks; blk += gridDim.x) {
-        float acc[8], res[8];
+        const int row0 = j_first + blk * 32 + wave * 8;  // (a row past n: values that are masked)
+        float acc[RR], res[RR], sc[RR];
 #pragma unroll
-        for (int rr = 0; rr < 8; ++rr) acc[rr] = res[rr] = 0.f;
+        for (int rr = 0; rr < RR; ++rr) {
+            acc[rr] = res[rr] = 0.f;
+            sc[rr] = scale;
+        }
+        if constexpr (KIND == kPackCosine) {
+            float sq[8];
+            const float* row[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                sq[i] = 0.f;
+                row[i] = X + (int64_t)min(row0 + i, n - 1) * ldx;
+            }
+            for (int t = lane; t < d; t += kWave) {
+                float v[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) v[i] = row[i][t];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) sq[i] = fmaf(v[i], v[i], sq[i]);
+            }
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+#pragma unroll
+                for (int s = 32; s > 0; s >>= 1) sq[i] += __shfl_xor(sq[i], s);
+                const float inverse = sq[i] > 0.f ? 1.f / sqrtf(sq[i]) : 0.f;
+                if (row0 + i < n) {
+                    if (lane == 0) xn[row0 + i] = inverse;
+                    most = fmaxf(most, inverse);
+                }
+                if (sub == i % G) sc[i / G] = inverse;
+            }
+        }
         for (int c0 = 0; c0 < nch; c0 += kPbSeg) {
             const int cs = min(kPbSeg, nch - c0);
-            for (int m = lane; m < 2 * cs; m += 64) {  // piece m of the pass: chunk c0 + m / 2, half m % 2
+            for (int m = m0; m < 2 * cs; m += P) {  // piece m of the pass: chunk c0 + m / 2, half m % 2
                 const int col = c0 * 16 + m * 8;
-                f32x4 v0[8], v1[8];
+                f32x4 v0[RR], v1[RR];
 #pragma unroll
-                for (int rr = 0; rr < 8; ++rr) {
-                    const int j = j_first + blk * 32 + wave * 8 + rr;
+                for (int rr = 0; rr < RR; ++rr) {
+                    const int j = row0 + rr * G + sub;
                     v0[rr] = load_row4<WHOLE>(X, ldx, j, n, col, d);
                     v1[rr] = load_row4<WHOLE>(X, ldx, j, n, col + 4, d);
                 }
 #pragma unroll
-                for (int rr = 0; rr < 8; ++rr) {
-                    const int jr = j_first + blk * 32 + wave * 8 + rr;
-                    const bool ok = jr < n;
-                    // (row_scale: every row times its own factor - the cosine metric's 1 / |x|)
-                    const float sc = row_scale ? row_scale[ok ? jr : 0] : scale;
-                    const f32x4 a0 = mask_row4(v0[rr], ok, col, d, sc);
-                    const f32x4 a1 = mask_row4(v1[rr], ok, col + 4, d, sc);
-                    if (NORMS) {
+                for (int rr = 0; rr < RR; ++rr) {
+                    const bool ok = row0 + rr * G + sub < n;
+                    const f32x4 a0 = mask_row4(v0[rr], ok, col, d, sc[rr]);
+                    const f32x4 a1 = mask_row4(v1[rr], ok, col + 4, d, sc[rr]);
+                    if (KIND != kPackPlain) {
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
                             acc[rr] = fmaf(a0[e], a0[e], acc[rr]);
@@ -103,7 +140,7 @@ __global__ __launch_bounds__(256) void knn_pack_block_kernel(const float* __rest
                     }
                     const uint4 w = {round_pair(a0[0], a0[1]), round_pair(a0[2], a0[3]), round_pair(a1[0], a1[1]),
                                      round_pair(a1[2], a1[3])};
-                    ops[(m >> 1) * kPbOperandStride + (m & 1) * 33 + wave * 8 + rr] = w;
+                    ops[(m >> 1) * kPbOperandStride + (m & 1) * 33 + wave * 8 + rr * G + sub] = w;
                 }
             }
             __syncthreads();
@@ -111,26 +148,39 @@ __global__ __launch_bounds__(256) void knn_pack_block_kernel(const float* __rest
                 Xp[((size_t)blk * nch + c0 + c) * 64 + lane] = ops[c * kPbOperandStride + (lane >> 5) * 33 + (lane & 31)];
             __syncthreads();
         }
-        if (NORMS) {
+        if (KIND != kPackPlain) {
 #pragma unroll
-            for (int rr = 0; rr < 8; ++rr) {
+            for (int rr = 0; rr < RR; ++rr) {
                 float a = acc[rr], r = res[rr];
 #pragma unroll
-                for (int sft = 32; sft > 0; sft >>= 1) {
-                    a += __shfl_xor(a, sft);
-                    r += __shfl_xor(r, sft);
+                for (int s = P / 2; s > 0; s >>= 1) {
+                    a += __shfl_xor(a, s);
+                    r += __shfl_xor(r, s);
                 }
-                const int j = j_first + blk * 32 + wave * 8 + rr;
-                if (xn && lane == 0 && j < n) xn[j] = a;
+                const int j = row0 + rr * G + sub;
+                if (KIND == kPackNorms && j < n) {
+                    if (m0 == 0) xn[j] = a;
+                    most = fmaxf(most, a);
+                }
                 worst = fmaxf(worst, r);
             }
         }
     }
-    if (NORMS) {  // one atomic per workgroup (they all go to the same word)
-        if (lane == 0) wmax[wave] = worst;
+    if (KIND != kPackPlain) {  // one request per workgroup (they all go to the same words)
+#pragma unroll
+        for (int s = 32; s >= P; s >>= 1) {
+            worst = fmaxf(worst, __shfl_xor(worst, s));
+            most = fmaxf(most, __shfl_xor(most, s));
+        }
+        if (lane == 0) {
+            wmax[0][wave] = most;
+            wmax[1][wave] = worst;
+        }
         __syncthreads();
-        if (threadIdx.x == 0)
-            atomicMax(hdr + 1, __float_as_uint(fmaxf(fmaxf(wmax[0], wmax[1]), fmaxf(wmax[2], wmax[3]))));
+        if (threadIdx.x < 2) {
+            const float* const w = wmax[threadIdx.x];
+            raise_word(hdr + threadIdx.x, __float_as_uint(fmaxf(fmaxf(w[0], w[1]), fmaxf(w[2], w[3]))));
+        }
     }
 }
 
@@ -746,17 +796,30 @@ __global__ __launch_bounds__(64 * WV, WV / 4) void knn_packed_kernel(const PkArg
 
 hipError_t launch_pack_operands(const float* X, int64_t ldx, int64_t n, int d, int64_t j_first,
                                 int64_t points, void* xp, hipStream_t stream, float scale, float* xn,
-                                void* hdr, const float* row_scale) {
+                                void* hdr, bool cosine) {
     const int nch = pk_padded_chunks(d);
-    if ((xn || row_scale) && !hdr) return hipErrorInvalidValue;
+    if ((xn && !hdr) || (cosine && !xn)) return hipErrorInvalidValue;
     const int nblocks = (int)(points / 32);
     const dim3 grid((unsigned)(nblocks < 16384 ? nblocks : 16384));
     auto go = [&](auto kernel) {
-        kernel<<<grid, dim3(256), 0, stream>>>(X, ldx, (int)n, d, nch, (int)j_first, nblocks, scale, row_scale,
+        kernel<<<grid, dim3(256), 0, stream>>>(X, ldx, (int)n, d, nch, (int)j_first, nblocks, scale,
                                                static_cast<uint4*>(xp), xn, static_cast<unsigned*>(hdr));
     };
-    if (xn || row_scale) whole_rows(d) ? go(knn_pack_block_kernel<true, true>) : go(knn_pack_block_kernel<true, false>);
-    else whole_rows(d) ? go(knn_pack_block_kernel<false, true>) : go(knn_pack_block_kernel<false, false>);
+    auto by_kind = [&](auto whole, auto lanes) {
+        constexpr bool kWhole = decltype(whole)::value;
+        constexpr int kLanes = decltype(lanes)::value;
+        if (cosine) go(knn_pack_block_kernel<kPackCosine, kWhole, kLanes>);
+        else if (xn) go(knn_pack_block_kernel<kPackNorms, kWhole, kLanes>);
+        else go(knn_pack_block_kernel<kPackPlain, kWhole, kLanes>);
+    };
+    auto by_length = [&](auto whole) {  // (two pieces per chunk)
+        using std::integral_constant;
+        if (nch <= 4) by_kind(whole, integral_constant<int, 8>{});
+        else if (nch <= 8) by_kind(whole, integral_constant<int, 16>{});
+        else if (nch <= 16) by_kind(whole, integral_constant<int, 32>{});
+        else by_kind(whole, integral_constant<int, 64>{});
+    };
+    whole_rows(d) ? by_length(std::true_type{}) : by_length(std::false_type{});
     return hipGetLastError();
 }
 

@@ -32,16 +32,6 @@ __global__ void knn_split_init_kernel(unsigned* __restrict__ hdr) {
     if (threadIdx.x < 2) hdr[threadIdx.x] = 0u;  // (word 1: the largest bf16 rounding residual, path 6)
 }
 
-__global__ __launch_bounds__(256) void knn_max_norm_kernel(const float* __restrict__ xn, int64_t n,
-                                                           unsigned* __restrict__ hdr) {
-    float m = 0.f;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
-        m = fmaxf(m, xn[i]);
-#pragma unroll
-    for (int s = 32; s > 0; s >>= 1) m = fmaxf(m, __shfl_xor(m, s));
-    if ((threadIdx.x & 63) == 0) atomicMax(hdr, __float_as_uint(m));
-}
-
 // B operands of the queries of one chunk: per row and 16-coordinate chunk 32 bytes,
 // [bf16(-2 q): coordinates 0..7 | 8..15], zero past d.
 template <bool ALIGNED>
@@ -410,7 +400,10 @@ __global__ __launch_bounds__(512, 2) void knn_split_kernel(
     auto fetchX = [&](XS& g) {
 #pragma unroll
         for (int kk = 0; kk < W; ++kk)
-            g.x[kk] = load_row4<ALIGNED>(frow, 0, 0, 1, (f_c * W + kk) * 16 + squad * 4, d);
+            // (the shifting only in the chunk that needs it: the same branch for the whole workgroup)
+            g.x[kk] = !ALIGNED && (f_c * W + kk) * 16 + 16 <= d
+                          ? load4(frow + (f_c * W + kk) * 16 + squad * 4)
+                          : load_row4<ALIGNED>(frow, 0, 0, 1, (f_c * W + kk) * 16 + squad * 4, d);
         if (f_c == 0) g.xnv = xn[min(j0 + f_tile * TX + (tid & (TX - 1)), j1 - 1)];
         if (++f_c == nst) {
             f_c = 0;
@@ -570,14 +563,6 @@ hipError_t launch_header_init(void* hdr, hipStream_t stream) {
     return hipGetLastError();
 }
 
-hipError_t launch_max_norm(const float* xn, int64_t n, void* hdr, hipStream_t stream) {
-    unsigned* w = static_cast<unsigned*>(hdr);
-    int64_t blocks = (n + 255) / 256;
-    if (blocks > 1024) blocks = 1024;
-    knn_max_norm_kernel<<<dim3((unsigned)blocks), dim3(256), 0, stream>>>(xn, n, w);
-    return hipGetLastError();
-}
-
 hipError_t launch_fill_words(void* p, int64_t count, unsigned value, hipStream_t stream) {
     if (count > 0)
         knn_fill_words_kernel<<<dim3((unsigned)((count + 255) / 256)), dim3(256), 0, stream>>>(
@@ -636,7 +621,8 @@ hipError_t launch_split(const float* Q, int64_t ldq, const float* X, int64_t ldx
     // in registers (up to d = 256; W * N is the chunk count rounded up to a shape that is
     // instantiated), N = 0: any d, queries streamed.  Wide steps keep more bytes of the point
     // stream in flight, which is what the kernel waits for; the shapes are the fastest measured
-    // among those that fit the register budget (rows that are not whole groups of four take narrower steps).
+    // among those that fit the register budget (rows that are not whole groups of four take narrower steps where
+    // the wide ones spill).
     // (No shape with one step per tile: its loop is unrolled over two tiles and then spills two
     // registers to private memory, which the runtime would have to provide beside the workspace.)
     if (aligned) {
@@ -653,10 +639,10 @@ hipError_t launch_split(const float* Q, int64_t ldq, const float* X, int64_t ldx
         else if (nch <= 4) KNN_SPLIT_LAUNCH(2, 2, false);
         else if (nch <= 6) KNN_SPLIT_LAUNCH(2, 3, false);
         else if (nch <= 8) KNN_SPLIT_LAUNCH(2, 4, false);
-        else if (nch <= 10) KNN_SPLIT_LAUNCH(2, 5, false);
+        else if (nch <= 9) KNN_SPLIT_LAUNCH(3, 3, false);
         else if (nch <= 12) KNN_SPLIT_LAUNCH(2, 6, false);
-        else if (nch <= kSpResidentMaxChunks) KNN_SPLIT_LAUNCH(2, 8, false);
-        else KNN_SPLIT_LAUNCH(2, 0, false);
+        else if (nch <= kSpResidentMaxChunks) KNN_SPLIT_LAUNCH(4, 4, false);
+        else KNN_SPLIT_LAUNCH(4, 0, false);
     }
 #undef KNN_SPLIT_LAUNCH
     return hipGetLastError();
