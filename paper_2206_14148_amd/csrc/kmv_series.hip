@@ -30,16 +30,18 @@
 //
 // What bounds it: a wave's chain of boxes (the table's row, then P multiply-adds that wait for each
 // other), and for many sources the look of every box's workgroups at all of them.  n = m = 1e6 in fp32,
-// l = 1, normal points (10 boxes): bounds 5.6 us, moments 44.5, table 5.4, rows 49, against 160 ms
-// for the entries one by one; 2e5 x 2e5 in fp64: 4.8, 59, 6.2, 43 us against 35.4 ms.  Error against
+// l = 1, normal points (10 boxes): bounds 5.6 us, moments 26, table 4.7, rows 32, against 160 ms
+// for the entries one by one; 2e5 x 2e5 in fp64: 4.8, 30, 5.8, 39 us against 35.4 ms.  Error against
 // 64 bits 7e-16 (fp32 entry by entry: 2.6e-7; fp64: 5e-15).
 #include <hip/hip_runtime.h>
 
 #include <cmath>
 #include <cstdint>
+#include <type_traits>
 
 #include "kmv_kernels.h"
 #include "knn_config.h"
+#include "knn_device.h"
 
 namespace kmv {
 
@@ -68,10 +70,11 @@ struct Series<double> {
 constexpr int kRow = 64;          // doubles per box: P moments, W, and in the table the centre at kRow - 1
 constexpr int kWeight = kRow - 2;  // in the table: log2 W as a float
 constexpr double kNear = 8.0;      // |a| up to which the series loses next to nothing
+constexpr int64_t kManyRows = 1 << 15;  // from here on two rows per lane
 constexpr int kBoundsGroups = 256;
 constexpr int kMaxBoxes = 1024;
 constexpr int kMomentGroups = 2048;  // workgroups of the moment kernel: box x slice of the sources
-constexpr int kMaxSlices = 64;
+constexpr int kMaxSlices = 128;
 
 // workspace: header | bounds of the workgroups [3][256] | the boxes' table | partial moments | how many tiles
 // of 256 rows are left to the general kernel (-1: all), and for each (fp64) whether it is done
@@ -121,8 +124,31 @@ __global__ __launch_bounds__(256) void kmv_bounds_kernel(const T* __restrict__ Z
     }
 }
 
-// Workgroup (box, slice): the moments of the box's sources among one slice of them.  A thread
-// walks its sources in ascending order; threads are added in a fixed tree.
+// Sums over the wave of N values a lane: with every step a lane hands half of its values to the lane S away and
+// keeps the others, so about N exchanges make all sums (a butterfly per value would take 6 N).  Afterwards a
+// lane holds, in a[0], the sum of value number wave_sums_place(lane).  A fixed tree.
+template <int S, int N>
+__device__ __forceinline__ void wave_sums(double (&a)[N], int lane) {
+    constexpr int H = (N + 1) / 2;
+    double half[H];
+    const bool upper = lane & S;
+#pragma unroll
+    for (int i = 0; i < H; ++i) {
+        const double even = a[2 * i], odd = 2 * i + 1 < N ? a[2 * i + 1 < N ? 2 * i + 1 : 0] : 0.0;
+        const double give = upper ? even : odd;
+        const int lo = knn::lane_xor<S>(__double2loint(give)), hi = knn::lane_xor<S>(__double2hiint(give));
+        half[i] = (upper ? odd : even) + __hiloint2double(hi, lo);
+    }
+    if constexpr (S > 1) wave_sums<S / 2, H>(half, lane);
+    a[0] = half[0];
+}
+__device__ __forceinline__ int wave_sums_place(int lane) { return (int)(__brev((unsigned)lane) >> 26); }
+
+// Workgroup (box, slice): the moments of the box's sources among one slice of them.  A wave puts
+// the box's sources among those it looks at into a queue in LDS, in ascending order, and takes 64 at a
+// time from it, so that all lanes have a source to raise to its powers (without the queue, every wave
+// did so for its few lanes inside the box: 44 us at n = m = 1e6 in fp32, 26 with it; 2e5 in fp64 60 and 30).  Lanes and waves are added in
+// a fixed tree.
 template <typename T>
 __global__ __launch_bounds__(256) void kmv_moments_kernel(const T* __restrict__ Z, int64_t ldz,
                                                           const T* __restrict__ v, int64_t m, int64_t n,
@@ -135,6 +161,7 @@ __global__ __launch_bounds__(256) void kmv_moments_kernel(const T* __restrict__ 
     constexpr int N = P + (sizeof(T) == 8 ? 1 : 0);  // sums: the moments, and in fp64 their terms' magnitude
     __shared__ double sum[4][N];
     __shared__ double part[3][4];
+    __shared__ double queue_b[4][128], queue_v[4][128];  // a ring per wave
     const int wave = threadIdx.x >> 6;
     const int lane = threadIdx.x & 63;
     // every workgroup puts the bounds together for itself
@@ -193,69 +220,96 @@ __global__ __launch_bounds__(256) void kmv_moments_kernel(const T* __restrict__ 
     const int64_t len = (m + slices - 1) / slices;
     const int64_t j0 = slice * len;
     const int64_t j1 = j0 + len < m ? j0 + len : m;
-    constexpr int U = 4;
-    for (int64_t j = j0 + threadIdx.x; j < j1; j += 256 * U) {
-        double z[U];
+    auto take = [&](double b, double v) {
+        double w = v * exp(-0.5 * b * b);
+        if constexpr (N > P) acc[P] += fabs(w);
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+            acc[p] += w;
+            w *= b;
+        }
+    };
+    constexpr int U = 8;
+    int head = 0, count = 0;  // (the same in all lanes)
+    for (int64_t jw = j0 + wave * 64; jw < j1; jw += 256 * U) {
+        T z[U], v_[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int64_t jj = j + 256 * u;
-            z[u] = (double)Z[(jj < j1 ? jj : j1 - 1) * ldz];
+            const int64_t jj = jw + lane + 256 * u;
+            const int64_t jc = jj < j1 ? jj : j1 - 1;
+            z[u] = Z[jc * ldz];
+            v_[u] = v[jc];
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int64_t jj = j + 256 * u;
-            int g = (int)((z[u] - lo) * rw);
+            int g = (int)(((double)z[u] - lo) * rw);
             if (g > boxes - 1) g = boxes - 1;
-            if (g == box && jj < j1) {
-                const double b = (z[u] - c) * rl;
-                double w = (double)v[jj] * exp(-0.5 * b * b);
-                if constexpr (N > P) acc[P] += fabs(w);
-#pragma unroll
-                for (int p = 0; p < P; ++p) {
-                    acc[p] += w;
-                    w *= b;
-                }
+            const bool mine = g == box && jw + lane + 256 * u < j1;
+            const uint64_t in = __builtin_amdgcn_ballot_w64(mine);
+            if (in == 0) continue;
+            if (mine) {
+                const int at = (head + count + __builtin_popcountll(in & ((1ull << lane) - 1))) & 127;
+                queue_b[wave][at] = ((double)z[u] - c) * rl;
+                queue_v[wave][at] = (double)v_[u];
+            }
+            count += __builtin_popcountll(in);
+            if (count >= 64) {
+                knn::wave_sync();
+                const int at = (head + lane) & 127;
+                take(queue_b[wave][at], queue_v[wave][at]);
+                head = (head + 64) & 127;
+                count -= 64;
+                knn::wave_sync();  // (read before it is written again)
             }
         }
     }
-#pragma unroll
-    for (int p = 0; p < N; ++p) {
-        double s = acc[p];
-#pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) s += __shfl_xor(s, o);
-        if (lane == 0) sum[wave][p] = s;
-    }
+    knn::wave_sync();
+    if (lane < count) take(queue_b[wave][(head + lane) & 127], queue_v[wave][(head + lane) & 127]);
+    static_assert(N <= 64, "a lane per sum");
+    wave_sums<32, N>(acc, lane);
+    if (wave_sums_place(lane) < N) sum[wave][wave_sums_place(lane)] = acc[0];
     __syncthreads();
     const int t = threadIdx.x;
     if (t < N) partial[(int64_t)blockIdx.x * kRow + t] = (sum[0][t] + sum[1][t]) + (sum[2][t] + sum[3][t]);
     if (slice == 0 && t == kRow - 1) table[(int64_t)box * kRow + kRow - 1] = c;
 }
 
-// table[box][p] = (sum over the slices, ascending) / p!; at kWeight log2 of the magnitudes' sum
+// table[box][p] = (sum over the slices, a wave every fourth, then the waves) / p!; at kWeight log2 of the magnitudes' sum
 template <typename T>
-__global__ __launch_bounds__(64) void kmv_table_kernel(const Header* __restrict__ header,
-                                                       const double* __restrict__ partial,
-                                                       double* __restrict__ table) {
+__global__ __launch_bounds__(256) void kmv_table_kernel(const Header* __restrict__ header,
+                                                        const double* __restrict__ partial,
+                                                        double* __restrict__ table) {
     constexpr int P = Series<T>::P;
     static_assert(P < kWeight, "a lane per moment and one for their magnitude, the centre behind them");
-    const int box = blockIdx.x, p = threadIdx.x;
-    if (!header->ok || box >= header->boxes || p > P || (p == P && sizeof(T) != 8)) return;
+    __shared__ double sum[4][64];
+    const int box = blockIdx.x, p = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (!header->ok || box >= header->boxes) return;  // whole workgroup
+    const bool have = p < P || (p == P && sizeof(T) == 8);
     const int slices = header->slices;
-    double s = 0.0, factorial = 1.0;
+    double s = 0.0;
+    if (have) {
 #pragma unroll 8
-    for (int i = 0; i < slices; ++i) s += partial[((int64_t)box * slices + i) * kRow + p];
+        for (int i = wave; i < slices; i += 4) s += partial[((int64_t)box * slices + i) * kRow + p];
+    }
+    sum[wave][p] = s;
+    __syncthreads();
+    if (wave != 0 || !have) return;
+    s = (sum[0][p] + sum[1][p]) + (sum[2][p] + sum[3][p]);
     if (p == P) {
         *reinterpret_cast<float*>(table + (int64_t)box * kRow + kWeight) = (float)log2(s);
         return;
     }
+    double factorial = 1.0;
     for (int i = 2; i <= p; ++i) factorial *= (double)i;
     table[(int64_t)box * kRow + p] = s / factorial;
 }
 
-// One row per lane; the boxes are the same for the whole wave, so their moments come through
-// scalar loads.  Per box and row: P multiply-adds and one exponential.  In fp64 done[1 + tile] = 1 where y
+// R rows per lane, one of each of R tiles of 256; the boxes are the same for the whole wave, so their moments come
+// through scalar loads, whose round trips bound the kernel: R rows share them and have chains of their own.
+// (n = 1e6 in fp32: the call 84 us with one row, 66 with two, 67 with four; n = 2e5 in fp64 85, 79, 93; n = 5e4 69, 65.)
+// Per box and row: P multiply-adds and one exponential.  In fp64 done[1 + tile] = 1 where y
 // is complete, 0 where the general kernel has to make the tile's rows; done[0] counts those.
-template <typename T>
+template <typename T, int R>
 __global__ __launch_bounds__(256) void kmv_series_kernel(const T* __restrict__ X, int64_t ldx, int64_t n,
                                                          double lengthscale, double variance,
                                                          const Header* __restrict__ header,
@@ -264,37 +318,64 @@ __global__ __launch_bounds__(256) void kmv_series_kernel(const T* __restrict__ X
     constexpr int P = Series<T>::P;
     if (!header->ok) return;
     const int boxes = header->boxes;
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const double rl = 1.0 / lengthscale;
-    const double x = (double)X[(i < n ? i : n - 1) * ldx];
-    double total = 0.0;
-    float surely = -HUGE_VALF, lost = -HUGE_VALF;  // log2: the largest terms of the two sums above
+    double x[R], total[R];
+    float surely[R], lost[R];  // log2: the largest terms of the two sums above
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int64_t i = ((int64_t)blockIdx.x * R + r) * 256 + threadIdx.x;
+        x[r] = (double)X[(i < n ? i : n - 1) * ldx];
+        total[r] = 0.0;
+        surely[r] = lost[r] = -HUGE_VALF;
+    }
     for (int box = 0; box < boxes; ++box) {
         const double* __restrict__ row = table + (int64_t)box * kRow;
-        const double a = (x - row[kRow - 1]) * rl;
-        const double e = 0.5 * a * a;
-        if (__builtin_amdgcn_ballot_w64(e <= Series<T>::far) == 0) continue;
-        if constexpr (sizeof(T) == 8) {
-            constexpr float kLog2e = 1.44269504f;
-            const float fa = fabsf((float)a);
-            const float w = *reinterpret_cast<const float*>(row + kWeight) - 0.5f * kLog2e * fa * fa;
-            const float spread = (float)Series<T>::h * kLog2e * fa;
-            surely = fmaxf(surely, w - spread);
-            if (fa > (float)kNear) lost = fmaxf(lost, w + spread);
-        }
-        double s = row[P - 1];
+        double a[R], s[R];
+        bool near = false;
 #pragma unroll
-        for (int p = P - 2; p >= 0; --p) s = fma(s, a, row[p]);
-        if (e <= Series<T>::far) total = fma(exp(-e), s, total);
+        for (int r = 0; r < R; ++r) {
+            a[r] = (x[r] - row[kRow - 1]) * rl;
+            near |= 0.5 * a[r] * a[r] <= Series<T>::far;
+        }
+        if (__builtin_amdgcn_ballot_w64(near) == 0) continue;
+        if constexpr (sizeof(T) == 8) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                if (!(0.5 * a[r] * a[r] <= Series<T>::far)) continue;
+                constexpr float kLog2e = 1.44269504f;
+                const float fa = fabsf((float)a[r]);
+                const float w = *reinterpret_cast<const float*>(row + kWeight) - 0.5f * kLog2e * fa * fa;
+                const float spread = (float)Series<T>::h * kLog2e * fa;
+                surely[r] = fmaxf(surely[r], w - spread);
+                if (fa > (float)kNear) lost[r] = fmaxf(lost[r], w + spread);
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) s[r] = row[P - 1];
+#pragma unroll
+        for (int p = P - 2; p >= 0; --p) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) s[r] = fma(s[r], a[r], row[p]);
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const double e = 0.5 * a[r] * a[r];
+            if (e <= Series<T>::far) total[r] = fma(exp(-e), s[r], total[r]);
+        }
     }
-    if (x != x) total = x;  // as the sum over such entries of K
-    if (i < n) y[i] = variance * total;
-    if constexpr (sizeof(T) == 8) {
-        // (at most 160 boxes are within reach of a row: 160 / 2^6 = 2.5)
-        const int leave = __syncthreads_or(i < n && lost > surely - 6.f);
-        if (threadIdx.x == 0) {
-            done[1 + blockIdx.x] = leave ? 0 : 1;
-            if (leave) atomicAdd(done, 1);
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int64_t tile = (int64_t)blockIdx.x * R + r, i = tile * 256 + threadIdx.x;
+        if (x[r] != x[r]) total[r] = x[r];  // as the sum over such entries of K
+        if (i < n) y[i] = variance * total[r];
+        if constexpr (sizeof(T) == 8) {
+            if (tile * 256 >= n) break;  // (whole workgroup)
+            // (at most 160 boxes are within reach of a row: 160 / 2^6 = 2.5)
+            const int leave = __syncthreads_or(i < n && lost[r] > surely[r] - 6.f);
+            if (threadIdx.x == 0) {
+                done[1 + tile] = leave ? 0 : 1;
+                if (leave) atomicAdd(done, 1);
+            }
         }
     }
 }
@@ -337,9 +418,14 @@ hipError_t launch_series(const T* X, int64_t ldx, const T* Z, int64_t ldz, const
     kmv_bounds_kernel<T><<<dim3(kBoundsGroups), dim3(256), 0, stream>>>(Z, ldz, v, m, bounds);
     kmv_moments_kernel<T><<<dim3(kMomentGroups), dim3(256), 0, stream>>>(
         Z, ldz, v, m, n, lengthscale, general_time_us(n, m, S, sizeof(T) == 8), bounds, header, table, partial, flags);
-    kmv_table_kernel<T><<<dim3(kMaxBoxes), dim3(64), 0, stream>>>(header, partial, table);
-    kmv_series_kernel<T><<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream>>>(
-        X, ldx, n, lengthscale, variance, header, table, flags, y);
+    kmv_table_kernel<T><<<dim3(kMaxBoxes), dim3(256), 0, stream>>>(header, partial, table);
+    // (as many rows per lane as leave enough waves for every SIMD)
+    auto rows = [&](auto kernel, int64_t per_lane) {
+        kernel<<<dim3((unsigned)((n + 256 * per_lane - 1) / (256 * per_lane))), dim3(256), 0, stream>>>(
+            X, ldx, n, lengthscale, variance, header, table, flags, y);
+    };
+    if (n >= kManyRows) rows(kmv_series_kernel<T, 2>, 2);
+    else rows(kmv_series_kernel<T, 1>, 1);
     return hipGetLastError();
 }
 
