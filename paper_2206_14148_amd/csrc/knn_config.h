@@ -169,6 +169,15 @@ constexpr int kWarmupPointsPerK = 64;     // list warm-up of one point range, in
 constexpr int kWarmupPointsPerKBf16 = 4700;
 constexpr int kWarmupPointsPerKFilter = 1800;
 constexpr int kMaxSplits = 64;
+// Up to here a query's lists are merged by a workgroup of its own however many they are, so the split path may
+// have a range for every compute unit (in place of 64: 23 x 2.8e6, d = 230, k = 5 3.12 -> 1.54 ms; 20 x 9e5, d = 245,
+// cosine 1.46 -> 0.75; 60 x 4e4, d = 100, k = 256 10.2 -> 4.8).
+constexpr int64_t kSpFewRows = 128;
+constexpr int kSpFewMaxK = 256;
+// With lists this short it is then faster than paths 6 and 7, ms here / there: 100 queries, path 7 by n, d, k: 5e5, 301, 5
+// 0.84 / 1.49, 5e5, 301, 20 2.17 / 1.99, 5e5, 768, 5 1.49 / 2.20, 5e5, 768, 20 3.27 / 2.52; path 6: 1e6, 230, 1 0.73 /
+// 1.11, 1e6, 230, 8 1.08 / 1.27, 1e6, 230, 20 2.12 / 1.32, 4e6, 31, 8 0.98 / 1.31; cosine, 64 x 1e6, 100, 8 0.77 / 0.87.
+constexpr int kSpFewShortK = 8;
 constexpr int64_t kMaxPoints = ((int64_t)1 << 31) - 65536;
 constexpr int64_t kMaxChunkRows = 1 << 22;  // keeps per-launch row counts and grids in int range
 constexpr int kMinSplitPoints = 2048;    // a point range shorter than this is not worth a split

@@ -199,11 +199,18 @@ __global__ __launch_bounds__(64 * kFewWaves) void knn_few_kernel(
 //   1000, 1e4, 16, 1: 68 / 161      1000, 1e4, 128, 1: 133 / 220     1000, 1e4, 300, 1: 287 / 382
 //   1000, 65536, 16, 1: 214 / 206   1000, 65536, 9, 1: 336 / 221     1000, 65536, 9, 10: 394 / 754
 //   1000, 2e5, 9, 1: 877 / 286      2e4, 1e4, 9, 10: 939 / 687       4000, 1e4, 50, 10: 513 / 649
+// Up to 64 queries, against a split path with a range for every compute unit, k = 1 / 10 / 100, here and there:
+//   40, 1e6, 230: 1754 1747 1935 / 710 1104 5610      40, 2e6, 50: 667 686 989 / 543 884 4084
+//   16, 1e6, 230: 522 566 1051 / 587 839 3354         40, 5e6, 12: 706 759 1158 / 451 928 4769
 // From 65 queries on the line is a bound from below of what the filters take, up to 5e9 in all.
 bool few_applies(int64_t m, int64_t n, int d, int k, bool aligned) {
     const double work = (double)m * (double)n * (double)(d + 16);
     if (k > kFewMaxK) return false;
-    if (m <= 64) return work <= (m <= 16 ? 2e10 : 1e10);
+    if (m <= 64) {
+        // the split path reads the points twice, whatever m is, and restarts its lists in a range per compute unit
+        const double split_us = 300.0 + 1.8e-6 * (double)n * d + 40.0 * k;
+        return work <= (m <= 16 ? 2e10 : 1e10) && 40.0 + 1.2e-7 * work <= 1.25 * split_us;
+    }
     const double here_us = 40.0 + work * (aligned ? 1.0e-7 : 1.75e-7);
     const double copy_us = 3e-5 * (double)n * d;
     const double filter_us = (aligned ? 150.0 + 0.75 * d : 165.0 + 1.5 * d) + (copy_us < 150.0 ? copy_us : 150.0) +

@@ -401,7 +401,7 @@ hipError_t launch_merge_refine(const float* Q, int64_t ldq, const float* X, int6
     // wave several rounds, or, for few rows, a search through many lists each (LDS for its lists: k <= 256).
     // Whole calls, us, wave / workgroup per row: 4 x 65536, d = 128, k = 1, 256 lists a query 200 / 50;
     // 1024 x 4e6, d = 100, k = 1, 64 lists 2295 / 2412
-    if (rows <= 4 * kNumCU && ((int64_t)S * k > 4 * kWave || (S > 32 && rows <= 128)) && S > 1 && k <= 256) {
+    if (rows <= 4 * kNumCU && ((int64_t)S * k > 4 * kWave || (S > 32 && rows <= kSpFewRows)) && S > 1 && k <= kSpFewMaxK) {
         const size_t lds = (size_t)k * sizeof(double) + (size_t)kFewMergeWaves * k * 8 +
                            (size_t)kFewMergeWaves * (2 * kWave + 2 * k) * 4;
         hipError_t e = raise_lds_limit(knn_merge_refine_few_kernel, lds);

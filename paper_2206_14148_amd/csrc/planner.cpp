@@ -233,7 +233,7 @@ extern "C" knn_status knn_plan_metric(int64_t m, int64_t n, int32_t d, int32_t k
     const bool cosine6 = metric == KNN_METRIC_COSINE;
     if (split && (metric == KNN_METRIC_L2SQ || cosine6) && d <= kPkMaxD &&
         n >= kPkMinPoints && n >= 4 * pk_seed_points_min(k) &&
-        m >= (d <= kSpKC ? kPkMinQueriesOneChunk : kPkMinQueries)) {
+        m >= (d <= kSpKC ? kPkMinQueriesOneChunk : kPkMinQueries) && !(m <= kSpFewRows && k <= kSpFewShortK)) {
         const int nch_p = pk_padded_chunks(d);
         const int sets_max = pk_max_sets(nch_p, k);
         const uint64_t n64 = ((uint64_t)n + kPkStep - 1) / kPkStep * kPkStep;
@@ -319,7 +319,7 @@ extern "C" knn_status knn_plan_metric(int64_t m, int64_t n, int32_t d, int32_t k
     // both operands (knn_wide.hip).  The workspace is path 5's plus the packed points (all of them,
     // or one slab at a time as on path 6) with the queries' B operands in operand order.
     if (split && metric == KNN_METRIC_L2SQ && d > kPkMaxD && k <= kWdMaxK && n >= kWdMinPoints &&
-        m >= kWdMinQueries) {
+        m >= kWdMinQueries && !(m <= kSpFewRows && k <= kSpFewShortK)) {
         const int nch_p = pk_padded_chunks(d);
         const uint64_t qrow7 = 32ull * (uint64_t)nch_p;
         const uint64_t n64 = ((uint64_t)n + kPkStep - 1) / kPkStep * kPkStep;
@@ -388,7 +388,9 @@ extern "C" knn_status knn_plan_metric(int64_t m, int64_t n, int32_t d, int32_t k
     // little list warm-up: they may be shorter)
     int64_t s_max = n / (split ? kSpMinSplitPoints : kMinSplitPoints);
     if (s_max < 1) s_max = 1;
-    if (s_max > kMaxSplits) s_max = kMaxSplits;
+    // (few queries on the split path: a range per compute unit, for the merge with a workgroup per query)
+    const int64_t most = split && m <= kSpFewRows && k <= kSpFewMaxK ? kNumCU : kMaxSplits;
+    if (s_max > most) s_max = most;
     const int64_t slots = lowd ? kLowdResidentWorkgroups : kSpResidentWorkgroups;
     int64_t best_s = 0, best_rows = 0;
     double best_cost = 0.0;
