@@ -44,10 +44,10 @@ PROFILED_TRAFFIC = {
     "c6_cosine_d100": ("knn_packed_kernel", 8.37e9, "profiles/knn_packed_kernel_c6.md"),
     "c7_l1_d100": ("knn_l1_sad_kernel", 12.1e9, "profiles/knn_l1_sad_kernel_c7.md"),
     "kmv1_d1": ("kmv_series_kernel", 12.1e6, "profiles/kmv_series_kernel_kmv1.md"),
-    "kmv2_d32": ("kmv_mfma_kernel", 1.47e9, "profiles/kmv_mfma_kernel_kmv2.md"),
-    "kmv3_d1_f64": ("kmv_series_kernel", 16.3e6, "profiles/kmv_series_kernel_kmv3.md"),
-    "sgpr1_road_d3_m10000": ("sgpr_syrk_kernel", 3.71e9, "profiles/sgpr_syrk_kernel_sgpr1.md"),
-    "sgpr2_electric_d11_m4000": ("sgpr_syrk_kernel", 0.949e9, "profiles/sgpr_syrk_kernel_sgpr2.md"),
+    "kmv2_d32": ("kmv_pieces_kernel", 1.75e9, "profiles/kmv_pieces_kernel_kmv2.md"),
+    "kmv3_d1_f64": ("kmv_series_kernel", 16.4e6, "profiles/kmv_series_kernel_kmv3.md"),
+    "sgpr1_road_d3_m10000": ("sgpr_product_kernel", 37.4e9, "profiles/sgpr_product_kernel_sgpr1.md"),
+    "sgpr2_electric_d11_m4000": ("sgpr_product_kernel", 3.25e9, "profiles/sgpr_product_kernel_sgpr2.md"),
 }
 
 
