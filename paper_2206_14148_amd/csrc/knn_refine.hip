@@ -209,11 +209,17 @@ __global__ __launch_bounds__(256) void knn_merge_refine_kernel(
 }
 
 // The same for few rows with many lists each: a workgroup of eight waves per row.  A wave goes
-// through every eighth list, 64 entries at a time, and merges those under its own k-th entry into a
+// through every eighth run of 64 entries and merges those under its own k-th entry into a
 // list of its own (LDS); the first wave then merges the eight and goes on as above.  (A wave per row
 // that ranks every entry by binary searches in all the other lists walks S log k dependent loads per
 // entry: 295 us for 16 rows of 64 lists of 10.)
 constexpr int kFewMergeWaves = 8;
+// A lane has this many entries in flight.  Up to kFewMergeFirstK the first of each lane's fill the list, and of
+// what is left almost nothing comes before its last: one or two merges in place of one every 64 entries.
+// Whole calls, us before / now: 16 x 1e5, d = 50, k = 10 (391 lists a query) 86.1 / 71.3, k = 50 177 / 161; 1 x 1e6,
+// d = 32, k = 10 97.9 / 65.7.  (At k = 64 the last of 64 such entries bounds little: 210 / 215.)
+constexpr int kFewMergeLoads = 8;
+constexpr int kFewMergeFirstK = 52;
 __global__ __launch_bounds__(64 * kFewMergeWaves) void knn_merge_refine_few_kernel(
     const float* __restrict__ Q, int64_t ldq, const float* __restrict__ X, int64_t ldx, int n, int d, int k,
     int S, int metric, int aligned, const float* __restrict__ lk, const int* __restrict__ li,
@@ -256,9 +262,38 @@ __global__ __launch_bounds__(64 * kFewMergeWaves) void knn_merge_refine_few_kern
     const float* rk = lk + (size_t)r * S * k;
     const int* ri = li + (size_t)r * S * k;
     const int total = S * k;
-    for (int e0 = wave * kWave; e0 < total; e0 += NW * kWave) {
-        const int e = e0 + lane;
-        take(e < total ? rk[e] : kInf, e < total ? ri[e] : kNoIdx);
+    const int one = wave * kWave + lane;
+    if (total <= NW * kWave) take(one < total ? rk[one] : kInf, one < total ? ri[one] : kNoIdx);
+    else for (int e0 = wave * kWave; e0 < total; e0 += kFewMergeLoads * NW * kWave) {
+        float key[kFewMergeLoads];
+        int id[kFewMergeLoads];
+#pragma unroll
+        for (int u = 0; u < kFewMergeLoads; ++u) {
+            const int e = e0 + u * NW * kWave + lane;
+            key[u] = e < total ? rk[e] : kInf;
+            id[u] = e < total ? ri[e] : kNoIdx;
+        }
+        if (k <= kFewMergeFirstK) {
+            int at = 0;
+            float best = key[0];
+            int best_id = id[0];
+#pragma unroll
+            for (int u = 1; u < kFewMergeLoads; ++u)
+                if (before(key[u], id[u], best, best_id)) {
+                    at = u;
+                    best = key[u];
+                    best_id = id[u];
+                }
+            take(best, best_id);
+#pragma unroll
+            for (int u = 0; u < kFewMergeLoads; ++u)
+                if (u == at) {
+                    key[u] = kInf;
+                    id[u] = kNoIdx;
+                }
+        }
+#pragma unroll
+        for (int u = 0; u < kFewMergeLoads; ++u) take(key[u], id[u]);
     }
     __syncthreads();
     if (wave != 0) return;

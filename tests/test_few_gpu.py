@@ -54,3 +54,27 @@ def test_equal_points_keep_the_lowest_indices(K):
     idx, dist = K.knn_search(X[:6] + 0.5, X, 9, W.GB)
     torch.cuda.synchronize()
     assert (idx == torch.arange(9, device="cuda", dtype=torch.int32)).all() and (dist == 5.0).all()
+
+
+# hundreds of lists a query, merged from the lanes' first entries up to k = 52: neighbours spread over the lists, all in
+# one of them, at one place of every list (multiples of the stride of a lane's entries), and equal ones
+@pytest.mark.parametrize("k", [1, 2, 10, 51, 52, 53, 64])
+@pytest.mark.parametrize("place", ["spread", "one", "stride", "equal"])
+def test_merge_of_many_lists(K, oracle, k, place):
+    from parity import check
+    m, n, d = 3, 150_001, 12
+    print("case", k, place, flush=True)
+    Q, X = W.random_case(8900 + k, m, n, d)
+    near = {"one": slice(777, 777 + 40), "stride": slice(5, n, 4096)}.get(place)
+    if near is not None:
+        X[near] *= 1e-3
+        Q *= 1e-3
+    if place == "equal":
+        Q, X = Q.round(), X.round()
+    Qd, Xd = torch.from_numpy(Q).cuda(), torch.from_numpy(X).cuda()
+    idx, dist = K.knn_search(Qd, Xd, k, W.GB)
+    t_idx, t_dist = K.knn_search(Qd, Xd, k, K.knn_plan(m, n, d, k, W.GB).min_limit_bytes)
+    torch.cuda.synchronize()
+    o_idx, o_dist, o_next = oracle.knn(Q, X, k)
+    check(idx.cpu().numpy(), dist.cpu().numpy(), o_idx, o_dist, o_next, n)
+    assert torch.equal(idx, t_idx) and torch.equal(dist, t_dist)
