@@ -4,16 +4,22 @@
 //
 // K_ij = variance exp2(a_i . b_j - |a_i|^2 / 2 - |b_j|^2 / 2), a and b the rows of X and Z times sqrt(2 c2).  In
 // these units a value as two fp16 pieces, hi + lo, is off by 2^-23 of itself or 2^-25, whichever is larger;
-// three products of pieces (lo hi, hi lo, hi hi) stand for the six that three bf16 pieces need.  The norms are
-// those of the pieces, without the product of the low ones that the inner products leave out as well:
-// so the exponent is that of two slightly moved points, exactly 0 where they are the same one, and not
-// a difference of numbers that were rounded apart.  They are summed in fp64 and added last, as three
-// exact bf16 pieces each times one, by one more matrix instruction, which costs no vector instruction
-// and adds the largest numbers once.
+// the norms are those of the pieces (hi + lo)^2, so the exponent is that of two slightly moved points and not
+// a difference of numbers that were rounded apart.  Four products of pieces (lo lo, lo hi, hi lo, hi hi) stand for
+// the six that three bf16 pieces need.  The first is left out, per tile and wave, where the low pieces of every
+// point and row are below 2^-22 in the sum of their squares: then it moves an entry by less than 2^-22, and
+// points as close to the origin as that (some two lengthscales) have no pair so far apart that an entry of a
+// point with itself, where it is a loss and not a rounding, would be the whole of a sum.  Error against 64
+// bits in parts of the six-product kernel's (2000 x 2000, d = 9 .. 64, lengthscales 0.05 to 5 sqrt(d), means 0 to 100, clusters,
+// weights of one sign or both): 0.4 to 1.0 in the mean of each kind of data, at most 1.07 but for a fifth of the points a
+// thousand times as far out as the others (1.33).  Left out everywhere, and out of the norms: up to 2.2 off the origin.
+// The norms are summed in fp64 and added last, as three exact bf16 pieces each times one, by one more matrix
+// instruction, which costs no vector instruction and adds the largest numbers once.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
 #include <cstdint>
+#include <type_traits>
 
 #include "kmv_kernels.h"
 #include "knn_config.h"
@@ -34,8 +40,13 @@ typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 constexpr int kFragment = 1024;       // bytes: 32 points x 16 coordinates of one piece, in operand order
 constexpr float kMostHalf = 32768.f;  // coordinates beyond this go to the slow way
 constexpr float kFar = -1e30f;        // exponent of what pads the last tile
+constexpr float kSmallLow = 0x1p-22f;  // |low pieces|^2 of a point up to which their products are left out
 
-// Points of a tile: what two of its records in LDS leave room for four workgroups per compute unit.
+// of a tile's points, and of a wave's rows: |low|^2 <= kSmallLow for all, all in the pieces' range, neither
+enum Kind { kTileSmallLows, kTileFits, kTileOutOfRange };
+
+// Points of a tile: two of its records in LDS leave room for four workgroups per compute unit, as the registers do up to
+// 48 coordinates (beyond, for three).
 template <int NCH>
 constexpr int kTilePoints = NCH <= 2 ? 128 : 64;
 
@@ -47,8 +58,8 @@ struct Record {
     static constexpr int blocks = kTilePoints<NCH> / 32;
     static constexpr int norms_at = NCH * 2 * blocks * kFragment;
     static constexpr int weights_at = norms_at + blocks * 512;
-    static constexpr int flag_at = weights_at + kTilePoints<NCH> * 4;
-    static constexpr int bytes = (flag_at + 4 + kFragment - 1) / kFragment * kFragment;
+    static constexpr int kind_at = weights_at + kTilePoints<NCH> * 4;
+    static constexpr int bytes = (kind_at + 4 + kFragment - 1) / kFragment * kFragment;
 };
 
 __device__ __forceinline__ void split3(float x, __bf16& hi, __bf16& mid, __bf16& lo) {
@@ -58,38 +69,55 @@ __device__ __forceinline__ void split3(float x, __bf16& hi, __bf16& mid, __bf16&
     lo = (__bf16)(r - (float)mid);
 }
 
-// pieces, whether all are in their range (not so for a NaN), and the square of what they stand for
-__device__ __forceinline__ bool split2(const float (&x)[8], double scale, f16x8& hi, f16x8& lo, double& square) {
+// A coordinate a as two pieces: whether it is in their range (not so for a NaN), and what they stand for,
+// a itself where it is not.
+__device__ __forceinline__ bool split2(double a, _Float16& hi, _Float16& lo, double& stands) {
+    hi = (_Float16)(float)a;
+    const double high = (double)(float)hi;
+    lo = (_Float16)(float)(a - high);
+    const bool fits = fabs(a) <= (double)kMostHalf;
+    stands = fits ? high + (double)(float)lo : a;
+    return fits;
+}
+
+// the same of eight coordinates times `scale`, with the squares of what the pieces stand for and of the low ones
+__device__ __forceinline__ bool split2_row(const float (&x)[8], double scale, f16x8& hi, f16x8& lo, double& square,
+                                           float& low) {
     bool fits = true;
     square = 0.0;
+    low = 0.f;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-        const double a = scale * (double)x[e];
-        hi[e] = (_Float16)(float)a;
-        const double high = (double)(float)hi[e];
-        lo[e] = (_Float16)(float)(a - high);
-        const bool fit = fabs(a) <= (double)kMostHalf;
-        square += fit ? high * high + 2.0 * high * (double)(float)lo[e] : a * a;
-        fits &= fit;
+        _Float16 h, l;
+        double a;
+        fits &= split2(scale * (double)x[e], h, l, a);
+        hi[e] = h;
+        lo[e] = l;
+        square += a * a;
+        low = fmaf((float)l, (float)l, low);
     }
     return fits;
 }
 
-__device__ __forceinline__ void split3_row(const float (&x)[8], bf16x8& hi, bf16x8& mid, bf16x8& lo) {
+// three pieces of what the two pieces of eight coordinates times `scale` stand for
+__device__ __forceinline__ void split3_row(const float (&x)[8], double scale, bf16x8& hi, bf16x8& mid, bf16x8& lo) {
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
+        _Float16 h, l;
+        double stands;
+        split2(scale * (double)x[e], h, l, stands);
         __bf16 a, b, c;
-        split3(x[e], a, b, c);
+        split3((float)stands, a, b, c);
         hi[e] = a;
         mid[e] = b;
         lo[e] = c;
     }
 }
 
-// coordinates t0 .. t0 + 7 of a row, times `scale`; zeros past d and for rows that are not there
-__device__ __forceinline__ void load8(const float* __restrict__ row, bool there, int t0, int d, float scale, float (&x)[8]) {
+// coordinates t0 .. t0 + 7 of a row; zeros past d and for rows that are not there
+__device__ __forceinline__ void load8(const float* __restrict__ row, bool there, int t0, int d, float (&x)[8]) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) x[e] = there && t0 + e < d ? row[t0 + e] * scale : 0.f;
+    for (int e = 0; e < 8; ++e) x[e] = there && t0 + e < d ? row[t0 + e] : 0.f;
 }
 
 // One workgroup per tile.
@@ -100,19 +128,18 @@ __global__ __launch_bounds__(256) void kmv_records_kernel(const float* __restric
     using R = Record<NCH>;
     constexpr int TP = kTilePoints<NCH>, G = 2 * NCH;  // groups of 8 coordinates
     __shared__ double squares[TP][G + 1];
-    __shared__ int bad;
+    __shared__ float lows[TP][G + 1];
+    __shared__ int kind;
     unsigned char* __restrict__ out = records + (int64_t)blockIdx.x * R::bytes;
-    if (threadIdx.x == 0) bad = 0;
+    if (threadIdx.x == 0) kind = kTileSmallLows;
     __syncthreads();
     for (int k = threadIdx.x; k < TP * G; k += 256) {
         const int point = k / G, g = k % G;
         const int64_t j = (int64_t)blockIdx.x * TP + point;
         float x[8];
-        load8(Z + (j < m ? j : 0) * ldz, j < m, g * 8, d, 1.f, x);
+        load8(Z + (j < m ? j : 0) * ldz, j < m, g * 8, d, x);
         f16x8 hi, lo;
-        double square;
-        if (!split2(x, scale, hi, lo, square)) bad = 1;
-        squares[point][g] = square;
+        if (!split2_row(x, scale, hi, lo, squares[point][g], lows[point][g])) atomicMax(&kind, kTileOutOfRange);
         unsigned char* at = out + ((g >> 1) * 2 * R::blocks + (point >> 5)) * kFragment + (g & 1) * 512 + (point & 31) * 16;
         *reinterpret_cast<f16x8*>(at) = hi;
         *reinterpret_cast<f16x8*>(at + R::blocks * kFragment) = lo;
@@ -121,8 +148,13 @@ __global__ __launch_bounds__(256) void kmv_records_kernel(const float* __restric
     if ((int)threadIdx.x < TP) {
         const int64_t j = (int64_t)blockIdx.x * TP + threadIdx.x;
         double sq = 0.0;
+        float low = 0.f;
 #pragma unroll
-        for (int g = 0; g < G; ++g) sq += squares[threadIdx.x][g];
+        for (int g = 0; g < G; ++g) {
+            sq += squares[threadIdx.x][g];
+            low += lows[threadIdx.x][g];
+        }
+        if (!(low <= kSmallLow)) atomicMax(&kind, kTileFits);
         bf16x8 norm;
         __bf16 hi, mid, lo;
         split3(j < m ? fmaxf((float)(-0.5 * sq), -3e38f) : kFar, hi, mid, lo);
@@ -134,7 +166,8 @@ __global__ __launch_bounds__(256) void kmv_records_kernel(const float* __restric
         *reinterpret_cast<bf16x8*>(out + R::norms_at + threadIdx.x * 16) = norm;
         *reinterpret_cast<float*>(out + R::weights_at + threadIdx.x * 4) = j < m ? v[j] : 0.f;
     }
-    if (threadIdx.x == 0) *reinterpret_cast<int*>(out + R::flag_at) = bad;
+    __syncthreads();
+    if (threadIdx.x == 0) *reinterpret_cast<int*>(out + R::kind_at) = kind;
 }
 
 // One wave's 64 x 16 bytes from memory, base + the lane's offset, into LDS at m in lane order.
@@ -152,12 +185,14 @@ __device__ __forceinline__ void load_to_lds(const unsigned char* base, unsigned 
 // rounding left above 0 gives 1: the result of exp2 is clamped to [0, 1].
 //
 // A tile with a coordinate out of range, and rows with one, take the products of three bf16 pieces, made from
-// memory on the way.  So far from the origin (2e4 lengthscales) the expansion has no digits left in fp32.
+// memory on the way, of what the two pieces stand for where they are in range.  So far from the origin (2e4
+// lengthscales) the expansion has no digits left in fp32.
 //
-// Bound by the power of the matrix and vector units together: at n = m = 200000, d = 32 7.9 ms (14.3 with
+// Bound by the power of the matrix and vector units together: at n = m = 200000, d = 32 7.8 ms (14.2 with
 // three bf16 pieces cut in every workgroup, kmv_mfma_kernel), at a clock of 1.4 GHz that both keep busy for
 // about 70 % of its cycles (seven matrix instructions and 33 vector instructions, 16 of them exp2, per 1024 entries and
-// wave); one more product of pieces (lo lo) made it 9.5 ms.
+// wave).  With the lo lo products in every tile 9.0 ms; n = m = 1e5, lengthscale 0.3 sqrt(d), where every tile has them, d = 9 / 17 / 64
+// 1.48 / 2.12 / 4.43 ms against 2.31 / 3.63 / 7.14 by kmv_mfma_kernel.
 // ---------------------------------------------------------------------------------------
 template <int NCH>
 __global__ __launch_bounds__(256) void kmv_pieces_kernel(const float* __restrict__ X, int64_t ldx,
@@ -189,17 +224,22 @@ __global__ __launch_bounds__(256) void kmv_pieces_kernel(const float* __restrict
     f16x8 bh[NCH], bl[NCH];
     bf16x8 norm;
     bool fits = true;
+    double sum = 0.0;
+    float low = 0.f;
     {
         double sq = 0.0;
 #pragma unroll
         for (int c = 0; c < NCH; ++c) {
             float x[8];
             double square;
-            load8(xp, true, c * 16 + h * 8, d, 1.f, x);
-            fits &= split2(x, scale, bh[c], bl[c], square);
+            float part;
+            load8(xp, true, c * 16 + h * 8, d, x);
+            fits &= split2_row(x, scale, bh[c], bl[c], square, part);
             sq += square;
+            low += part;
         }
         sq += __shfl_xor(sq, 32);
+        low += __shfl_xor(low, 32);
         __bf16 hi, mid, lo;
         split3(fmaxf((float)(-0.5 * sq), -3e38f), hi, mid, lo);
         const __bf16 one = (__bf16)(h ? 0.f : 1.f), zero = (__bf16)0.f;  // the upper half wave's coordinates 8 .. 15: none
@@ -209,9 +249,8 @@ __global__ __launch_bounds__(256) void kmv_pieces_kernel(const float* __restrict
         norm[5] = h ? zero : lo;
         norm[6] = norm[7] = zero;
     }
-    const bool rows_fit = __ballot(!fits) == 0;
+    const int rows_kind = __ballot(!fits) ? kTileOutOfRange : __ballot(!(low <= kSmallLow)) ? kTileFits : kTileSmallLows;
 
-    double sum = 0.0;
     for (int tile = 0; tile < count; ++tile) {
         const int buf = tile & 1;
         // this tile's record is in LDS, and every wave is through with the other one
@@ -221,7 +260,7 @@ __global__ __launch_bounds__(256) void kmv_pieces_kernel(const float* __restrict
         const unsigned char* frag = rec + lane * 16;
         const unsigned char* norms = rec + R::norms_at + i32 * 16;
         const float* weights = reinterpret_cast<const float*>(rec + R::weights_at) + h * 4;
-        const bool usual = rows_fit && __builtin_amdgcn_readfirstlane(*reinterpret_cast<const int*>(rec + R::flag_at)) == 0;
+        const int kind = max(rows_kind, __builtin_amdgcn_readfirstlane(*reinterpret_cast<const int*>(rec + R::kind_at)));
         float part = 0.f;
         auto add = [&](const f32x16& arg, int block) {
 #pragma unroll
@@ -232,7 +271,7 @@ __global__ __launch_bounds__(256) void kmv_pieces_kernel(const float* __restrict
                     part = fmaf(__builtin_amdgcn_fmed3f(__builtin_amdgcn_exp2f(arg[g * 4 + e]), 0.f, 1.f), w[e], part);
             }
         };
-        if (usual) {
+        auto blocks = [&](auto low_product) {
             auto products = [&](int block) {
                 f32x16 acc;
 #pragma unroll
@@ -242,6 +281,8 @@ __global__ __launch_bounds__(256) void kmv_pieces_kernel(const float* __restrict
                 for (int c = 0; c < NCH; ++c) {
                     ah[c] = *reinterpret_cast<const f16x8*>(frag + (c * 2 * NB + block) * kFragment);
                     const f16x8 al = *reinterpret_cast<const f16x8*>(frag + (c * 2 * NB + NB + block) * kFragment);
+                    if constexpr (decltype(low_product)::value)
+                        acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(al, bl[c], acc, 0, 0, 0);
                     acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(al, bh[c], acc, 0, 0, 0);
                     acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah[c], bl[c], acc, 0, 0, 0);
                 }
@@ -258,6 +299,11 @@ __global__ __launch_bounds__(256) void kmv_pieces_kernel(const float* __restrict
                 add(now, block);
                 now = next;
             }
+        };
+        if (kind == kTileSmallLows) {
+            blocks(std::false_type{});
+        } else if (kind == kTileFits) {
+            blocks(std::true_type{});
         } else {
             for (int block = 0; block < NB; ++block) {
                 f32x16 acc;
@@ -267,10 +313,10 @@ __global__ __launch_bounds__(256) void kmv_pieces_kernel(const float* __restrict
                 for (int c = 0; c < NCH; ++c) {
                     float x[8];
                     bf16x8 a[3], b[3];
-                    load8(Z + (j < m ? j : 0) * ldz, j < m, c * 16 + h * 8, d, (float)scale, x);
-                    split3_row(x, a[0], a[1], a[2]);
-                    load8(xp, true, c * 16 + h * 8, d, (float)scale, x);
-                    split3_row(x, b[0], b[1], b[2]);
+                    load8(Z + (j < m ? j : 0) * ldz, j < m, c * 16 + h * 8, d, x);
+                    split3_row(x, scale, a[0], a[1], a[2]);
+                    load8(xp, true, c * 16 + h * 8, d, x);
+                    split3_row(x, scale, b[0], b[1], b[2]);
                     acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[2], b[0], acc, 0, 0, 0);
                     acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], b[2], acc, 0, 0, 0);
                     acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1], b[1], acc, 0, 0, 0);

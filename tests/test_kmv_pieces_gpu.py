@@ -2,7 +2,7 @@
 of the pieces' range, against the fp64 oracle.
 
 Tolerance (eps = 2^-24, c = 1 / (2 l^2)): a coordinate in exponent units is moved by at most 2 eps of itself or 2 eps,
-so an exponent by 2 eps (|a| + |b|) (|a - b| + sqrt(d)); the sums of products and the norms round a few times at
+so an exponent by 2 eps (|a| + |b|) (|a - b| + sqrt(d)), and by 4 eps where a product is left out; the sums of products and the norms round a few times at
 (|a| + |b|)^2 / 2: together within (d + 8) eps (sqrt(c) (|x| + |z|) + 1)^2.  Sums of at most 64 entries in fp32 and
 exp2's last bit add 4e-6 of the magnitudes."""
 import numpy as np
@@ -59,12 +59,47 @@ def test_matches_oracle(oracle, case, wide):
     assert np.array_equal(y, run(X, Z, v, lengthscale))
 
 
-def test_a_point_with_itself_is_one():
-    # the norms are those of the pieces, so the exponent of a point with itself has no rounding of the inputs in it
-    X, _, _ = W.random_kmv_case(5, 100, 1, 30)
-    X *= 50.0  # nothing else is near: 50 lengthscales apart and more
-    y = run(X, X, np.ones(100, np.float32), 1.0)
-    assert np.allclose(y, 1.5, rtol=30 * EPS * (X.astype(np.float64) ** 2).sum(1).max())
+@pytest.mark.parametrize("far", [False, True], ids=["usual", "beside_a_far_point"])
+def test_products_and_norms_are_of_the_same_points(far):
+    # Everything up to the exponential is exact here: the lengthscale makes the unit of the pieces that of the
+    # coordinates, 32 + 2^-6 takes both pieces, its square and the norms fit fp32.  The product of the low pieces is 2^-12:
+    # left out of the products or of the norms alone it moves an entry by 1e-4.  exp2's last bit and the sum: 4 eps.
+    d = 30
+    X = np.zeros((d, d), np.float32)
+    X[np.arange(d), np.arange(d)] = 32 + 2.0 ** -6
+    Z = X.copy()
+    Z[np.arange(d), (np.arange(d) + 1) % d] = 1.0
+    v = np.ones(d, np.float32)
+    lengthscale = float(np.sqrt(np.log2(np.e)))
+    if far:  # its tile takes the products of three pieces
+        Z = np.concatenate([Z, np.full((1, d), 1e5, np.float32)])
+        v = np.append(v, np.float32(1))
+    assert np.allclose(run(X, X, np.ones(d, np.float32), lengthscale), 1.5, rtol=4 * EPS, atol=0)
+    assert np.allclose(run(X, Z, v, lengthscale), 1.5 * 2.0 ** -0.5, rtol=4 * EPS, atol=0)
+
+
+@pytest.mark.parametrize("d", [9, 16, 24, 32, 64])
+@pytest.mark.parametrize("wide", [0.6, 1.5])
+@pytest.mark.parametrize("mean", [0.0, 1.0, 10.0, 100.0])
+def test_errors_are_those_of_six_products(oracle, d, wide, mean):
+    """Against 64 bits, weights of one sign (a loss that all entries share does not average out): no more than the kernel
+    that the plan's workspace leads to, whose six products of bf16 pieces are those of fp32.  Both errors are roundings
+    that a seed draws: 1.15 for what is left of that over three seeds of 300 rows."""
+    import paper_2206_14148_amd as K
+
+    lengthscale, n, m = wide * d ** 0.5, 300, 2_000
+    small = torch.empty(K.kmv_plan(n, m, d, W.GB).workspace_bytes, dtype=torch.uint8, device="cuda")
+    assert small.numel() < K.load().kmv_workspace_bytes(n, m, d, lengthscale, W.GB)
+    errors = np.zeros(2)
+    for seed in range(3):
+        rng = np.random.default_rng(seed)
+        Z = (mean + rng.standard_normal((m, d))).astype(np.float32)
+        v = (rng.random(m) + 0.5).astype(np.float32)
+        ref = oracle.kmv(Z[:n], Z, v, 1.5, lengthscale)
+        for i, ws in enumerate((small, None)):
+            errors[i] += np.linalg.norm(run(Z[:n].copy(), Z, v, lengthscale, workspace=ws) - ref) / np.linalg.norm(ref)
+    print("  six products %.2e  pieces %.2e" % tuple(errors / 3), flush=True)
+    assert errors[1] <= 1.15 * errors[0]
 
 
 @pytest.mark.parametrize("d", [12, 40])
