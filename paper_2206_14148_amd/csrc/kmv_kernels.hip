@@ -282,7 +282,8 @@ __global__ __launch_bounds__(256, 2) void kmv_mfma_kernel(
             const int64_t jj = (int64_t)j0 + (int64_t)tile * TZ + tid;
             // points past the range: exponent -inf and weight 0, so they add exactly 0
             zns[(tile & 1) * TZ + tid] = jj < j1 ? g.znv : -kInf;
-            vs[(tile & 1) * TZ + tid] = jj < j1 ? g.vv : 0.f;
+            // (a point with a NaN: entries of 0 below, and so its weight makes every sum a NaN)
+            vs[(tile & 1) * TZ + tid] = jj >= j1 ? 0.f : g.znv != g.znv ? g.znv : g.vv;
         }
     };
 
@@ -366,8 +367,9 @@ __global__ __launch_bounds__(256, 2) void kmv_mfma_kernel(
                     const f32x4 w = *reinterpret_cast<const f32x4*>(vt + pb * 32 + g * 8 + h * 4);
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
-                        const float arg = fminf(acc[pb][g * 4 + e] + nxn, 0.f);
-                        part = fmaf(__builtin_amdgcn_exp2f(arg), w[e], part);
+                        // (an exponent that rounding left above 0 gives 1, a NaN, of an infinite coordinate, 0)
+                        const float entry = __builtin_amdgcn_exp2f(acc[pb][g * 4 + e] + nxn);
+                        part = fmaf(__builtin_amdgcn_fmed3f(entry, 0.f, 1.f), w[e], part);
                     }
                 }
             }
@@ -413,6 +415,7 @@ __global__ __launch_bounds__(256, 2) void kmv_mfma_kernel(
             }
         }
     }
+    if (nxn != nxn) sum = nxn;  // a row with a NaN
     const double other = __shfl_xor(sum, 32);
     if (active && h == 0) out[(int64_t)s * n + r] = variance * (sum + other);
 }

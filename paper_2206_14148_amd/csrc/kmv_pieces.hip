@@ -164,7 +164,8 @@ __global__ __launch_bounds__(256) void kmv_records_kernel(const float* __restric
         norm[3] = norm[4] = norm[5] = (__bf16)1.f;
         norm[6] = norm[7] = (__bf16)0.f;
         *reinterpret_cast<bf16x8*>(out + R::norms_at + threadIdx.x * 16) = norm;
-        *reinterpret_cast<float*>(out + R::weights_at + threadIdx.x * 4) = j < m ? v[j] : 0.f;
+        // (a point with a NaN: entries of 0 below, and so its weight makes every sum a NaN)
+        *reinterpret_cast<float*>(out + R::weights_at + threadIdx.x * 4) = j >= m ? 0.f : sq != sq ? (float)sq : v[j];
     }
     __syncthreads();
     if (threadIdx.x == 0) *reinterpret_cast<int*>(out + R::kind_at) = kind;
@@ -182,7 +183,7 @@ __device__ __forceinline__ void load_to_lds(const unsigned char* base, unsigned 
 // range of tiles through LDS (two records, loaded directly).  Points are the M side, rows the N side, so
 // the 16 values a lane holds of a 32 x 32 block belong to one row: it takes their exponentials, times the
 // points' weights, into one fp32 sum per tile and half wave, and those into an fp64 sum.  An exponent that
-// rounding left above 0 gives 1: the result of exp2 is clamped to [0, 1].
+// rounding left above 0 gives 1: the result of exp2 is clamped to [0, 1], a NaN (of an infinite coordinate) to 0.
 //
 // A tile with a coordinate out of range, and rows with one, take the products of three bf16 pieces, made from
 // memory on the way, of what the two pieces stand for where they are in range.  So far from the origin (2e4
@@ -224,7 +225,7 @@ __global__ __launch_bounds__(256) void kmv_pieces_kernel(const float* __restrict
     f16x8 bh[NCH], bl[NCH];
     bf16x8 norm;
     bool fits = true;
-    double sum = 0.0;
+    double sum = 0.0;  // (from a NaN on where the row has one: its entries come out as 0)
     float low = 0.f;
     {
         double sq = 0.0;
@@ -240,6 +241,7 @@ __global__ __launch_bounds__(256) void kmv_pieces_kernel(const float* __restrict
         }
         sq += __shfl_xor(sq, 32);
         low += __shfl_xor(low, 32);
+        if (sq != sq) sum = sq;
         __bf16 hi, mid, lo;
         split3(fmaxf((float)(-0.5 * sq), -3e38f), hi, mid, lo);
         const __bf16 one = (__bf16)(h ? 0.f : 1.f), zero = (__bf16)0.f;  // the upper half wave's coordinates 8 .. 15: none

@@ -114,3 +114,27 @@ def test_rows_and_points_out_of_range(oracle, d):
     near[[200, 201]] = False  # entries of exactly 0 for every row, out of the bound's formula
     assert y[40] == 0.0 and ref[40] == 0.0
     assert (np.abs(y - ref)[keep] <= bound(X[keep], Z[near], v[near], 3.0)).all()
+
+
+@pytest.mark.parametrize("roomy", [True, False], ids=["pieces", "plan"])
+@pytest.mark.parametrize("d", [9, 20, 64, 100])
+def test_nans_show_and_infinite_coordinates_are_far(oracle, d, roomy):
+    # as with up to 8 coordinates: a NaN row gives NaN, a NaN point makes every sum NaN, an entry of a point at
+    # infinity with one that is not is 0; whatever the workspace
+    import paper_2206_14148_amd as K
+
+    X, Z, v = W.random_kmv_case(78, 300, 500, d)
+    lengthscale = 0.5 * d ** 0.5
+    size = (K.load().kmv_workspace_bytes(300, 500, d, lengthscale, W.GB) if roomy
+            else K.kmv_plan(300, 500, d, W.GB).workspace_bytes)
+    assert roomy or d > 64 or size < K.load().kmv_workspace_bytes(300, 500, d, lengthscale, W.GB)
+    ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+    X[40, 3], X[41, 0], X[299, d - 1], Z[200, d - 1], Z[201] = np.nan, np.inf, -np.inf, -np.inf, np.inf
+    y = run(X, Z, v, lengthscale, workspace=ws)
+    keep, near = np.ones(300, bool), np.ones(500, bool)
+    keep[[40, 41, 299]], near[[200, 201]] = False, False
+    assert np.isnan(y[40]) and (y[[41, 299]] == 0).all()
+    ref = oracle.kmv(X[keep], Z[near], v[near], 1.5, lengthscale)
+    assert (np.abs(y[keep] - ref) <= bound(X[keep], Z[near], v[near], lengthscale)).all()
+    Z[499, 1] = np.nan
+    assert np.isnan(run(X, Z, v, lengthscale, workspace=ws)).all()
