@@ -218,6 +218,12 @@ constexpr int kFewMergeWaves = 8;
 // what is left almost nothing comes before its last: one or two merges in place of one every 64 entries.
 // Whole calls, us before / now: 16 x 1e5, d = 50, k = 10 (391 lists a query) 86.1 / 71.3, k = 50 177 / 161; 1 x 1e6,
 // d = 32, k = 10 97.9 / 65.7.  (At k = 64 the last of 64 such entries bounds little: 210 / 215.)
+// Not where a lane has few entries in all (three, or k / 8): 1 x 23041, d = 16, k = 8 28.3 against 25.5 without, 64 x 23041,
+// k = 16 70.7 against 67.9.  The runs are turned against each other so that a lane's entries have places in their
+// lists that lie 3 k / 8 apart: where k divides the 512 entries between them they would have the same place, and
+// the first ones fill the list with last places.  As they lie / turned / without first ones: 1 x 6e4, d = 16, k = 32 87.1 / 49.7 /
+// 83.7; 18 x 2e5, k = 16 111.5 / 84.3 / 109.1, k = 44 143 / 166 / 170, k = 51 191 / 158 / 182; 80 sizes of each k of sixteen from 1 to 51
+// in the mean 83.5 / 81.9 / 89.
 constexpr int kFewMergeLoads = 8;
 constexpr int kFewMergeFirstK = 52;
 __global__ __launch_bounds__(64 * kFewMergeWaves) void knn_merge_refine_few_kernel(
@@ -262,6 +268,7 @@ __global__ __launch_bounds__(64 * kFewMergeWaves) void knn_merge_refine_few_kern
     const float* rk = lk + (size_t)r * S * k;
     const int* ri = li + (size_t)r * S * k;
     const int total = S * k;
+    const int turn = ((3 * k + 4) / 8 + k - NW * kWave % k) % k & (kWave - 1);
     const int one = wave * kWave + lane;
     if (total <= NW * kWave) take(one < total ? rk[one] : kInf, one < total ? ri[one] : kNoIdx);
     else for (int e0 = wave * kWave; e0 < total; e0 += kFewMergeLoads * NW * kWave) {
@@ -269,11 +276,11 @@ __global__ __launch_bounds__(64 * kFewMergeWaves) void knn_merge_refine_few_kern
         int id[kFewMergeLoads];
 #pragma unroll
         for (int u = 0; u < kFewMergeLoads; ++u) {
-            const int e = e0 + u * NW * kWave + lane;
+            const int e = e0 + u * NW * kWave + ((lane + u * turn) & (kWave - 1));
             key[u] = e < total ? rk[e] : kInf;
             id[u] = e < total ? ri[e] : kNoIdx;
         }
-        if (k <= kFewMergeFirstK) {
+        if (k <= kFewMergeFirstK && total - e0 > max(3, k / 8) * NW * kWave) {
             int at = 0;
             float best = key[0];
             int best_id = id[0];

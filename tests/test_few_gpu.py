@@ -78,3 +78,17 @@ def test_merge_of_many_lists(K, oracle, k, place):
     o_idx, o_dist, o_next = oracle.knn(Q, X, k)
     check(idx.cpu().numpy(), dist.cpu().numpy(), o_idx, o_dist, o_next, n)
     assert torch.equal(idx, t_idx) and torch.equal(dist, t_dist)
+
+
+# a few entries a lane, and their line to the lanes' first ones (three runs of 512 entries, or k / 8); k that divide 512, whose
+# entries of a lane would be of one place, and others
+@pytest.mark.parametrize("m,n,k", [(1, 16_000, 8), (3, 50_001, 8), (2, 23_041, 16), (1, 13_000, 32), (18, 60_000, 32),
+                                   (5, 10_000, 44), (3, 40_000, 44), (4, 100_003, 48), (1, 33_000, 2)])
+def test_merge_where_a_lane_has_few_entries(K, oracle, m, n, k):
+    from parity import check
+    print("case", m, n, k, flush=True)
+    Q, X = W.random_case(9000 + k, m, n, 16)
+    idx, dist = K.knn_search(torch.from_numpy(Q).cuda(), torch.from_numpy(X).cuda(), k, W.GB)
+    torch.cuda.synchronize()
+    o_idx, o_dist, o_next = oracle.knn(Q, X, k)
+    check(idx.cpu().numpy(), dist.cpu().numpy(), o_idx, o_dist, o_next, n)
