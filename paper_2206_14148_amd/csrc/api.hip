@@ -265,7 +265,9 @@ knn_status run_search(const knn_plan_t& plan, const float* Q, int64_t ldq, const
         if (e == hipSuccess && copy_now)  // (as always on path 6 with the cosine metric)
             e = launch_pack_operands(X, ldx, n, d, 0, (int64_t)n64, xp, stream, 1.f, xn, hdr, cosine);
         else if (e == hipSuccess)
-            e = launch_row_norms(X, ldx, n, d, cosine, xn, stream, hdr);
+            // (path 5 needs no maxima with the cosine metric, and every workgroup raising them at once is 4 us: 3 x 1e4,
+            // d = 100 71.1 us with, 64.3 without)
+            e = launch_row_norms(X, ldx, n, d, cosine, xn, stream, cosine && !packed_plan ? nullptr : hdr);
         if (e == hipSuccess && packed_plan && cosine) e = launch_fill_words(sum0, (int64_t)n64, 0u, stream);
         if (e == hipSuccess && packed_plan) e = launch_pad_norms(sum0, n, stream);
         if (e != hipSuccess) {
