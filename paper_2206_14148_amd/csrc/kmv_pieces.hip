@@ -32,6 +32,7 @@ namespace {
 using knn::f32x16;
 using knn::f32x4;
 using knn::load_row4;
+using knn::load_to_lds;
 using knn::mask_row4;
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -169,13 +170,6 @@ __global__ __launch_bounds__(256) void kmv_records_kernel(const float* __restric
     }
     __syncthreads();
     if (threadIdx.x == 0) *reinterpret_cast<int*>(out + R::kind_at) = kind;
-}
-
-// One wave's 64 x 16 bytes from memory, base + the lane's offset, into LDS at m in lane order.
-__device__ __forceinline__ void load_to_lds(const unsigned char* base, unsigned offset, unsigned m) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :
-                 : "s"(__builtin_amdgcn_readfirstlane(m)), "v"(offset), "s"(base)
-                 : "memory");
 }
 
 // ---------------------------------------------------------------------------------------

@@ -388,6 +388,15 @@ __device__ __forceinline__ f32x4 mask_row4(f32x4 v, bool row_ok, int col, int d,
     for (int e = 0; e < 4; ++e) v[e] = (row_ok && col + e < d) ? v[e] * scale : 0.f;
     return v;
 }
+// One wave's 64 x 16 bytes from memory, base + the lane's offset, into LDS at m in lane order, without registers
+// in between.  base and m: the same for all lanes.  (Counted by vmcnt: the caller waits.)
+__device__ __forceinline__ void load_to_lds(const unsigned char* base, unsigned offset, unsigned m) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                 :
+                 : "s"(__builtin_amdgcn_readfirstlane(m)), "v"(offset), "s"(base)
+                 : "memory", "m0");
+}
+
 // *word = max(*word, value).  Many workgroups raise the same word, and the memory takes one such request after
 // the other (some 12 ns each: 4096 of them made a maximum of 1e6 norms 48 us): most find it raised already.
 __device__ __forceinline__ void raise_word(unsigned* word, unsigned value) {
