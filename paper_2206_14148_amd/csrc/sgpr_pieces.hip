@@ -14,7 +14,6 @@
 
 #include <cmath>
 #include <cstdint>
-#include <utility>
 
 #include "knn_config.h"
 #include "knn_device.h"
@@ -26,6 +25,7 @@ namespace {
 
 using knn::f32x16;
 using knn::f32x4;
+using knn::load_to_lds;
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -270,22 +270,6 @@ struct Shares {
     }
 };
 
-// One wave's 64 x 16 bytes from memory, base + the lane's offset, into LDS at m + MORE in lane order,
-// without registers in between.  base and m: the same for all lanes.
-template <int MORE>
-__device__ __forceinline__ void load_to_lds(const unsigned char* base, unsigned offset, unsigned m) {
-    asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                 :
-                 : "s"(m), "v"(offset), "s"(base), "n"(MORE)
-                 : "memory", "scc");
-}
-
-template <int N, int... L>
-__device__ __forceinline__ void load_all(const unsigned char* base, const unsigned (&offset)[N], unsigned m,
-                                         std::integer_sequence<int, L...>) {
-    (load_to_lds<L * 4 * kFragment>(base, offset[L], m), ...);
-}
-
 // ---------------------------------------------------------------------------------------
 // Chunk product.  Stages of 16 columns go from memory into LDS directly, kStages deep.  A wave holds 64 x
 // 64 entries of the tile: per stage four operands of each piece from LDS (conflict free: 64 lanes read
@@ -299,8 +283,14 @@ __device__ __forceinline__ void load_all(const unsigned char* base, const unsign
 // total by an addition whose rounding error goes to the small ones, which are 2^8 or more below it, so
 // the error does not grow with the chunk.
 //
-// Bound by the matrix cores: 1.10 PFLOP/s of fp16 products, 1.15 of bf16 (m = 4000); a large
+// Bound by the matrix cores: 1.10 PFLOP/s of fp16 products, 1.25 of bf16 (m = 4000); a large
 // product of the vendor's library reaches 1.21 here.
+//
+// Registers: 192 accumulators and 48 of operands of the 256 a lane may have.  So the operands of a run's first stage
+// are read after the additions of the run before, and where a fragment lies is kept in scalars: with both in
+// vector registers 87 were spilled, to private memory outside the workspace (252 bytes a lane, 33 MB).  Whole calls with
+// and without the spills, ms: 4000 inducing points, 2e6 rows of 11 101.7 / 101.6, as three pieces 182.3 / 167.5; 10000, 5e5
+// of 3 293.5 / 257.1; 300, 1e5 of 11 0.257 / 0.241.
 // ---------------------------------------------------------------------------------------
 template <int NP>
 struct Pieces;
@@ -383,7 +373,7 @@ __device__ __forceinline__ void multiply_tiles(const ProductArgs& g, double scal
             if (first) {
                 int r, c;
                 tile_at(tile, m, r, c);
-                for (int e = threadIdx.x; e < kTile * kTile; e += 256) {
+                for (int e = wave * 64 + lane; e < kTile * kTile; e += 256) {
                     const int row = r * kTile + e / kTile, col = c * kTile + e % kTile;
                     if (!into_a)
                         buffer[e] = 0.0;
@@ -395,21 +385,22 @@ __device__ __forceinline__ void multiply_tiles(const ProductArgs& g, double scal
         }
         int r, c;
         tile_at(tile, m, r, c);
+        r = __builtin_amdgcn_readfirstlane(r);
+        c = __builtin_amdgcn_readfirstlane(c);
 
-        // fragments that this wave loads: wave, wave + 4, ... of a stage's [piece][row blocks, column blocks]
-        const int64_t step_bytes = (int64_t)g.row_blocks * kFragment;  // from one (16 columns, piece) to the next
+        // from one (16 columns, piece) to the next
+        const int64_t step_bytes = (int64_t)g.row_blocks * kFragment;
         const unsigned char* base = g.fragments + (int64_t)s0 * NP * step_bytes;
-        unsigned from_at[kLoads];
-#pragma unroll
-        for (int l = 0; l < kLoads; ++l) {
-            const int f = wave + 4 * l, kp = f / kFrags, in = f % kFrags;
-            const int block = in < kSide ? r * kSide + in : c * kSide + in - kSide;
-            from_at[l] = (unsigned)(kp * step_bytes) + block * kFragment + lane_bytes;
-        }
+        // this wave's fragments: wave, wave + 4, ... of a stage's [piece][row blocks, column blocks]
         auto request = [&](int stage, unsigned buf) {  // stage from s0
             const unsigned char* from = base + (int64_t)stage * NP * step_bytes;
             const unsigned to = lds + buf + wave * kFragment;
-            load_all(from, from_at, to, std::make_integer_sequence<int, kLoads>{});
+#pragma unroll
+            for (int l = 0; l < kLoads; ++l) {
+                const int piece = 4 * l / kFrags, in = wave + 4 * l - piece * kFrags;
+                const int block = in < kSide ? r * kSide + in : c * kSide + in - kSide;
+                load_to_lds(from + piece * step_bytes + (int64_t)block * kFragment, lane_bytes, to + 4 * l * kFragment);
+            }
         };
 
         vec a[WR][NP], b[2][NP];
@@ -457,20 +448,21 @@ __device__ __forceinline__ void multiply_tiles(const ProductArgs& g, double scal
         for (int ahead = 0; ahead < kStages<NP>; ++ahead)  // past the end: a harmless second load
             request(min(ahead, count - 1), ahead * kStageBytes);
         asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"((kStages<NP> - 1) * kLoads) : "memory");
-        operands(0);
 
         int stage = 0;
         while (stage < count) {
             const int run_end = min(stage + kRun, count);
-            do {
+            operands(buf);  // (none is kept over the additions below: their registers are needed there)
+            for (;;) {
                 const unsigned next = buf + kStageBytes == kStages<NP> * kStageBytes ? 0 : buf + kStageBytes;
                 multiply();
                 // the next stage is in LDS, and every wave has read the whole of this one
                 asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((kStages<NP> - 2) * kLoads) : "memory");
                 request(min(stage + kStages<NP>, count - 1), buf);
-                operands(next);
                 buf = next;
-            } while (++stage < run_end);
+                if (++stage == run_end) break;
+                operands(buf);
+            }
 #pragma unroll
             for (int block = 0; block < 2 * WR; ++block) drain(block);
         }
