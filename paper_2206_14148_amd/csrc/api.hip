@@ -185,14 +185,7 @@ knn_status run_search(const knn_plan_t& plan, const float* Q, int64_t ldq, const
     float* xn = reinterpret_cast<float*>(ws);
     // path 5: [squared norms][header: their maximum] | [split queries][query norms][shared
     // thresholds] | lists; L1 path: [transposed queries] | lists
-    // A wide plan's room holds what path 5 needs.  Its kernel is the better one for lists of one or two and rows that are
-    // not long, where there are a few tiles of queries: too few workgroups for path 7's tiles of 512, and little to gain
-    // from its thresholds.  (m = 1000, us here / on path 7, by n, d, k: 150001, 259, 1 970 / 1371; 150001, 399, 1 1391 /
-    // 1657; 150001, 301, 2 1240 / 1536; 450000, 301, 1 1786 / 2038; but 150001, 515, 1 1720 / 1600, 450000, 301, 3 2256 /
-    // 2124; m = 1500 70001, 301, 1 1052 / 1184, 300000, 301, 1 2065 / 1792; m = 257 200000, 301, 3 1579 / 1278.)
-    const bool short_lists = d + 64 * (k - 1) <= 420 && m > 256 &&
-                             ((m <= 1024 && n <= 500000) || (m <= 1536 && n <= 160000)) && !block_d64;
-    const bool wide_plan = plan.path == KNN_PATH_MFMA_WIDE && !short_lists;
+    const bool wide_plan = plan.path == KNN_PATH_MFMA_WIDE;
     const bool packed_plan = plan.path == KNN_PATH_MFMA_PACKED || wide_plan;
     const uint64_t n64 = ((uint64_t)n + kPkStep - 1) / kPkStep * kPkStep;
     unsigned char* hdr = ws + align_up((packed_plan ? n64 : (uint64_t)n) * 4);
@@ -200,7 +193,7 @@ knn_status run_search(const knn_plan_t& plan, const float* Q, int64_t ldq, const
     unsigned char* qs = ws + plan.norms_bytes;
     // (path 7: the B operands in operand order, rows rounded up to 64, chunks to an even count)
     const uint64_t qs_bytes =
-        plan.path == KNN_PATH_MFMA_WIDE ? ((uint64_t)plan.chunk_rows + 63) / 64 * 64 * 32 * (uint64_t)pk_padded_chunks(d)
+        wide_plan ? ((uint64_t)plan.chunk_rows + 63) / 64 * 64 * 32 * (uint64_t)pk_padded_chunks(d)
                   : (uint64_t)plan.chunk_rows * 32 * (((uint64_t)d + kSpKC - 1) / kSpKC);
     float* qn = reinterpret_cast<float*>(qs + align_up(qs_bytes));
     unsigned char* tsh = reinterpret_cast<unsigned char*>(qn) + align_up((uint64_t)plan.chunk_rows * 4);
@@ -230,7 +223,7 @@ knn_status run_search(const knn_plan_t& plan, const float* Q, int64_t ldq, const
     // Small searches of the squared-Euclidean metric skip the filter and all that prepares it: the
     // whole workspace holds lists.  (One chunk only; a search over blocks of host points keeps its
     // plan's path, whose thresholds carry over from block to block.)
-    if ((plan.path == KNN_PATH_MFMA_SPLIT || plan.path == KNN_PATH_MFMA_WIDE || packed_plan) && metric == KNN_METRIC_L2SQ && plan.q_chunks == 1 &&
+    if ((plan.path == KNN_PATH_MFMA_SPLIT || packed_plan) && metric == KNN_METRIC_L2SQ && plan.q_chunks == 1 &&
         !block_d64 && few_applies(m, n, d, k, whole_rows(d))) {
         const int S1 = few_splits(m, n, k, plan.workspace_bytes);
         if (S1 > 0) {
@@ -253,7 +246,7 @@ knn_status run_search(const knn_plan_t& plan, const float* Q, int64_t ldq, const
             return KNN_OK;
         }
     }
-    const bool split_plan = plan.path == KNN_PATH_MFMA_SPLIT || (plan.path == KNN_PATH_MFMA_WIDE && !wide_plan);
+    const bool split_plan = plan.path == KNN_PATH_MFMA_SPLIT;
     if (split_plan || packed_plan) {
         hipEvent_t t0 = mark(stream);
         // (the header's second word: the points' largest bf16 rounding residual, which the

@@ -144,6 +144,14 @@ constexpr int kWdRoom = 4;                            // a buffer with fewer fre
 constexpr int64_t kWdMinPoints = 65536;               // fewer points or queries: the split path
 constexpr int64_t kWdMinQueries = 16;                 // (n = 1e6, d = 784: one query 3.6 ms against the split path's
                                                       // 3.4, 16 queries 3.9 against 5.7, 256 queries 5.6 against 10.6)
+// Lists of one or two of rows that are not long, where there are a few tiles of queries: too few workgroups for tiles of 512, and
+// little to gain from this path's thresholds, so the split path is the better one.  (m = 1000, us there / here, by n, d, k:
+// 150001, 259, 1 970 / 1371; 150001, 399, 1 1391 / 1657; 150001, 301, 2 1240 / 1536; 450000, 301, 1 1786 / 2038; but 150001,
+// 515, 1 1720 / 1600, 450000, 301, 3 2256 / 2124; m = 1500 70001, 301, 1 1052 / 1184, 300000, 301, 1 2065 / 1792; m = 257
+// 200000, 301, 3 1579 / 1278.)
+constexpr inline bool wd_short_lists(int64_t m, int64_t n, int d, int k) {
+    return d + 64 * (k - 1) <= 420 && m > 256 && ((m <= 1024 && n <= 500000) || (m <= 1536 && n <= 160000));
+}
 constexpr int kWdMaxSplits = 64;                      // (a wave's lanes read the ranges' words of a query)
 constexpr int kWdMaxK = 512;                          // larger k: the split path (LDS)
 // LDS bytes of a workgroup: two stage buffers of the points' operands, two tiles of norms, the

@@ -319,7 +319,7 @@ extern "C" knn_status knn_plan_metric(int64_t m, int64_t n, int32_t d, int32_t k
     // both operands (knn_wide.hip).  The workspace is path 5's plus the packed points (all of them,
     // or one slab at a time as on path 6) with the queries' B operands in operand order.
     if (split && metric == KNN_METRIC_L2SQ && d > kPkMaxD && k <= kWdMaxK && n >= kWdMinPoints &&
-        m >= kWdMinQueries && !(m <= kSpFewRows && k <= kSpFewShortK)) {
+        m >= kWdMinQueries && !(m <= kSpFewRows && k <= kSpFewShortK) && !wd_short_lists(m, n, d, k)) {
         const int nch_p = pk_padded_chunks(d);
         const uint64_t qrow7 = 32ull * (uint64_t)nch_p;
         const uint64_t n64 = ((uint64_t)n + kPkStep - 1) / kPkStep * kPkStep;

@@ -353,3 +353,14 @@ def test_host_entry_points_reject_bad_arguments_without_a_gpu():
     assert st == K.KNN_ERR_INVALID_ARG
     st = K.knn_search_raw(0, 3, 256, 3, 0, 10, 3, 2, 0, 0, 0, 0, 0, 0)  # m == 0: nothing to do
     assert st == K.KNN_OK
+
+
+def test_lists_of_one_or_two_are_planned_for_the_split_path():
+    # d > 256: rows of up to 420 coordinates (356 for k = 2), 257 to 1024 queries and 5e5 points or 1536 and 160000
+    def path(m, n, d, k):
+        return K.knn_plan(m, n, d, k, 10 ** 9).path
+
+    split, wide = K.KNN_PATH_MFMA_SPLIT, K.KNN_PATH_MFMA_WIDE
+    assert {path(257, 65_536, 257, 1), path(1024, 500_000, 420, 1), path(1536, 160_000, 356, 2)} == {split}
+    assert {path(256, 70_000, 300, 1), path(1024, 500_001, 300, 1), path(1536, 160_001, 300, 1),
+            path(1537, 70_000, 300, 1), path(1000, 70_000, 421, 1), path(1000, 70_000, 300, 3)} == {wide, wide}

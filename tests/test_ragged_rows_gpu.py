@@ -18,8 +18,8 @@ def spread(a, before, after):
     return wide[:, before:before + a.shape[1]]
 
 
-# (m, n, d, k, metric): path 6 (d from 17 to 256), path 7 (lists staged in the stops; k = 1 on path 5's kernel), path
-# 5 with a range per compute unit and with fewer, few queries; the cosine metric with fewer coordinates than one group, and on path 6
+# (m, n, d, k, metric): path 6 (d from 17 to 256), path 7 (lists staged in the stops), path
+# 5 (k = 1 of 300 queries; with a range per compute unit and with fewer), few queries; the cosine metric with fewer coordinates than one group, and on path 6
 CASES = [(70, 66_000, 21, 9, "l2"), (130, 66_000, 50, 100, "l2"), (70, 66_000, 131, 10, "l2"), (130, 66_000, 255, 3, "l2"),
          (40, 66_000, 301, 12, "l2"), (300, 66_000, 259, 1, "l2"), (20, 66_000, 514, 2, "l2"), (130, 66_000, 514, 2, "l2"), (70, 66_000, 200, 5, "l2"),
          (700, 5_000, 30, 40, "l2"), (300, 3_000, 515, 300, "l2"), (5, 3_000, 33, 10, "l2"), (3, 1_000, 35, 4, "l2"),

@@ -157,7 +157,7 @@ def test_wide_strided_rows_unaligned_rows_and_query_chunks(K, oracle):
     torch.cuda.synchronize()
     assert K.knn_last_stats()[0].path == K.KNN_PATH_MFMA_WIDE
     assert torch.equal(ref_i, i1) and torch.equal(ref_d.view(torch.int32), d1.view(torch.int32))
-    # rows that are not 16-byte aligned: the same plan runs on the split kernel
+    # rows that are not 16-byte aligned
     Xu = torch.from_numpy(rng.standard_normal((n, 301), dtype=np.float32)).cuda()
     Xu[:, :d] = Xd
     i3, d3 = K.knn_search(Qd, Xu[:, :d], k, big)
@@ -205,3 +205,18 @@ def test_wide_slabs_under_a_limit_without_room_for_the_whole_copy(K, oracle):
         assert torch.equal(ref_i, i2) and torch.equal(ref_d.view(torch.int32), d2.view(torch.int32)), p
     assert len(seen) >= 2, seen
     against_oracle(oracle, Q, X, k, ref_i.cpu().numpy(), ref_d.cpu().numpy(), np.arange(0, m, 127))
+
+
+@pytest.mark.parametrize("m,n,d", [(257, 65_536, 257), (1024, 66_001, 419), (1536, 70_000, 300)])
+def test_short_lists_are_planned_for_the_split_path(K, m, n, d):
+    # the edges of its rule, beside lists long enough for the wide path: the nearest point has the same bits
+    g = torch.Generator(device="cuda").manual_seed(m)
+    X = torch.randn(n, d, generator=g, device="cuda")
+    Q = torch.randn(m, d, generator=g, device="cuda")
+    i1, d1 = K.knn_search(Q, X, 1, W.GB)
+    torch.cuda.synchronize()
+    assert K.knn_last_stats()[0].path == K.KNN_PATH_MFMA_SPLIT == K.knn_plan(m, n, d, 1, W.GB).path
+    i9, d9 = K.knn_search(Q, X, 9, W.GB)
+    torch.cuda.synchronize()
+    assert K.knn_last_stats()[0].path == K.KNN_PATH_MFMA_WIDE
+    assert torch.equal(i1[:, 0], i9[:, 0]) and torch.equal(d1[:, 0], d9[:, 0])
