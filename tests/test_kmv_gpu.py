@@ -59,17 +59,22 @@ def tolerance(X, Z, v, variance, lengthscale, rows, mfma):
     return tol
 
 
-def run_gpu(K, X, Z, v, variance, lengthscale, limit, z_is_x=False):
+def run_gpu(K, X, Z, v, variance, lengthscale, limit, z_is_x=False, least=False):
+    # least: with the plan's workspace, which leaves out what the call is best given
     Xd = torch.from_numpy(X).cuda()
     Zd = Xd if z_is_x else torch.from_numpy(Z).cuda()
     vd = torch.from_numpy(v).cuda()
-    y = K.kmv_apply(Xd, Zd, vd, variance, lengthscale, limit)
+    ws = None
+    if least:
+        size = K.kmv_plan(len(X), len(Z), X.shape[1], limit).workspace_bytes
+        ws = torch.empty(max(size, 256), dtype=torch.uint8, device="cuda")[:size]
+    y = K.kmv_apply(Xd, Zd, vd, variance, lengthscale, limit, workspace=ws)
     torch.cuda.synchronize()
     return y.cpu().numpy()
 
 
-def parity(K, oracle, X, Z, v, variance, lengthscale, limit=64 * W.MB, rows=None, z_is_x=False):
-    y = run_gpu(K, X, Z, v, variance, lengthscale, limit, z_is_x)
+def parity(K, oracle, X, Z, v, variance, lengthscale, limit=64 * W.MB, rows=None, z_is_x=False, least=False):
+    y = run_gpu(K, X, Z, v, variance, lengthscale, limit, z_is_x, least)
     assert y.shape == (X.shape[0],) and y.dtype == np.float64
     assert np.isfinite(y).all()
     sel = np.arange(X.shape[0]) if rows is None else np.asarray(rows)
@@ -103,18 +108,22 @@ SMALL = [
     (16, 400, 800, 2, 1.0, 1.0, 30.0),    # large coordinates
     (17, 400, 800, 24, 1.0, 40.0, 10.0),  # large coordinates on the expansion path
     (18, 200, 900, 48, 1.0, 7.0, 1.0),    # three K chunks of rows kept in registers, aligned
+    (22, 200, 900, 47, 1.0, 7.0, 1.0),    # unaligned
+    (23, 129, 1300, 31, 1.0, 5.0, 1.0),   # two, unaligned
     (19, 200, 900, 64, 1.0, 8.0, 1.0),    # four: the last dimension with resident rows
     (20, 130, 500, 65, 1.0, 8.0, 1.0),    # first dimension whose rows stream through LDS
     (21, 150, 700, 100, 1.0, 10.0, 1.0),  # streamed rows, odd number of chunks, aligned
 ]
 
 
+# (d = 1 and 9 to 64 run on other kernels with the plan's workspace alone: the entries one by one, six bf16 products)
+@pytest.mark.parametrize("least", [False, True], ids=["best", "plan"])
 @pytest.mark.parametrize("case", SMALL, ids=lambda c: "s%d_n%d_m%d_d%d" % c[:4])
-def test_small_cases_match_oracle(K, oracle, case):
+def test_small_cases_match_oracle(K, oracle, case, least):
     seed, n, m, d, variance, lengthscale, spread = case
-    say("case", case)
+    say("case", case, least)
     X, Z, v = W.random_kmv_case(seed, n, m, d, spread)
-    parity(K, oracle, X, Z, v, variance, lengthscale)
+    parity(K, oracle, X, Z, v, variance, lengthscale, least=least)
 
 
 @pytest.mark.parametrize("d", [2, 16])

@@ -192,9 +192,9 @@ def test_packed_strided_rows_and_query_chunks(K, oracle):
     against_oracle(oracle, Q, X, k, ref_i.cpu().numpy(), ref_d.cpu().numpy(), np.arange(0, m, 97))
 
 
-def test_packed_unaligned_rows_fall_back_to_the_split_kernel(K, oracle):
-    # d % 4 != 0: the plan is the packed one, the call runs the split kernel inside its workspace
-    say("packed plan, unaligned rows")
+def test_packed_rows_off_whole_groups_of_four(K, oracle):
+    # d % 4 != 0: the last group of a row is shifted into place
+    say("packed path, rows off whole groups of four")
     rng = np.random.default_rng(11)
     n, d, m, k = 70000, 30, 2150, 6
     X = rng.standard_normal((n, d), dtype=np.float32)

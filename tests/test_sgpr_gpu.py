@@ -43,18 +43,23 @@ def a_max(U, X, lengthscale):
     return 0.5 * ((hi - lo) ** 2).sum() / lengthscale ** 2
 
 
-def run_gpu(K, U, X, y, variance, lengthscale, limit):
+def run_gpu(K, U, X, y, variance, lengthscale, limit, least=False):
+    # least: with the plan's workspace, which mostly has no room for the entries as pieces
+    ws = None
+    if least:
+        size = K.sgpr_plan(len(U), len(X), X.shape[1], limit).workspace_bytes
+        ws = torch.empty(max(size, 256), dtype=torch.uint8, device="cuda")[:size]
     A, b = K.sgpr_accumulate(torch.from_numpy(U).cuda(), torch.from_numpy(X).cuda(),
-                             torch.from_numpy(y).cuda(), variance, lengthscale, limit)
+                             torch.from_numpy(y).cuda(), variance, lengthscale, limit, workspace=ws)
     torch.cuda.synchronize()
     return A.cpu().numpy(), b.cpu().numpy()
 
 
-def parity(K, oracle, U, X, y, variance, lengthscale, limit=64 * W.MB):
+def parity(K, oracle, U, X, y, variance, lengthscale, limit=64 * W.MB, least=False):
     m, d = U.shape
     plan = K.sgpr_plan(m, X.shape[0], d, limit)
     assert plan.workspace_bytes <= limit
-    A, b = run_gpu(K, U, X, y, variance, lengthscale, limit)
+    A, b = run_gpu(K, U, X, y, variance, lengthscale, limit, least)
     assert A.shape == (m, m) and b.shape == (m,) and np.isfinite(A).all() and np.isfinite(b).all()
     assert np.array_equal(A, A.T)
     rA, rb = oracle.sgpr_accumulate(U, X, y, variance, lengthscale)
@@ -76,19 +81,23 @@ SMALL = [
     (1, 5, 100, 1, 1.0, 1.0, 64 * W.MB),
     (2, 128, 16, 2, 2.5, 0.7, 64 * W.MB),       # one tile, one K step
     (3, 129, 777, 3, 0.3, 1.5, 64 * W.MB),      # ragged tile pair, ragged columns
-    (4, 300, 5003, 11, 1.0, 3.0, 64 * W.MB),    # two chunks of 4096 / 907 columns, six tile pairs
+    (4, 300, 5003, 11, 1.0, 3.0, 64 * W.MB),    # six tile pairs; the plan's workspace: chunks of 4096 / 907 columns
     (5, 257, 1000, 4, 1.0, 2.0, 257 * 64 + 255),  # the smallest limit: chunks of 16 columns
     (6, 200, 3000, 3, 1.7, 1.0, 200 * 4 * 100),   # chunks of 96 columns
     (7, 513, 2048, 2, 1.0, 1.0, 64 * W.MB),     # 15 tile pairs
+    (8, 130, 20_000, 3, 1.0, 1.0, 64 * W.MB),   # the plan's workspace: five chunks, eight groups of columns
+    (9, 200, 13_000, 5, 0.8, 2.0, 4_300_000),   # four groups
 ]
 
 
+# (the plan's workspace is too small for pieces in all of these: chunks of fp32 entries)
+@pytest.mark.parametrize("least", [False, True], ids=["best", "plan"])
 @pytest.mark.parametrize("case", SMALL, ids=lambda c: "s%d_m%d_n%d_d%d" % c[:4])
-def test_small_cases_match_oracle(K, oracle, case):
+def test_small_cases_match_oracle(K, oracle, case, least):
     seed, m, n, d, variance, lengthscale, limit = case
-    say("case", case)
+    say("case", case, least)
     U, X, y = W.random_sgpr_case(seed, m, n, d)
-    parity(K, oracle, U, X, y, variance, lengthscale, limit)
+    parity(K, oracle, U, X, y, variance, lengthscale, limit, least=least)
 
 
 def test_inducing_points_among_the_data(K, oracle):
