@@ -39,7 +39,8 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
 constexpr int kFragment = 1024;       // bytes: 32 points x 16 coordinates of one piece, in operand order
-constexpr float kMostHalf = 32768.f;  // coordinates beyond this go to the slow way
+constexpr float kMostHalf = 32768.f;  // coordinates beyond this are scaled down
+constexpr float kMostScaled = 0x1p60f;  // and beyond this are infinite: products of scaled ones back in fp32's range
 constexpr float kFar = -1e30f;        // exponent of what pads the last tile
 constexpr float kSmallLow = 0x1p-22f;  // |low pieces|^2 of a point up to which their products are left out
 
@@ -52,8 +53,8 @@ template <int NCH>
 constexpr int kTilePoints = NCH <= 2 ? 128 : 64;
 
 // A tile's record: [chunk of 16 coordinates][piece][block of 32 points] fragments, then per block 32 x 16
-// bytes for the norms' instruction, then the points' weights and one word that is not 0 where a
-// coordinate is out of the pieces' range.
+// bytes for the norms' instruction (its last word not used there: the factor 2^shift of the point), then the points'
+// weights and the tile's kind.
 template <int NCH>
 struct Record {
     static constexpr int blocks = kTilePoints<NCH> / 32;
@@ -70,18 +71,8 @@ __device__ __forceinline__ void split3(float x, __bf16& hi, __bf16& mid, __bf16&
     lo = (__bf16)(r - (float)mid);
 }
 
-// A coordinate a as two pieces: whether it is in their range (not so for a NaN), and what they stand for,
-// a itself where it is not.
-__device__ __forceinline__ bool split2(double a, _Float16& hi, _Float16& lo, double& stands) {
-    hi = (_Float16)(float)a;
-    const double high = (double)(float)hi;
-    lo = (_Float16)(float)(a - high);
-    const bool fits = fabs(a) <= (double)kMostHalf;
-    stands = fits ? high + (double)(float)lo : a;
-    return fits;
-}
-
-// the same of eight coordinates times `scale`, with the squares of what the pieces stand for and of the low ones
+// Eight coordinates times `scale` as two pieces each, with the squares of what the pieces stand for and of the low
+// ones; whether all are in the pieces' range (not so for a NaN).
 __device__ __forceinline__ bool split2_row(const float (&x)[8], double scale, f16x8& hi, f16x8& lo, double& square,
                                            float& low) {
     bool fits = true;
@@ -89,30 +80,48 @@ __device__ __forceinline__ bool split2_row(const float (&x)[8], double scale, f1
     low = 0.f;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-        _Float16 h, l;
-        double a;
-        fits &= split2(scale * (double)x[e], h, l, a);
-        hi[e] = h;
-        lo[e] = l;
-        square += a * a;
-        low = fmaf((float)l, (float)l, low);
+        const double a = scale * (double)x[e];
+        hi[e] = (_Float16)(float)a;
+        const double high = (double)(float)hi[e];
+        lo[e] = (_Float16)(float)(a - high);
+        const double stands = high + (double)(float)lo[e];
+        fits &= fabs(a) <= (double)kMostHalf;
+        square += stands * stands;
+        low = fmaf((float)lo[e], (float)lo[e], low);
     }
     return fits;
 }
 
-// three pieces of what the two pieces of eight coordinates times `scale` stand for
-__device__ __forceinline__ void split3_row(const float (&x)[8], double scale, bf16x8& hi, bf16x8& mid, bf16x8& lo) {
+// Rows and points with a coordinate out of range are cut into pieces times 2^-shift, one shift for all their coordinates.
+// largest: an upper bound of theirs, `scale` included; -1: too far for any (or a NaN, or infinite): pieces of 0.
+__device__ __forceinline__ int shift_of(float largest) {
+    if (!(largest <= kMostScaled)) return -1;
+    return largest <= kMostHalf ? 0 : __builtin_amdgcn_frexp_expf(largest) - 15;  // (below 2^15 then)
+}
+__device__ __forceinline__ float largest_of(const float (&x)[8], double scale) {
+    float most = 0.f;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-        _Float16 h, l;
-        double stands;
-        split2(scale * (double)x[e], h, l, stands);
-        __bf16 a, b, c;
-        split3((float)stands, a, b, c);
-        hi[e] = a;
-        mid[e] = b;
-        lo[e] = c;
+        const float a = fabsf((float)(scale * (double)x[e]));
+        most = a <= HUGE_VALF ? fmaxf(most, a) : HUGE_VALF;  // (a NaN: too far)
     }
+    return most;
+}
+// the pieces of eight of its coordinates, and their square as that of the whole numbers
+__device__ __forceinline__ void split2_shifted(const float (&x)[8], double scale, int shift, f16x8& hi, f16x8& lo,
+                                               double& square) {
+    if (shift < 0) {
+        square = 0.0;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            hi[e] = lo[e] = (_Float16)0.f;
+            square = fma(scale * (double)x[e], scale * (double)x[e], square);  // (a NaN, infinite, or past kMostScaled)
+        }
+        return;
+    }
+    float low;
+    split2_row(x, ldexp(scale, -shift), hi, lo, square, low);
+    square = ldexp(square, 2 * shift);
 }
 
 // coordinates t0 .. t0 + 7 of a row; zeros past d and for rows that are not there
@@ -130,6 +139,7 @@ __global__ __launch_bounds__(256) void kmv_records_kernel(const float* __restric
     constexpr int TP = kTilePoints<NCH>, G = 2 * NCH;  // groups of 8 coordinates
     __shared__ double squares[TP][G + 1];
     __shared__ float lows[TP][G + 1];
+    __shared__ float largest[TP][G + 1];
     __shared__ int kind;
     unsigned char* __restrict__ out = records + (int64_t)blockIdx.x * R::bytes;
     if (threadIdx.x == 0) kind = kTileSmallLows;
@@ -146,6 +156,33 @@ __global__ __launch_bounds__(256) void kmv_records_kernel(const float* __restric
         *reinterpret_cast<f16x8*>(at + R::blocks * kFragment) = lo;
     }
     __syncthreads();
+    const bool shifted = kind == kTileOutOfRange;  // (the same for the whole workgroup)
+    auto shift_at = [&](int point) {
+        float most = 0.f;
+#pragma unroll
+        for (int g = 0; g < G; ++g) most = fmaxf(most, largest[point][g]);
+        return shift_of(most);
+    };
+    if (shifted) {
+        for (int pass = 0; pass < 2; ++pass) {
+            for (int k = threadIdx.x; k < TP * G; k += 256) {
+                const int point = k / G, g = k % G;
+                const int64_t j = (int64_t)blockIdx.x * TP + point;
+                float x[8];
+                load8(Z + (j < m ? j : 0) * ldz, j < m, g * 8, d, x);
+                if (pass == 0) {
+                    largest[point][g] = largest_of(x, scale);
+                    continue;
+                }
+                f16x8 hi, lo;
+                split2_shifted(x, scale, shift_at(point), hi, lo, squares[point][g]);
+                unsigned char* at = out + ((g >> 1) * 2 * R::blocks + (point >> 5)) * kFragment + (g & 1) * 512 + (point & 31) * 16;
+                *reinterpret_cast<f16x8*>(at) = hi;
+                *reinterpret_cast<f16x8*>(at + R::blocks * kFragment) = lo;
+            }
+            __syncthreads();
+        }
+    }
     if ((int)threadIdx.x < TP) {
         const int64_t j = (int64_t)blockIdx.x * TP + threadIdx.x;
         double sq = 0.0;
@@ -163,7 +200,8 @@ __global__ __launch_bounds__(256) void kmv_records_kernel(const float* __restric
         norm[1] = mid;
         norm[2] = lo;
         norm[3] = norm[4] = norm[5] = (__bf16)1.f;
-        norm[6] = norm[7] = (__bf16)0.f;
+        norm[6] = (__bf16)0.f;
+        norm[7] = (__bf16)(shifted ? ldexpf(1.f, max(shift_at(threadIdx.x), 0)) : 1.f);
         *reinterpret_cast<bf16x8*>(out + R::norms_at + threadIdx.x * 16) = norm;
         // (a point with a NaN: entries of 0 below, and so its weight makes every sum a NaN)
         *reinterpret_cast<float*>(out + R::weights_at + threadIdx.x * 4) = j >= m ? 0.f : sq != sq ? (float)sq : v[j];
@@ -179,9 +217,10 @@ __global__ __launch_bounds__(256) void kmv_records_kernel(const float* __restric
 // points' weights, into one fp32 sum per tile and half wave, and those into an fp64 sum.  An exponent that
 // rounding left above 0 gives 1: the result of exp2 is clamped to [0, 1], a NaN (of an infinite coordinate) to 0.
 //
-// A tile with a coordinate out of range, and rows with one, take the products of three bf16 pieces, made from
-// memory on the way, of what the two pieces stand for where they are in range.  So far from the origin (2e4
-// lengthscales) the expansion has no digits left in fp32.
+// In a tile with a coordinate out of range, and for rows with one, the products are multiplied back by the powers of two of
+// point and row before the norms are added; those of points and rows that are in range are what they are elsewhere.  (So
+// far from the origin, 27000 lengthscales, the expansion has no digits left in fp32.  With six products of bf16 pieces made
+// there from memory such tiles took 10 to 17 times the time of kmv_mfma_kernel.)
 //
 // Bound by the power of the matrix and vector units together: at n = m = 200000, d = 32 7.8 ms (14.2 with
 // three bf16 pieces cut in every workgroup, kmv_mfma_kernel), at a clock of 1.4 GHz that both keep busy for
@@ -190,7 +229,8 @@ __global__ __launch_bounds__(256) void kmv_records_kernel(const float* __restric
 // 1.48 / 2.12 / 4.43 ms against 2.31 / 3.63 / 7.14 by kmv_mfma_kernel.
 // ---------------------------------------------------------------------------------------
 template <int NCH>
-__global__ __launch_bounds__(256) void kmv_pieces_kernel(const float* __restrict__ X, int64_t ldx,
+__global__ __launch_bounds__(256)
+__attribute__((amdgpu_waves_per_eu(NCH <= 3 ? 4 : 3, NCH <= 3 ? 4 : 3))) void kmv_pieces_kernel(const float* __restrict__ X, int64_t ldx,
                                                          const float* __restrict__ Z, int64_t ldz,
                                                          const unsigned char* __restrict__ records, int n, int m, int d,
                                                          int range_tiles, double scale,
@@ -220,7 +260,8 @@ __global__ __launch_bounds__(256) void kmv_pieces_kernel(const float* __restrict
     bf16x8 norm;
     bool fits = true;
     double sum = 0.0;  // (from a NaN on where the row has one: its entries come out as 0)
-    float low = 0.f;
+    float low = 0.f, factor = 1.f;
+    int rows_kind;
     {
         double sq = 0.0;
 #pragma unroll
@@ -233,8 +274,28 @@ __global__ __launch_bounds__(256) void kmv_pieces_kernel(const float* __restrict
             sq += square;
             low += part;
         }
-        sq += __shfl_xor(sq, 32);
         low += __shfl_xor(low, 32);
+        rows_kind = __ballot(!fits) ? kTileOutOfRange : __ballot(!(low <= kSmallLow)) ? kTileFits : kTileSmallLows;
+        if (rows_kind == kTileOutOfRange) {
+            float largest = 0.f;
+            for (int c = 0; c < NCH; ++c) {
+                float x[8];
+                load8(xp, true, c * 16 + h * 8, d, x);
+                largest = fmaxf(largest, largest_of(x, scale));
+            }
+            const int shift = shift_of(fmaxf(largest, __shfl_xor(largest, 32)));
+            factor = ldexpf(1.f, max(shift, 0));
+            sq = 0.0;
+#pragma unroll
+            for (int c = 0; c < NCH; ++c) {
+                float x[8];
+                double square;
+                load8(xp, true, c * 16 + h * 8, d, x);
+                split2_shifted(x, scale, shift, bh[c], bl[c], square);
+                sq += square;
+            }
+        }
+        sq += __shfl_xor(sq, 32);
         if (sq != sq) sum = sq;
         __bf16 hi, mid, lo;
         split3(fmaxf((float)(-0.5 * sq), -3e38f), hi, mid, lo);
@@ -245,7 +306,6 @@ __global__ __launch_bounds__(256) void kmv_pieces_kernel(const float* __restrict
         norm[5] = h ? zero : lo;
         norm[6] = norm[7] = zero;
     }
-    const int rows_kind = __ballot(!fits) ? kTileOutOfRange : __ballot(!(low <= kSmallLow)) ? kTileFits : kTileSmallLows;
 
     for (int tile = 0; tile < count; ++tile) {
         const int buf = tile & 1;
@@ -267,7 +327,7 @@ __global__ __launch_bounds__(256) void kmv_pieces_kernel(const float* __restrict
                     part = fmaf(__builtin_amdgcn_fmed3f(__builtin_amdgcn_exp2f(arg[g * 4 + e]), 0.f, 1.f), w[e], part);
             }
         };
-        auto blocks = [&](auto low_product) {
+        auto blocks = [&](auto low_product, auto shifted) {
             auto products = [&](int block) {
                 f32x16 acc;
 #pragma unroll
@@ -284,6 +344,13 @@ __global__ __launch_bounds__(256) void kmv_pieces_kernel(const float* __restrict
                 }
 #pragma unroll
                 for (int c = 0; c < NCH; ++c) acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah[c], bh[c], acc, 0, 0, 0);
+                if constexpr (decltype(shifted)::value) {
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) {
+                        const unsigned char* of = rec + R::norms_at + (block * 32 + (e >> 2) * 8 + h * 4 + (e & 3)) * 16 + 14;
+                        acc[e] *= factor * (float)*reinterpret_cast<const __bf16*>(of);
+                    }
+                }
                 const bf16x8 an = *reinterpret_cast<const bf16x8*>(norms + block * 512);
                 return __builtin_amdgcn_mfma_f32_32x32x16_bf16(an, norm, acc, 0, 0, 0);
             };
@@ -297,32 +364,11 @@ __global__ __launch_bounds__(256) void kmv_pieces_kernel(const float* __restrict
             }
         };
         if (kind == kTileSmallLows) {
-            blocks(std::false_type{});
+            blocks(std::false_type{}, std::false_type{});
         } else if (kind == kTileFits) {
-            blocks(std::true_type{});
+            blocks(std::true_type{}, std::false_type{});
         } else {
-            for (int block = 0; block < NB; ++block) {
-                f32x16 acc;
-#pragma unroll
-                for (int e = 0; e < 16; ++e) acc[e] = 0.f;
-                const int64_t j = (int64_t)(first + tile) * TP + block * 32 + i32;
-                for (int c = 0; c < NCH; ++c) {
-                    float x[8];
-                    bf16x8 a[3], b[3];
-                    load8(Z + (j < m ? j : 0) * ldz, j < m, c * 16 + h * 8, d, x);
-                    split3_row(x, scale, a[0], a[1], a[2]);
-                    load8(xp, true, c * 16 + h * 8, d, x);
-                    split3_row(x, scale, b[0], b[1], b[2]);
-                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[2], b[0], acc, 0, 0, 0);
-                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], b[2], acc, 0, 0, 0);
-                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1], b[1], acc, 0, 0, 0);
-                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1], b[0], acc, 0, 0, 0);
-                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], b[1], acc, 0, 0, 0);
-                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0], b[0], acc, 0, 0, 0);
-                }
-                const bf16x8 an = *reinterpret_cast<const bf16x8*>(norms + block * 512);
-                add(__builtin_amdgcn_mfma_f32_32x32x16_bf16(an, norm, acc, 0, 0, 0), block);
-            }
+            blocks(std::true_type{}, std::true_type{});
         }
         sum += (double)part;
     }

@@ -71,7 +71,7 @@ def test_products_and_norms_are_of_the_same_points(far):
     Z[np.arange(d), (np.arange(d) + 1) % d] = 1.0
     v = np.ones(d, np.float32)
     lengthscale = float(np.sqrt(np.log2(np.e)))
-    if far:  # its tile takes the products of three pieces
+    if far:  # the products of its tile are scaled back
         Z = np.concatenate([Z, np.full((1, d), 1e5, np.float32)])
         v = np.append(v, np.float32(1))
     assert np.allclose(run(X, X, np.ones(d, np.float32), lengthscale), 1.5, rtol=4 * EPS, atol=0)
@@ -104,7 +104,7 @@ def test_errors_are_those_of_six_products(oracle, d, wide, mean):
 
 @pytest.mark.parametrize("d", [12, 40])
 def test_rows_and_points_out_of_range(oracle, d):
-    # coordinates beyond 32768 exponent units: their tile and their rows take the products of three pieces
+    # coordinates beyond 32768 exponent units: the products of their tile and of their rows are scaled back
     X, Z, v = W.random_kmv_case(77, 300, 500, d)
     X[40, 3], Z[200, d - 1], Z[201] = 1e6, -3e5, 4e4
     y = run(X, Z, v, 3.0)
@@ -114,6 +114,19 @@ def test_rows_and_points_out_of_range(oracle, d):
     near[[200, 201]] = False  # entries of exactly 0 for every row, out of the bound's formula
     assert y[40] == 0.0 and ref[40] == 0.0
     assert (np.abs(y - ref)[keep] <= bound(X[keep], Z[near], v[near], 3.0)).all()
+
+
+@pytest.mark.parametrize("d", [9, 20, 40, 64])
+def test_far_points_meet_themselves(d):
+    # powers of two up to 2^59 units of the pieces, which all fit: an entry of a point with itself is exactly 1, however far,
+    # beside rows and points that are in range, and every other one 0
+    n = 300
+    X = np.zeros((n, d), np.float32)
+    X[np.arange(n), np.arange(n) * 7 % d] = 2.0 ** (6 + np.arange(n) * 11 % 54) * np.where(np.arange(n) // d % 2, 1, -1)
+    X = np.unique(X, axis=0)
+    v = np.random.default_rng(d).standard_normal(len(X)).astype(np.float32)
+    y = run(X, X, v, float(np.sqrt(np.log2(np.e))))
+    assert np.allclose(y, 1.5 * v.astype(np.float64), rtol=4 * EPS, atol=0)
 
 
 @pytest.mark.parametrize("roomy", [True, False], ids=["pieces", "plan"])
