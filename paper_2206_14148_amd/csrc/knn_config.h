@@ -182,10 +182,17 @@ constexpr int kMaxSplits = 64;
 // cosine 1.46 -> 0.75; 60 x 4e4, d = 100, k = 256 10.2 -> 4.8).
 constexpr int64_t kSpFewRows = 128;
 constexpr int kSpFewMaxK = 256;
+// Longer lists than kSpFewShortK for every other one: what a range's list costs before it bounds anything grows with k.
+// 64 / 128 / 256 ranges, ms: 64 x 6e6, d = 16, k = 128 7.15 / 6.25 / 8.36, k = 20 3.02 / 1.86 / 2.04, k = 8 2.33 / 1.16 / 1.03;
+// cosine, 20 x 6e6, d = 64, k = 100 5.14 / 4.68 / 5.69; 102 sizes of each k from 20 to 256 in the mean 1.28 to 1.58 / 1 / 1.01 to 1.03.
+constexpr int kSpFewLongSplits = 128;
 // With lists this short it is then faster than paths 6 and 7, ms here / there: 100 queries, path 7 by n, d, k: 5e5, 301, 5
 // 0.84 / 1.49, 5e5, 301, 20 2.17 / 1.99, 5e5, 768, 5 1.49 / 2.20, 5e5, 768, 20 3.27 / 2.52; path 6: 1e6, 230, 1 0.73 /
 // 1.11, 1e6, 230, 8 1.08 / 1.27, 1e6, 230, 20 2.12 / 1.32, 4e6, 31, 8 0.98 / 1.31; cosine, 64 x 1e6, 100, 8 0.77 / 0.87.
 constexpr int kSpFewShortK = 8;
+// Than path 7 not with long rows as well: 128 queries, us here / there by n, d, k: 66000, 640, 8 1021 / 931, 66000, 1024, 8 1457
+// / 1283, 1e5, 1024, 6 1108 / 1078 (65 queries), 66000, 768, 4 723 / 917, 3e5, 768, 4 1163 / 1654.
+constexpr int kSpFewWideKD = 4608;
 constexpr int64_t kMaxPoints = ((int64_t)1 << 31) - 65536;
 constexpr int64_t kMaxChunkRows = 1 << 22;  // keeps per-launch row counts and grids in int range
 constexpr int kMinSplitPoints = 2048;    // a point range shorter than this is not worth a split

@@ -319,7 +319,7 @@ extern "C" knn_status knn_plan_metric(int64_t m, int64_t n, int32_t d, int32_t k
     // both operands (knn_wide.hip).  The workspace is path 5's plus the packed points (all of them,
     // or one slab at a time as on path 6) with the queries' B operands in operand order.
     if (split && metric == KNN_METRIC_L2SQ && d > kPkMaxD && k <= kWdMaxK && n >= kWdMinPoints &&
-        m >= kWdMinQueries && !(m <= kSpFewRows && k <= kSpFewShortK) && !wd_short_lists(m, n, d, k)) {
+        m >= kWdMinQueries && !(m <= kSpFewRows && k <= kSpFewShortK && k * d <= kSpFewWideKD) && !wd_short_lists(m, n, d, k)) {
         const int nch_p = pk_padded_chunks(d);
         const uint64_t qrow7 = 32ull * (uint64_t)nch_p;
         const uint64_t n64 = ((uint64_t)n + kPkStep - 1) / kPkStep * kPkStep;
@@ -388,8 +388,10 @@ extern "C" knn_status knn_plan_metric(int64_t m, int64_t n, int32_t d, int32_t k
     // little list warm-up: they may be shorter)
     int64_t s_max = n / (split ? kSpMinSplitPoints : kMinSplitPoints);
     if (s_max < 1) s_max = 1;
-    // (few queries on the split path: a range per compute unit, for the merge with a workgroup per query)
-    const int64_t most = split && m <= kSpFewRows && k <= kSpFewMaxK ? kNumCU : kMaxSplits;
+    // (few queries on the split path: a range per compute unit, or every other one, for the merge with a workgroup per
+    // query)
+    const int64_t most =
+        !(split && m <= kSpFewRows && k <= kSpFewMaxK) ? kMaxSplits : k <= kSpFewShortK ? kNumCU : kSpFewLongSplits;
     if (s_max > most) s_max = most;
     const int64_t slots = lowd ? kLowdResidentWorkgroups : kSpResidentWorkgroups;
     int64_t best_s = 0, best_rows = 0;
