@@ -225,7 +225,7 @@ knn_status run_search(const knn_plan_t& plan, const float* Q, int64_t ldq, const
     // plan's path, whose thresholds carry over from block to block.)
     if ((plan.path == KNN_PATH_MFMA_SPLIT || packed_plan) && metric == KNN_METRIC_L2SQ && plan.q_chunks == 1 &&
         !block_d64 && few_applies(m, n, d, k, whole_rows(d))) {
-        const int S1 = few_splits(m, n, k, plan.workspace_bytes);
+        const int S1 = few_splits(m, n, d, k, plan.workspace_bytes);
         if (S1 > 0) {
             float* lk = reinterpret_cast<float*>(ws);
             int* li = reinterpret_cast<int*>(ws + align_up((uint64_t)m * S1 * k * 4));

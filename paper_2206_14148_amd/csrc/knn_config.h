@@ -166,6 +166,11 @@ static_assert(wd_lds_bytes(kWdMaxK) <= kPkLdsBytes, "the largest k must fit the 
 constexpr int kFewQueries = 4;
 constexpr int kFewMaxK = 128;
 constexpr int kFewMaxSplits = 1024;
+// Longer lists than kFewLongK: ranges up to that many entries a query in all, or that many coordinates of points (d + 16 each) a
+// range, in whole 32s.
+constexpr int kFewLongK = 52;
+constexpr int64_t kFewLongEntries = 12288;
+constexpr int64_t kFewLongWork = 131072;
 
 // Workgroups the chip holds at once (LDS-limited): the planner sizes launches in rounds of these.
 constexpr int kLowdResidentWorkgroups = 4 * kNumCU;

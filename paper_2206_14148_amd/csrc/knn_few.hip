@@ -218,15 +218,23 @@ bool few_applies(int64_t m, int64_t n, int d, int k, bool aligned) {
     return work <= 5e9 && here_us <= filter_us;
 }
 
-int few_splits(int64_t rows, int64_t n, int k, uint64_t workspace_bytes) {
-    // as many waves as the chip holds at once (two a SIMD, by the 173 registers of the variant for rows
-    // that are not aligned; three of the other) where the points last (ranges of at least 256), lists that
-    // fit.  (Three for both: 1000 x 1e4, d = 9, k = 10 139 us against 102, d = 50 202 against 158, d = 16
-    // 98.5 against 90.4; 16 x 1e6, d = 50 322 against 246: a second round of workgroups that is nearly empty.)
+int few_splits(int64_t rows, int64_t n, int d, int k, uint64_t workspace_bytes) {
+    // two waves a SIMD where the points last (ranges of at least 256), lists that fit.  (Registers and LDS leave room for three, but
+    // a wave's list begins anew in every range: us with two / three / four 1000 x 1e4, d = 16, k = 10 91 / 100 / 133, 16 x 1e6,
+    // d = 100 261 / 308 / 441; 300 x 3e4, d = 257 334 / 277 / 430; 312 sizes in the mean 107.4 / 108.8 / 120.3.)
     const int64_t groups = (rows + kFewQueries - 1) / kFewQueries;
     int64_t S = 2 * 4 * kNumCU / groups;
     if (S > (n + 255) / 256) S = (n + 255) / 256;
     if (S > kFewMaxSplits) S = kFewMaxSplits;
+    // Long lists are merged at length, at some 2 us for 64 entries: no more ranges than keep that below what they save.  us with and
+    // without this line: 16 x 3e5, d = 16, k = 128 389 / 495, 1 x 1e6, k = 100 315 / 528; where a range is much work they pay: 64 x 3e5,
+    // d = 300, k = 100 875 with 128 ranges, 1129 with 122 (whole 32s: the groups of queries that read a range share an L2).
+    if (k > kFewLongK) {
+        int64_t most = n * (d + 16) / kFewLongWork;
+        if (most < kFewLongEntries / k) most = kFewLongEntries / k;
+        most = (most + 31) / 32 * 32;
+        if (S > most) S = most;
+    }
     const uint64_t room = workspace_bytes / 2 / kAlign * kAlign;  // keys and indices, each aligned
     const int64_t fit = (int64_t)(room / ((uint64_t)rows * (uint64_t)k * 4));
     if (S > fit) S = fit;

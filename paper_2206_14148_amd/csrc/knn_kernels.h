@@ -99,7 +99,7 @@ hipError_t launch_split(const float* Q, int64_t ldq, const float* X, int64_t ldx
 //   few_splits   point ranges for a chunk of rows: their lists are at most what fits into half of
 //                workspace_bytes for each of keys and indices (0: not even one range's do)
 bool few_applies(int64_t m, int64_t n, int d, int k, bool aligned);
-int few_splits(int64_t rows, int64_t n, int k, uint64_t workspace_bytes);
+int few_splits(int64_t rows, int64_t n, int d, int k, uint64_t workspace_bytes);
 hipError_t launch_few(const float* Q, int64_t ldq, const float* X, int64_t ldx, int64_t rows, int64_t n, int d,
                       int k, int S, float* lk, int* li, hipStream_t stream);
 
