@@ -364,3 +364,16 @@ def test_lists_of_one_or_two_are_planned_for_the_split_path():
     assert {path(257, 65_536, 257, 1), path(1024, 500_000, 420, 1), path(1536, 160_000, 356, 2)} == {split}
     assert {path(256, 70_000, 300, 1), path(1024, 500_001, 300, 1), path(1536, 160_001, 300, 1),
             path(1537, 70_000, 300, 1), path(1000, 70_000, 421, 1), path(1000, 70_000, 300, 3)} == {wide, wide}
+
+
+def test_ranges_and_paths_of_up_to_128_queries():
+    # the split path: a range for every compute unit up to k = 8, for every other one beyond; path 7 from rows and
+    # lists of k d > 4608 on
+    def plan(m, n, d, k):
+        return K.knn_plan(m, n, d, k, 8 * 10 ** 9)
+
+    assert 128 < plan(64, 6_000_000, 16, 8).n_splits <= 256
+    assert 64 < plan(64, 6_000_000, 16, 9).n_splits <= 128
+    assert plan(64, 6_000_000, 16, 257).n_splits <= 64 and plan(2000, 6_000_000, 9, 8).n_splits <= 64
+    assert plan(128, 66_000, 576, 8).path == plan(128, 66_000, 1024, 4).path == K.KNN_PATH_MFMA_SPLIT
+    assert plan(128, 66_000, 577, 8).path == plan(128, 66_000, 1024, 5).path == K.KNN_PATH_MFMA_WIDE
