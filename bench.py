@@ -36,18 +36,18 @@ PEAK_HBM_GBS = 8000.0
 # a workload on the kernel named; a run with other sizes, another limit or another kernel reports
 # null.  {workload: (kernel, bytes, profile)}
 PROFILED_TRAFFIC = {
-    "c1_random_d16": ("knn_few_kernel", 8.3e6, "profiles/knn_few_kernel_c1.md"),
+    "c1_random_d16": ("knn_few_kernel", 4.7e6, "profiles/knn_few_kernel_c1.md"),
     "c2_pointcloud_d3": ("knn_grid_kernel", 0.315e9, "profiles/knn_grid_kernel_c2.md"),
-    "c3_imagelike_d784": ("knn_wide_kernel", 50.6e9, "profiles/knn_wide_kernel_c3.md"),
+    "c3_imagelike_d784": ("knn_wide_kernel", 50.7e9, "profiles/knn_wide_kernel_c3.md"),
     "c4_clustered_d128": ("knn_packed_kernel", 435.6e9, "profiles/knn_packed_kernel_c4.md"),
-    "c5_memsweep_d256": ("knn_packed_kernel", 15.2e9, "profiles/knn_packed_kernel_c5_1GB.md"),  # per launch, two a step
-    "c6_cosine_d100": ("knn_packed_kernel", 8.37e9, "profiles/knn_packed_kernel_c6.md"),
+    "c5_memsweep_d256": ("knn_packed_kernel", 14.3e9, "profiles/knn_packed_kernel_c5_1GB.md"),  # per launch, two a step
+    "c6_cosine_d100": ("knn_packed_kernel", 8.35e9, "profiles/knn_packed_kernel_c6.md"),
     "c7_l1_d100": ("knn_l1_sad_kernel", 12.1e9, "profiles/knn_l1_sad_kernel_c7.md"),
     "kmv1_d1": ("kmv_series_kernel", 12.1e6, "profiles/kmv_series_kernel_kmv1.md"),
     "kmv2_d32": ("kmv_pieces_kernel", 1.75e9, "profiles/kmv_pieces_kernel_kmv2.md"),
     "kmv3_d1_f64": ("kmv_series_kernel", 16.4e6, "profiles/kmv_series_kernel_kmv3.md"),
-    "sgpr1_road_d3_m10000": ("sgpr_product_kernel", 37.4e9, "profiles/sgpr_product_kernel_sgpr1.md"),
-    "sgpr2_electric_d11_m4000": ("sgpr_product_kernel", 3.25e9, "profiles/sgpr_product_kernel_sgpr2.md"),
+    "sgpr1_road_d3_m10000": ("sgpr_product_kernel", 19.4e9, "profiles/sgpr_product_kernel_sgpr1.md"),
+    "sgpr2_electric_d11_m4000": ("sgpr_product_kernel", 3.19e9, "profiles/sgpr_product_kernel_sgpr2.md"),
 }
 
 

@@ -14,7 +14,8 @@
  * procedure the section refers to sums over the data in chunks and needs O(m^2).  Here the
  * data axis is cut into chunks of chunk_cols points (section 4.3: the largest splittable
  * axis); one chunk of K_uf lives in the workspace, is multiplied by its own transpose on the
- * fp32 matrix cores and added to A in fp64, and is dropped.  When m is small (few 128 x 128
+ * matrix cores, its entries as 16-bit pieces, and added to A in fp64, and is dropped.  In the plan's
+ * workspace a chunk is kept in fp32 and cut into pieces as it is multiplied; when m is small (few 128 x 128
  * tiles of A for 256 compute units) and the limit has room, the columns of a chunk are cut
  * into col_groups groups whose products run concurrently into partial copies of A kept in
  * the workspace; the copies are added in a fixed order at the end.

@@ -9,10 +9,10 @@
 // wave and come through scalar loads, and every point value read feeds NQ queries.  Pairs under a
 // query's current k-th key wait in a buffer of 64 and are merged into its list when that is full.
 //
-// What bounds it: the round trips of a wave's groups of points more than its arithmetic, two VALU
-// operations per pair and coordinate (1000 x 1e4, d = 16: vector units busy a third of the wave cycles,
-// waits another third); at 16 queries x 1e5 points, d = 50, k = 10 63 us here and 33 us for the merge of
-// 376 lists a query.
+// What bounds it: 1000 x 1e4, d = 16, k = 10 3.1e7 vector instructions, of which the keys, two operations per pair and
+// coordinate, are 5e6 and most others the lists' merges; vector units active in 39 % of the wave cycles, waits 35 %.  At 16
+// queries x 1e5 points, d = 50, k = 10 the round trips of a wave's groups of points: 50 us here, 18 us for the merge of
+// 391 lists a query.
 #include <hip/hip_runtime.h>
 
 #include <climits>

@@ -344,9 +344,9 @@ __global__ __launch_bounds__(256) void knn_l1_seed_kernel(const float* __restric
     }
 }
 
-// Bound by the vector units: d / 4 sums per pair (v_sad_u8 measured at half the rate of an fp32
-// operation: 1e4 queries, 1e6 points, d = 100 take 16.5 ms with the candidates left out) and one LDS
-// read of 16 bytes per QL * 4 of them.  A lane keeps QL queries' bytes in registers, the workgroup
+// d / 4 sums per pair (v_sad_u8 measured at half the rate of an fp32 operation: 1e4 queries, 1e6 points, d = 100
+// need 12.7 ms at 2.4 GHz and take 16.5 with the candidates left out; waits are 62 % of the wave cycles, so that the
+// vector units are not all that binds) and one LDS read of 16 bytes per QL * 4 of them.  A lane keeps QL queries' bytes in registers, the workgroup
 // rounds a tile of 64 points to bytes in LDS and every wave reads a point's bytes as a broadcast.
 // Two queries per lane and two workgroups per compute unit: the second hides the first one's
 // flushes and barriers (four queries per lane, one workgroup: 27.6 ms against 21.6).  Whole search

@@ -283,7 +283,7 @@ struct Shares {
 // total by an addition whose rounding error goes to the small ones, which are 2^8 or more below it, so
 // the error does not grow with the chunk.
 //
-// Bound by the matrix cores: 1.10 PFLOP/s of fp16 products, 1.25 of bf16 (m = 4000); a large
+// Bound by the matrix cores: 1.10 PFLOP/s of fp16 products (m = 4000), 1.22 of bf16 (m = 10000); a large
 // product of the vendor's library reaches 1.21 here.
 //
 // Registers: 192 accumulators and 48 of operands of the 256 a lane may have.  So the operands of a run's first stage
