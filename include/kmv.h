@@ -79,6 +79,8 @@ int kmv_plan(int64_t n, int64_t m, int32_t d, int64_t mem_limit_bytes, kmv_plan_
  *              (kmv_workspace_bytes(...) of it lets d = 1 run through the series below, and 9 <= d <= 64
  *              with two fp16 pieces of a coordinate in place of three bf16 ones)
  *   y          DEVICE  fp64 [n], fully overwritten (all zeros when m == 0)
+ *              (a NaN in a row of X: NaN; in Z or v: every sum NaN; an entry of a point at infinity with one that
+ *              is not: 0)
  *   stream     hipStream_t (NULL: the default stream).  The call only
  *              enqueues work; it allocates nothing and does not synchronise.
  * Each y_i is a sum in a fixed order (64-point groups in fp32, groups and

@@ -11,7 +11,7 @@
 //
 // What bounds it: 1000 x 1e4, d = 16, k = 10 3.1e7 vector instructions, of which the keys, two operations per pair and
 // coordinate, are 5e6 and most others the lists' merges; vector units active in 39 % of the wave cycles, waits 35 %.  At 16
-// queries x 1e5 points, d = 50, k = 10 the round trips of a wave's groups of points: 50 us here, 18 us for the merge of
+// queries x 1e5 points, d = 50, k = 10 the round trips of a wave's groups of points: 50 us here, 22 us for the merge of
 // 391 lists a query.
 #include <hip/hip_runtime.h>
 
